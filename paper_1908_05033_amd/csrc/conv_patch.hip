@@ -6,69 +6,107 @@
 
 namespace {
 
+// Patch rows of the worst tile: the padded-row span of its output rows plus the
+// filter.  A tile covers the strip pixels [t, t + BP), t a multiple of BP, i.e. d + 1
+// strip rows, and passes from one image to the next k times:
+//   span = d*stride + k*e,  e = Hp - Ho*stride  (the rows an image boundary adds).
+// Which tiles exist depends on t modulo the pixels of one image's strip, TW*Ho; as BP is
+// a power of two those residues are the multiples of G = gcd(BP, TW*Ho), so the maximum
+// needs a look at the few rows where d and k can both be largest instead of a walk over
+// all tiles (50 000 per strip width on a 224x224 layer at batch 32: the walk took 3.4 ms a
+// call there, 10 to 80 times the kernel).  For strips that do not hold every residue the
+// result may be a row or two above the exact value, which only costs LDS.
+int patch_rows(const DsqConvArgs &a, int BP, int TW, int row_tiles)
+{
+    const int NHo = a.N * a.Ho, Hp = a.H + 2 * a.pad;
+    if (row_tiles <= 32) {                      // short strips: the tiles one by one
+        int PR = 0;
+        for (int tr = 0; tr < row_tiles; ++tr) {
+            const int tA = tr * BP, tB = tA + BP - 1;
+            int g0 = tA / TW, g1 = tB / TW;
+            if (g1 >= NHo) g1 = NHo - 1;
+            const int nA = g0 / a.Ho, nB = g1 / a.Ho;
+            const int rows = (nB * Hp + (g1 - nB * a.Ho) * a.stride) - (nA * Hp + (g0 - nA * a.Ho) * a.stride) + a.R;
+            if (rows > PR) PR = rows;
+        }
+        return PR;
+    }
+    const int image = TW * a.Ho, e = Hp - a.Ho * a.stride;
+    const int G = (image & -image) < BP ? (image & -image) : BP;         // gcd with a power of two
+    const int gw = (TW & -TW) < BP ? (TW & -TW) : BP;
+    const int d = (TW - gw + BP - 1) / TW;      // most row steps of a tile: from the last reachable column
+    if (a.N == 1) return d * a.stride + a.R;
+    const int k_few = d / a.Ho, k_most = (a.Ho - 1 + d) / a.Ho;
+    int span = d * a.stride + k_few * e;
+    if (e > 0 && k_most > k_few) {
+        // d row steps and k_most boundaries together: a residue in one of the last rows of
+        // the image, at a column from which d steps are reached
+        const int col = d * TW - BP + 1 > 0 ? d * TW - BP + 1 : 0;
+        bool both = false;
+        for (int row = k_most * a.Ho - d > 0 ? k_most * a.Ho - d : 0; row < a.Ho && !both; ++row)
+            both = ((row * TW + col + G - 1) & ~(G - 1)) < (row + 1) * TW;
+        const int one_less = (d - 1) * a.stride + k_most * e;
+        if (both) span = d * a.stride + k_most * e;
+        else if (one_less > span) span = one_less;
+    }
+    return span + a.R;
+}
+
 bool plan_patch(const DsqConvArgs &a, int BP, int BC, int PF, int CT, int UPT, int lds_limit, int KS, PatchPlan &best)
 {
     // epilogue staging of the four waves (+ the partial sums of a second wave group)
     const int epi_bytes = 4 * KS * (32 * (128 + 16) + PF * 128) + (KS == 2 ? 8 * PF * (CT / 2) * 4096 : 0);
     const int cont = a.cont;
     const int UPP = cont == 2 ? 1 : 2;
-    const int NHo = a.N * a.Ho;
+    const int PIX_STRIDE = pix_stride(cont);
     const int Hp = a.H + 2 * a.pad;
+    const int tiles_c = (a.C_out + BC - 1) / BC;
+    // keep the operands of the index arithmetic small
+    if ((long long)a.N * a.Ho >= (1 << 22) || (long long)a.N * Hp >= (1 << 22)) return false;
+    const int NHo = a.N * a.Ho;
+    // a layer whose wave groups each see a single stage never touches the second
+    // buffer of a group: leave it out, so that more workgroups fit a CU
+    const int nbuf = a.Cp / 64 > KS ? 2 : 1;
     bool found = false;
     long long best_cost = 0;
-    for (int TW = 1; TW <= a.Wo; ++TW) {
-        // widths that split the row evenly, the full row, or wide strips with a ragged last one
-        const int tiles_w = (a.Wo + TW - 1) / TW;
-        if (TW != a.Wo && a.Wo % TW != 0 && TW < 16) continue;
-        PatchPlan p;
-        p.TW = TW; p.BP = BP; p.Hp = Hp;
-        p.tiles_w = tiles_w;
+    // Strip widths that split the row evenly, the full row, or wide strips with a ragged
+    // last one, from the widest down.  A plan's cost is led by its number of tiles, which the
+    // full row has least of, so nearly all other widths are dismissed by that number alone.
+    for (int TW = a.Wo; TW >= 1; --TW) {
         const long long strip_pixels = (long long)NHo * TW;
         if (strip_pixels + BP >= (1 << 22)) continue;          // keeps every index well inside 32 bits
-        p.row_tiles = (int)((strip_pixels + BP - 1) / BP);
+        const int tiles_w = (int)((unsigned)(a.Wo + TW - 1) / (unsigned)TW);
+        if (TW < 16 && TW != a.Wo && tiles_w * TW != a.Wo) continue;
+        const int row_tiles = (int)(((unsigned)strip_pixels + BP - 1) / (unsigned)BP);
+        const long long tiles = (long long)tiles_w * row_tiles;
+        if ((found && tiles * 100000 > best_cost) || tiles * tiles_c >= (1 << 22)) continue;
+        PatchPlan p;
+        p.TW = TW; p.BP = BP; p.Hp = Hp; p.tiles_w = tiles_w; p.row_tiles = row_tiles;
         p.PC = (TW - 1) * a.stride + a.R;
-        // patch rows: padded-row span of the tile's output rows, worst tile
-        int PR = 0;
-        for (int tr = 0; tr < p.row_tiles; ++tr) {
-            long long tA = (long long)tr * BP, tB = tA + BP - 1;
-            int g0 = (int)(tA / TW), g1 = (int)(tB / TW);
-            if (g1 >= NHo) g1 = NHo - 1;
-            int nA = g0 / a.Ho, nB = g1 / a.Ho;
-            int vA = nA * Hp + (g0 - nA * a.Ho) * a.stride;
-            int vB = nB * Hp + (g1 - nB * a.Ho) * a.stride;
-            int pr = vB - vA + a.R;
-            if (pr > PR) PR = pr;
-        }
-        p.PR = PR;
+        p.PR = patch_rows(a, BP, TW, row_tiles);
         // row skew: consecutive tile pixels keep advancing by one pixel stride
         // (mod 256 bytes) when a fragment wraps from one strip row to the next
-        const int PIX_STRIDE = pix_stride(cont);
         int skew = ((TW * a.stride - p.PC) * PIX_STRIDE) % 256;
         if (skew < 0) skew += 256;
         p.RP = p.PC * PIX_STRIDE + (a.stride == 1 ? skew : 0);
         p.buf_bytes = (p.PR * p.RP + 64 + 255) & ~255;   // + dump slot for idle fetch units
         p.units = p.PR * p.PC * UPP;
-        p.mg_TW = division_constant(TW); p.mg_Hp = division_constant(Hp); p.mg_Ho = division_constant(a.Ho);
-        p.mg_PC = division_constant(p.PC); p.mg_tiles_w = division_constant(tiles_w);
-        p.step_q = (256 / UPP) / p.PC;
-        p.step_r = (256 / UPP) % p.PC;
-        // a layer whose wave groups each see a single stage never touches the second
-        // buffer of a group: leave it out, so that more workgroups fit a CU
-        const int nbuf = a.Cp / 64 > KS ? 2 : 1;
-        p.aux_off = nbuf * KS * p.buf_bytes > epi_bytes ? nbuf * KS * p.buf_bytes : epi_bytes;
-        if (plan_lds_bytes(p, BC, a.rq != 0) > lds_limit) continue;
         if (p.units > 256 * UPT) continue;
-        const long long tiles = (long long)p.tiles_w * p.row_tiles;
-        // keep the operands of the index arithmetic small
-        if (tiles * ((a.C_out + BC - 1) / BC) >= (1 << 22) || (long long)a.N * Hp >= (1 << 22) || NHo >= (1 << 22)) continue;
-        // equal work: prefer a footprint that lets three (else two) workgroups share a CU,
-        // then the smaller patch
+        p.aux_off = nbuf * KS * p.buf_bytes > epi_bytes ? nbuf * KS * p.buf_bytes : epi_bytes;
         const int lds_bytes = plan_lds_bytes(p, BC, a.rq != 0);
+        if (lds_bytes > lds_limit) continue;
+        // equal work: prefer a footprint that lets three (else two) workgroups share a CU,
+        // then the smaller patch, then the narrower strip
         const long long cost = tiles * 100000 + (lds_bytes <= 52 * 1024 ? 0 : lds_bytes <= 78 * 1024 ? 20000 : 40000) +
                                (long long)p.PR * p.PC;
-        if (!found || cost < best_cost) { best = p; best_cost = cost; found = true; }
+        if (!found || cost <= best_cost) { best = p; best_cost = cost; found = true; }
     }
-    return found;
+    if (!found) return false;
+    best.mg_TW = division_constant(best.TW); best.mg_Hp = division_constant(Hp); best.mg_Ho = division_constant(a.Ho);
+    best.mg_PC = division_constant(best.PC); best.mg_tiles_w = division_constant(best.tiles_w);
+    best.step_q = (256 / UPP) / best.PC;
+    best.step_r = (256 / UPP) % best.PC;
+    return true;
 }
 
 struct TileCfg { int WP, WC, PF, CT; };
@@ -154,13 +192,6 @@ bool choose_plan(const DsqConvArgs &a, int force_tile, int &which, int &ks, Patc
 
 }  // namespace
 
-bool dsq_conv_patch_supported(const DsqConvArgs &a, int force_tile)
-{
-    int which, ks;
-    PatchPlan pl;
-    return choose_plan(a, force_tile, which, ks, pl);
-}
-
 int dsq_conv_patch_describe(const DsqConvArgs &a, int force_tile, char *text, size_t n)
 {
     int which, ks;
@@ -178,11 +209,11 @@ int dsq_conv_patch_describe(const DsqConvArgs &a, int force_tile, char *text, si
     return 1;
 }
 
-hipError_t dsq_launch_conv_patch(const DsqConvArgs &args, int force_tile, hipStream_t stream)
+bool dsq_launch_conv_patch(const DsqConvArgs &args, int force_tile, hipStream_t stream, hipError_t &status)
 {
     int which, ks;
     PatchPlan pl;
-    if (!choose_plan(args, force_tile, which, ks, pl)) return hipErrorInvalidValue;
+    if (!choose_plan(args, force_tile, which, ks, pl)) return false;
     DsqConvArgs a = args;
     if (a.rq) {
         // Next layer's pixel sums: a layer no wider than the tile has each pixel's
@@ -194,11 +225,12 @@ hipError_t dsq_launch_conv_patch(const DsqConvArgs &args, int force_tile, hipStr
     }
     const int need = (pl.units + 255) / 256;      // fetch units per thread: instantiated 2, 4, 8, 12
     switch (2 * a.cont + (a.R == 3 ? 0 : 1)) {
-    case 8: return dsq_conv_patch_c4r3(a, pl, which, ks, need, stream);
-    case 9: return dsq_conv_patch_c4r1(a, pl, which, ks, need, stream);
-    case 6: return dsq_conv_patch_c3r3(a, pl, which, ks, need, stream);
-    case 7: return dsq_conv_patch_c3r1(a, pl, which, ks, need, stream);
-    case 4: return dsq_conv_patch_c2r3(a, pl, which, ks, need, stream);
-    default: return dsq_conv_patch_c2r1(a, pl, which, ks, need, stream);
+    case 8: status = dsq_conv_patch_c4r3(a, pl, which, ks, need, stream); break;
+    case 9: status = dsq_conv_patch_c4r1(a, pl, which, ks, need, stream); break;
+    case 6: status = dsq_conv_patch_c3r3(a, pl, which, ks, need, stream); break;
+    case 7: status = dsq_conv_patch_c3r1(a, pl, which, ks, need, stream); break;
+    case 4: status = dsq_conv_patch_c2r3(a, pl, which, ks, need, stream); break;
+    default: status = dsq_conv_patch_c2r1(a, pl, which, ks, need, stream); break;
     }
+    return true;
 }

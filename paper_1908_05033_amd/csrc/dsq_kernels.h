@@ -111,10 +111,10 @@ hipError_t dsq_launch_fill_zero(int32_t *p, size_t n, hipStream_t stream);
 
 hipError_t dsq_launch_conv_simple(const DsqConvArgs &a, hipStream_t stream);
 // force_tile: -1 = choose by problem size; 0 / 1 / 2 / 3 = the 128x64 / 128x128 /
-// 256x128 / 256x64 (pixels x channels) workgroup tile.
-hipError_t dsq_launch_conv_patch(const DsqConvArgs &a, int force_tile, hipStream_t stream);
-// Whether the LDS-patch kernel supports this geometry with that tile.
-bool dsq_conv_patch_supported(const DsqConvArgs &a, int force_tile);
+// 256x128 / 256x64 (pixels x channels) workgroup tile.  Returns false, with nothing
+// launched, if the LDS-patch kernel does not take this geometry with that tile;
+// otherwise `status` is the launch's.
+bool dsq_launch_conv_patch(const DsqConvArgs &a, int force_tile, hipStream_t stream, hipError_t &status);
 // The launch configuration it would use, as text; returns 0 if it does not take the geometry.
 int dsq_conv_patch_describe(const DsqConvArgs &a, int force_tile, char *text, size_t n);
 

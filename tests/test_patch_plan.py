@@ -1,0 +1,43 @@
+"""The LDS-patch kernel's plan against a walk over all of its tiles (CPU only): the patch must
+hold the input rows of every tile, and little more."""
+import random
+import re
+
+import pytest
+
+from paper_1908_05033_amd import binding as B
+
+
+def _rows_of_every_tile(N, H, Ho, stride, pad, R, TW, BP):
+    rows, NHo, Hp = 0, N * Ho, H + 2 * pad
+    for t in range(0, NHo * TW, BP):
+        g0, g1 = t // TW, min((t + BP - 1) // TW, NHo - 1)
+        first = g0 // Ho * Hp + g0 % Ho * stride
+        last = g1 // Ho * Hp + g1 % Ho * stride
+        rows = max(rows, last - first + R)
+    return rows
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_patch_holds_the_rows_of_every_tile(seed):
+    rng = random.Random(seed)
+    planned = 0
+    while planned < 60:
+        R, stride = rng.choice([1, 3]), rng.choice([1, 2])
+        pad, N = rng.randint(0, R - 1), rng.choice([1, 2, 3, 5, 17, 40])
+        H, W = rng.choice([1, 2, 7, 14, 27, 53, 56, 101]), rng.choice([1, 3, 7, 14, 28, 53, 56, 113])
+        if min(H, W) + 2 * pad < R:
+            continue
+        Ho = (H + 2 * pad - R) // stride + 1
+        d = B.make_desc(N, rng.choice([16, 64, 200]), H, W, rng.choice([24, 64, 256]), R, R, stride, pad,
+                        rng.choice([2, 4]), rng.choice([2, 3, 4, 5, 6]))
+        try:
+            text = B.dsq_conv2d_plan(d)
+        except B.DsqError:
+            continue                # the forced tile does not take this layer
+        planned += 1
+        BP = int(re.search(r"tile (\d+)x", text).group(1))
+        TW = int(re.search(r"strip width (\d+)", text).group(1))
+        PR = int(re.search(r"patch (\d+)x", text).group(1))
+        need = _rows_of_every_tile(N, H, Ho, stride, pad, R, TW, BP)
+        assert need <= PR <= need + 2, text
