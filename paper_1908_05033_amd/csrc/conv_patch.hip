@@ -93,7 +93,7 @@ bool plan_patch(const DsqConvArgs &a, int BP, int BC, int PF, int CT, int UPT, i
         p.units = p.PR * p.PC * UPP;
         if (p.units > 256 * UPT) continue;
         p.aux_off = nbuf * KS * p.buf_bytes > epi_bytes ? nbuf * KS * p.buf_bytes : epi_bytes;
-        const int lds_bytes = plan_lds_bytes(p, BC, a.rq != 0);
+        const int lds_bytes = plan_lds_bytes(p, BC, a);
         if (lds_bytes > lds_limit) continue;
         // equal work: prefer a footprint that lets three (else two) workgroups share a CU,
         // then the smaller patch, then the narrower strip
@@ -205,7 +205,7 @@ int dsq_conv_patch_describe(const DsqConvArgs &a, int force_tile, char *text, si
     snprintf(text, n, "patch kernel: container %d, %dx%d filter, tile %dx%d (pixels x channels), %d wave group%s, "
              "%d fetch units per thread%s; strip width %d, patch %dx%d, %d workgroups, %d LDS bytes",
              a.cont, a.R, a.R, 32 * tc.PF * tc.WP, BC, ks, ks == 1 ? "" : "s", upt,
-             a.rq ? ", chained epilogue" : "", pl.TW, pl.PR, pl.PC, blocks, plan_lds_bytes(pl, BC, a.rq != 0));
+             a.rq ? ", chained epilogue" : "", pl.TW, pl.PR, pl.PC, blocks, plan_lds_bytes(pl, BC, a));
     return 1;
 }
 

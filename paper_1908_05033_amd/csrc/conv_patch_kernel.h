@@ -80,24 +80,6 @@ __device__ __forceinline__ int idiv(int x, int d, uint32_t m, int &rem)
     return q;
 }
 
-// The kernel's first argument where it lives: in the kernel-argument segment.
-__device__ __forceinline__ const DsqConvArgs &kernarg_conv_args()
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    return *reinterpret_cast<const DsqConvArgs *>(__builtin_amdgcn_kernarg_segment_ptr());
-#else
-    return *static_cast<const DsqConvArgs *>(nullptr);      // (host pass of the compiler: never executed)
-#endif
-}
-
-// Epilogue for the cases the kernel's inline fast path does not cover; kept out
-// of line so that its address arithmetic does not weigh on the main kernel.
-__device__ __noinline__ void store4_general(const DsqConvArgs &a, int m, int o0, v4i acc, float delta_a)
-{
-    const DsqPixel px = dsq_pixel_info(a, m, a.N * a.Ho * a.Wo);
-    dsq_store4(a, px, m, o0, acc, delta_a);
-}
-
 // Chained mode, per output channel o: the constants of the code-unit form of the
 // layer-to-layer map.  With P = Da*Dw[o], Q = Da*l_w[o] (binary64, exact), scale sc
 // and shift sh, the real value of the next layer's input in units of its quantizer
@@ -147,12 +129,25 @@ __device__ __forceinline__ float chained_channel_constants(const DsqConvArgs &a,
     return (float)((double)a.rq_t_margin - E);
 }
 
-// RQ selects the chained-mode epilogue at compile time, so that the plain
-// kernels' register allocation is exactly what it is without that mode.
-template <int CONT, int R, int WP, int WC, int PF, int CT, int UPT, int WD, int OCC, int KS, bool RQ>
+// What the kernel's results become; chosen at compile time, so that the register
+// allocation of each epilogue is its own.
+//   OUT_PLAIN    fp32 NHWC tensor, l_a = 0, C_out a multiple of 4, no raw accumulators
+//   OUT_CODES    the next layer's codes (chained mode)
+//   OUT_GENERAL  everything else: NCHW, l_a != 0 (terms that depend on which taps lie
+//                inside the image), any C_out, raw accumulators
+enum { OUT_PLAIN = 0, OUT_CODES = 1, OUT_GENERAL = 2 };
+
+inline int output_mode(const DsqConvArgs &a)
+{
+    if (a.rq) return OUT_CODES;
+    return !a.out_nchw && (a.C_out & 3) == 0 && a.l_a == 0.0f && a.acc == nullptr ? OUT_PLAIN : OUT_GENERAL;
+}
+
+template <int CONT, int R, int WP, int WC, int PF, int CT, int UPT, int WD, int OCC, int KS, int OUT>
 __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, OCC))) void conv_patch_kernel(DsqConvArgs a, PatchPlan pl)
 {
     constexpr int T = R * R;
+    constexpr bool RQ = OUT == OUT_CODES;
     // CONT: 2 / 4 = container width of the packed activation codes, 3 = dense 3-bit units
     // (12 bytes per 32 channels; everything after the patch store is the 4-bit path)
     constexpr int UPP = CONT == 2 ? 1 : 2;        // fetch units per patch pixel and 64 channels
@@ -182,6 +177,11 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     // largest distance from 1/2 of the fraction of t at which every channel's code is safe
     float4 *ft_lds = reinterpret_cast<float4 *>(thr_lds + 16);
     int *te_lds = reinterpret_cast<int *>(ft_lds + BC);              // (the bits of a float: see below)
+    // general results of a layer with l_a != 0 (in the place of the chained mode's tables):
+    // l_a*Dw and l_a*l_w of the workgroup's channels, the sum of a full pixel's border terms,
+    // and the weight code sums of every tap as [tap][channel]
+    double *la_lds = reinterpret_cast<double *>(ss_lds);
+    int *swt_lds = reinterpret_cast<int *>(la_lds + 3 * BC);
 
     // KS = 2: two groups of four waves work on alternating 64-channel blocks of K
     // (each with its own patch buffers) and add their accumulators at the end, so
@@ -342,12 +342,31 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         rq_const = tab != nullptr && o < a.C_out ? tab[o] : (tid < BC ? 1.0f : 0.0f);
     }
 
+    const bool has_la = OUT == OUT_GENERAL && a.l_a != 0.0f;
+    if (has_la) {
+        const double la = (double)a.l_a;
+        for (int i = (int)threadIdx.x; i < BC; i += 256 * KS) {
+            const int o = blk_y * BC + i;                     // < Cop: the side tables cover it
+            const double ldw = la * (double)a.delta_w[o], llw = la * (double)a.l_w[o];
+            la_lds[i] = ldw;
+            la_lds[BC + i] = llw;
+            la_lds[2 * BC + i] = ldw * (double)a.sw_total[o] + (double)(a.C_in * T) * llw;
+        }
+        if (T > 1)
+            for (int i = (int)threadIdx.x; i < BC * T; i += 256 * KS) {
+                const int o = i / T, t = i - o * T;
+                swt_lds[t * BC + o] = a.sw_tap[(size_t)blk_y * BC * T + i];
+            }
+    }
+
     // ---- per-lane LDS offsets of the fragments' pixels -----------------------
     // Tile pixels past the end of the strip multiply patch pixel 0 and are
     // never stored.
     int frag_off[PF];       // byte offset of the pixel's first tap inside a patch buffer
     int frag_pp[PF];        // index of that patch pixel (prow*PC + pcol)
     int frag_m[PF];         // output pixel index n*Ho*Wo + oy*Wo + ox, or -1
+    int frag_base[PF];      // general results, NCHW: element index of the pixel in channel 0
+    int frag_taps[PF];      // general results, l_a != 0: bit t set = tap t lies inside the image
 #pragma unroll
     for (int f = 0; f < PF; ++f) {
         const int t = t0 + (wp * PF + f) * 32 + col;
@@ -356,11 +375,25 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         const int ow = ow0 + tc;
         const bool ok = gr < NHo && ow < a.Wo;
         int prow = 0, pcol = 0;
+        frag_base[f] = 0;
+        frag_taps[f] = (1 << T) - 1;
         if (ok) {
             int oh;
             const int n = idiv(gr, a.Ho, pl.mg_Ho, oh);
             prow = n * pl.Hp + oh * a.stride - v0;
             pcol = tc * a.stride;
+            if (OUT == OUT_GENERAL) {
+                frag_base[f] = n * (a.C_out - 1) * (a.Ho * a.Wo) + gr * a.Wo + ow;
+                if (T > 1) {
+                    int rows = 0, cols = 0;                  // taps of a column / of a row inside the image
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        if ((unsigned)(oh * a.stride - a.pad + r) < (unsigned)a.H) rows |= 1 << (r * R);
+                        if ((unsigned)(ow * a.stride - a.pad + r) < (unsigned)a.W) cols |= 1 << r;
+                    }
+                    frag_taps[f] = rows * cols;              // (no carries: each bit of rows places its own copy of cols)
+                }
+            }
         }
         frag_m[f] = ok ? gr * a.Wo + ow : -1;
         frag_pp[f] = prow * pl.PC + pcol;
@@ -489,9 +522,6 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     }
     // ---- side values of the epilogue (see conv_epilogue.h for the algebra) ------
     const int top = (1 << a.bits) - 1;
-    const float delta_a = a.delta_a;
-    // fast path: NHWC fp32 output only, l_a = 0, C_out a multiple of 4
-    const bool fast = !a.out_nchw && (a.C_out & 3) == 0 && a.l_a == 0.0f && a.acc == nullptr;
     // per fragment: SA = code sums of the patch pixels under the taps (0 in the padding)
     double dsa[PF];
     float fsa[PF];          // (the same sums in binary32: exact, they stay below 2^24 wherever this is used)
@@ -522,7 +552,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     const bool early_tables = KS == 2 && CT == 2;
     if (early_tables) {
         sum_sa();
-        if (fast) load_pq(grp, P0, Q0);
+        if (OUT == OUT_PLAIN) load_pq(grp, P0, Q0);
     }
     if (grp + n_full * KS < NCB) compute(std::false_type{}, patch_buf(n_full & 1), grp + n_full * KS, 0, nullptr);
     // every wave of the workgroup takes part in n_iter - 1 stage barriers
@@ -723,7 +753,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
                 else atomicAdd(a.rq_pix + frag_m[f], psum[f]);
             }
         }
-    } else if (fast) {
+    } else if (OUT == OUT_PLAIN) {
         if (h == 0) {
 #pragma unroll
             for (int f = 0; f < PF; ++f) m_stage[f * 32 + col] = frag_m[f];
@@ -775,27 +805,98 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
             }
         }
     } else {
-        // general path: l_a != 0 (terms that depend on which taps are inside the
-        // image), NCHW output, raw accumulators wanted, or C_out not a multiple of 4.
-        // (the out-of-line function takes the arguments by reference: point it at the
-        // kernel-argument segment, where `a` is the first argument, instead of copying the
-        // structure to scratch memory -- the compiler hoists such a copy to the top of the
-        // kernel, where it splits the one batch of argument loads into several round trips)
-        const DsqConvArgs &a_copy = kernarg_conv_args();
+        // The values of OUT_PLAIN plus, for l_a != 0, the terms of conv_epilogue.h that depend on
+        // which taps lie inside the image, in its order of operations (the same bits).  A pixel
+        // with all taps inside takes them from a table; fragments that hold other pixels add up
+        // the tap sums under their masks.  NCHW: the accumulator layout already has 32
+        // consecutive pixels of a channel in 32 lanes, so each store writes two runs of 128
+        // bytes.  NHWC: staged like OUT_PLAIN, in single floats where C_out is not a
+        // multiple of 4.  Bound by the store of the tensor; measured against the out-of-line
+        // per-lane function that stood here (it worked out the pixel's divisions and code sums
+        // again for every four channels): 24 -> 144 at 56x56 x 64 with l_a != 0 201 -> 41 us,
+        // 128 -> 256 stride 2 at 28x28 x 64 to NCHW 40 -> 14 us.
+        if (h == 0) {
 #pragma unroll
-        for (int f = 0; f < PF; ++f) {
-            const int m = frag_m[f];
-            if (m < 0) continue;
+            for (int f = 0; f < PF; ++f) m_stage[f * 32 + col] = frag_m[f];
+        }
+        const int plane = a.Ho * a.Wo;
 #pragma unroll
-            for (int c = 0; c < CT; ++c)
+        for (int c = 0; c < CT; ++c) {
+            if (KS == 2 && (c & 1) != grp) continue;
+            const int o_tile = (ct0 + c) * 32;
+            const int ol = (wc * CT + c) * 32 + 4 * h;     // this lane's first channel inside the workgroup
+#pragma unroll
+            for (int f = 0; f < PF; ++f) {
+                const bool border = T > 1 && has_la && __builtin_amdgcn_ballot_w64(frag_taps[f] != (1 << T) - 1) != 0;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int o0 = (ct0 + c) * 32 + 8 * q + 4 * h;
-                    if (o0 < a.C_out && (KS == 1 || (c & 1) == grp))
-                        store4_general(a_copy, m, o0,
-                                       (v4i){acc[f][c][4 * q], acc[f][c][4 * q + 1], acc[f][c][4 * q + 2], acc[f][c][4 * q + 3]},
-                                       delta_a);
+                    const int o0 = o_tile + 8 * q + 4 * h;
+                    double v[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        v[j] = __builtin_fma(pq_lds[ol + 8 * q + j], (double)acc[f][c][4 * q + j],
+                                             pq_lds[BC + ol + 8 * q + j] * dsa[f]);
+                    if (has_la) {
+                        double w[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) w[j] = la_lds[2 * BC + ol + 8 * q + j];
+                        if (border) {
+                            int sw[4] = {0, 0, 0, 0};
+#pragma unroll
+                            for (int t = 0; t < T; ++t) {
+                                const v4i s4 = *reinterpret_cast<const v4i *>(swt_lds + t * BC + ol + 8 * q);
+                                const int in = -(frag_taps[f] >> t & 1);
+                                sw[0] += s4.x & in; sw[1] += s4.y & in; sw[2] += s4.z & in; sw[3] += s4.w & in;
+                            }
+                            const double kv = (double)(a.C_in * __builtin_popcount((unsigned)frag_taps[f]));
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                const double e = la_lds[ol + 8 * q + j] * (double)sw[j] + kv * la_lds[BC + ol + 8 * q + j];
+                                w[j] = frag_taps[f] == (1 << T) - 1 ? w[j] : e;
+                            }
+                        }
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) v[j] += w[j];
+                    }
+                    if (a.out_nchw) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (frag_m[f] >= 0 && o0 + j < a.C_out)
+                                a.out[(size_t)frag_base[f] + (size_t)(o0 + j) * plane] = (float)v[j];
+                    } else {
+                        *reinterpret_cast<float4 *>(stage + col * ROWB + (8 * q + 4 * h) * 4) =
+                            make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+                    }
+                    if (a.acc != nullptr && frag_m[f] >= 0) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (o0 + j < a.C_out)
+                                a.acc[a.out_nchw ? (size_t)frag_base[f] + (size_t)(o0 + j) * plane
+                                                 : (size_t)frag_m[f] * a.C_out + o0 + j] = acc[f][c][4 * q + j];
+                    }
                 }
+                if (a.out_nchw) continue;
+                // (LDS operations of one wave execute in order: no barrier needed)
+                if ((a.C_out & 3) == 0) {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        const int p = k * 8 + (lane >> 3), o = o_tile + (lane & 7) * 4;
+                        typedef float v4f __attribute__((ext_vector_type(4)));
+                        const v4f t = *reinterpret_cast<const v4f *>(stage + p * ROWB + (lane & 7) * 16);
+                        const int rm = m_stage[f * 32 + p];
+                        if (rm >= 0 && o < a.C_out)
+                            __builtin_nontemporal_store(t, reinterpret_cast<v4f *>(a.out + (size_t)rm * a.C_out + o));
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k) {
+                        const int p = k * 2 + h, o = o_tile + col;
+                        const float t = *reinterpret_cast<const float *>(stage + p * ROWB + col * 4);
+                        const int rm = m_stage[f * 32 + p];
+                        if (rm >= 0 && o < a.C_out) a.out[(size_t)rm * a.C_out + o] = t;
+                    }
+                }
+            }
         }
     }
 }
@@ -809,27 +910,30 @@ inline uint32_t division_constant(int d)
     return m > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)m;
 }
 
-inline int plan_lds_bytes(const PatchPlan &p, int BC, bool chained)
+inline int plan_lds_bytes(const PatchPlan &p, int BC, const DsqConvArgs &a)
 {
     // tables behind the buffers: Da*Dw, Da*l_w (binary64), the patch pixels' code
-    // sums, the chained mode's scale, shift and quantizer thresholds and (chained
-    // kernels only) its per-channel constants of the code-unit form
-    return ((p.aux_off + 2 * BC * 8 + p.PR * p.PC * 4 + 15) & ~15) + 2 * BC * 4 + 16 * 8 + (chained ? BC * 16 + 16 : 0);
+    // sums; then the chained mode's scale, shift, quantizer thresholds and per-channel
+    // constants of the code-unit form, or the general results' tables for l_a != 0
+    const int tables = (p.aux_off + 2 * BC * 8 + p.PR * p.PC * 4 + 15) & ~15;
+    const int chained = 2 * BC * 4 + 16 * 8 + BC * 16 + 16;
+    const int border = 3 * BC * 8 + (a.R > 1 ? a.R * a.R * BC * 4 : 0);
+    return tables + (a.rq ? chained : a.l_a != 0.0f ? border : 0);
 }
 
-template <int CONT, int R, int WP, int WC, int PF, int CT, int UPT, int WD, int OCC, int KS, bool RQ>
+template <int CONT, int R, int WP, int WC, int PF, int CT, int UPT, int WD, int OCC, int KS, int OUT>
 hipError_t launch_kernel(const DsqConvArgs &a, const PatchPlan &pl, hipStream_t stream)
 {
-    auto kern = conv_patch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, RQ>;
+    auto kern = conv_patch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, OUT>;
     const int BC = 32 * CT * WC;
-    const size_t lds = (size_t)plan_lds_bytes(pl, BC, RQ);      // pl.aux_off already accounts for KS
+    const size_t lds = (size_t)plan_lds_bytes(pl, BC, a);      // pl.aux_off already accounts for KS
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
     // chained mode, layer wider than the tile: the workgroups add to the next
     // layer's pixel sums, which a fill kernel clears first (unless the caller did)
-    if (RQ && !a.rq_store && !a.rq_zeroed) {
+    if (OUT == OUT_CODES && !a.rq_store && !a.rq_zeroed) {
         const hipError_t e = dsq_launch_fill_zero(a.rq_pix, (size_t)a.N * a.Ho * a.Wo, stream);
         if (e != hipSuccess) return e;
     }
@@ -847,11 +951,14 @@ hipError_t launch_kernel(const DsqConvArgs &a, const PatchPlan &pl, hipStream_t 
 //   medium 128 x 128   waves 2x2, 2 x 2
 //   large  256 x 128   waves 2x2, 4 x 2
 //   tall   256 x  64   waves 4x1, 2 x 2  (layers with at most 64 output channels)
-template <int CONT, int R, int WP, int WC, int PF, int CT, int UPT, int WD, int OCC, int KS = 1>
+template <int CONT, int R, int WP, int WC, int PF, int CT, int UPT, int WD, int OCC, int KS = 1, bool CHAINED = true>
 hipError_t launch_cfg(const DsqConvArgs &a, const PatchPlan &pl, hipStream_t stream)
 {
-    if (a.rq) return launch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, true>(a, pl, stream);
-    return launch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, false>(a, pl, stream);
+    const int out = output_mode(a);
+    if constexpr (CHAINED)
+        if (out == OUT_CODES) return launch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, OUT_CODES>(a, pl, stream);
+    if (out == OUT_GENERAL) return launch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, OUT_GENERAL>(a, pl, stream);
+    return launch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, OUT_PLAIN>(a, pl, stream);
 }
 
 enum { TILE_SMALL = 0, TILE_MEDIUM = 1, TILE_LARGE = 2, TILE_TALL = 3 };
@@ -868,8 +975,7 @@ hipError_t dispatch_variant(const DsqConvArgs &a, const PatchPlan &pl, int which
 #define DSQ_TILE(CONT, RR, UPT)                                                                \
     do {                                                                                       \
         if (which == TILE_LARGE) {                                                             \
-            if constexpr (CONT == 2) return launch_cfg<CONT, RR, 2, 2, 4, 2, UPT, (RR == 3 ? 3 : 1), 2>(a, pl, stream); \
-            else return launch_kernel<CONT, RR, 2, 2, 4, 2, UPT, (RR == 3 ? 3 : 1), 2, 1, false>(a, pl, stream);  \
+            return launch_cfg<CONT, RR, 2, 2, 4, 2, UPT, (RR == 3 ? 3 : 1), 2, 1, CONT == 2>(a, pl, stream); \
         }                                                                                      \
         if (which == TILE_MEDIUM && ks == 2) return launch_cfg<CONT, RR, 2, 2, 2, 2, UPT, (RR == 3 ? 3 : 1), 2, 2>(a, pl, stream); \
         if (which == TILE_MEDIUM) return launch_cfg<CONT, RR, 2, 2, 2, 2, UPT, (RR == 3 ? 3 : 1), 3>(a, pl, stream); \

@@ -1,0 +1,46 @@
+"""The LDS-patch kernel's results other than the plain NHWC tensor (NCHW, l_a != 0, odd channel
+counts, raw accumulators) against the simple kernel, bit for bit: both evaluate the same
+expressions in the same order."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1908_05033_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+# N, C_in, H, W, C_out, R, stride, pad
+GEOMS = [(2, 24, 7, 9, 33, 3, 1, 1), (1, 130, 13, 11, 130, 3, 2, 1), (3, 64, 1, 1, 66, 3, 1, 2), (2, 70, 9, 6, 259, 1, 2, 0),
+         (2, 129, 12, 17, 64, 3, 1, 0)]
+
+
+def _run(geom, bits, flags, la, layout, with_acc):
+    N, C, H, W, K, R, stride, pad = geom
+    g = torch.Generator().manual_seed(sum(geom) + bits)
+    buf = B.alloc_layer(N, C, H, W, K, R, R, stride, pad, bits, with_acc=with_acc, flags=flags)
+    x = torch.randn((N, H, W, C), generator=g).cuda()
+    w = torch.randn((K, C, R, R), generator=g).cuda()
+    lw, uw = w.reshape(K, -1).amin(1) * 0.9, w.reshape(K, -1).amax(1)
+    B.dsq_quantize_act(x, B.DSQ_NHWC, N, C, H, W, la, 2.5, bits, buf.act_packed, buf.pix_code_sum)
+    B.dsq_pack_weights(w, lw.contiguous(), uw.contiguous(), None, K, C, R, R, bits, buf.w_packed, buf.w_aux)
+    out = torch.full_like(buf.out.reshape(-1), float("nan"))
+    acc = torch.full_like(out, -1, dtype=torch.int32) if with_acc else None
+    B.dsq_conv2d(buf.desc, buf.act_packed, buf.pix_code_sum, la, 2.5, buf.w_packed, buf.w_aux, out, layout, acc)
+    torch.cuda.synchronize()
+    return out.cpu().numpy().view(np.int32), acc.cpu().numpy() if with_acc else None
+
+
+@pytest.mark.parametrize("layout", [B.DSQ_NHWC, B.DSQ_NCHW])
+@pytest.mark.parametrize("la", [0.0, -2.1, 0.3])
+@pytest.mark.parametrize("bits", [2, 4])
+@pytest.mark.parametrize("geom", GEOMS)
+def test_same_bits_as_the_simple_kernel(geom, bits, la, layout):
+    want = _run(geom, bits, B.DSQ_CONV_KERNEL(1), la, layout, True)
+    for kernel in (2, 3, 4, 5, 6):                 # the patch kernel's own choice and its four tiles
+        for with_acc in (False, True):
+            try:
+                got = _run(geom, bits, B.DSQ_CONV_KERNEL(kernel), la, layout, with_acc)
+            except B.DsqError:
+                continue                           # the tile does not take this layer
+            assert np.array_equal(got[0], want[0]), kernel
+            assert not with_acc or np.array_equal(got[1], want[1]), kernel
