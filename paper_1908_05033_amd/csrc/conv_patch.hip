@@ -4,8 +4,6 @@
 
 #include "conv_patch_kernel.h"
 
-namespace {
-
 // Patch rows of the worst tile: the padded-row span of its output rows plus the
 // filter.  A tile covers the strip pixels [t, t + BP), t a multiple of BP, i.e. d + 1
 // strip rows, and passes from one image to the next k times:
@@ -16,7 +14,7 @@ namespace {
 // all tiles (50 000 per strip width on a 224x224 layer at batch 32: the walk took 3.4 ms a
 // call there, 10 to 80 times the kernel).  For strips that do not hold every residue the
 // result may be a row or two above the exact value, which only costs LDS.
-int patch_rows(const DsqConvArgs &a, int BP, int TW, int row_tiles)
+int dsq_patch_rows(const DsqConvArgs &a, int BP, int TW, int row_tiles)
 {
     const int NHo = a.N * a.Ho, Hp = a.H + 2 * a.pad;
     if (row_tiles <= 32) {                      // short strips: the tiles one by one
@@ -52,6 +50,8 @@ int patch_rows(const DsqConvArgs &a, int BP, int TW, int row_tiles)
     return span + a.R;
 }
 
+namespace {
+
 bool plan_patch(const DsqConvArgs &a, int BP, int BC, int PF, int CT, int UPT, int lds_limit, int KS, PatchPlan &best)
 {
     // epilogue staging of the four waves (+ the partial sums of a second wave group)
@@ -83,7 +83,7 @@ bool plan_patch(const DsqConvArgs &a, int BP, int BC, int PF, int CT, int UPT, i
         PatchPlan p;
         p.TW = TW; p.BP = BP; p.Hp = Hp; p.tiles_w = tiles_w; p.row_tiles = row_tiles;
         p.PC = (TW - 1) * a.stride + a.R;
-        p.PR = patch_rows(a, BP, TW, row_tiles);
+        p.PR = dsq_patch_rows(a, BP, TW, row_tiles);
         // row skew: consecutive tile pixels keep advancing by one pixel stride
         // (mod 256 bytes) when a fragment wraps from one strip row to the next
         int skew = ((TW * a.stride - p.PC) * PIX_STRIDE) % 256;
@@ -102,8 +102,8 @@ bool plan_patch(const DsqConvArgs &a, int BP, int BC, int PF, int CT, int UPT, i
         if (!found || cost <= best_cost) { best = p; best_cost = cost; found = true; }
     }
     if (!found) return false;
-    best.mg_TW = division_constant(best.TW); best.mg_Hp = division_constant(Hp); best.mg_Ho = division_constant(a.Ho);
-    best.mg_PC = division_constant(best.PC); best.mg_tiles_w = division_constant(best.tiles_w);
+    best.mg_TW = dsq_division_constant(best.TW); best.mg_Hp = dsq_division_constant(Hp); best.mg_Ho = dsq_division_constant(a.Ho);
+    best.mg_PC = dsq_division_constant(best.PC); best.mg_tiles_w = dsq_division_constant(best.tiles_w);
     best.step_q = (256 / UPP) / best.PC;
     best.step_r = (256 / UPP) % best.PC;
     return true;

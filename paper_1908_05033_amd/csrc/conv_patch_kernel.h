@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "conv_epilogue.h"
+#include "patch_plan.h"
 
 struct PatchPlan {
     int TW;            // strip width in output columns
@@ -46,7 +47,7 @@ struct PatchPlan {
     int tiles_c;       // channel tiles (workgroups per pixel tile)
     int total_blocks;  // pixel tiles * channel tiles
     int xcd_chunk;     // ceil(total_blocks / 8)
-    uint32_t mg_tiles_c;   // division constants (see idiv) of tiles_c ...
+    uint32_t mg_tiles_c;   // division constants (see dsq_idiv) of tiles_c ...
     int step_q, step_r;   // (256 / units-per-pixel) divided by PC: quotient and remainder
     uint32_t mg_PC, mg_TW, mg_Hp, mg_Ho, mg_tiles_w;   // ... and of PC, TW, Hp, Ho, tiles_w
 };
@@ -65,19 +66,6 @@ constexpr int pix_stride(int cont) { return cont == 2 ? 48 : 80; }
 __device__ __forceinline__ void lds_barrier()
 {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// x / d for x >= 0 and d >= 1 by multiplication: with m = min(floor(2^32 / d), 2^32 - 1)
-// (computed on the host, division_constant below) the high word of x * m is the
-// quotient or one less, so one correction suffices.  Wave-uniform operands stay
-// on the scalar unit.
-__device__ __forceinline__ int idiv(int x, int d, uint32_t m, int &rem)
-{
-    int q = (int)__umulhi((uint32_t)x, m);
-    int r = x - q * d;
-    if (r >= d) { ++q; r -= d; }
-    rem = r;
-    return q;
 }
 
 // Chained mode, per output channel o: the constants of the code-unit form of the
@@ -215,7 +203,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     const int logical = ((int)blockIdx.x & 7) * pl.xcd_chunk + ((int)blockIdx.x >> 3);
     if (logical >= pl.total_blocks) return;
     int blk_y;
-    const int blk_x = idiv(logical, pl.tiles_c, pl.mg_tiles_c, blk_y);
+    const int blk_x = dsq_idiv(logical, pl.tiles_c, pl.mg_tiles_c, blk_y);
 
     const int NCB = a.Cp / 64;
     const int NHo = a.N * a.Ho;
@@ -244,13 +232,13 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
 
     // ---- tile position -------------------------------------------------------
     int tile_w;
-    const int tile_r = idiv(blk_x, pl.tiles_w, pl.mg_tiles_w, tile_w);
+    const int tile_r = dsq_idiv(blk_x, pl.tiles_w, pl.mg_tiles_w, tile_w);
     const int t0 = tile_r * pl.BP;              // first pixel of the tile, numbered inside the strip
     const int ow0 = tile_w * pl.TW;
     int tc0;
-    const int gr0 = idiv(t0, pl.TW, pl.mg_TW, tc0);   // its output row (batch-wide numbering)
+    const int gr0 = dsq_idiv(t0, pl.TW, pl.mg_TW, tc0);   // its output row (batch-wide numbering)
     int oh0;
-    const int n0 = idiv(gr0, a.Ho, pl.mg_Ho, oh0);
+    const int n0 = dsq_idiv(gr0, a.Ho, pl.mg_Ho, oh0);
     const int v0 = n0 * pl.Hp + oh0 * a.stride;   // first padded input row of the patch
     const int vc0 = ow0 * a.stride;               // first padded input column of the patch
     const uint32_t row_bytes = (uint32_t)a.Cp * CONT / 8;
@@ -266,8 +254,8 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     const int half = UPP == 2 ? (tid & 1) : 0;
     {
         int pcol, ihp;
-        int prow = idiv(UPP == 2 ? (tid >> 1) : tid, pl.PC, pl.mg_PC, pcol);
-        int n = idiv(v0 + prow, pl.Hp, pl.mg_Hp, ihp);
+        int prow = dsq_idiv(UPP == 2 ? (tid >> 1) : tid, pl.PC, pl.mg_PC, pcol);
+        int n = dsq_idiv(v0 + prow, pl.Hp, pl.mg_Hp, ihp);
 #pragma unroll
         for (int k = 0; k < UPT; ++k) {
             const int ih = ihp - a.pad, iw = vc0 + pcol - a.pad;
@@ -371,7 +359,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     for (int f = 0; f < PF; ++f) {
         const int t = t0 + (wp * PF + f) * 32 + col;
         int tc;
-        const int gr = idiv(t, pl.TW, pl.mg_TW, tc);
+        const int gr = dsq_idiv(t, pl.TW, pl.mg_TW, tc);
         const int ow = ow0 + tc;
         const bool ok = gr < NHo && ow < a.Wo;
         int prow = 0, pcol = 0;
@@ -379,7 +367,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         frag_taps[f] = (1 << T) - 1;
         if (ok) {
             int oh;
-            const int n = idiv(gr, a.Ho, pl.mg_Ho, oh);
+            const int n = dsq_idiv(gr, a.Ho, pl.mg_Ho, oh);
             prow = n * pl.Hp + oh * a.stride - v0;
             pcol = tc * a.stride;
             if (OUT == OUT_GENERAL) {
@@ -903,13 +891,6 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
 
 // ---- host side ---------------------------------------------------------------
 
-// m of idiv() for the divisor d >= 1
-inline uint32_t division_constant(int d)
-{
-    const unsigned long long m = (1ull << 32) / (unsigned long long)d;
-    return m > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)m;
-}
-
 inline int plan_lds_bytes(const PatchPlan &p, int BC, const DsqConvArgs &a)
 {
     // tables behind the buffers: Da*Dw, Da*l_w (binary64), the patch pixels' code
@@ -939,7 +920,7 @@ hipError_t launch_kernel(const DsqConvArgs &a, const PatchPlan &pl, hipStream_t 
     }
     PatchPlan p2 = pl;
     p2.tiles_c = (a.C_out + BC - 1) / BC;
-    p2.mg_tiles_c = division_constant(p2.tiles_c);
+    p2.mg_tiles_c = dsq_division_constant(p2.tiles_c);
     p2.total_blocks = pl.tiles_w * pl.row_tiles * p2.tiles_c;
     p2.xcd_chunk = (p2.total_blocks + 7) / 8;
     kern<<<dim3(8 * p2.xcd_chunk), 256 * KS, lds, stream>>>(a, p2);

@@ -1,109 +1,527 @@
 // dsq_conv2d_wq: a layer whose weights are quantized and whose activations are not
 // (the "b/32" rows of the paper's Tables 3, 6 and 7: b-bit weights, 32-bit
-// activations).  Algorithm 1 steps 4 and 5 with a_hat = a: the weight codes are
-// turned back into their levels l_w + Dw*code, one binary32 rounding each, and
-// convolved with the binary32 activations on the fp32 matrix instruction
-// (v_mfma_f32_32x32x2_f32: products are not rounded, sums are accumulated in
-// binary32).  There is no integer path here: the inner product is a
-// floating-point contraction, which is why this is a kernel of its own.
+// activations).  Algorithm 1 steps 4 and 5 with a_hat = a: the binary32 activations
+// are convolved with the weight levels l_w + Dw*code.
 //
-// One wave per tile of 32 output pixels x 32 output channels, operands straight
-// from global memory: rows of the first operand are output channels (the packed
-// 4-bit weight layout of dsq_pack_weights_for(.., bits_w, 4, ..): a lane holds
-// the 16 channels 64cb + 32kh + 16h + 0..15 of its row), columns of the second
-// are pixels, and a lane walks its 16 channels one matrix instruction (K = 2:
-// one channel per lane half) at a time.
+// The inner product runs on the bf16 matrix instruction (v_mfma_f32_32x32x16_bf16,
+// 16 times the rate of the binary32 one) without rounding an operand:
+//   - an activation is the sum of three bf16 numbers of 8 significant bits each
+//     (its 24 bits cut in three; every step of the split is exact),
+//   - a level is Dw*(code + zq) + lr, zq = l_w/Dw rounded so that code + zq is a
+//     bf16 number for every code, lr = l_w - Dw*zq (0 for the symmetric ranges of
+//     1-bit weights; at most Dw/128 at 2 bits, Dw/32 at 4 bits),
+// so that out = Dw * sum (code + zq)*(x2 + x1 + x0) + lr * sum x.  Products of two
+// such terms have at most 16 bits and are exact; the sums are binary32.  Three matrix
+// instructions of 32 clk for 16 channels against eight of 64 clk.  Sums of centred
+// levels (and not of the codes themselves) keep the partial sums as small as those of
+// the levels.  The split needs the activations of a tile to stay clear of the ends of
+// the exponent range: a tile whose largest |x| is 2^100 or more (infinities and NaN
+// among them) or below 2^-60 is computed with the binary32 matrix instruction from
+// the levels themselves.
+//
+// A workgroup owns BP output pixels of a strip of TW columns (pixels are numbered row
+// by row through the batch) and BC output channels.  Per stage of KC input channels
+// the input patch under its taps is read once, split, and kept in LDS (as three bf16
+// planes per pixel); the R*R taps read shifted windows of it.  Weight codes go from
+// global memory to registers, all of a stage's in flight while the patch is staged.
 #include "dsq_device.h"
 #include "dsq_kernels.h"
+#include "patch_plan.h"
 
 namespace {
 
-typedef float v16f_t __attribute__((ext_vector_type(16)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void conv_wq_kernel(DsqConvArgs a, const float *__restrict__ x, int x_nchw)
+struct WqPlan {
+    int TW, PC, npx;           // strip width; patch columns, patch pixels (1x1: the tile's pixels)
+    int Hp, tiles_w, tiles_c, total_blocks, xcd_chunk;
+    uint32_t mg_TW, mg_PC, mg_Hp, mg_Ho, mg_tiles_w, mg_tiles_c;
+};
+
+__host__ __device__ constexpr int kc_of(int R) { return R == 3 ? 32 : 64; }              // channels per stage
+__host__ __device__ constexpr int pixel_bytes(int R) { return kc_of(R) * 6 + 16; }       // odd multiple of 16: 8 pixels in distinct banks
+constexpr int ROWB = 128 + 16;                                       // staged bytes per output pixel
+// LDS: [patch, then the epilogue's staging][channel-group sums of x][patch addresses]
+//      [zq, Dw, lr of BC channels][largest |x|]
+__host__ __device__ constexpr int tables_at(int R, int KW, int tiles, int npx)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = lane & 31, h = lane >> 5;
-    const int M = a.N * a.Ho * a.Wo;
-    const int m = blockIdx.x * 32 + col;
-    const int ct = blockIdx.y * 4 + wave;
-    if (ct * 32 >= a.C_out) return;                     // (uniform per wave)
-    const int T = a.R * a.R;
-    const int NCB = a.Cp / 64;
-    const bool valid = m < M;
-    const int mm = valid ? m : 0;
-    const int ox = mm % a.Wo, oy = (mm / a.Wo) % a.Ho, n = mm / (a.Wo * a.Ho);
-    const int o_row = ct * 32 + col;                    // this lane's weight row (< Cop: the side table covers it)
-    const float dw = a.delta_w[o_row], lw = a.l_w[o_row];
-    const uint32_t *wq = (const uint32_t *)a.wq;
-    const bool vec = !x_nchw && (a.C_in & 3) == 0;
+    const int staging = KW > 1 ? KW * tiles * 4096 : 4 * 32 * ROWB;      // (tiles: 32x32 tiles of a wave)
+    return npx * pixel_bytes(R) > staging ? npx * pixel_bytes(R) : staging;
+}
+constexpr int lds_bytes(int R, int KW, int tiles, int BC, int npx)
+{
+    return tables_at(R, KW, tiles, npx) + npx * (kc_of(R) / 8 * 4 + 4) + 3 * BC * 4 + 16;
+}
 
-    v16f_t acc0, acc1;
+// One 32x32 tile with the binary32 matrix instruction: the levels themselves
+// (l_w + Dw*code, rounded once) times the activations.  Lane: pixel (n, oy, ox).
+__device__ __forceinline__ v16f wq_exact_tile(const DsqConvArgs &a, const float *x, int x_nchw, int lane, int ct, bool valid,
+                                              int n, int oy, int ox)
+{
+    const int col = lane & 31, h = lane >> 5;
+    const int T = a.R * a.R, NCB = a.Cp / 64;
+    const float dw = a.delta_w[ct * 32 + col], lw = a.l_w[ct * 32 + col];
+    const uint32_t *wq = (const uint32_t *)a.wq;
+    v16f acc;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { acc0[r] = 0.f; acc1[r] = 0.f; }
-    for (int cb = 0; cb < NCB; ++cb) {
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int cb = 0; cb < NCB; ++cb)
         for (int tap = 0; tap < T; ++tap) {
             const int r = tap / a.R, s = tap % a.R;
             const int iy = oy * a.stride - a.pad + r, ix = ox * a.stride - a.pad + s;
             const bool inside = valid && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
             const uint32_t *wp = wq + ((((size_t)ct * NCB + cb) * T + tap) * 64 + lane) * 4;
+            for (int w = 0; w < 4; ++w) {                 // a word: 8 channels
+                const int c0 = 64 * cb + 32 * (w >> 1) + 16 * h + 8 * (w & 1);
+                uint32_t b[2];
+                dsq_unpack4(wp[w], b[0], b[1]);
 #pragma unroll
-            for (int kh = 0; kh < 2; ++kh) {
-                const int c0 = 64 * cb + 32 * kh + 16 * h;      // this lane's 16 channels
-                float av[16];
-#pragma unroll
-                for (int j = 0; j < 16; ++j) av[j] = 0.f;       // padding and channels >= C_in: the real number 0
-                if (inside) {
-                    if (vec) {
-                        const float *p = x + (((size_t)n * a.H + iy) * a.W + ix) * a.C_in + c0;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            if (c0 + 4 * q < a.C_in) {
-                                const float4 t = *reinterpret_cast<const float4 *>(p + 4 * q);
-                                av[4 * q] = t.x; av[4 * q + 1] = t.y; av[4 * q + 2] = t.z; av[4 * q + 3] = t.w;
-                            }
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 16; ++j)
-                            if (c0 + j < a.C_in)
-                                av[j] = x_nchw ? x[(((size_t)n * a.C_in + c0 + j) * a.H + iy) * a.W + ix]
-                                               : x[(((size_t)n * a.H + iy) * a.W + ix) * a.C_in + c0 + j];
-                    }
-                }
-                // the 16 weight codes of this half: two words of the 4-bit container format
-                uint32_t b[4];
-                dsq_unpack4(wp[2 * kh], b[0], b[1]);
-                dsq_unpack4(wp[2 * kh + 1], b[2], b[3]);
-#pragma unroll
-                for (int j = 0; j < 16; ++j) {
+                for (int j = 0; j < 8; ++j) {
+                    float v = 0.f;                        // padding and channels >= C_in: the real number 0
+                    if (inside && c0 + j < a.C_in)
+                        v = x_nchw ? x[(((size_t)n * a.C_in + c0 + j) * a.H + iy) * a.W + ix]
+                                   : x[(((size_t)n * a.H + iy) * a.W + ix) * a.C_in + c0 + j];
                     const float code = (float)((b[j >> 2] >> (8 * (j & 3))) & 0xFFu);
-                    const float level = __builtin_fmaf(dw, code, lw);          // l_w + Dw*code, rounded once
-                    if (j & 1) acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(level, av[j], acc1, 0, 0, 0);
-                    else acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(level, av[j], acc0, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_fmaf(dw, code, lw), v, acc, 0, 0, 0);
                 }
             }
         }
+    return acc;
+}
+
+// zq of a channel: l/d on the grid on which every code + zq, code <= top, has 8
+// significant bits; 0 where no such grid holds the integers (|l| >> d, or d = 0).
+__device__ __forceinline__ float centre_of(float l, float d, int top)
+{
+    const double z = (double)l / (double)d;
+    const double m = __builtin_fmax(__builtin_fabs(z), __builtin_fabs(z + top));
+    if (!(m < 256.0)) return 0.0f;
+    int e = 0;                                            // 2^(e-1) <= m < 2^e (m >= top/2)
+    if (m < 1.0) e = 0;
+    else while (m >= (double)(1 << e)) ++e;
+    const double grid = (double)(1 << e) / 256.0;
+    return (float)(__builtin_rint(z / grid) * grid);
+}
+
+// WP x WC waves of PF x CT 32x32 tiles; KW > 1: the waves share one such block and
+// take every KW-th 16-channel step of K (layers that yield few blocks).
+// VEC: NHWC activations with whole float4s (C_in a multiple of 4).
+template <int R, int WP, int WC, int KW, int PF, int CT, int OCC, bool VEC>
+__global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const float *__restrict__ x, int x_nchw, int top, WqPlan pl)
+{
+    constexpr int T = R * R;
+    constexpr int KC = kc_of(R), G = KC / 8, STEPS = T * KC / 16, NS = (STEPS + KW - 1) / KW;
+    constexpr int PIXB = pixel_bytes(R);
+    constexpr int BP = 32 * PF * WP, BC = 32 * CT * WC;
+    static_assert(WP * WC * KW == 4 && (KW == 1 || KW == 4) && BC <= 256, "four waves per workgroup");
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    float *sx_lds = reinterpret_cast<float *>(lds + tables_at(R, KW, PF * CT, pl.npx));
+    int *addr_lds = reinterpret_cast<int *>(sx_lds + G * pl.npx);
+    float *zq_lds = reinterpret_cast<float *>(addr_lds + pl.npx);
+    float *dw_lds = zq_lds + BC, *lr_lds = dw_lds + BC;
+    int *max_lds = reinterpret_cast<int *>(lr_lds + BC);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, h = lane >> 5;
+    const int kw = KW == 1 ? 0 : wave, wp = KW == 1 ? wave % WP : 0, wc = KW == 1 ? wave / WP : 0;
+
+    // every XCD (workgroups are dealt to them in turn) gets a contiguous range of tiles
+    const int logical = ((int)blockIdx.x & 7) * pl.xcd_chunk + ((int)blockIdx.x >> 3);
+    if (logical >= pl.total_blocks) return;
+    int blk_c, tile_w, tc0, oh0;
+    const int blk_p = dsq_idiv(logical, pl.tiles_c, pl.mg_tiles_c, blk_c);
+    const int t0 = dsq_idiv(blk_p, pl.tiles_w, pl.mg_tiles_w, tile_w) * BP;
+    const int ow0 = tile_w * pl.TW, NHo = a.N * a.Ho;
+    const int gr0 = dsq_idiv(t0, pl.TW, pl.mg_TW, tc0);
+    const int n0 = dsq_idiv(gr0, a.Ho, pl.mg_Ho, oh0);
+    const int v0 = n0 * pl.Hp + oh0 * a.stride;           // first padded input row of the patch
+    const int ct0 = blk_c * (BC / 32) + wc * CT;
+    const int NCB = a.Cp / 64;
+
+    // ---- tables: where the patch pixels are, and the channels' constants ---------
+    for (int p = tid; p < pl.npx; p += 256) {
+        int n, ih, iw;
+        bool ok;
+        if (R == 1) {
+            int tc, oh;
+            const int gr = dsq_idiv(t0 + p, pl.TW, pl.mg_TW, tc);
+            n = dsq_idiv(gr, a.Ho, pl.mg_Ho, oh);
+            ok = gr < NHo;
+            ih = oh * a.stride; iw = tc * a.stride;
+        } else {
+            int pcol;
+            const int prow = dsq_idiv(p, pl.PC, pl.mg_PC, pcol);
+            n = dsq_idiv(v0 + prow, pl.Hp, pl.mg_Hp, ih);
+            ih -= a.pad; iw = ow0 * a.stride + pcol - a.pad;
+            ok = n < a.N && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
+        }
+        addr_lds[p] = !ok ? -1 : x_nchw ? (n * a.C_in * a.H + ih) * a.W + iw : ((n * a.H + ih) * a.W + iw) * a.C_in;
     }
-    if (!valid) return;
+    if (tid < BC) {
+        const float d = a.delta_w[blk_c * BC + tid], l = a.l_w[blk_c * BC + tid];      // (Cop covers them)
+        const float zq = centre_of(l, d, top);
+        zq_lds[tid] = zq;
+        dw_lds[tid] = d;
+        lr_lds[tid] = (float)((double)l - (double)d * (double)zq);
+    }
+    if (tid == 0) *max_lds = 0;
+    __syncthreads();
+
+    // ---- the lane's pixels and weight rows ----------------------------------------
+    int frag_off[PF], frag_pp[PF], frag_m[PF], frag_n[PF], frag_y[PF], frag_x[PF];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int f = 0; f < PF; ++f) {
+        const int p = (wp * PF + f) * 32 + col;
+        int tc, oh;
+        const int gr = dsq_idiv(t0 + p, pl.TW, pl.mg_TW, tc);
+        const int n = dsq_idiv(gr, a.Ho, pl.mg_Ho, oh);
+        const bool ok = gr < NHo && ow0 + tc < a.Wo;
+        frag_m[f] = ok ? gr * a.Wo + ow0 + tc : -1;
+        frag_n[f] = n; frag_y[f] = oh; frag_x[f] = ow0 + tc;
+        // (pixels past the end multiply patch pixel 0 and are never stored)
+        frag_pp[f] = R == 1 ? p : ok ? (n * pl.Hp + oh * a.stride - v0) * pl.PC + tc * a.stride : 0;
+        frag_off[f] = frag_pp[f] * PIXB + 32 * h;
+    }
+    float zq[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) zq[c] = zq_lds[(wc * CT + c) * 32 + col];
+
+    v16f acc[PF][CT];
+#pragma unroll
+    for (int f = 0; f < PF; ++f)
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[f][c][r] = 0.f;
+
+    // ---- staging ---------------------------------------------------------------------
+    const int HW = a.H * a.W;
+    uint32_t max_bits = 0, seen = 0;                      // largest |x|; all weight words or'ed together
+    auto put = [&](int px, int g, bool first, const float (&v)[8]) {
+        uint32_t hi[8], mid[8], lo[8];
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t b = __float_as_uint(v[j]);
+            max_bits = max(max_bits, b & 0x7FFFFFFFu);
+            hi[j] = b & 0xFFFF0000u;
+            const float r1 = v[j] - __uint_as_float(hi[j]);
+            mid[j] = __float_as_uint(r1) & 0xFFFF0000u;
+            lo[j] = __float_as_uint(r1 - __uint_as_float(mid[j]));
+            s += v[j];
+        }
+        v4i w[3];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int o = ct * 32 + 8 * q + 4 * h + j;
-            if (o < a.C_out) {
-                const float v = acc0[4 * q + j] + acc1[4 * q + j];
-                if (a.out_nchw) a.out[(((size_t)n * a.C_out + o) * a.Ho + oy) * a.Wo + ox] = v;
-                else a.out[(size_t)m * a.C_out + o] = v;
+            w[0][j] = (int)__builtin_amdgcn_perm(hi[2 * j + 1], hi[2 * j], 0x07060302u);
+            w[1][j] = (int)__builtin_amdgcn_perm(mid[2 * j + 1], mid[2 * j], 0x07060302u);
+            w[2][j] = (int)__builtin_amdgcn_perm(lo[2 * j + 1], lo[2 * j], 0x07060302u);
+        }
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<v4i *>(lds + px * PIXB + p * KC * 2 + g * 16) = w[p];
+        sx_lds[g * pl.npx + px] = first ? s : sx_lds[g * pl.npx + px] + s;
+    };
+    // Unit k of a thread: one patch pixel, 8 channels.  NHWC with whole float4s: a thread keeps
+    // its channels and the G groups of a pixel sit in neighbouring lanes; otherwise (NCHW, odd
+    // C_in) a wave keeps its channels and its lanes run along the pixels.
+    const int n_units = VEC ? (pl.npx + 256 / G - 1) / (256 / G) : (pl.npx + 63) / 64 * (G / 4);
+    auto unit_px = [&](int k) { return VEC ? tid / G + k * (256 / G) : lane + k / (G / 4) * 64; };
+    auto unit_g = [&](int k) { return VEC ? tid % G : wave + 4 * (k % (G / 4)); };
+    // (branch-free: what does not exist reads the tensor's first values and is blanked below)
+    auto load_unit = [&](int k, int st, float (&v)[8]) {
+        const int q = unit_px(k), c0 = st * KC + 8 * unit_g(k);
+        const int ad = q < pl.npx ? addr_lds[q] : -1;
+        const float *p = x + (ad >= 0 ? ad : 0);
+        if constexpr (VEC) {
+            const v4f lo4 = *reinterpret_cast<const v4f *>(p + (c0 < a.C_in ? c0 : 0));
+            const v4f hi4 = *reinterpret_cast<const v4f *>(p + (c0 + 4 < a.C_in ? c0 + 4 : 0));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { v[j] = lo4[j]; v[4 + j] = hi4[j]; }
+        } else {
+            const int cs = x_nchw ? HW : 1;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = p[c0 + j < a.C_in ? (size_t)(c0 + j) * cs : 0];
+        }
+    };
+    auto put_unit = [&](int k, int st, const float (&raw)[8]) {
+        const int q = unit_px(k), g = unit_g(k), c0 = st * KC + 8 * g;
+        if (q >= pl.npx) return;
+        const bool on = addr_lds[q] >= 0;
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = on && c0 + j < a.C_in ? raw[j] : 0.f;
+        put(q, g, st == 0, v);
+    };
+    const int stages = (a.C_in + KC - 1) / KC;
+    for (int st = 0; st < stages; ++st) {
+        // the stage's weight words of this wave: step s = tap, 16-channel slice
+        const int cb = st * KC / 64;
+        uint32_t wreg[NS][CT];
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            int s = kw + KW * j;
+            if (KW > 1 && s >= STEPS) s = STEPS - 1;
+            const int t = s / (KC / 16), sl = s % (KC / 16) + (KC == 32 ? 2 * (st & 1) : 0);
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+                wreg[j][c] = ((const uint32_t *)a.wq)[((((size_t)(ct0 + c) * NCB + cb) * T + t) * 64 + lane) * 4 + sl];
+        }
+        if (st > 0) __syncthreads();                      // every wave is done with the previous patch
+        // (loads of NU units are in flight together.  Fetching the next stage's patch under the
+        // multiplication instead, with the registers that takes, measured 5-15 % slower: the
+        // workgroups that share a CU hide each other's loads)
+        constexpr int NU = VEC ? 4 : 2;
+        for (int k = 0; k < n_units; k += NU) {
+            float v[NU][8];
+#pragma unroll
+            for (int u = 0; u < NU; ++u) load_unit(k + u, st, v[u]);
+#pragma unroll
+            for (int u = 0; u < NU; ++u) put_unit(k + u, st, v[u]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            const int s = kw + KW * j;
+            if (KW > 1 && s >= STEPS) break;
+            const int t = s / (KC / 16), sl = s % (KC / 16);
+            // slice sl of the stage: the lane's 8 channels are group 2*h + (sl & 1) of half sl / 2
+            const int off = ((t / R) * pl.PC + t % R) * (R == 1 ? 0 : PIXB) + (sl >> 1) * 64 + (sl & 1) * 16;
+            v8bf xf[PF][3];
+#pragma unroll
+            for (int f = 0; f < PF; ++f)
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    xf[f][p] = *reinterpret_cast<const v8bf *>(lds + frag_off[f] + off + p * KC * 2);
+            v8bf wf[CT];
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                uint32_t b[2];
+                dsq_unpack4(wreg[j][c], b[0], b[1]);
+                seen |= wreg[j][c];
+                v4i w;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float e0 = (float)((b[i >> 1] >> (16 * (i & 1))) & 0xFFu) + zq[c];
+                    const float e1 = (float)((b[i >> 1] >> (16 * (i & 1) + 8)) & 0xFFu) + zq[c];
+                    w[i] = (int)__builtin_amdgcn_perm(__float_as_uint(e1), __float_as_uint(e0), 0x07060302u);
+                }
+                wf[c] = __builtin_bit_cast(v8bf, w);
+            }
+#pragma unroll
+            for (int p = 2; p >= 0; --p)                  // small terms first
+#pragma unroll
+                for (int c = 0; c < CT; ++c)
+#pragma unroll
+                    for (int f = 0; f < PF; ++f)
+                        acc[f][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[c], xf[f][p], acc[f][c], 0, 0, 0);
+        }
+    }
+    // ---- epilogue -------------------------------------------------------------------
+    {
+        // codes wider than the layer's bits are not on the grid of zq: such a tile is not split either
+        if (seen & ~((uint32_t)top * 0x11111111u)) max_bits = 0x7FFFFFFFu;
+#pragma unroll
+        for (int sft = 32; sft >= 1; sft >>= 1) max_bits = max(max_bits, (uint32_t)__shfl_xor((int)max_bits, sft));
+        if (lane == 0) atomicMax(max_lds, (int)max_bits);
+    }
+    float sx[PF];                                         // sum of x under the pixel's taps
+#pragma unroll
+    for (int f = 0; f < PF; ++f) {
+        sx[f] = 0.f;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int g = 0; g < G; ++g) sx[f] += sx_lds[g * pl.npx + frag_pp[f] + (t / R) * pl.PC + t % R];
+    }
+    __syncthreads();                                      // the patch is free from here on
+    const uint32_t tile_max = (uint32_t)*max_lds;
+    const bool exact = tile_max >= 0x71800000u || (tile_max != 0 && tile_max < 0x21800000u);   // 2^100, 2^-60
+    const size_t plane = (size_t)a.Ho * a.Wo;
+    auto store4 = [&](int f, int o, const float (&v)[4]) {        // four consecutive channels of the lane's pixel
+        if (frag_m[f] < 0) return;
+        if (!a.out_nchw && (a.C_out & 3) == 0) {
+            if (o < a.C_out) *reinterpret_cast<v4f *>(a.out + (size_t)frag_m[f] * a.C_out + o) = (v4f){v[0], v[1], v[2], v[3]};
+            return;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (o + j < a.C_out) {
+                if (a.out_nchw) a.out[((size_t)frag_n[f] * a.C_out + o + j) * plane + (size_t)frag_y[f] * a.Wo + frag_x[f]] = v[j];
+                else a.out[(size_t)frag_m[f] * a.C_out + o + j] = v[j];
+            }
+    };
+    if (exact) {
+        // (uniform over the workgroup)
+        if (kw == 0)
+            for (int c = 0; c < CT; ++c) {
+                if ((ct0 + c) * 32 >= a.C_out) continue;
+#pragma unroll
+                for (int f = 0; f < PF; ++f) {
+                    const v16f r = wq_exact_tile(a, x, x_nchw, lane, ct0 + c, frag_m[f] >= 0, frag_n[f], frag_y[f], frag_x[f]);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const float v[4] = {r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]};
+                        store4(f, (ct0 + c) * 32 + 8 * q + 4 * h, v);
+                    }
+                }
+            }
+        return;
+    }
+    if constexpr (KW > 1) {
+        // the partial tiles of the four waves meet in LDS; wave w finishes channels 8w + 4h ..
+        v4f *part = reinterpret_cast<v4f *>(lds);         // [tile][wave][quarter][lane]
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+#pragma unroll
+            for (int c = 0; c < CT; ++c)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    part[(((f * CT + c) * KW + kw) * 4 + q) * 64 + lane] =
+                        (v4f){acc[f][c][4 * q], acc[f][c][4 * q + 1], acc[f][c][4 * q + 2], acc[f][c][4 * q + 3]};
+        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                v4f s = part[((f * CT + c) * KW * 4 + kw) * 64 + lane];
+#pragma unroll
+                for (int w = 1; w < KW; ++w) s += part[(((f * CT + c) * KW + w) * 4 + kw) * 64 + lane];
+                const int ol = c * 32 + 8 * kw + 4 * h;
+                float v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = __builtin_fmaf(dw_lds[ol + j], s[j], lr_lds[ol + j] * sx[f]);
+                store4(f, ct0 * 32 + ol, v);
+            }
+        return;
+    }
+    // NHWC: through this wave's slice of the idle patch area, so that a store
+    // instruction writes 128 consecutive bytes of 8 pixels.  NCHW: 32 lanes already
+    // hold 32 consecutive pixels of a channel.
+    char *mine = lds + wave * (32 * ROWB);
+    const bool staged = !a.out_nchw && (a.C_out & 3) == 0;
+#pragma unroll
+    for (int c = 0; c < CT; ++c)
+#pragma unroll
+        for (int f = 0; f < PF; ++f) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int ol = (wc * CT + c) * 32 + 8 * q + 4 * h;
+                float v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = __builtin_fmaf(dw_lds[ol + j], acc[f][c][4 * q + j], lr_lds[ol + j] * sx[f]);
+                if (staged) *reinterpret_cast<v4f *>(mine + col * ROWB + (8 * q + 4 * h) * 4) = (v4f){v[0], v[1], v[2], v[3]};
+                else store4(f, blk_c * BC + ol, v);
+            }
+            if (staged) {
+                // (LDS operations of one wave execute in order: no barrier needed)
+                const int o = (ct0 + c) * 32 + (lane & 7) * 4;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int p = k * 8 + (lane >> 3);
+                    const v4f t = *reinterpret_cast<const v4f *>(mine + p * ROWB + (lane & 7) * 16);
+                    const int m = __shfl(frag_m[f], p);
+                    if (m >= 0 && o < a.C_out) __builtin_nontemporal_store(t, reinterpret_cast<v4f *>(a.out + (size_t)m * a.C_out + o));
+                }
             }
         }
 }
 
+// ---- host side -------------------------------------------------------------------
+
+struct WqTile { int BP, BC, KW, tiles; };
+constexpr WqTile kSquare = {64, 64, 1, 1}, kRow = {64, 128, 1, 2}, kLarge = {128, 128, 1, 4}, kNarrow = {128, 32, 1, 1},
+                 kSplit = {32, 32, 4, 1};
+
+// Strip width: the patch costs about 8/54 of a tile pixel's matrix work per patch
+// pixel, and its LDS bytes decide how many workgroups share a CU.
+bool plan_wq(const DsqConvArgs &a, const WqTile &t, WqPlan &best, int &lds)
+{
+    const int NHo = a.N * a.Ho, Hp = a.H + 2 * a.pad;
+    double best_cost = 0.0;
+    bool found = false;
+    for (int TW = a.Wo; TW >= 1; --TW) {
+        if (a.R == 1 && TW != a.Wo) break;
+        const int tiles_w = (a.Wo + TW - 1) / TW;
+        const long long strip = (long long)NHo * TW;
+        const int row_tiles = (int)((strip + t.BP - 1) / t.BP);
+        const double tiles = (double)tiles_w * row_tiles;
+        if (found && tiles * t.BP * 54 > best_cost) continue;
+        WqPlan p;
+        p.TW = TW; p.Hp = Hp; p.tiles_w = tiles_w;
+        p.PC = a.R == 1 ? 1 : (TW - 1) * a.stride + a.R;
+        const long long npx = a.R == 1 ? t.BP : (long long)dsq_patch_rows(a, t.BP, TW, row_tiles) * p.PC;
+        if (npx > 1024) continue;
+        p.npx = (int)npx;
+        const int bytes = lds_bytes(a.R, t.KW, t.tiles, t.BC, p.npx);
+        if (bytes > 150 * 1024) continue;
+        const double cost = tiles * ((double)t.BP * 54 + (double)p.npx * 8) *
+                            (bytes <= 53 * 1024 ? 1.0 : bytes <= 80 * 1024 ? 1.15 : 1.6);
+        if (!found || cost < best_cost) {
+            found = true; best_cost = cost; best = p; lds = bytes;
+            best.total_blocks = (int)(tiles_w * (long long)row_tiles);
+        }
+    }
+    if (!found) return false;
+    best.tiles_c = (a.C_out + t.BC - 1) / t.BC;
+    const long long total = (long long)best.total_blocks * best.tiles_c;
+    if (total > 0x7FFFFF00LL / 8) return false;
+    best.total_blocks = (int)total;
+    best.xcd_chunk = (best.total_blocks + 7) / 8;
+    best.mg_TW = dsq_division_constant(best.TW); best.mg_PC = dsq_division_constant(best.PC);
+    best.mg_Hp = dsq_division_constant(best.Hp); best.mg_Ho = dsq_division_constant(a.Ho);
+    best.mg_tiles_w = dsq_division_constant(best.tiles_w); best.mg_tiles_c = dsq_division_constant(best.tiles_c);
+    return true;
+}
+
+template <int R, int WP, int WC, int KW, int PF, int CT, int OCC>
+hipError_t launch(const DsqConvArgs &a, const float *x, int x_nchw, const WqPlan &pl, int lds, hipStream_t stream)
+{
+    auto kern = !x_nchw && (a.C_in & 3) == 0 ? conv_wq_kernel<R, WP, WC, KW, PF, CT, OCC, true>
+                                             : conv_wq_kernel<R, WP, WC, KW, PF, CT, OCC, false>;
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
+    kern<<<dim3(8 * pl.xcd_chunk), 256, lds, stream>>>(a, x, x_nchw, (1 << a.bits) - 1, pl);
+    return hipGetLastError();
+}
+
 }  // namespace
 
+// Tile by shape, from a sweep over 1x1 and 3x3 layers of 49 to 200704 pixels and 16 to 512
+// channels (us, the tile named first against the one it was preferred to):
+//   128x32   at most 32 output channels: nothing wider is filled (16->24 at 120x120 x 10: 18 against 24)
+//   32x32    K split over the four waves, fewer than 160 tiles of 64x64: the others leave most of the
+//            chip idle (512->512 at 7x7 x 1: 30 against 49; from 196 tiles on it loses, 18 against 16)
+//   128x128  1x1 layers that still give 192 of them: staging is most of their time and wide tiles
+//            stage least (256->512 stride 2 at 28x28 x 64: 21 against 26)
+//   64x128   3x3 stride 2: a patch of four times the pixels, staged for twice the channels
+//            (64->128 at 56x56 x 64: 43 against 52)
+//   64x64    the rest: four workgroups on a CU cover each other's staging, and the last round of
+//            workgroups is short (128->128 at 28x28 x 64: 57 against 58 for 128x128, 8 images 16 against 31)
 hipError_t dsq_launch_conv_wq(const DsqConvArgs &a, const float *x, int x_nchw, hipStream_t stream)
 {
-    const int M = a.N * a.Ho * a.Wo;
-    dim3 grid((M + 31) / 32, (a.C_out + 127) / 128);
-    conv_wq_kernel<<<grid, 256, 0, stream>>>(a, x, x_nchw);
-    return hipGetLastError();
+    const long long M = (long long)a.N * a.Ho * a.Wo;
+    auto blocks = [&](const WqTile &t) { return ((M + t.BP - 1) / t.BP) * ((a.C_out + t.BC - 1) / t.BC); };
+    const bool wide = 4 * ((a.C_out + 127) / 128 * 128 - a.C_out) <= (a.C_out + 127) / 128 * 128;
+    WqPlan pl;
+    int lds = 0;
+    if (blocks(kSquare) >= 160) {
+        if (a.C_out <= 32 && plan_wq(a, kNarrow, pl, lds))
+            return a.R == 3 ? launch<3, 4, 1, 1, 1, 1, 4>(a, x, x_nchw, pl, lds, stream)
+                            : launch<1, 4, 1, 1, 1, 1, 4>(a, x, x_nchw, pl, lds, stream);
+        if (a.R == 1 && wide && blocks(kLarge) >= 192 && plan_wq(a, kLarge, pl, lds))
+            return launch<1, 2, 2, 1, 2, 2, 2>(a, x, x_nchw, pl, lds, stream);
+        if (a.R == 3 && a.stride == 2 && wide && blocks(kRow) >= 320 && plan_wq(a, kRow, pl, lds))
+            return launch<3, 2, 2, 1, 1, 2, 3>(a, x, x_nchw, pl, lds, stream);
+        if (plan_wq(a, kSquare, pl, lds))
+            return a.R == 3 ? launch<3, 2, 2, 1, 1, 1, 4>(a, x, x_nchw, pl, lds, stream)
+                            : launch<1, 2, 2, 1, 1, 1, 4>(a, x, x_nchw, pl, lds, stream);
+    }
+    // (its patch fits for every geometry: 32 pixels of images of one output column and row, at
+    // most 4 padded rows apart, are 32*4 rows of at most 4 columns)
+    if (!plan_wq(a, kSplit, pl, lds)) return hipErrorInvalidValue;
+    return a.R == 3 ? launch<3, 1, 1, 4, 1, 1, 4>(a, x, x_nchw, pl, lds, stream)
+                    : launch<1, 1, 1, 4, 1, 1, 4>(a, x, x_nchw, pl, lds, stream);
 }

@@ -1,0 +1,94 @@
+"""dsq_conv2d_wq on the bf16 matrix instruction: every tile shape at its edges, tiles whose
+activations leave the range of the three-term split, and weight ranges far from symmetric.
+Bounds as in test_gpu_weight_only (the classical one of a binary32 sum of K terms)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1908_05033_amd import binding as B
+from paper_1908_05033_amd import inputs
+from test_gpu_weight_only import check, run_wq
+
+pytestmark = pytest.mark.gpu
+
+TILES = [  # N, C_in, H, W, C_out, R, stride, pad
+    (16, 36, 28, 29, 70, 3, 1, 1),       # 64x64, 3x3
+    (16, 130, 28, 28, 100, 1, 1, 0),     # 64x64, 1x1
+    (4, 17, 56, 57, 24, 3, 1, 1),        # 128x32, 3x3, odd C_in
+    (4, 68, 56, 57, 32, 1, 1, 0),        # 128x32, 1x1
+    (16, 33, 57, 57, 256, 3, 2, 1),      # 64x128, stride 2
+    (32, 72, 28, 28, 200, 1, 1, 0),      # 128x128, 1x1
+    (2, 40, 57, 57, 70, 1, 2, 0),        # 32x32 split, stride 2
+    (300, 8, 1, 1, 9, 3, 1, 1),          # one-pixel images: 3 padded rows per output pixel
+    (40, 12, 2, 2, 40, 3, 2, 1),         # 4 padded rows per output row
+]
+
+
+@pytest.mark.parametrize("layouts", [(B.DSQ_NHWC, B.DSQ_NHWC), (B.DSQ_NCHW, B.DSQ_NCHW)])
+@pytest.mark.parametrize("geom", TILES)
+def test_tiles(geom, layouts):
+    N, Ci, H, W, Co, R, stride, pad = geom
+    layer, inp = inputs.small_random_case(sum(geom), N, Ci, H, W, Co, R, stride, pad, 4, l_a=-1.0, u_a=1.0)
+    bits = 1 + sum(geom) % 4
+    code = oracle.quantize_weights(inp["w"].numpy(), inp["l_w"], inp["u_w"], bits)
+    ref, scale = oracle.conv_weight_only(inp["x"].numpy(), code, inp["l_w"], inp["u_w"], bits, stride, pad)
+    check(run_wq(layer, inp["x"], inp["w"], inp["l_w"], inp["u_w"], bits, *layouts), ref, scale, Ci * R * R)
+
+
+@pytest.mark.parametrize("special", [np.inf, -np.inf, np.nan, 3.0e38, 2.0 ** 100])
+@pytest.mark.parametrize("geom", [(1, 20, 9, 10, 40, 3, 1, 1), (16, 36, 28, 28, 70, 3, 1, 1), (32, 72, 28, 28, 200, 1, 1, 0)])
+def test_values_past_the_split(geom, special):
+    """One such activation: the outputs it does not reach are ordinary, the others what binary64 gives
+    (level 1/8 at least: no product of 3e38 leaves binary32)."""
+    N, Ci, H, W, Co, R, stride, pad = geom
+    layer, inp = inputs.small_random_case(sum(geom), N, Ci, H, W, Co, R, stride, pad, 4, l_a=-1.0, u_a=1.0)
+    x = inp["x"].clone()
+    x[0, 3, 4, 5] = special
+    lw, uw = np.full(Co, -0.125, np.float32), np.full(Co, 0.375, np.float32)
+    code = oracle.quantize_weights(inp["w"].numpy(), lw, uw, 1)
+    w = torch.from_numpy(np.where(code > 0, 0.375, -0.125))
+    ref = torch.nn.functional.conv2d(x.double(), w, stride=stride, padding=pad).numpy()
+    scale = torch.nn.functional.conv2d(x.double().abs(), w.abs(), stride=stride, padding=pad).numpy()
+    got = run_wq(layer, x, inp["w"], lw, uw, 1)
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.isinf(got), np.isinf(ref)) and np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fine = np.isfinite(ref)
+    assert (np.abs(got[fine] - ref[fine]) <= (Ci * R * R + 2) * 2.0 ** -24 * scale[fine]).all()
+
+
+@pytest.mark.parametrize("size", [2.0 ** -61, 1e-30, 1e-33, 2.0 ** -59, 2.0 ** 99])
+def test_scaled_activations_give_scaled_outputs(size):
+    """Small and large tiles on both sides of the split's limits: the bound scales along."""
+    layer, inp = inputs.small_random_case(3, 4, 48, 30, 31, 40, 3, 1, 1, 4, l_a=-1.0, u_a=1.0)
+    x = (inp["x"] / inp["x"].abs().max() * size).float()
+    code = oracle.quantize_weights(inp["w"].numpy(), inp["l_w"], inp["u_w"], 2)
+    ref, scale = oracle.conv_weight_only(x.numpy(), code, inp["l_w"], inp["u_w"], 2, 1, 1)
+    check(run_wq(layer, x, inp["w"], inp["l_w"], inp["u_w"], 2), ref, scale, 48 * 9)
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+@pytest.mark.parametrize("lo,hi", [(0.0, 1.0), (5.0, 5.5), (-100.0, -99.9), (-1.0, 1e-3), (1000.0, 1000.01), (-3.3, 3.0), (1e-20, 3e-20)])
+def test_weight_ranges(lo, hi, bits):
+    layer, inp = inputs.small_random_case(11, 2, 40, 12, 13, 36, 3, 1, 1, 4, l_a=-1.0, u_a=1.0)
+    lw, uw = np.full(36, lo, np.float32), np.full(36, hi, np.float32)
+    codes = np.random.default_rng(bits).integers(0, 1 << bits, (36, 40, 3, 3)).astype(np.uint8)
+    ref, scale = oracle.conv_weight_only(inp["x"].numpy(), codes, lw, uw, bits, 1, 1)
+    check(run_wq(layer, inp["x"], inp["w"], lw, uw, bits, w_codes=codes), ref, scale, 40 * 9)
+
+
+def test_codes_wider_than_the_descriptor_says():
+    """The levels come from the packed codes and the side table; `bits` of the descriptor is only a promise."""
+    layer, inp = inputs.small_random_case(12, 2, 40, 12, 13, 36, 3, 1, 1, 4, l_a=-1.0, u_a=1.0)
+    L = layer
+    lw, uw = np.full(36, -1.37, np.float32), np.full(36, 1.1, np.float32)
+    codes = np.random.default_rng(0).integers(0, 16, (36, 40, 3, 3)).astype(np.uint8)
+    ref, scale = oracle.conv_weight_only(inp["x"].numpy(), codes, lw, uw, 4, 1, 1)
+    wp = torch.empty(B.dsq_wgt_packed_bytes(36, 40, 3, 3, 4), dtype=torch.uint8, device="cuda")
+    aux = torch.empty(B.dsq_wgt_aux_bytes(36, 3, 3), dtype=torch.uint8, device="cuda")
+    B.dsq_pack_weights_for(None, torch.from_numpy(lw).cuda(), torch.from_numpy(uw).cuda(), torch.from_numpy(codes).cuda(),
+                           36, 40, 3, 3, 4, 4, wp, aux)
+    out = torch.empty((2, L.Ho, L.Wo, 36), device="cuda")
+    B.dsq_conv2d_wq(B.make_desc(2, 40, 12, 13, 36, 3, 3, 1, 1, 1), inp["x"].permute(0, 2, 3, 1).contiguous().cuda(), B.DSQ_NHWC,
+                    wp, aux, out, B.DSQ_NHWC)
+    check(out.cpu().numpy().transpose(0, 3, 1, 2), ref, scale, 40 * 9)
