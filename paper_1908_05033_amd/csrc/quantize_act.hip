@@ -4,10 +4,10 @@
 // needs for the l_w zero-point term.
 //
 // The kernels are bound by HBM traffic (4 B read and container/8 B written per
-// element).  The NHWC kernels evaluate the recipe in its step-function form
-// (thresholds found on the host with the recipe itself: exactly the same codes,
-// without the IEEE division, which costs more than the memory time per element);
-// the NCHW kernel divides.
+// element).  They evaluate the recipe in its step-function form (thresholds found
+// on the host with the recipe itself: exactly the same codes, without the IEEE
+// division, which costs more than the memory time per element), small NHWC
+// tensors excepted.
 #include "dsq_device.h"
 #include "dsq_kernels.h"
 
@@ -262,43 +262,124 @@ __global__ __launch_bounds__(256) void quantize_act_nhwc_coalesced_kernel(
     }
 }
 
-// NCHW input.  Lanes run along the pixels of one image plane (contiguous in
-// memory for a fixed channel), the four waves of a block take every fourth
-// packed word of those pixels.
+// NHWC input of few, deep pixels (the input of a fully connected layer): a block of 1024
+// threads owns one pixel, and a thread has the loads of U packed words in flight.  Bound by
+// the latency of the 4*C bytes that one compute unit reads.  C is a multiple of 4.
 template <int CONT>
-__global__ __launch_bounds__(256) void quantize_act_nchw_kernel(
+__global__ __launch_bounds__(1024) void quantize_act_deep_kernel(const float *__restrict__ x, uint32_t *__restrict__ codes,
+                                                                 int32_t *__restrict__ pix_sum, int C, int DP, float l, float u,
+                                                                 int top, DsqThresholds th)
+{
+    constexpr int CPD = 32 / CONT, FPW = CPD / 4;    // channels and float4 groups per packed word
+    constexpr int MODE = CONT == 2 ? 1 : 2, U = 8 / FPW;
+    __shared__ int part[16];
+    __shared__ float2 tpairs[16];
+    const QuantParams qp = {l, u, 0.f, th.inv_delta, th.thr[1], th.thr[2], th.thr[3], top};
+    if (MODE == 2) fill_threshold_pairs(tpairs, th);
+    __syncthreads();
+    const int tid = threadIdx.x;
+    const float *px = x + (size_t)blockIdx.x * C;
+    uint32_t *row = codes + (size_t)blockIdx.x * DP;
+    int sum = 0;
+    for (int base = tid; base < DP; base += 1024 * U) {
+        float4 f[U][FPW];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int g = 0; g < FPW; ++g) {
+                const int c = (base + k * 1024) * CPD + 4 * g;
+                f[k][g] = *reinterpret_cast<const float4 *>(px + (c < C ? c : 0));      // (blanked below)
+            }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int d = base + k * 1024;
+            uint32_t word = 0;
+#pragma unroll
+            for (int g = 0; g < FPW; ++g) {
+                const uint32_t b = dsq_bytes4(qcode<MODE>(f[k][g].x, qp, tpairs), qcode<MODE>(f[k][g].y, qp, tpairs),
+                                              qcode<MODE>(f[k][g].z, qp, tpairs), qcode<MODE>(f[k][g].w, qp, tpairs));
+                const uint32_t m = d * CPD + 4 * g < C ? b : 0u;
+                word |= m << (CONT * g);
+                sum += dsq_bytesum(m);
+            }
+            if (d < DP) row[d] = word;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off);
+    if ((tid & 63) == 0) part[tid >> 6] = sum;
+    __syncthreads();
+    if (tid == 0) {
+        int s = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) s += part[w];
+        pix_sum[blockIdx.x] = s;
+    }
+}
+
+// NCHW input.  Lanes run along 64 pixels of one image plane (contiguous in memory for a
+// fixed channel); the NW waves of a block take the packed words of those pixels in turn.
+// The words of up to 64 per pixel meet in LDS, from where the block writes them out as the
+// contiguous run that 64 pixels of the packed tensor are (lanes that store one word each
+// touch 64 separate rows per instruction).  Step-function form of the recipe, as in the NHWC
+// kernels.
+template <int CONT, int NW>
+__global__ __launch_bounds__(64 * NW) void quantize_act_nchw_kernel(
     const float *__restrict__ x, uint32_t *__restrict__ codes, int32_t *__restrict__ pix_sum,
-    int C, int HW, int DP, float l, float u, int top)
+    int C, int HW, int DP, float l, float u, int top, DsqThresholds th)
 {
     constexpr int CPD = 32 / CONT;
-    __shared__ int ssum[4][64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int hw = blockIdx.x * 64 + lane;
+    constexpr int MODE = CONT == 2 ? 1 : 2;
+    constexpr int MOST = 64;                         // words per pixel and pass
+    __shared__ uint32_t words[64 * (MOST + 1)];      // (odd row length: no bank conflicts)
+    __shared__ int ssum[NW][64];
+    __shared__ float2 tpairs[16];
+    const QuantParams qp = {l, u, 0.f, th.inv_delta, th.thr[1], th.thr[2], th.thr[3], top};
+    if (MODE == 2) {
+        fill_threshold_pairs(tpairs, th);
+        __syncthreads();
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int hw0 = blockIdx.x * 64;
+    const int npix = min(64, HW - hw0);
     const int n = blockIdx.y;
-    const bool active = hw < HW;
-    const float delta = dsq_delta(l, u, top);
+    const float *xn = x + (size_t)n * C * HW + hw0 + min(lane, npix - 1);
+    const size_t pixel0 = (size_t)n * HW + hw0;
     int s = 0;
-    if (active) {
-        const float *xn = x + (size_t)n * C * HW + hw;
-        uint32_t *crow = codes + ((size_t)n * HW + hw) * DP;
-        for (int d = wave; d < DP; d += 4) {
+    for (int d0 = 0; d0 < DP; d0 += MOST) {
+        const int nd = min(MOST, DP - d0);           // a multiple of 4, like DP
+        for (int d = wave; d < nd; d += NW) {
+            const int c0 = (d0 + d) * CPD;
+            float v[CPD];
+#pragma unroll
+            for (int j = 0; j < CPD; ++j) v[j] = xn[(size_t)(c0 + j < C ? c0 + j : 0) * HW];
             uint32_t word = 0;
 #pragma unroll
             for (int j = 0; j < CPD; ++j) {
-                int c = d * CPD + j;
-                int q = 0;
-                if (c < C) q = dsq_code(xn[(size_t)c * HW], l, u, delta, top);
+                const int q = c0 + j < C ? qcode<MODE>(v[j], qp, tpairs) : 0;
                 s += q;
                 // channel j of the word sits in byte j%4 at bit offset CONT*(j/4)
                 word |= (uint32_t)q << (8 * (j & 3) + CONT * (j >> 2));
             }
-            crow[d] = word;
+            words[lane * (MOST + 1) + d] = word;
         }
+        __syncthreads();
+        const int quads = nd / 4;
+        for (int i = tid; i < npix * quads; i += 64 * NW) {
+            const int p = i / quads, d = 4 * (i - p * quads);
+            const uint32_t *w = words + p * (MOST + 1) + d;
+            *reinterpret_cast<uint4 *>(codes + (pixel0 + p) * DP + d0 + d) = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+        if (d0 + MOST < DP) __syncthreads();         // before the next pass overwrites the words
     }
     ssum[wave][lane] = s;
     __syncthreads();
-    if (wave == 0 && active)
-        pix_sum[(size_t)n * HW + hw] = ssum[0][lane] + ssum[1][lane] + ssum[2][lane] + ssum[3][lane];
+    if (tid < npix) {
+        int t = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += ssum[w][tid];
+        pix_sum[pixel0 + tid] = t;
+    }
 }
 
 // ---- dense 3-bit output ---------------------------------------------------------
@@ -398,14 +479,18 @@ hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C
     const int Cp = dsq_round_up(C, 64);
     const int DP = Cp * cont / 32;
     const int total_pixels = N * H * W;
-    if (layout_nchw) {
+    // (one pixel per image: the two layouts are the same memory)
+    if (layout_nchw && H * W > 1) {
         dim3 grid((H * W + 63) / 64, N);
-        if (cont == 4)
-            quantize_act_nchw_kernel<4><<<grid, 256, 0, stream>>>(x, (uint32_t *)codes, pix_sum, C,
-                                                                  H * W, DP, l, u, top);
-        else
-            quantize_act_nchw_kernel<2><<<grid, 256, 0, stream>>>(x, (uint32_t *)codes, pix_sum, C,
-                                                                  H * W, DP, l, u, top);
+        // one wave per packed word of 64 pixels where a word is all a wave gets to load: 16 waves
+        // per block unless that leaves waves without a word, or the tensor fills the chip anyway
+        const bool many = DP >= 16 && (long long)grid.x * grid.y < 4096;
+#define DSQ_NCHW_LAUNCH(CONT, NW)                                                            \
+        quantize_act_nchw_kernel<CONT, NW><<<grid, 64 * NW, 0, stream>>>(                    \
+            x, (uint32_t *)codes, pix_sum, C, H * W, DP, l, u, top, th)
+        if (cont == 4) { if (many) DSQ_NCHW_LAUNCH(4, 16); else DSQ_NCHW_LAUNCH(4, 4); }
+        else           { if (many) DSQ_NCHW_LAUNCH(2, 16); else DSQ_NCHW_LAUNCH(2, 4); }
+#undef DSQ_NCHW_LAUNCH
         return hipGetLastError();
     }
     // Words per thread: few for small tensors (enough blocks to cover the
@@ -419,6 +504,13 @@ hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C
     int dp_shift = -1;
     if ((DP & (DP - 1)) == 0) { dp_shift = 0; while ((1 << dp_shift) < DP) ++dp_shift; }
     const bool vec = (C % 4 == 0) && (((uintptr_t)x & 15) == 0);
+    if (vec && DP >= 1024 && total_pixels <= 512) {
+        if (cont == 4)
+            quantize_act_deep_kernel<4><<<total_pixels, 1024, 0, stream>>>(x, (uint32_t *)codes, pix_sum, C, DP, l, u, top, th);
+        else
+            quantize_act_deep_kernel<2><<<total_pixels, 1024, 0, stream>>>(x, (uint32_t *)codes, pix_sum, C, DP, l, u, top, th);
+        return hipGetLastError();
+    }
     // The lane-contiguous kernel wins on tensors large enough to be bandwidth bound
     // (measured: 4.0 -> 5.0 TB/s at 2 bits); small ones are latency bound and do
     // better with the kernel below, which has less per-block set-up.
