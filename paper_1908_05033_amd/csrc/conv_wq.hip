@@ -494,12 +494,13 @@ hipError_t launch(const DsqConvArgs &a, const float *x, int x_nchw, const WqPlan
 //   128x32   at most 32 output channels: nothing wider is filled (16->24 at 120x120 x 10: 18 against 24)
 //   32x32    K split over the four waves, fewer than 160 tiles of 64x64: the others leave most of the
 //            chip idle (512->512 at 7x7 x 1: 30 against 49; from 196 tiles on it loses, 18 against 16)
-//   128x128  1x1 layers that still give 192 of them: staging is most of their time and wide tiles
-//            stage least (256->512 stride 2 at 28x28 x 64: 21 against 26)
+//   128x128  layers that still give 192 of them, 3x3 stride 2 excepted: least staging, and least LDS
+//            traffic per matrix instruction (128->128 at 28x28 x 64: 47 against 58; 1x1 256->512
+//            stride 2 at 28x28 x 64: 21 against 26)
 //   64x128   3x3 stride 2: a patch of four times the pixels, staged for twice the channels
 //            (64->128 at 56x56 x 64: 43 against 52)
 //   64x64    the rest: four workgroups on a CU cover each other's staging, and the last round of
-//            workgroups is short (128->128 at 28x28 x 64: 57 against 58 for 128x128, 8 images 16 against 31)
+//            workgroups is short (128->128 at 28x28 x 8: 16 against 31 for 128x128)
 hipError_t dsq_launch_conv_wq(const DsqConvArgs &a, const float *x, int x_nchw, hipStream_t stream)
 {
     const long long M = (long long)a.N * a.Ho * a.Wo;
@@ -511,8 +512,9 @@ hipError_t dsq_launch_conv_wq(const DsqConvArgs &a, const float *x, int x_nchw, 
         if (a.C_out <= 32 && plan_wq(a, kNarrow, pl, lds))
             return a.R == 3 ? launch<3, 4, 1, 1, 1, 1, 4>(a, x, x_nchw, pl, lds, stream)
                             : launch<1, 4, 1, 1, 1, 1, 4>(a, x, x_nchw, pl, lds, stream);
-        if (a.R == 1 && wide && blocks(kLarge) >= 192 && plan_wq(a, kLarge, pl, lds))
-            return launch<1, 2, 2, 1, 2, 2, 2>(a, x, x_nchw, pl, lds, stream);
+        if ((a.R == 1 || a.stride == 1) && wide && blocks(kLarge) >= 192 && plan_wq(a, kLarge, pl, lds))
+            return a.R == 3 ? launch<3, 2, 2, 1, 2, 2, 2>(a, x, x_nchw, pl, lds, stream)
+                            : launch<1, 2, 2, 1, 2, 2, 2>(a, x, x_nchw, pl, lds, stream);
         if (a.R == 3 && a.stride == 2 && wide && blocks(kRow) >= 320 && plan_wq(a, kRow, pl, lds))
             return launch<3, 2, 2, 1, 1, 2, 3>(a, x, x_nchw, pl, lds, stream);
         if (plan_wq(a, kSquare, pl, lds))

@@ -19,6 +19,7 @@ TILES = [  # N, C_in, H, W, C_out, R, stride, pad
     (4, 68, 56, 57, 32, 1, 1, 0),        # 128x32, 1x1
     (16, 33, 57, 57, 256, 3, 2, 1),      # 64x128, stride 2
     (32, 72, 28, 28, 200, 1, 1, 0),      # 128x128, 1x1
+    (33, 37, 28, 27, 100, 3, 1, 1),      # 128x128, 3x3
     (2, 40, 57, 57, 70, 1, 2, 0),        # 32x32 split, stride 2
     (300, 8, 1, 1, 9, 3, 1, 1),          # one-pixel images: 3 padded rows per output pixel
     (40, 12, 2, 2, 40, 3, 2, 1),         # 4 padded rows per output row
