@@ -41,7 +41,7 @@ struct FcLayout {
 };
 
 template <int CONT>
-__global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a)
+__global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, int tiles_m, int total, int xcd_chunk)
 {
     typedef FcLayout<CONT> Lay;
     constexpr int KB_BYTES = Lay::KB_BYTES;
@@ -54,9 +54,13 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a)
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int col = lane & 31, h = lane >> 5;
     const int M = a.N * a.Ho * a.Wo;             // = N*H*W: 1x1, stride 1, no padding
-    const int m0 = blockIdx.x * 32;
+    // Workgroups are dealt to the 8 XCDs in turn: every XCD gets a contiguous range of tiles, the
+    // pixel tiles of one channel tile together, so that its weights are read into one L2 only
+    const int logical = ((int)blockIdx.x & 7) * xcd_chunk + ((int)blockIdx.x >> 3);
+    if (logical >= total) return;
+    const int ct = logical / tiles_m;            // 32-channel tile; ct*32 < Cop by construction (Cop >= rq_Cp)
+    const int m0 = (logical - ct * tiles_m) * 32;
     const int m = m0 + col;
-    const int ct = blockIdx.y;                   // 32-channel tile; ct*32 < Cop by construction (Cop >= rq_Cp)
     const int NCB = a.Cp / 64;
     const size_t row_bytes = (size_t)a.Cp * CONT / 8;
     const uint32_t *wq = (const uint32_t *)a.wq + ((size_t)ct * NCB * 64 + lane) * 4;
@@ -74,31 +78,36 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a)
 #pragma unroll
     for (int r = 0; r < 16; ++r) { acc[r] = 0; facc[r] = 0.f; }
 
-    for (int base = cb0; base < cb1; base += FC_CHUNK) {
-        const int nblk = min(FC_CHUNK, cb1 - base);
-        // weights: already in lane order, one 16-byte load per channel block
-        v4i wp[FC_CHUNK];
+    // Loads of a chunk: weights are already in lane order, one 16-byte load per channel block;
+    // activations come as contiguous 16-byte units of PPI pixel rows per instruction.  Blocks and
+    // pixels past the end re-read the first one (no branch between the loads); such blocks are
+    // not multiplied, such pixels not stored.
+    auto load_weights = [&](int base, v4i (&wp)[FC_CHUNK]) {
 #pragma unroll
-        for (int i = 0; i < FC_CHUNK; ++i) {
-            wp[i] = (v4i){0, 0, 0, 0};
-            if (i < nblk) wp[i] = *reinterpret_cast<const v4i *>(wq + (size_t)(base + i) * 64 * 4);
-        }
-        // activations: contiguous 16-byte units of PPI pixel rows per instruction
-        v4i au[32 / PPI];
-        const bool unit_on = s_unit * 16 < nblk * KB_BYTES;
+        for (int i = 0; i < FC_CHUNK; ++i)
+            wp[i] = *reinterpret_cast<const v4i *>(wq + (size_t)min(base + i, cb1 - 1) * 64 * 4);
+    };
+    auto load_acts = [&](int base, v4i (&au)[32 / PPI]) {
+        const int off = base * KB_BYTES + s_unit * 16 < cb1 * KB_BYTES ? base * KB_BYTES + s_unit * 16 : 0;
 #pragma unroll
         for (int g = 0; g < 32 / PPI; ++g) {
             const int pm = m0 + g * PPI + s_pix;
-            au[g] = (v4i){0, 0, 0, 0};
-            if (unit_on && pm < M)
-                au[g] = *reinterpret_cast<const v4i *>((const char *)a.act + (size_t)pm * row_bytes +
-                                                       (size_t)base * KB_BYTES + s_unit * 16);
+            au[g] = *reinterpret_cast<const v4i *>((const char *)a.act + (size_t)(pm < M ? pm : m0) * row_bytes + off);
         }
+    };
+    v4i wa[FC_CHUNK], wb[FC_CHUNK], au[32 / PPI];
+    auto chunk = [&](int base, const v4i (&wp)[FC_CHUNK], v4i (&wn)[FC_CHUNK]) {
+        const int nblk = min(FC_CHUNK, cb1 - base);
 #pragma unroll
         for (int g = 0; g < 32 / PPI; ++g) {
             char *d = stage + (g * PPI + s_pix) * Lay::ROW + s_unit * 16;      // 8-byte aligned
             *reinterpret_cast<v2i *>(d) = (v2i){au[g].x, au[g].y};
             *reinterpret_cast<v2i *>(d + 8) = (v2i){au[g].z, au[g].w};
+        }
+        // the next chunk's loads are in flight while this one is multiplied
+        if (base + FC_CHUNK < cb1) {
+            load_weights(base + FC_CHUNK, wn);
+            load_acts(base + FC_CHUNK, au);
         }
         // (the region is private to this wave and LDS operations of a wave execute in order)
         const char *rowp = stage + col * Lay::ROW;
@@ -120,6 +129,15 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a)
                 }
             }
         }
+    };
+    if (cb0 < cb1) {
+        load_weights(cb0, wa);
+        load_acts(cb0, au);
+    }
+    // (two sets of weight registers in turn: a copy of the prefetched set would wait for it)
+    for (int base = cb0; base < cb1; base += 2 * FC_CHUNK) {
+        chunk(base, wa, wb);
+        if (base + FC_CHUNK < cb1) chunk(base + FC_CHUNK, wb, wa);
     }
     if (CONT == 2) acc = dsq_fp4_acc_to_int(facc);
 
@@ -188,14 +206,15 @@ hipError_t launch_fc(const DsqConvArgs &a, hipStream_t stream)
     }
     const int M = a.N * a.Ho * a.Wo;
     // (chained mode also writes the code-0 padding channels up to a multiple of 64)
-    dim3 grid((M + 31) / 32, ((a.rq ? a.rq_Cp : a.C_out) + 31) / 32);
+    const int tiles_m = (M + 31) / 32, total = tiles_m * (((a.rq ? a.rq_Cp : a.C_out) + 31) / 32);
+    const int xcd_chunk = (total + 7) / 8;
     // chained mode: the channel tiles add to the next layer's pixel sums, which a
     // fill kernel clears first unless the caller did (no memset node: the call may be under graph capture)
     if (a.rq && !a.rq_zeroed) {
         const hipError_t e = dsq_launch_fill_zero(a.rq_pix, (size_t)M, stream);
         if (e != hipSuccess) return e;
     }
-    kern<<<grid, 64 * FC_WAVES, lds, stream>>>(a);
+    kern<<<8 * xcd_chunk, 64 * FC_WAVES, lds, stream>>>(a, tiles_m, total, xcd_chunk);
     return hipGetLastError();
 }
 
