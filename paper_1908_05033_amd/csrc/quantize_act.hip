@@ -264,7 +264,8 @@ __global__ __launch_bounds__(256) void quantize_act_nhwc_coalesced_kernel(
 
 // NHWC input of few, deep pixels (the input of a fully connected layer): a block of 1024
 // threads owns one pixel, and a thread has the loads of U packed words in flight.  Bound by
-// the latency of the 4*C bytes that one compute unit reads.  C is a multiple of 4.
+// the latency of the 4*C bytes that one compute unit reads: 25088 channels x 64 pixels 7.1 us,
+// 12.6 with blocks of 256 threads and one word in flight each.  C is a multiple of 4.
 template <int CONT>
 __global__ __launch_bounds__(1024) void quantize_act_deep_kernel(const float *__restrict__ x, uint32_t *__restrict__ codes,
                                                                  int32_t *__restrict__ pix_sum, int C, int DP, float l, float u,
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(1024) void quantize_act_deep_kernel(const float *__
 // The words of up to 64 per pixel meet in LDS, from where the block writes them out as the
 // contiguous run that 64 pixels of the packed tensor are (lanes that store one word each
 // touch 64 separate rows per instruction).  Step-function form of the recipe, as in the NHWC
-// kernels.
+// kernels.  128 channels at 28x28 x 64: 10.1 us, 16.9 with word stores and divisions (29 MB).
 template <int CONT, int NW>
 __global__ __launch_bounds__(64 * NW) void quantize_act_nchw_kernel(
     const float *__restrict__ x, uint32_t *__restrict__ codes, int32_t *__restrict__ pix_sum,
