@@ -14,10 +14,12 @@
 // such terms have at most 16 bits and are exact; the sums are binary32.  Three matrix
 // instructions of 32 clk for 16 channels against eight of 64 clk.  Sums of centred
 // levels (and not of the codes themselves) keep the partial sums as small as those of
-// the levels.  The split needs the activations of a tile to stay clear of the ends of
-// the exponent range: a tile whose largest |x| is 2^100 or more (infinities and NaN
-// among them) or below 2^-60 is computed with the binary32 matrix instruction from
-// the levels themselves.
+// the levels.  The three terms of a number reach 23 binary places below it, past the
+// smallest bf16 number where |x| < 2^-110: the split is made of x * 2^54 (exact, as every
+// non-zero |x| is a multiple of 2^-149), whose terms and products are all normal numbers,
+// and Dw is scaled back.  A tile that holds an |x| of 2^46 or more (infinities and NaN
+// among them), or a step that cannot be scaled back exactly, is computed with the
+// binary32 matrix instruction from the levels themselves.
 //
 // A workgroup owns BP output pixels of a strip of TW columns (pixels are numbered row
 // by row through the batch) and BC output channels.  Per stage of KC input channels
@@ -45,8 +47,9 @@ struct WqPlan {
 __host__ __device__ constexpr int kc_of(int R) { return R == 3 ? 32 : 64; }              // channels per stage
 __host__ __device__ constexpr int pixel_bytes(int R) { return kc_of(R) * 6 + 16; }       // odd multiple of 16: 8 pixels in distinct banks
 constexpr int ROWB = 128 + 16;                                       // staged bytes per output pixel
+constexpr float kUp = 0x1p54f, kDown = 0x1p-54f;                     // scale of the split activations
 // LDS: [patch, then the epilogue's staging][channel-group sums of x][patch addresses]
-//      [zq, Dw, lr of BC channels][largest |x|]
+//      [zq, Dw * 2^-54, lr of BC channels][largest |x| * 2^54]
 __host__ __device__ constexpr int tables_at(int R, int KW, int tiles, int npx)
 {
     const int staging = KW > 1 ? KW * tiles * 4096 : 4 * 32 * ROWB;      // (tiles: 32x32 tiles of a wave)
@@ -161,11 +164,13 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
         }
         addr_lds[p] = !ok ? -1 : x_nchw ? (n * a.C_in * a.H + ih) * a.W + iw : ((n * a.H + ih) * a.W + iw) * a.C_in;
     }
+    bool unscalable = false;                              // Dw * 2^-54 is not exact (or Dw infinite)
     if (tid < BC) {
         const float d = a.delta_w[blk_c * BC + tid], l = a.l_w[blk_c * BC + tid];      // (Cop covers them)
         const float zq = centre_of(l, d, top);
         zq_lds[tid] = zq;
-        dw_lds[tid] = d;
+        dw_lds[tid] = d * kDown;
+        unscalable = __builtin_fabsf(d) == __builtin_inff() || (d != 0.0f && __builtin_fabsf(d) < 0x1p-72f);
         lr_lds[tid] = (float)((double)l - (double)d * (double)zq);
     }
     if (tid == 0) *max_lds = 0;
@@ -200,16 +205,18 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
 
     // ---- staging ---------------------------------------------------------------------
     const int HW = a.H * a.W;
-    uint32_t max_bits = 0, seen = 0;                      // largest |x|; all weight words or'ed together
+    uint32_t max_bits = unscalable ? 0x7FFFFFFFu : 0;     // largest |x| * 2^54, as its bits
+    uint32_t seen = 0;                                    // all weight words or'ed together
     auto put = [&](int px, int g, bool first, const float (&v)[8]) {
         uint32_t hi[8], mid[8], lo[8];
         float s = 0.f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const uint32_t b = __float_as_uint(v[j]);
+            const float z = v[j] * kUp;
+            const uint32_t b = __float_as_uint(z);
             max_bits = max(max_bits, b & 0x7FFFFFFFu);
             hi[j] = b & 0xFFFF0000u;
-            const float r1 = v[j] - __uint_as_float(hi[j]);
+            const float r1 = z - __uint_as_float(hi[j]);
             mid[j] = __float_as_uint(r1) & 0xFFFF0000u;
             lo[j] = __float_as_uint(r1 - __uint_as_float(mid[j]));
             s += v[j];
@@ -339,7 +346,7 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
     }
     __syncthreads();                                      // the patch is free from here on
     const uint32_t tile_max = (uint32_t)*max_lds;
-    const bool exact = tile_max >= 0x71800000u || (tile_max != 0 && tile_max < 0x21800000u);   // 2^100, 2^-60
+    const bool exact = tile_max >= 0x71800000u;           // |x| >= 2^46
     const size_t plane = (size_t)a.Ho * a.Wo;
     auto store4 = [&](int f, int o, const float (&v)[4]) {        // four consecutive channels of the lane's pixel
         if (frag_m[f] < 0) return;

@@ -58,6 +58,27 @@ def test_values_past_the_split(geom, special):
     assert (np.abs(got[fine] - ref[fine]) <= (Ci * R * R + 2) * 2.0 ** -24 * scale[fine]).all()
 
 
+@pytest.mark.parametrize("small", [2.0 ** -112, 2.0 ** -120, 2.0 ** -126, 2.0 ** -135])
+@pytest.mark.parametrize("geom", [(2, 36, 9, 24, 40, 3, 1, 1), (16, 36, 28, 32, 70, 3, 1, 1), (32, 72, 28, 32, 200, 1, 1, 0)])
+def test_small_activations_beside_ordinary_ones(geom, small):
+    """The right part of every image is tiny, the left ordinary, so that tiles hold both: the
+    outputs that reach only tiny activations keep the bound of their own products.  (Levels of
+    2^20: those outputs are normal numbers, and no absolute term hides an error.)"""
+    N, Ci, H, W, Co, R, stride, pad = geom
+    layer, inp = inputs.small_random_case(sum(geom), N, Ci, H, W, Co, R, stride, pad, 4, l_a=-1.0, u_a=1.0)
+    x = inp["x"].clone()
+    x[..., 10:] *= small / x.abs().max()
+    for bits, lo, hi in ((1, -2.0 ** 20, 2.0 ** 20), (2, -1.1e6, 0.7e6)):
+        lw, uw = np.full(Co, lo, np.float32), np.full(Co, hi, np.float32)
+        code = oracle.quantize_weights(inp["w"].numpy(), lw / 2.0 ** 22, uw / 2.0 ** 22, bits)
+        levels = lw[0].astype(np.float64) + (np.float64(uw[0] - lw[0]) / ((1 << bits) - 1)).astype(np.float32) * code.astype(np.float64)
+        w = torch.from_numpy(levels)
+        ref = torch.nn.functional.conv2d(x.double(), w, stride=stride, padding=pad).numpy()
+        scale = torch.nn.functional.conv2d(x.double().abs(), w.abs(), stride=stride, padding=pad).numpy()
+        got = run_wq(layer, x, inp["w"], lw, uw, bits, w_codes=code)
+        assert (np.abs(got - ref) <= (Ci * R * R + 2) * 2.0 ** -24 * scale).all()
+
+
 @pytest.mark.parametrize("size", [2.0 ** -61, 1e-30, 1e-33, 2.0 ** -59, 2.0 ** 99])
 def test_scaled_activations_give_scaled_outputs(size):
     """Small and large tiles on both sides of the split's limits: the bound scales along."""
@@ -66,6 +87,18 @@ def test_scaled_activations_give_scaled_outputs(size):
     code = oracle.quantize_weights(inp["w"].numpy(), inp["l_w"], inp["u_w"], 2)
     ref, scale = oracle.conv_weight_only(x.numpy(), code, inp["l_w"], inp["u_w"], 2, 1, 1)
     check(run_wq(layer, x, inp["w"], inp["l_w"], inp["u_w"], 2), ref, scale, 48 * 9)
+
+
+@pytest.mark.parametrize("size", [1e-38, 2.0 ** 45, 2.0 ** 46, 2.0 ** 47])
+def test_scaled_activations_at_the_ends_of_the_split(size):
+    # (not smaller ones: at 1e-44 half the spacing 2^-149 of the results themselves, 7e-46 rms 4e-46,
+    # is above the root-mean-square bound 4 * sqrt(432) * 2^-24 * 7e-44 = 3e-49)
+    test_scaled_activations_give_scaled_outputs(size)
+
+
+@pytest.mark.parametrize("bits", [1, 2, 3, 4])
+def test_steps_too_small_to_be_scaled(bits):
+    test_weight_ranges(-1e-22, 1e-22, bits)
 
 
 @pytest.mark.parametrize("bits", [1, 2, 3, 4])
