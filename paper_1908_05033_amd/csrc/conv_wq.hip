@@ -48,8 +48,9 @@ __host__ __device__ constexpr int kc_of(int R) { return R == 3 ? 32 : 64; }     
 __host__ __device__ constexpr int pixel_bytes(int R) { return kc_of(R) * 6 + 16; }       // odd multiple of 16: 8 pixels in distinct banks
 constexpr int ROWB = 128 + 16;                                       // staged bytes per output pixel
 constexpr float kUp = 0x1p54f, kDown = 0x1p-54f;                     // scale of the split activations
+constexpr uint32_t kMostBits = 0x71800000u;                          // 2^100: |x| = 2^46
 // LDS: [patch, then the epilogue's staging][channel-group sums of x][patch addresses]
-//      [zq, Dw * 2^-54, lr of BC channels][largest |x| * 2^54]
+//      [zq, Dw * 2^-54, lr of BC channels][whether the tile cannot be split]
 __host__ __device__ constexpr int tables_at(int R, int KW, int tiles, int npx)
 {
     const int staging = KW > 1 ? KW * tiles * 4096 : 4 * 32 * ROWB;      // (tiles: 32x32 tiles of a wave)
@@ -60,40 +61,102 @@ constexpr int lds_bytes(int R, int KW, int tiles, int BC, int npx)
     return tables_at(R, KW, tiles, npx) + npx * (kc_of(R) / 8 * 4 + 4) + 3 * BC * 4 + 16;
 }
 
-// One 32x32 tile with the binary32 matrix instruction: the levels themselves
-// (l_w + Dw*code, rounded once) times the activations.  Lane: pixel (n, oy, ox).
-__device__ __forceinline__ v16f wq_exact_tile(const DsqConvArgs &a, const float *x, int x_nchw, int lane, int ct, bool valid,
-                                              int n, int oy, int ox)
+// The wave's PF x CT tiles with the binary32 matrix instruction: the levels themselves
+// (l_w + Dw*code, rounded once) times the activations, both straight from global memory, in
+// steps of 8 channels of a tap and lane half (every KW-th one, from kw on).  A step's loads are in flight
+// while the one before is multiplied, and its fragments are shared by the wave's tiles.  A lane
+// belongs to pixel (py, px) of image n of each fragment (valid: there is one).
+// Bound by the matrix instruction (64 clk for 2 channels) and by rounds of workgroups.  An
+// infinity in every tile, against one wave per 32x32 tile with its loads waited for (us):
+// 128->128 3x3 at 28x28 x 64 188 -> 182, 64->64 at 56x56 x 64 240 -> 194, 512->512 at 7x7 x 1
+// 141 -> 66, 24->144 1x1 at 56x56 x 64 88 -> 73, 4096->4096 x 64 153 -> 96; 64->128 stride 2
+// at 56x56 x 64 101 -> 119 (two stages, one of them split in vain).
+template <int R, int KW, int PF, int CT, bool VEC>
+__device__ __forceinline__ void wq_exact_tiles(const DsqConvArgs &a, const float *__restrict__ x, int x_nchw, int lane, int kw, int ct0,
+                                               const int (&m)[PF], const int (&n)[PF], const int (&py)[PF], const int (&px)[PF],
+                                               v16f (&acc)[PF][CT])
 {
+    constexpr int T = R * R;
     const int col = lane & 31, h = lane >> 5;
-    const int T = a.R * a.R, NCB = a.Cp / 64;
-    const float dw = a.delta_w[ct * 32 + col], lw = a.l_w[ct * 32 + col];
-    const uint32_t *wq = (const uint32_t *)a.wq;
-    v16f acc;
+    const int NCB = a.Cp / 64;
+    // a lane half has 32 channels of a block in four words, 0..7 / 16..23 of it in the first: the last block's
+    // words that start past C_in are left out
+    const int rest = a.C_in - 64 * (NCB - 1), words = 1 + (rest > 8) + (rest > 32) + (rest > 40);
+    const int steps = ((NCB - 1) * 4 + words) * T;
+    const int live = (a.C_out + 31) / 32 - ct0;           // tiles with channels
+    const int cs = x_nchw ? a.H * a.W : 1, ps = x_nchw ? 1 : a.C_in;      // strides of channels and of pixels
+    int at[PF], taps[PF];                                 // of the pixel's first tap; bit t: tap t lies inside the image
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    for (int cb = 0; cb < NCB; ++cb)
-        for (int tap = 0; tap < T; ++tap) {
-            const int r = tap / a.R, s = tap % a.R;
-            const int iy = oy * a.stride - a.pad + r, ix = ox * a.stride - a.pad + s;
-            const bool inside = valid && iy >= 0 && iy < a.H && ix >= 0 && ix < a.W;
-            const uint32_t *wp = wq + ((((size_t)ct * NCB + cb) * T + tap) * 64 + lane) * 4;
-            for (int w = 0; w < 4; ++w) {                 // a word: 8 channels
-                const int c0 = 64 * cb + 32 * (w >> 1) + 16 * h + 8 * (w & 1);
-                uint32_t b[2];
-                dsq_unpack4(wp[w], b[0], b[1]);
+    for (int f = 0; f < PF; ++f) {
+        const int iy = py[f] * a.stride - a.pad, ix = px[f] * a.stride - a.pad;
+        at[f] = x_nchw ? (n[f] * a.C_in * a.H + iy) * a.W + ix : ((n[f] * a.H + iy) * a.W + ix) * a.C_in;
+        taps[f] = 0;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    float v = 0.f;                        // padding and channels >= C_in: the real number 0
-                    if (inside && c0 + j < a.C_in)
-                        v = x_nchw ? x[(((size_t)n * a.C_in + c0 + j) * a.H + iy) * a.W + ix]
-                                   : x[(((size_t)n * a.H + iy) * a.W + ix) * a.C_in + c0 + j];
-                    const float code = (float)((b[j >> 2] >> (8 * (j & 3))) & 0xFFu);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_fmaf(dw, code, lw), v, acc, 0, 0, 0);
-                }
+        for (int t = 0; t < T; ++t)
+            if (m[f] >= 0 && (unsigned)(iy + t / R) < (unsigned)a.H && (unsigned)(ix + t % R) < (unsigned)a.W) taps[f] |= 1 << t;
+    }
+    float dw[CT], lw[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) { dw[c] = a.delta_w[(ct0 + c) * 32 + col]; lw[c] = a.l_w[(ct0 + c) * 32 + col]; }
+#pragma unroll
+    for (int f = 0; f < PF; ++f)
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[f][c][r] = 0.f;
+
+    struct Step { v4f v[PF][2]; uint32_t w[CT]; bool inside[PF]; int c0; };
+    auto load = [&](int s, Step &st) {
+        const int t = s % T, w = s / T % 4, cb = s / T / 4;
+        st.c0 = 64 * cb + 32 * (w >> 1) + 16 * h + 8 * (w & 1);
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+            st.w[c] = ((const uint32_t *)a.wq)[((((size_t)(ct0 + c) * NCB + cb) * T + t) * 64 + lane) * 4 + w];
+#pragma unroll
+        for (int f = 0; f < PF; ++f) {
+            st.inside[f] = taps[f] >> t & 1;
+            // (branch-free: what does not exist reads the tensor's first values and is blanked below)
+            const float *p = x + (st.inside[f] ? at[f] + (t / R * a.W + t % R) * ps : 0);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int c = st.c0 + 4 * q;
+                if constexpr (VEC) st.v[f][q] = *reinterpret_cast<const v4f *>(p + (c < a.C_in ? c : 0));
+                else
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) st.v[f][q][j] = p[c + j < a.C_in ? (size_t)(c + j) * cs : 0];
             }
         }
-    return acc;
+    };
+    auto multiply = [&](const Step &st) {
+        float v[PF][8];                                   // padding and channels >= C_in: the real number 0
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                v[f][j] = st.inside[f] && st.c0 + (VEC ? j & 4 : j) < a.C_in ? st.v[f][j >> 2][j & 3] : 0.f;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            if (c >= live) continue;
+            uint32_t b[2];
+            dsq_unpack4(st.w[c], b[0], b[1]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float level = __builtin_fmaf(dw[c], (float)((b[j >> 2] >> (8 * (j & 3))) & 0xFFu), lw[c]);
+#pragma unroll
+                for (int f = 0; f < PF; ++f) acc[f][c] = __builtin_amdgcn_mfma_f32_32x32x2f32(level, v[f][j], acc[f][c], 0, 0, 0);
+            }
+        }
+    };
+    Step even, odd;
+    // (loads without a branch, the last step's again past the end: the compiler then knows how many
+    // are in flight behind the one it waits for)
+    load(min(kw, steps - 1), even);
+    for (int s = kw; s < steps; s += 2 * KW) {
+        load(min(s + KW, steps - 1), odd);
+        multiply(even);
+        load(min(s + 2 * KW, steps - 1), even);
+        if (s + KW < steps) multiply(odd);
+    }
 }
 
 // zq of a channel: l/d on the grid on which every code + zq, code <= top, has 8
@@ -126,7 +189,7 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
     int *addr_lds = reinterpret_cast<int *>(sx_lds + G * pl.npx);
     float *zq_lds = reinterpret_cast<float *>(addr_lds + pl.npx);
     float *dw_lds = zq_lds + BC, *lr_lds = dw_lds + BC;
-    int *max_lds = reinterpret_cast<int *>(lr_lds + BC);
+    int *whole_lds = reinterpret_cast<int *>(lr_lds + BC);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, h = lane >> 5;
@@ -173,7 +236,7 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
         unscalable = __builtin_fabsf(d) == __builtin_inff() || (d != 0.0f && __builtin_fabsf(d) < 0x1p-72f);
         lr_lds[tid] = (float)((double)l - (double)d * (double)zq);
     }
-    if (tid == 0) *max_lds = 0;
+    if (tid == 0) *whole_lds = 0;
     __syncthreads();
 
     // ---- the lane's pixels and weight rows ----------------------------------------
@@ -205,7 +268,7 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
 
     // ---- staging ---------------------------------------------------------------------
     const int HW = a.H * a.W;
-    uint32_t max_bits = unscalable ? 0x7FFFFFFFu : 0;     // largest |x| * 2^54, as its bits
+    uint32_t max_bits = unscalable ? kMostBits : 0;       // largest |x| * 2^54, as its bits
     uint32_t seen = 0;                                    // all weight words or'ed together
     auto put = [&](int px, int g, bool first, const float (&v)[8]) {
         uint32_t hi[8], mid[8], lo[8];
@@ -264,6 +327,7 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
         put(q, g, st == 0, v);
     };
     const int stages = (a.C_in + KC - 1) / KC;
+    int whole = 0;
     for (int st = 0; st < stages; ++st) {
         // the stage's weight words of this wave: step s = tap, 16-channel slice
         const int cb = st * KC / 64;
@@ -289,7 +353,9 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
 #pragma unroll
             for (int u = 0; u < NU; ++u) put_unit(k + u, st, v[u]);
         }
+        if (KW == 1 && max_bits >= kMostBits) *whole_lds = 1;
         __syncthreads();
+        if (KW == 1) whole = *whole_lds;                  // (looked at after the stage: its latency is covered)
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
             const int s = kw + KW * j;
@@ -326,15 +392,14 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
                     for (int f = 0; f < PF; ++f)
                         acc[f][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[c], xf[f][p], acc[f][c], 0, 0, 0);
         }
+        // (the same in all waves; not with KW = 4, whose stages are as short as the look is long: 64 -> 70 us
+        // for 4096->4096 x 64, and whose second pass is cheap.  Looking before the first stage's multiplication
+        // as well made the 128x128 tile 10 % slower on NCHW tensors)
+        if (KW == 1 && __builtin_amdgcn_readfirstlane(whole)) break;
     }
     // ---- epilogue -------------------------------------------------------------------
-    {
-        // codes wider than the layer's bits are not on the grid of zq: such a tile is not split either
-        if (seen & ~((uint32_t)top * 0x11111111u)) max_bits = 0x7FFFFFFFu;
-#pragma unroll
-        for (int sft = 32; sft >= 1; sft >>= 1) max_bits = max(max_bits, (uint32_t)__shfl_xor((int)max_bits, sft));
-        if (lane == 0) atomicMax(max_lds, (int)max_bits);
-    }
+    // codes wider than the layer's bits are not on the grid of zq: such a tile is not split either
+    if (max_bits >= kMostBits || (seen & ~((uint32_t)top * 0x11111111u))) *whole_lds = 1;
     float sx[PF];                                         // sum of x under the pixel's taps
 #pragma unroll
     for (int f = 0; f < PF; ++f) {
@@ -345,8 +410,7 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
             for (int g = 0; g < G; ++g) sx[f] += sx_lds[g * pl.npx + frag_pp[f] + (t / R) * pl.PC + t % R];
     }
     __syncthreads();                                      // the patch is free from here on
-    const uint32_t tile_max = (uint32_t)*max_lds;
-    const bool exact = tile_max >= 0x71800000u;           // |x| >= 2^46
+    const bool exact = __builtin_amdgcn_readfirstlane(*whole_lds) != 0;
     const size_t plane = (size_t)a.Ho * a.Wo;
     auto store4 = [&](int f, int o, const float (&v)[4]) {        // four consecutive channels of the lane's pixel
         if (frag_m[f] < 0) return;
@@ -361,22 +425,12 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
                 else a.out[(size_t)frag_m[f] * a.C_out + o + j] = v[j];
             }
     };
-    if (exact) {
-        // (uniform over the workgroup)
-        if (kw == 0)
-            for (int c = 0; c < CT; ++c) {
-                if ((ct0 + c) * 32 >= a.C_out) continue;
+    if (exact) {                                          // (uniform over the workgroup)
+        wq_exact_tiles<R, KW, PF, CT, VEC>(a, x, x_nchw, lane, kw, ct0, frag_m, frag_n, frag_y, frag_x, acc);
 #pragma unroll
-                for (int f = 0; f < PF; ++f) {
-                    const v16f r = wq_exact_tile(a, x, x_nchw, lane, ct0 + c, frag_m[f] >= 0, frag_n[f], frag_y[f], frag_x[f]);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float v[4] = {r[4 * q], r[4 * q + 1], r[4 * q + 2], r[4 * q + 3]};
-                        store4(f, (ct0 + c) * 32 + 8 * q + 4 * h, v);
-                    }
-                }
-            }
-        return;
+        for (int f = 0; f < PF; ++f) sx[f] = 0.f;
+        if (tid < BC) { dw_lds[tid] = 1.0f; lr_lds[tid] = 0.f; }
+        __syncthreads();
     }
     if constexpr (KW > 1) {
         // the partial tiles of the four waves meet in LDS; wave w finishes channels 8w + 4h ..

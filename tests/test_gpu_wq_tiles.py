@@ -58,6 +58,50 @@ def test_values_past_the_split(geom, special):
     assert (np.abs(got[fine] - ref[fine]) <= (Ci * R * R + 2) * 2.0 ** -24 * scale[fine]).all()
 
 
+@pytest.mark.parametrize("layouts", [(B.DSQ_NHWC, B.DSQ_NHWC), (B.DSQ_NCHW, B.DSQ_NCHW)])
+@pytest.mark.parametrize("geom", TILES + [(1, ci, 7, 9, 40, 3, 1, 1) for ci in (8, 9, 32, 33, 40, 41, 73)] +
+                         [(64, 24, 28, 28, 144, 1, 1, 0)])
+def test_every_tile_past_the_split(geom, layouts):
+    """Every tile holds such a value (2^48 here and there), so all of the layer runs on the binary32
+    instruction: all tile shapes, the words of a last channel block, tiles without channels."""
+    N, Ci, H, W, Co, R, stride, pad = geom
+    layer, inp = inputs.small_random_case(sum(geom), N, Ci, H, W, Co, R, stride, pad, 4, l_a=-1.0, u_a=1.0)
+    x = inp["x"].clone()
+    x.reshape(-1)[sum(geom) % 5::97] *= 2.0 ** 48
+    bits = 1 + sum(geom) % 4
+    code = oracle.quantize_weights(inp["w"].numpy(), inp["l_w"], inp["u_w"], bits)
+    ref, scale = oracle.conv_weight_only(x.numpy(), code, inp["l_w"], inp["u_w"], bits, stride, pad)
+    check(run_wq(layer, x, inp["w"], inp["l_w"], inp["u_w"], bits, *layouts), ref, scale, Ci * R * R)
+
+
+def test_time_of_tiles_past_the_split():
+    """An infinity in every tile sends them all to the binary32 instruction, a quarter of the speed: it
+    is used at its own rate (3.6 times the time of an ordinary tensor; 11 times when the tiles waited for
+    each load)."""
+    layer, inp = inputs.small_random_case(3, 64, 128, 28, 28, 128, 3, 1, 1, 4, l_a=-1.0, u_a=1.0)
+    wp = torch.empty(B.dsq_wgt_packed_bytes(128, 128, 3, 3, 4), dtype=torch.uint8, device="cuda")
+    aux = torch.empty(B.dsq_wgt_aux_bytes(128, 3, 3), dtype=torch.uint8, device="cuda")
+    B.dsq_pack_weights_for(inp["w"].cuda(), torch.from_numpy(inp["l_w"]).cuda(), torch.from_numpy(inp["u_w"]).cuda(), None,
+                           128, 128, 3, 3, 1, 4, wp, aux)
+    out = torch.empty((64, 28, 28, 128), device="cuda")
+    d = B.make_desc(64, 128, 28, 28, 128, 3, 3, 1, 1, 1)
+    took = []
+    for special in (1.0, np.inf):
+        x = inp["x"].permute(0, 2, 3, 1).contiguous().cuda()
+        x.view(-1)[::97] = special
+        best = np.inf
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                B.dsq_conv2d_wq(d, x, B.DSQ_NHWC, wp, aux, out, B.DSQ_NHWC)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        took.append(best)
+    assert took[1] < 7 * took[0], took
+
+
 @pytest.mark.parametrize("small", [2.0 ** -112, 2.0 ** -120, 2.0 ** -126, 2.0 ** -135])
 @pytest.mark.parametrize("geom", [(2, 36, 9, 24, 40, 3, 1, 1), (16, 36, 28, 32, 70, 3, 1, 1), (32, 72, 28, 32, 200, 1, 1, 0)])
 def test_small_activations_beside_ordinary_ones(geom, small):
