@@ -94,7 +94,7 @@ bool plan_patch(const DsqConvArgs &a, int BP, int BC, int PF, int CT, int UPT, i
         if (p.units > 256 * UPT) continue;
         p.aux_off = nbuf * KS * p.buf_bytes > epi_bytes ? nbuf * KS * p.buf_bytes : epi_bytes;
         const int lds_bytes = plan_lds_bytes(p, BC, a);
-        if (lds_bytes > lds_limit) continue;
+        if (plan_limit_bytes(p, BC, a) > lds_limit) continue;
         // equal work: prefer a footprint that lets three (else two) workgroups share a CU,
         // then the smaller patch, then the narrower strip
         const long long cost = tiles * 100000 + (lds_bytes <= 52 * 1024 ? 0 : lds_bytes <= 78 * 1024 ? 20000 : 40000) +
@@ -162,6 +162,7 @@ int pick_tile(const DsqConvArgs &a)
 }
 
 constexpr int kLdsLimit = 150 * 1024;
+static_assert(kLdsLimit + border_table_bytes(3, 128) <= 160 * 1024, "the tables for l_a != 0 fit beside the largest patch");
 
 }  // namespace
 

@@ -891,15 +891,24 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
 
 // ---- host side ---------------------------------------------------------------
 
+// tables behind the buffers: Da*Dw, Da*l_w (binary64), the patch pixels' code
+// sums; then the chained mode's scale, shift, quantizer thresholds and per-channel
+// constants of the code-unit form, or the general results' tables for l_a != 0
+constexpr int border_table_bytes(int R, int BC) { return 3 * BC * 8 + (R > 1 ? R * R * BC * 4 : 0); }
+
 inline int plan_lds_bytes(const PatchPlan &p, int BC, const DsqConvArgs &a)
 {
-    // tables behind the buffers: Da*Dw, Da*l_w (binary64), the patch pixels' code
-    // sums; then the chained mode's scale, shift, quantizer thresholds and per-channel
-    // constants of the code-unit form, or the general results' tables for l_a != 0
     const int tables = (p.aux_off + 2 * BC * 8 + p.PR * p.PC * 4 + 15) & ~15;
     const int chained = 2 * BC * 4 + 16 * 8 + BC * 16 + 16;
-    const int border = 3 * BC * 8 + (a.R > 1 ? a.R * a.R * BC * 4 : 0);
-    return tables + (a.rq ? chained : a.l_a != 0.0f ? border : 0);
+    return tables + (a.rq ? chained : a.l_a != 0.0f ? border_table_bytes(a.R, BC) : 0);
+}
+
+// What a plan is held against its limit with: the same for a layer with l_a != 0 as for one
+// with l_a = 0 (room for scale, shift and thresholds is always counted), so that which layers
+// and forced tiles the kernel takes does not depend on l_a.
+inline int plan_limit_bytes(const PatchPlan &p, int BC, const DsqConvArgs &a)
+{
+    return ((p.aux_off + 2 * BC * 8 + p.PR * p.PC * 4 + 15) & ~15) + 2 * BC * 4 + 16 * 8 + (a.rq ? BC * 16 + 16 : 0);
 }
 
 template <int CONT, int R, int WP, int WC, int PF, int CT, int UPT, int WD, int OCC, int KS, int OUT>

@@ -44,3 +44,14 @@ def test_same_bits_as_the_simple_kernel(geom, bits, la, layout):
                 continue                           # the tile does not take this layer
             assert np.array_equal(got[0], want[0]), kernel
             assert not with_acc or np.array_equal(got[1], want[1]), kernel
+
+
+@pytest.mark.parametrize("layout", [B.DSQ_NHWC, B.DSQ_NCHW])
+def test_largest_patch_with_the_tables_of_l_a(layout):
+    """The most LDS a launch asks for: a patch near the limit and the tables of l_a != 0 behind it."""
+    geom = (300, 512, 1, 3, 300, 3, 2, 2)
+    d = B.make_desc(*geom[:5], 3, 3, 2, 2, 2, B.DSQ_CONV_KERNEL(6))
+    assert int(B.dsq_conv2d_plan(d, l_a=-2.1).split()[-3]) > 150 * 1024
+    want = _run(geom, 2, B.DSQ_CONV_KERNEL(1), -2.1, layout, True)
+    got = _run(geom, 2, B.DSQ_CONV_KERNEL(6), -2.1, layout, True)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])

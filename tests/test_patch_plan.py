@@ -41,3 +41,22 @@ def test_patch_holds_the_rows_of_every_tile(seed):
         PR = int(re.search(r"patch (\d+)x", text).group(1))
         need = _rows_of_every_tile(N, H, Ho, stride, pad, R, TW, BP)
         assert need <= PR <= need + 2, text
+
+
+@pytest.mark.parametrize("geom,flags,l_a", [((300, 512, 2, 3, 64, 3, 3, 2, 2, 3), B.DSQ_CONV_ACT_DENSE3, -1.0),
+                                            ((300, 512, 2, 224, 128, 3, 3, 2, 1, 3), B.DSQ_CONV_ACT_DENSE3, -1.0),
+                                            ((300, 512, 1, 3, 300, 3, 3, 2, 2, 2), B.DSQ_CONV_KERNEL(6), -1.0)])
+def test_largest_patches_are_taken_for_any_l_a(geom, flags, l_a):
+    """The tables of a layer with l_a != 0 do not count against the patch."""
+    d = B.make_desc(*geom, flags)
+    assert B.dsq_conv2d_plan(d).startswith("patch kernel")
+    assert B.dsq_conv2d_plan(d, l_a=l_a).startswith("patch kernel")
+    assert int(re.search(r"(\d+) LDS bytes", B.dsq_conv2d_plan(d, l_a=l_a)).group(1)) <= 160 * 1024
+
+
+@pytest.mark.parametrize("l_a", [0.0, -1.0])
+def test_patches_past_the_limit_stay_refused(l_a):
+    d = B.make_desc(17, 200, 14, 14, 24, 3, 3, 2, 2, 3, B.DSQ_CONV_ACT_DENSE3 | B.DSQ_CONV_KERNEL(5))
+    with pytest.raises(B.DsqError) as e:
+        B.dsq_conv2d_plan(d, l_a=l_a)
+    assert e.value.status == 5
