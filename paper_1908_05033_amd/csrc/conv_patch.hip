@@ -4,48 +4,64 @@
 
 #include "conv_patch_kernel.h"
 
-// Patch rows of the worst tile: the padded-row span of its output rows plus the
-// filter.  A tile covers the strip pixels [t, t + BP), t a multiple of BP, i.e. d + 1
-// strip rows, and passes from one image to the next k times:
+// Patch rows of the worst tile: the padded-row span of its output rows plus the filter.
+// A tile covers the strip pixels [t, t + BP), t a multiple of BP, i.e. d + 1 strip rows,
+// and passes from one image to the next k times:
 //   span = d*stride + k*e,  e = Hp - Ho*stride  (the rows an image boundary adds).
-// Which tiles exist depends on t modulo the pixels of one image's strip, TW*Ho; as BP is
-// a power of two those residues are the multiples of G = gcd(BP, TW*Ho), so the maximum
-// needs a look at the few rows where d and k can both be largest instead of a walk over
-// all tiles (50 000 per strip width on a 224x224 layer at batch 32: the walk took 3.4 ms a
-// call there, 10 to 80 times the kernel).  For strips that do not hold every residue the
-// result may be a row or two above the exact value, which only costs LDS.
+// Exact (but for some 1x1 layers with stride 2 on odd heights, where e = -1 and the result can
+// be one row too large), without a walk over all tiles (50 000 per strip width on a 224x224
+// layer at batch 32: 3.4 ms a call, 10 to 80 times the kernel):
+//   - images smaller than a tile: t modulo the strip pixels of an image repeats after fewer
+//     than BP tiles;
+//   - otherwise a tile inside an image passes (BP - 1) / TW rows, and one more if it begins in
+//     one of the last columns: some tile does if they go through all the columns they can
+//     (multiples of the gcd of TW and BP), else their first columns tell; and only one tile
+//     crosses each image boundary: those tiles are looked at, until one spans the most that it
+//     can or the boundaries' places inside a tile repeat.
+// (A bound in place of the exact number, a row or two too large on some layers, had some of
+// the largest patches refused and others staged in more units per thread.)
 int dsq_patch_rows(const DsqConvArgs &a, int BP, int TW, int row_tiles)
 {
-    const int NHo = a.N * a.Ho, Hp = a.H + 2 * a.pad;
-    if (row_tiles <= 32) {                      // short strips: the tiles one by one
-        int PR = 0;
-        for (int tr = 0; tr < row_tiles; ++tr) {
-            const int tA = tr * BP, tB = tA + BP - 1;
-            int g0 = tA / TW, g1 = tB / TW;
-            if (g1 >= NHo) g1 = NHo - 1;
-            const int nA = g0 / a.Ho, nB = g1 / a.Ho;
-            const int rows = (nB * Hp + (g1 - nB * a.Ho) * a.stride) - (nA * Hp + (g0 - nA * a.Ho) * a.stride) + a.R;
-            if (rows > PR) PR = rows;
-        }
-        return PR;
-    }
-    const int image = TW * a.Ho, e = Hp - a.Ho * a.stride;
-    const int G = (image & -image) < BP ? (image & -image) : BP;         // gcd with a power of two
+    const int Ho = a.Ho, NHo = a.N * Ho, e = a.H + 2 * a.pad - Ho * a.stride;
+    const int image = TW * Ho;
+    const int G = (image & -image) < BP ? (image & -image) : BP;         // gcds with a power of two
     const int gw = (TW & -TW) < BP ? (TW & -TW) : BP;
-    const int d = (TW - gw + BP - 1) / TW;      // most row steps of a tile: from the last reachable column
-    if (a.N == 1) return d * a.stride + a.R;
-    const int k_few = d / a.Ho, k_most = (a.Ho - 1 + d) / a.Ho;
-    int span = d * a.stride + k_few * e;
-    if (e > 0 && k_most > k_few) {
-        // d row steps and k_most boundaries together: a residue in one of the last rows of
-        // the image, at a column from which d steps are reached
-        const int col = d * TW - BP + 1 > 0 ? d * TW - BP + 1 : 0;
-        bool both = false;
-        for (int row = k_most * a.Ho - d > 0 ? k_most * a.Ho - d : 0; row < a.Ho && !both; ++row)
-            both = ((row * TW + col + G - 1) & ~(G - 1)) < (row + 1) * TW;
-        const int one_less = (d - 1) * a.stride + k_most * e;
-        if (both) span = d * a.stride + k_most * e;
-        else if (one_less > span) span = one_less;
+    int span = 0;
+    auto look_at = [&](int t) {
+        const int g0 = t / TW, end = (t + BP - 1) / TW, g1 = end < NHo ? end : NHo - 1;
+        const int s = (g1 - g0) * a.stride + (g1 / Ho - g0 / Ho) * e;
+        if (s > span) span = s;
+    };
+    const int repeat = image / G, columns = TW / gw;
+    if (image < BP || (e < 0 && row_tiles <= columns)) {
+        for (int i = 0; i < row_tiles && i < repeat; ++i) look_at(i * BP);
+    } else {
+        int d = (BP - 1) / TW;
+        const int late = TW - (BP - 1) % TW, step = BP % TW;              // first column from which a tile passes d + 1 rows
+        if (row_tiles > columns) {
+            if (TW - gw >= late) ++d;
+        } else {
+            look_at((row_tiles - 1) * BP);                                // (cut off by the end of the strip)
+            if (row_tiles == 1) return span + a.R;
+            if (TW >= BP) {                                               // (the last whole tile step of the first row)
+                if (row_tiles - 1 > TW / BP) ++d;
+            } else for (int i = 1, c = 0; i < row_tiles - 1; ++i) {
+                c += step;
+                if (c >= TW) c -= TW;
+                if (c >= late) { ++d; break; }
+            }
+        }
+        if (d * a.stride > span) span = d * a.stride;
+        if (e < 0 && a.N > 1) {
+            // (a tile spans most rows inside an image: one that does has to begin in a row from which
+            // that many follow, at a column that reaches the last of them)
+            const int col = d * TW - BP + 1 > 0 ? d * TW - BP + 1 : 0;
+            bool inside = false;
+            for (int row = 0; row + d < Ho && row < G / gw && !inside; ++row)
+                inside = ((row * TW + col + G - 1) & -G) < (row + 1) * TW;
+            if (!inside) span -= a.stride;
+        }
+        for (int n = 1; n < a.N && n <= BP / G && span < d * a.stride + e; ++n) look_at((n * image - 1) & -BP);
     }
     return span + a.R;
 }
@@ -67,12 +83,17 @@ bool plan_patch(const DsqConvArgs &a, int BP, int BC, int PF, int CT, int UPT, i
     // a layer whose wave groups each see a single stage never touches the second
     // buffer of a group: leave it out, so that more workgroups fit a CU
     const int nbuf = a.Cp / 64 > KS ? 2 : 1;
+    const int e = Hp - a.Ho * a.stride, advance = a.stride + (e < 0 ? e : 0);
     bool found = false;
     long long best_cost = 0;
     // Strip widths that split the row evenly, the full row, or wide strips with a ragged
     // last one, from the widest down.  A plan's cost is led by its number of tiles, which the
     // full row has least of, so nearly all other widths are dismissed by that number alone.
-    for (int TW = a.Wo; TW >= 1; --TW) {
+    // Rows that are wider than any patch begin at the widest strip whose R rows fit, and a
+    // width is dismissed by the rows that its first tile needs before they are counted exactly
+    // (flat wide inputs, 3x4096: 1.7 ms a call without).
+    const int widest = (256 * UPT / (UPP * a.R) - a.R) / a.stride + 1;
+    for (int TW = a.Wo < widest ? a.Wo : widest; TW >= 1; --TW) {
         const long long strip_pixels = (long long)NHo * TW;
         if (strip_pixels + BP >= (1 << 22)) continue;          // keeps every index well inside 32 bits
         const int tiles_w = (int)((unsigned)(a.Wo + TW - 1) / (unsigned)TW);
@@ -83,6 +104,8 @@ bool plan_patch(const DsqConvArgs &a, int BP, int BC, int PF, int CT, int UPT, i
         PatchPlan p;
         p.TW = TW; p.BP = BP; p.Hp = Hp; p.tiles_w = tiles_w; p.row_tiles = row_tiles;
         p.PC = (TW - 1) * a.stride + a.R;
+        const int least = (row_tiles > 1 ? (BP - 1) / TW * advance : 0) + a.R;
+        if (least * p.PC * UPP > 256 * UPT || (found && tiles * 100000 + least * p.PC > best_cost)) continue;
         p.PR = dsq_patch_rows(a, BP, TW, row_tiles);
         // row skew: consecutive tile pixels keep advancing by one pixel stride
         // (mod 256 bytes) when a fragment wraps from one strip row to the next

@@ -43,6 +43,38 @@ def test_patch_holds_the_rows_of_every_tile(seed):
         assert need <= PR <= need + 2, text
 
 
+@pytest.mark.parametrize("seed", range(4))
+def test_patch_is_no_higher_than_its_tiles_need(seed):
+    """Exactly the rows of the worst tile: a row more costs LDS and fetch units, and the largest
+    patches are then not taken.  (1x1, stride 2, odd height: one row more at most.)"""
+    rng = random.Random(100 + seed)
+    planned = 0
+    while planned < 150:
+        R, stride = rng.choice([1, 3, 3]), rng.choice([1, 2])
+        pad, N = rng.randint(0, R - 1), rng.choice([1, 2, 3, 7, 16, 40])
+        H, W = rng.randint(1, 120), rng.choice([rng.randint(1, 120), 32, 64, 96])
+        if min(H, W) + 2 * pad < R:
+            continue
+        Ho = (H + 2 * pad - R) // stride + 1
+        d = B.make_desc(N, rng.choice([16, 200]), H, W, rng.choice([24, 256]), R, R, stride, pad, rng.choice([2, 4]),
+                        rng.choice([2, 3, 4, 5, 6]))
+        try:
+            text = B.dsq_conv2d_plan(d)
+        except B.DsqError:
+            continue
+        planned += 1
+        BP, TW, PR = (int(re.search(p, text).group(1)) for p in (r"tile (\d+)x", r"strip width (\d+)", r"patch (\d+)x"))
+        need = _rows_of_every_tile(N, H, Ho, stride, pad, R, TW, BP)
+        assert need <= PR <= need + (R == 1 and stride == 2 and H % 2), text
+
+
+@pytest.mark.parametrize("geom,flags,rows", [((17, 200, 13, 125, 64, 3, 3, 1, 2, 2), 6, 7), ((64, 64, 3, 125, 256, 3, 3, 1, 2, 2), 6, 7),
+                                             ((3, 64, 101, 224, 256, 3, 3, 2, 1, 4), 2, 9)])
+def test_patch_rows_of_some_layers(geom, flags, rows):
+    text = B.dsq_conv2d_plan(B.make_desc(*geom, B.DSQ_CONV_KERNEL(flags)))
+    assert int(re.search(r"patch (\d+)x", text).group(1)) == rows, text
+
+
 @pytest.mark.parametrize("geom,flags,l_a", [((300, 512, 2, 3, 64, 3, 3, 2, 2, 3), B.DSQ_CONV_ACT_DENSE3, -1.0),
                                             ((300, 512, 2, 224, 128, 3, 3, 2, 1, 3), B.DSQ_CONV_ACT_DENSE3, -1.0),
                                             ((300, 512, 1, 3, 300, 3, 3, 2, 2, 2), B.DSQ_CONV_KERNEL(6), -1.0)])
