@@ -31,35 +31,15 @@
 // the instruction's nominal rate.
 #include "dsq_device.h"
 #include "dsq_kernels.h"
-#include "patch_plan.h"
+#include "wq_plan.h"
 
 namespace {
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-struct WqPlan {
-    int TW, PC, npx;           // strip width; patch columns, patch pixels (1x1: the tile's pixels)
-    int Hp, tiles_w, tiles_c, total_blocks, xcd_chunk;
-    uint32_t mg_TW, mg_PC, mg_Hp, mg_Ho, mg_tiles_w, mg_tiles_c;
-};
-
-__host__ __device__ constexpr int kc_of(int R) { return R == 3 ? 32 : 64; }              // channels per stage
-__host__ __device__ constexpr int pixel_bytes(int R) { return kc_of(R) * 6 + 16; }       // odd multiple of 16: 8 pixels in distinct banks
-constexpr int ROWB = 128 + 16;                                       // staged bytes per output pixel
 constexpr float kUp = 0x1p54f, kDown = 0x1p-54f;                     // scale of the split activations
 constexpr uint32_t kMostBits = 0x71800000u;                          // 2^100: |x| = 2^46
-// LDS: [patch, then the epilogue's staging][channel-group sums of x][patch addresses]
-//      [zq, Dw * 2^-54, lr of BC channels][whether the tile cannot be split]
-__host__ __device__ constexpr int tables_at(int R, int KW, int tiles, int npx)
-{
-    const int staging = KW > 1 ? KW * tiles * 4096 : 4 * 32 * ROWB;      // (tiles: 32x32 tiles of a wave)
-    return npx * pixel_bytes(R) > staging ? npx * pixel_bytes(R) : staging;
-}
-constexpr int lds_bytes(int R, int KW, int tiles, int BC, int npx)
-{
-    return tables_at(R, KW, tiles, npx) + npx * (kc_of(R) / 8 * 4 + 4) + 3 * BC * 4 + 16;
-}
 
 // The wave's PF x CT tiles with the binary32 matrix instruction: the levels themselves
 // (l_w + Dw*code, rounded once) times the activations, both straight from global memory, in
@@ -492,51 +472,6 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
 }
 
 // ---- host side -------------------------------------------------------------------
-
-struct WqTile { int BP, BC, KW, tiles; };
-constexpr WqTile kSquare = {64, 64, 1, 1}, kRow = {64, 128, 1, 2}, kLarge = {128, 128, 1, 4}, kNarrow = {128, 32, 1, 1},
-                 kSplit = {32, 32, 4, 1};
-
-// Strip width: the patch costs about 8/54 of a tile pixel's matrix work per patch
-// pixel, and its LDS bytes decide how many workgroups share a CU.
-bool plan_wq(const DsqConvArgs &a, const WqTile &t, WqPlan &best, int &lds)
-{
-    const int NHo = a.N * a.Ho, Hp = a.H + 2 * a.pad;
-    double best_cost = 0.0;
-    bool found = false;
-    for (int TW = a.Wo; TW >= 1; --TW) {
-        if (a.R == 1 && TW != a.Wo) break;
-        const int tiles_w = (a.Wo + TW - 1) / TW;
-        const long long strip = (long long)NHo * TW;
-        const int row_tiles = (int)((strip + t.BP - 1) / t.BP);
-        const double tiles = (double)tiles_w * row_tiles;
-        if (found && tiles * t.BP * 54 > best_cost) continue;
-        WqPlan p;
-        p.TW = TW; p.Hp = Hp; p.tiles_w = tiles_w;
-        p.PC = a.R == 1 ? 1 : (TW - 1) * a.stride + a.R;
-        const long long npx = a.R == 1 ? t.BP : (long long)dsq_patch_rows(a, t.BP, TW, row_tiles) * p.PC;
-        if (npx > 1024) continue;
-        p.npx = (int)npx;
-        const int bytes = lds_bytes(a.R, t.KW, t.tiles, t.BC, p.npx);
-        if (bytes > 150 * 1024) continue;
-        const double cost = tiles * ((double)t.BP * 54 + (double)p.npx * 8) *
-                            (bytes <= 53 * 1024 ? 1.0 : bytes <= 80 * 1024 ? 1.15 : 1.6);
-        if (!found || cost < best_cost) {
-            found = true; best_cost = cost; best = p; lds = bytes;
-            best.total_blocks = (int)(tiles_w * (long long)row_tiles);
-        }
-    }
-    if (!found) return false;
-    best.tiles_c = (a.C_out + t.BC - 1) / t.BC;
-    const long long total = (long long)best.total_blocks * best.tiles_c;
-    if (total > 0x7FFFFF00LL / 8) return false;
-    best.total_blocks = (int)total;
-    best.xcd_chunk = (best.total_blocks + 7) / 8;
-    best.mg_TW = dsq_division_constant(best.TW); best.mg_PC = dsq_division_constant(best.PC);
-    best.mg_Hp = dsq_division_constant(best.Hp); best.mg_Ho = dsq_division_constant(a.Ho);
-    best.mg_tiles_w = dsq_division_constant(best.tiles_w); best.mg_tiles_c = dsq_division_constant(best.tiles_c);
-    return true;
-}
 
 template <int R, int WP, int WC, int KW, int PF, int CT, int OCC>
 hipError_t launch(const DsqConvArgs &a, const float *x, int x_nchw, const WqPlan &pl, int lds, hipStream_t stream)

@@ -3,6 +3,7 @@
 #pragma once
 #include "dsq_kernels.h"
 
+#if defined(__HIPCC__)
 // x / d for x >= 0 and d >= 1 by multiplication: with m = min(floor(2^32 / d), 2^32 - 1)
 // (dsq_division_constant, on the host) the high word of x * m is the quotient or one
 // less, so one correction suffices.  Wave-uniform operands stay on the scalar unit.
@@ -14,6 +15,7 @@ __device__ __forceinline__ int dsq_idiv(int x, int d, uint32_t m, int &rem)
     rem = r;
     return q;
 }
+#endif
 
 inline uint32_t dsq_division_constant(int d)
 {
