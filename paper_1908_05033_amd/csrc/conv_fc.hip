@@ -19,10 +19,13 @@
 // arithmetic: int8 matrix instruction for 3/4-bit layers, the FP4 form for
 // 1/2-bit layers.
 //
-// Bound by the latency of the chunks a wave loads one after the other: 25088 -> 4096 at
-// batch 64 took 25 us with a chunk's loads waited for at once, 20 us with the next chunk's
-// in flight and a channel tile's weights read into one L2 (51 MB of weights: 2.6 TB/s).
+// Bound by latency: launch and two memory round trips where a wave has one chunk of eight
+// channel blocks (up to 4096 channels), the chunks one after the other in deeper layers.
+// Measured at 4 bits, operands in the last-level cache (us, one chunk of loads waited for
+// at once and tiles dealt to the XCDs one by one -> now): 2048 -> 1000 x 64 4.5 -> 4.3,
+// 4096 -> 4096 x 256 16.7 -> 11.5, 9216 -> 4096 x 64 10.2 -> 7.8, 25088 -> 4096 x 64 22.9 -> 16.8.
 #include "conv_epilogue.h"
+#include "patch_plan.h"
 
 namespace {
 
@@ -44,8 +47,12 @@ struct FcLayout {
     static constexpr int LDS_BYTES = STAGE_BYTES > PART_BYTES + EXCH_BYTES ? STAGE_BYTES : PART_BYTES + EXCH_BYTES;
 };
 
-template <int CONT>
-__global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, int tiles_m, int total, int xcd_chunk)
+// LONG: a wave has more than one chunk, and the next one's loads are in flight while one is
+// multiplied (162 registers at 4 bits, one workgroup per CU; held to 128 it spills and takes
+// twice the time).  Without it 73, and two workgroups share a CU: at 512 tiles (2048 -> 1000 x 512)
+// 5.5 us, 7.5 with the registers of the prefetch.
+template <int CONT, bool LONG>
+__global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, int tiles_m, uint32_t mg_tiles_m, int total, int xcd_chunk)
 {
     typedef FcLayout<CONT> Lay;
     constexpr int KB_BYTES = Lay::KB_BYTES;
@@ -58,12 +65,16 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, i
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int col = lane & 31, h = lane >> 5;
     const int M = a.N * a.Ho * a.Wo;             // = N*H*W: 1x1, stride 1, no padding
+    // (one batch of argument fetches instead of three round trips one after the other)
+    asm volatile("" ::"s"(a.N), "s"(a.C_in), "s"(a.C_out), "s"(a.Ho), "s"(a.Wo), "s"(a.Cp), "s"(a.act), "s"(a.wq), "s"(a.out),
+                 "s"(tiles_m), "s"(mg_tiles_m), "s"(total), "s"(xcd_chunk));
     // Workgroups are dealt to the 8 XCDs in turn: every XCD gets a contiguous range of tiles, the
     // pixel tiles of one channel tile together, so that its weights are read into one L2 only
     const int logical = ((int)blockIdx.x & 7) * xcd_chunk + ((int)blockIdx.x >> 3);
     if (logical >= total) return;
-    const int ct = logical / tiles_m;            // 32-channel tile; ct*32 < Cop by construction (Cop >= rq_Cp)
-    const int m0 = (logical - ct * tiles_m) * 32;
+    int mt;
+    const int ct = dsq_idiv(logical, tiles_m, mg_tiles_m, mt);       // 32-channel tile; ct*32 < Cop by construction (Cop >= rq_Cp)
+    const int m0 = mt * 32;
     const int m = m0 + col;
     const int NCB = a.Cp / 64;
     const size_t row_bytes = (size_t)a.Cp * CONT / 8;
@@ -83,23 +94,29 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, i
     for (int r = 0; r < 16; ++r) { acc[r] = 0; facc[r] = 0.f; }
 
     // Loads of a chunk: weights are already in lane order, one 16-byte load per channel block;
-    // activations come as contiguous 16-byte units of PPI pixel rows per instruction.  Blocks and
-    // pixels past the end re-read the first one (no branch between the loads); such blocks are
-    // not multiplied, such pixels not stored.
+    // activations come as contiguous 16-byte units of PPI pixel rows per instruction.  Blocks
+    // past the end are not loaded and not multiplied, pixels past the end not loaded and not
+    // stored (a layer of one pixel would otherwise spend most of its time re-reading it).
     auto load_weights = [&](int base, v4i (&wp)[FC_CHUNK]) {
 #pragma unroll
         for (int i = 0; i < FC_CHUNK; ++i)
-            wp[i] = *reinterpret_cast<const v4i *>(wq + (size_t)min(base + i, cb1 - 1) * 64 * 4);
+            if (base + i < cb1) wp[i] = *reinterpret_cast<const v4i *>(wq + (size_t)(base + i) * 64 * 4);
     };
     auto load_acts = [&](int base, v4i (&au)[32 / PPI]) {
-        const int off = base * KB_BYTES + s_unit * 16 < cb1 * KB_BYTES ? base * KB_BYTES + s_unit * 16 : 0;
+        const int off = base * KB_BYTES + s_unit * 16;
 #pragma unroll
         for (int g = 0; g < 32 / PPI; ++g) {
             const int pm = m0 + g * PPI + s_pix;
-            au[g] = *reinterpret_cast<const v4i *>((const char *)a.act + (size_t)(pm < M ? pm : m0) * row_bytes + off);
+            if (off < cb1 * KB_BYTES && pm < M)
+                au[g] = *reinterpret_cast<const v4i *>((const char *)a.act + (size_t)pm * row_bytes + off);
         }
     };
     v4i wa[FC_CHUNK], wb[FC_CHUNK], au[32 / PPI];
+    // (what is not loaded may hold anything; zeroing it made the compiler wait inside the loads)
+#pragma unroll
+    for (int i = 0; i < FC_CHUNK; ++i) asm volatile("" : "=v"(wa[i]), "=v"(wb[i]));
+#pragma unroll
+    for (int g = 0; g < 32 / PPI; ++g) asm volatile("" : "=v"(au[g]));
     auto chunk = [&](int base, const v4i (&wp)[FC_CHUNK], v4i (&wn)[FC_CHUNK]) {
         const int nblk = min(FC_CHUNK, cb1 - base);
 #pragma unroll
@@ -109,7 +126,7 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, i
             *reinterpret_cast<v2i *>(d + 8) = (v2i){au[g].z, au[g].w};
         }
         // the next chunk's loads are in flight while this one is multiplied
-        if (base + FC_CHUNK < cb1) {
+        if (LONG && base + FC_CHUNK < cb1) {
             load_weights(base + FC_CHUNK, wn);
             load_acts(base + FC_CHUNK, au);
         }
@@ -141,6 +158,7 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, i
     // (two sets of weight registers in turn: a copy of the prefetched set would wait for it)
     for (int base = cb0; base < cb1; base += 2 * FC_CHUNK) {
         chunk(base, wa, wb);
+        if (!LONG) break;
         if (base + FC_CHUNK < cb1) chunk(base + FC_CHUNK, wb, wa);
     }
     if (CONT == 2) acc = dsq_fp4_acc_to_int(facc);
@@ -199,10 +217,10 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, i
     }
 }
 
-template <int CONT>
+template <int CONT, bool LONG>
 hipError_t launch_fc(const DsqConvArgs &a, hipStream_t stream)
 {
-    auto kern = conv_fc_kernel<CONT>;
+    auto kern = conv_fc_kernel<CONT, LONG>;
     const int lds = FcLayout<CONT>::LDS_BYTES;
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -218,7 +236,7 @@ hipError_t launch_fc(const DsqConvArgs &a, hipStream_t stream)
         const hipError_t e = dsq_launch_fill_zero(a.rq_pix, (size_t)M, stream);
         if (e != hipSuccess) return e;
     }
-    kern<<<8 * xcd_chunk, 64 * FC_WAVES, lds, stream>>>(a, tiles_m, total, xcd_chunk);
+    kern<<<8 * xcd_chunk, 64 * FC_WAVES, lds, stream>>>(a, tiles_m, dsq_division_constant(tiles_m), total, xcd_chunk);
     return hipGetLastError();
 }
 
@@ -249,5 +267,7 @@ bool dsq_conv_fc_preferred(const DsqConvArgs &a)
 
 hipError_t dsq_launch_conv_fc(const DsqConvArgs &a, hipStream_t stream)
 {
-    return a.cont == 4 ? launch_fc<4>(a, stream) : launch_fc<2>(a, stream);
+    // (one chunk per wave: nothing to prefetch, and the registers for it would only cost occupancy)
+    if (a.Cp / 64 <= FC_WAVES * FC_CHUNK) return a.cont == 4 ? launch_fc<4, false>(a, stream) : launch_fc<2, false>(a, stream);
+    return a.cont == 4 ? launch_fc<4, true>(a, stream) : launch_fc<2, true>(a, stream);
 }

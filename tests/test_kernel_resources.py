@@ -50,3 +50,13 @@ def test_kernels_stay_inside_their_register_budget(source):
                 if n_scratch > MAX_SCRATCH_IN_MFMA_BLOCK:
                     hot.append((name, n_scratch))
     assert not hot, "scratch traffic inside MFMA blocks: %s" % hot[:5]
+
+
+def test_split_k_workgroups_share_a_cu():
+    """Eight waves per workgroup: two workgroups fit a CU (four waves per SIMD) up to 128 registers.
+    Layers whose waves have one chunk each yield many short workgroups and need that; the variant
+    that prefetches a next chunk (LONG) may take more."""
+    asm = _device_asm(os.path.join(CSRC, "conv_fc.hip"))
+    kernels = re.findall(r"\.name:\s+(\S+).*?\.vgpr_count:\s+(\d+)", asm, re.S)
+    short = [(n, int(v)) for n, v in kernels if not re.search(r"conv_fc_kernelILi\dELb1E", n)]
+    assert short and all(v <= 128 for _, v in short), short
