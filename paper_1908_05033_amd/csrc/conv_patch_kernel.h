@@ -427,6 +427,12 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
                 const wpack_t wr = wreg[c][t % WD];
                 if (F4) {
                     wf[c][0] = wr;                       // FP4 nibbles go to the matrix cores as they are
+                    // (1x1 filters, two wave groups: the slot is refilled for the next stage right below.
+                    // The copy is made here, where the weights have to be there anyway; left to itself the
+                    // compiler loads into other registers and copies at the end of the stage, which waits
+                    // for the load: 25088 -> 4096 x 512 at 2 bits 133 us, 111 so.  With one group it does
+                    // not, and the copy costs 6 %)
+                    if constexpr (T == 1 && KS == 2) asm volatile("" : "+v"(wf[c][0]));
                 } else {
                     wf[c][0] = dsq_unpack16_c4((v2i){wr[0], wr[1]});
                     wf[c][KH - 1] = dsq_unpack16_c4((v2i){wr[2], wr[3]});

@@ -60,3 +60,20 @@ def test_split_k_workgroups_share_a_cu():
     kernels = re.findall(r"\.name:\s+(\S+).*?\.vgpr_count:\s+(\d+)", asm, re.S)
     short = [(n, int(v)) for n, v in kernels if not re.search(r"conv_fc_kernelILi\dELb1E", n)]
     assert short and all(v <= 128 for _, v in short), short
+
+
+def test_1x1_stages_do_not_wait_for_the_next_weights():
+    """FP4 variants of 1x1 layers with two wave groups: a stage ends with its barrier.  A wait for
+    global memory behind it is one for the weights of the next stage, fetched a moment before."""
+    asm = _device_asm(os.path.join(CSRC, "conv_patch_c2r1.hip"))
+    seen, late = 0, []
+    for m in re.finditer(r"\n(_Z\S*conv_patch_kernel(?:ILi2ELi1E)(?:Li\d+E){7}Li2EL\S+):", asm):
+        body = asm[m.start():asm.index("s_endpgm", m.start())]
+        for block in re.split(r"\n(?=\.LBB\d+_\d+:)", body):
+            label = block.split(":")[0].strip()
+            if "mfma" not in block or "s_barrier" not in block or not re.search(r"s_cbranch\S+ " + re.escape(label) + r"\b", block):
+                continue
+            seen += 1
+            if "vmcnt" in block[block.rindex("s_barrier"):]:
+                late.append(m.group(1))
+    assert seen >= 16 and not late, (seen, late[:3])
