@@ -263,9 +263,13 @@ __global__ __launch_bounds__(256) void quantize_act_nhwc_coalesced_kernel(
 }
 
 // NHWC input of few, deep pixels (the input of a fully connected layer): a block of 1024
-// threads owns one pixel, and a thread has the loads of U packed words in flight.  Bound by
-// the latency of the 4*C bytes that one compute unit reads: 25088 channels x 64 pixels 7.1 us,
-// 12.6 with blocks of 256 threads and one word in flight each.  C is a multiple of 4.
+// threads owns one pixel, and a thread has the loads of U packed words in flight.  Words past
+// the pixel's end are neither loaded nor quantized: with them 8192 channels, a quarter of the
+// block's words, took 6.4 us at 64 pixels, and the kernel was slower there than the one it
+// replaces.  Bound by the latency of the 4*C bytes that one compute unit reads.  4 bits, us,
+// against blocks of 256 threads with one word in flight each (tensor in the last-level cache):
+// 8192 channels x 1 / 64 / 512 pixels 4.3 -> 3.6 / 4.6 -> 3.9 / 6.6 -> 5.2, 25088 channels
+// 9.9 -> 5.6 / 10.6 -> 6.0 / 19.4 -> 12.6.  C is a multiple of 4.
 template <int CONT>
 __global__ __launch_bounds__(1024) void quantize_act_deep_kernel(const float *__restrict__ x, uint32_t *__restrict__ codes,
                                                                  int32_t *__restrict__ pix_sum, int C, int DP, float l, float u,
@@ -285,15 +289,18 @@ __global__ __launch_bounds__(1024) void quantize_act_deep_kernel(const float *__
     for (int base = tid; base < DP; base += 1024 * U) {
         float4 f[U][FPW];
 #pragma unroll
-        for (int k = 0; k < U; ++k)
+        for (int k = 0; k < U; ++k) {
+            if (base + k * 1024 >= DP) continue;     // (whole waves, but for the one that holds the pixel's end)
 #pragma unroll
             for (int g = 0; g < FPW; ++g) {
                 const int c = (base + k * 1024) * CPD + 4 * g;
                 f[k][g] = *reinterpret_cast<const float4 *>(px + (c < C ? c : 0));      // (blanked below)
             }
+        }
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const int d = base + k * 1024;
+            if (d >= DP) continue;
             uint32_t word = 0;
 #pragma unroll
             for (int g = 0; g < FPW; ++g) {
@@ -303,7 +310,7 @@ __global__ __launch_bounds__(1024) void quantize_act_deep_kernel(const float *__
                 word |= m << (CONT * g);
                 sum += dsq_bytesum(m);
             }
-            if (d < DP) row[d] = word;
+            row[d] = word;
         }
     }
 #pragma unroll
