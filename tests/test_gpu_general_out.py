@@ -40,8 +40,10 @@ def test_same_bits_as_the_simple_kernel(geom, bits, la, layout):
         for with_acc in (False, True):
             try:
                 got = _run(geom, bits, B.DSQ_CONV_KERNEL(kernel), la, layout, with_acc)
-            except B.DsqError:
-                continue                           # the tile does not take this layer
+            except B.DsqError as e:
+                if e.status != 5 or kernel == 2:   # (a forced tile may not take the layer; its own choice does)
+                    raise
+                continue
             assert np.array_equal(got[0], want[0]), kernel
             assert not with_acc or np.array_equal(got[1], want[1]), kernel
 
