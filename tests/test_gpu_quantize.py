@@ -161,8 +161,9 @@ def test_weight_codes_at_cfg2_size():
 def test_every_float_bit_pattern_gets_the_oracle_code(bits, l, u, layout):
     """All 2^32 binary32 patterns (NaNs of both kinds, infinities, denormals) against
     the oracle's division recipe, packed codes and pixel sums bit for bit: through
-    the large-tensor NHWC kernel, whose quantizer is the step-function form, and
-    through the NCHW kernel, which evaluates the recipe itself on the device."""
+    the large-tensor NHWC kernel and the NCHW kernel, whose quantizer is the
+    step-function form, and, in slices small enough for it, through the NHWC kernel
+    of small tensors, which evaluates the recipe itself on the device."""
     from concurrent.futures import ThreadPoolExecutor
     l, u = float(np.float32(l)), float(np.float32(u))
     CH = 1 << 27                                 # patterns per launch: 2^21 pixels of 64 channels
@@ -199,6 +200,15 @@ def test_every_float_bit_pattern_gets_the_oracle_code(bits, l, u, layout):
                 raise AssertionError("bits=%d range=(%r, %r): mismatch in the chunk of patterns starting at 0x%08x "
                                      "(first differing pixel %d, codes equal: %s, sums equal: %s)"
                                      % (bits, l, u, start, where, same, sums_same))
+            if layout == B.DSQ_NHWC:
+                small, step = torch.empty_like(codes), 1 << 20          # 2^14 pixels a call
+                small_pix = torch.empty_like(pix)
+                for k in range(0, CH, step):
+                    p0, p1 = k // C, (k + step) // C
+                    B.dsq_quantize_act(x[k:k + step], layout, 1, C, 16, 1024, l, u, bits, small.reshape(P, -1)[p0:p1].reshape(-1),
+                                       small_pix[p0:p1])
+                torch.cuda.synchronize()
+                assert torch.equal(small, codes) and torch.equal(small_pix, pix), "small tensors: chunk at 0x%08x" % start
             del x, oc, ref
 
 
