@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("layout,geom", [
     (B.DSQ_NCHW, (3, 5, 7, 9)), (B.DSQ_NCHW, (2, 128, 8, 8)), (B.DSQ_NCHW, (2, 130, 13, 5)), (B.DSQ_NCHW, (1, 1100, 3, 3)),
     (B.DSQ_NCHW, (70, 20, 64, 65)), (B.DSQ_NCHW, (5, 260, 1, 1)), (B.DSQ_NCHW, (2, 2050, 1, 3)),
+    (B.DSQ_NCHW, (4200, 520, 3, 5)), (B.DSQ_NCHW, (4100, 130, 2, 2)),
     (B.DSQ_NHWC, (3, 8192, 1, 1)), (B.DSQ_NHWC, (2, 16388, 1, 1)), (B.DSQ_NHWC, (1, 70000, 1, 2)), (B.DSQ_NCHW, (3, 25088, 1, 1)),
 ])
 def test_codes_and_sums(layout, geom, bits):

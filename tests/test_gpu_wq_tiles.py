@@ -18,6 +18,8 @@ TILES = [  # N, C_in, H, W, C_out, R, stride, pad
     (4, 17, 56, 57, 24, 3, 1, 1),        # 128x32, 3x3, odd C_in
     (4, 68, 56, 57, 32, 1, 1, 0),        # 128x32, 1x1
     (16, 33, 57, 57, 256, 3, 2, 1),      # 64x128, stride 2
+    (16, 36, 57, 57, 256, 3, 2, 1),      # ... whole float4s
+    (4, 20, 56, 57, 24, 3, 1, 1),        # 128x32, 3x3, whole float4s
     (32, 72, 28, 28, 200, 1, 1, 0),      # 128x128, 1x1
     (33, 37, 28, 27, 100, 3, 1, 1),      # 128x128, 3x3
     (2, 40, 57, 57, 70, 1, 2, 0),        # 32x32 split, stride 2
