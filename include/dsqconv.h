@@ -306,9 +306,10 @@ dsq_status dsq_conv2d_requant(const dsq_conv_desc *d, const void *act_packed,
  * The "b/32" rows of the paper's Tables 3, 6 and 7 (e.g. 1-bit weights and
  * 32-bit activations): Algorithm 1 with the activation quantizer left out, so
  * that step 5 convolves the dequantized weights w_hat = l_w + Dw*code (step 4)
- * with the activations themselves.  There is no integer path: levels and
- * activations are binary32 and neither is rounded, products are exact inside
- * the matrix instruction and sums are accumulated in binary32, so an output differs from
+ * with the activations themselves.  There is no integer path: activations and
+ * codes enter the matrix instruction exactly (an activation in three parts,
+ * subnormal ones included), products are exact and sums are accumulated in
+ * binary32, so an output differs from
  * the real-valued convolution by at most about (K + 2) * 2^-24 of the sum of
  * the absolute values of its K = R*S*C_in products (typically far less).
  *

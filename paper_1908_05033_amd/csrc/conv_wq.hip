@@ -4,12 +4,14 @@
 // are convolved with the weight levels l_w + Dw*code.
 //
 // The inner product runs on the bf16 matrix instruction (v_mfma_f32_32x32x16_bf16,
-// 16 times the rate of the binary32 one) without rounding an operand:
+// 16 times the rate of the binary32 one) on exact operands:
 //   - an activation is the sum of three bf16 numbers of 8 significant bits each
 //     (its 24 bits cut in three; every step of the split is exact),
 //   - a level is Dw*(code + zq) + lr, zq = l_w/Dw rounded so that code + zq is a
-//     bf16 number for every code, lr = l_w - Dw*zq (0 for the symmetric ranges of
-//     1-bit weights; at most Dw/128 at 2 bits, Dw/32 at 4 bits),
+//     bf16 number for every code, lr = l_w - Dw*zq, rounded once (0 for the symmetric
+//     ranges of 1-bit weights; at most Dw/128 at 2 bits and Dw/32 at 4 bits where the range
+//     holds 0, more where |l_w| is larger than Dw's multiples: Dw/8 at l_w = 30*Dw; l_w
+//     itself, with zq = 0, from |l_w| = 256*Dw on),
 // so that out = Dw * sum (code + zq)*(x2 + x1 + x0) + lr * sum x.  Products of two
 // such terms have at most 16 bits and are exact; the sums are binary32.  Three matrix
 // instructions of 32 clk for 16 channels against eight of 64 clk.  Sums of centred
@@ -27,8 +29,8 @@
 // planes per pixel); the R*R taps read shifted windows of it.  Weight codes go from
 // global memory to registers, all of a stage's in flight while the patch is staged.
 // Bound by staging and LDS reads between the matrix instructions: 128 -> 128 3x3 at
-// 28x28 x 64, 188 us on the binary32 instruction, 48 us (304 TFLOP/s) now, of 18 us at
-// the instruction's nominal rate.
+// 28x28 x 64, of 18 us at the instruction's nominal rate, 188 us on the binary32 instruction
+// and 48 now (304 TFLOP/s) with the tensor in the last-level cache; 50 to 57 cold.
 #include "dsq_device.h"
 #include "dsq_kernels.h"
 #include "wq_plan.h"
@@ -488,18 +490,21 @@ hipError_t launch(const DsqConvArgs &a, const float *x, int x_nchw, const WqPlan
 
 }  // namespace
 
-// Tile by shape, from a sweep over 1x1 and 3x3 layers of 49 to 200704 pixels and 16 to 512
-// channels (us, the tile named first against the one it was preferred to):
-//   128x32   at most 32 output channels: nothing wider is filled (16->24 at 120x120 x 10: 18 against 24)
+// Tile by shape, from a sweep of every tile over 1x1 and 3x3 layers of 49 to 200704 pixels and
+// 16 to 512 channels (us, tensors rotating over 700 MB, the tile named first against the one it
+// was preferred to; the order is the same with the tensor in the last-level cache, 1 to 6 % less):
+//   128x32   at most 32 output channels: nothing wider is filled (16->24 at 120x120 x 10: 20 against 25;
+//            1x1 144->24 at 56x56 x 64 46 against 44)
 //   32x32    K split over the four waves, fewer than 160 tiles of 64x64: the others leave most of the
-//            chip idle (512->512 at 7x7 x 1: 30 against 49; from 196 tiles on it loses, 18 against 16)
+//            chip idle (512->512 at 7x7 x 1: 32 against 55; level at 196 tiles, 18 against 19, and
+//            behind from there, 128->128 at 28x28 x 16: 30 against 23)
 //   128x128  layers that still give 192 of them, 3x3 stride 2 excepted: least staging, and least LDS
-//            traffic per matrix instruction (128->128 at 28x28 x 64: 47 against 58; 1x1 256->512
-//            stride 2 at 28x28 x 64: 21 against 26)
+//            traffic per matrix instruction (128->128 at 28x28 x 64: 50 against 59, x 32 34 against 36;
+//            1x1 256->512 stride 2 at 28x28 x 64: 23 against 28, 128->256 12 against 11)
 //   64x128   3x3 stride 2: a patch of four times the pixels, staged for twice the channels
-//            (64->128 at 56x56 x 64: 43 against 52)
+//            (64->128 at 56x56 x 64: 46 against 58)
 //   64x64    the rest: four workgroups on a CU cover each other's staging, and the last round of
-//            workgroups is short (128->128 at 28x28 x 8: 16 against 31 for 128x128)
+//            workgroups is short (128->128 at 28x28 x 8: 19 against 33 for 128x128)
 hipError_t dsq_launch_conv_wq(const DsqConvArgs &a, const float *x, int x_nchw, hipStream_t stream)
 {
     const long long M = (long long)a.N * a.Ho * a.Wo;

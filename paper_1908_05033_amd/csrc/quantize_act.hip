@@ -495,8 +495,11 @@ hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C
     // (one pixel per image: the two layouts are the same memory)
     if (layout_nchw && H * W > 1) {
         dim3 grid((H * W + 63) / 64, N);
-        // one wave per packed word of 64 pixels where a word is all a wave gets to load: 16 waves
-        // per block unless that leaves waves without a word, or the tensor fills the chip anyway
+        // 16 waves per block on tensors that do not fill the chip with four each, unless that leaves
+        // waves without a word.  us, four / 16 waves, 4 bits: 128 channels (16 words) at 14x14 x 64 6.6 /
+        // 4.6, 28x28 x 64 (832 blocks) 10.1 / 9.8, 56x56 x 64 (3136 blocks) 21.8 / 25.6, 112x112 x 32 (6272)
+        // 37 / 45; 512 channels 21.9 / 10.7 at 14x14 x 64, 95 / 89 at 56x56 x 64.  So from about 1000 blocks
+        // on pixels of 16 to 24 words are up to 20 % better off with four, deeper ones with 16.
         const bool many = DP >= 16 && (long long)grid.x * grid.y < 4096;
 #define DSQ_NCHW_LAUNCH(CONT, NW)                                                            \
         quantize_act_nchw_kernel<CONT, NW><<<grid, 64 * NW, 0, stream>>>(                    \
@@ -517,6 +520,9 @@ hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C
     int dp_shift = -1;
     if ((DP & (DP - 1)) == 0) { dp_shift = 0; while ((1 << dp_shift) < DP) ++dp_shift; }
     const bool vec = (C % 4 == 0) && (((uintptr_t)x & 15) == 0);
+    // us, the kernel below / the deep one, 4 bits: 8192 channels (1024 words) x 1 4.3 / 3.6, x 512 6.8 / 5.4,
+    // x 1024 10.2 / 9.1, x 2048 14.7 / 16.1; 25088 channels x 64 10.6 / 6.0, x 512 19.4 / 12.6; below, at 4096
+    // channels, level up to 512 pixels (3.5 / 3.5 x 64) and 6.0 / 6.5 x 1024.
     if (vec && DP >= 1024 && total_pixels <= 512) {
         if (cont == 4)
             quantize_act_deep_kernel<4><<<total_pixels, 1024, 0, stream>>>(x, (uint32_t *)codes, pix_sum, C, DP, l, u, top, th);

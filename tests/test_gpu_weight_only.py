@@ -2,8 +2,11 @@
 paper's Tables 3, 6 and 7) against the oracle's float64 convolution of the
 activations with the weight levels.
 
-Tolerance: the kernel forms every level with one binary32 rounding and sums the
-K = R*S*C_in exact products in binary32, so |gpu - ref| <= (K + 2) * 2^-24 * sum|a * w_hat|
+Tolerance: the kernel sums K = R*S*C_in products of centred codes and activations,
+exact on the bf16 matrix instruction (each activation in three parts), in binary32,
+and combines them with the channel's step and offset in one rounding each (tiles that
+cannot be split so: levels formed with one binary32 rounding, fp32 matrix
+instruction).  So |gpu - ref| <= (K + 2) * 2^-24 * sum|a * w_hat|
 (the classical bound of a length-K recursive sum); the tests demand that bound
 and, as a sharper statistical check, a root-mean-square error below
 4 * sqrt(K) * 2^-24 of the root-mean-square of that scale."""

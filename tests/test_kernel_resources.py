@@ -6,6 +6,7 @@ variant over its budget does not fail any numerical test -- the compiler spills
 to scratch memory and the layer just gets several times slower -- so the spill
 counts the compiler reports are pinned here.
 """
+import functools
 import os
 import re
 import subprocess
@@ -20,6 +21,7 @@ MAX_SPILLED_VGPRS = 40            # whole kernel
 MAX_SCRATCH_IN_MFMA_BLOCK = 48    # scratch instructions in a basic block that issues MFMAs
 
 
+@functools.lru_cache(maxsize=None)
 def _device_asm(src):
     with tempfile.TemporaryDirectory() as d:
         out = os.path.join(d, "k.s")
