@@ -127,7 +127,7 @@ def test_small_activations_beside_ordinary_ones(geom, small):
 
 @pytest.mark.parametrize("size", [2.0 ** -61, 1e-30, 1e-33, 2.0 ** -59, 2.0 ** 99])
 def test_scaled_activations_give_scaled_outputs(size):
-    """Small and large tiles on both sides of the split's limits: the bound scales along."""
+    """Small and large activations, split and (from 2^46 on) not: the bound scales along."""
     layer, inp = inputs.small_random_case(3, 4, 48, 30, 31, 40, 3, 1, 1, 4, l_a=-1.0, u_a=1.0)
     x = (inp["x"] / inp["x"].abs().max() * size).float()
     code = oracle.quantize_weights(inp["w"].numpy(), inp["l_w"], inp["u_w"], 2)
