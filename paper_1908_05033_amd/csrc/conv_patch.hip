@@ -33,22 +33,22 @@ int dsq_patch_rows(const DsqConvArgs &a, int BP, int TW, int row_tiles)
         if (s > span) span = s;
     };
     const int repeat = image / G, columns = TW / gw;
-    if (image < BP || (e < 0 && row_tiles <= columns)) {
+    if (image < BP || (e < 0 && a.N > 1 && row_tiles <= columns)) {
         for (int i = 0; i < row_tiles && i < repeat; ++i) look_at(i * BP);
     } else {
-        int d = (BP - 1) / TW;
-        const int late = TW - (BP - 1) % TW, step = BP % TW;              // first column from which a tile passes d + 1 rows
+        const int passed = (BP - 1) / TW, rest = (BP - 1) % TW;           // a tile passes one row more from column TW - rest on
+        int d = passed;
         if (row_tiles > columns) {
-            if (TW - gw >= late) ++d;
+            if (gw <= rest) ++d;
         } else {
             look_at((row_tiles - 1) * BP);                                // (cut off by the end of the strip)
             if (row_tiles == 1) return span + a.R;
             if (TW >= BP) {                                               // (the last whole tile step of the first row)
                 if (row_tiles - 1 > TW / BP) ++d;
-            } else for (int i = 1, c = 0; i < row_tiles - 1; ++i) {
+            } else for (int i = 1, c = 0, step = BP % TW; i < row_tiles - 1; ++i) {
                 c += step;
                 if (c >= TW) c -= TW;
-                if (c >= late) { ++d; break; }
+                if (c >= TW - rest) { ++d; break; }
             }
         }
         if (d * a.stride > span) span = d * a.stride;
@@ -61,7 +61,15 @@ int dsq_patch_rows(const DsqConvArgs &a, int BP, int TW, int row_tiles)
                 inside = ((row * TW + col + G - 1) & -G) < (row + 1) * TW;
             if (!inside) span -= a.stride;
         }
-        for (int n = 1; n < a.N && n <= BP / G && span < d * a.stride + e; ++n) look_at((n * image - 1) & -BP);
+        // the tile across the boundary after image n begins `back` pixels before it
+        int across = -1;                                                  // rows that one passes
+        for (int n = 1, back = 0; n < a.N && n <= BP / G && across <= passed; ++n) {
+            back = (back + image) & (BP - 1);
+            if (back == 0) continue;                                      // (the boundary is one between tiles)
+            const int m = back < TW ? back : back % TW;
+            across = m > 0 && m <= rest ? passed + 1 : across < passed ? passed : across;
+        }
+        if (across >= 0 && across * a.stride + e > span) span = across * a.stride + e;
     }
     return span + a.R;
 }
