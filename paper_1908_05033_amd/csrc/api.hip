@@ -23,6 +23,22 @@ bool range_ok(float l, float u)
 }
 const long long kMaxElems = (1LL << 31) - 1;
 
+// Constants of an activation quantizer (see DsqQuant).
+DsqQuant quantizer(float l, float u, int bits)
+{
+    DsqQuant q;
+    q.l = l; q.u = u; q.top = (1 << bits) - 1;
+    q.delta = (u - l) / (float)q.top;
+    q.inv_delta = 1.0f / q.delta;
+    const double r = 1.0 / (double)q.delta, c0 = -(double)l * r;
+    const double bound = 0x1p-23 * (fmax(fabs((double)l), fabs((double)u)) * r + fabs(c0) + 4.0 * q.top + 6.0);
+    q.t_lo = (float)(c0 - bound); q.t_hi = (float)(c0 + bound);
+    // (the corrected quotient has codes to decide, hence s >= Delta/4, and remainders of 2^-48 s)
+    q.plain = !(bound < 0.25 && q.delta >= 0x1p-60f && q.delta <= 0x1p60f);
+    if (!(bound < 0.25)) { q.inv_delta = 0.0f; q.t_lo = -1.0f; q.t_hi = 256.0f; }
+    return q;
+}
+
 void quantizer_thresholds(float l, float u, int bits, float thr[16]);
 
 }  // namespace
@@ -68,10 +84,7 @@ dsq_status dsq_quantize_act(const float *x, dsq_layout layout, int N, int C, int
     if (layout == DSQ_NCHW && N > 65535) return DSQ_ERR_UNSUPPORTED;
     if (!aligned16(x) || !aligned16(codes_packed) || !aligned16(pix_code_sum)) return DSQ_ERR_ALIGN;
     if (codes_bytes < dsq_act_packed_bytes(N, H, W, C, bits)) return DSQ_ERR_SIZE;
-    DsqThresholds th;
-    quantizer_thresholds(l, u, bits, th.thr);
-    th.inv_delta = 1.0f / ((u - l) / (float)((1 << bits) - 1));
-    hipError_t e = dsq_launch_quantize_act(x, layout == DSQ_NCHW, N, C, H, W, l, u, bits, th,
+    hipError_t e = dsq_launch_quantize_act(x, layout == DSQ_NCHW, N, C, H, W, bits, quantizer(l, u, bits),
                                            codes_packed, pix_code_sum, (hipStream_t)hip_stream);
     return e == hipSuccess ? DSQ_OK : DSQ_ERR_HIP;
 }
@@ -93,10 +106,7 @@ dsq_status dsq_quantize_act_ex(const float *x, dsq_layout layout, int N, int C, 
     if (layout == DSQ_NCHW && N > 65535) return DSQ_ERR_UNSUPPORTED;
     if (!aligned16(x) || !aligned16(codes_packed) || !aligned16(pix_code_sum)) return DSQ_ERR_ALIGN;
     if (codes_bytes < dsq_act_packed_bytes_ex(N, H, W, C, bits, packing)) return DSQ_ERR_SIZE;
-    DsqThresholds th;
-    quantizer_thresholds(l, u, bits, th.thr);
-    th.inv_delta = 1.0f / ((u - l) / 7.0f);
-    hipError_t e = dsq_launch_quantize_act_dense3(x, layout == DSQ_NCHW, N, C, H, W, l, u, th, codes_packed,
+    hipError_t e = dsq_launch_quantize_act_dense3(x, layout == DSQ_NCHW, N, C, H, W, quantizer(l, u, bits), codes_packed,
                                                   pix_code_sum, (hipStream_t)hip_stream);
     return e == hipSuccess ? DSQ_OK : DSQ_ERR_HIP;
 }

@@ -69,21 +69,28 @@ struct DsqConvArgs {
                               // pixels: plain stores to rq_pix, nothing to clear
 };
 
-// The quantizer of one tensor as a step function (see dsq_code_thr): thr[j],
-// j = 1..2^bits-1, is the smallest binary32 value whose code is >= j (NaN in
-// unused entries), found by the host with the recipe of dsq_code.
-struct DsqThresholds {
-    float thr[16];
-    float inv_delta;
+// The quantizer of one activation tensor.  With T(x) = (clip(x) - l)/Delta the recipe's code
+// is T rounded to the nearest integer (halves up), but for values within
+//   3*2^-24*(top + 1)
+// of a half-integer, where its three roundings (subtraction, division, addition of 1/2) may
+// decide; the kernels evaluate fma(clip(x), inv_delta, -l/Delta), which is within
+//   2^-24*(max(|l|, |u|)/Delta + |l|/Delta + top + 3)
+// of T (rounding of 1/Delta, of the constant and of the sum).  t_lo and t_hi are -l/Delta less
+// and plus twice the sum of the two: where both round to the same integer, that is the
+// recipe's code.  Ranges so far from 0 that the bound passes 1/4 get constants that never
+// agree (t_lo = -1, t_hi = 2^8: codes 0 and 255), and run the recipe on every value.
+struct DsqQuant {
+    float l, u, delta;        // delta: the recipe's binary32 value
+    float inv_delta, t_lo, t_hi;
+    int top;
+    int plain;                // the recipe has to divide (see quant4)
 };
 
-hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C, int H, int W,
-                                   float l, float u, int bits, const DsqThresholds &th, void *codes,
-                                   int32_t *pix_sum, hipStream_t stream);
+hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C, int H, int W, int bits,
+                                   const DsqQuant &q, void *codes, int32_t *pix_sum, hipStream_t stream);
 // The same into the dense 3-bit format (bits == 3, C rounded up to 64 at most 8192).
-hipError_t dsq_launch_quantize_act_dense3(const float *x, int layout_nchw, int N, int C, int H, int W,
-                                          float l, float u, const DsqThresholds &th, void *codes,
-                                          int32_t *pix_sum, hipStream_t stream);
+hipError_t dsq_launch_quantize_act_dense3(const float *x, int layout_nchw, int N, int C, int H, int W, const DsqQuant &q,
+                                          void *codes, int32_t *pix_sum, hipStream_t stream);
 
 // `cont`: the container (2 or 4 bits) of the layer the weights are for; codes of
 // `bits` <= cont bits are stored in it.

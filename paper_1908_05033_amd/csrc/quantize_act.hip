@@ -4,10 +4,11 @@
 // needs for the l_w zero-point term.
 //
 // The kernels are bound by HBM traffic (4 B read and container/8 B written per
-// element).  They evaluate the recipe in its step-function form (thresholds found
-// on the host with the recipe itself: exactly the same codes, without the IEEE
-// division, which costs more than the memory time per element), small NHWC
-// tensors excepted.
+// element) as long as an element costs few vector instructions.  The recipe's IEEE
+// division costs more than the memory time; looking the code up between two
+// thresholds in LDS (a dozen instructions per element) still kept the vector units busy
+// for 0.6 to 0.9 of the time.  Here (quant4) a code costs five instructions and a share
+// of one comparison, and the recipe itself runs only where those cannot decide.
 #include "dsq_device.h"
 #include "dsq_kernels.h"
 
@@ -19,98 +20,208 @@ __device__ __forceinline__ int dpp_add(int v)
     return v + __builtin_amdgcn_update_dpp(0, v, DPP_CTRL, 0xF, 0xF, true);
 }
 
-// Codes of up to four consecutive channels starting at c0 -> one byte each.
-// VEC: the pixel's channel count is a multiple of 4 and x is 16-B aligned, so
-// a group of four is either wholly inside [0,C) or wholly outside.
-// The codes come from the step-function form of the quantizer (dsq_code_thr):
-// LINEAR for 1- and 2-bit codes, the guess-and-correct form with the (lower,
-// upper) threshold pairs `tp` in LDS for 3- and 4-bit codes.
-struct QuantParams {
-    float l, u, delta, inv_delta, t1, t2, t3;
-    int top;
-};
-
-// MODE 0: the recipe itself (dsq_code, with its division); 1: compare chain;
-// 2: guess and correct against the threshold pairs in LDS.
-template <int MODE>
-__device__ __forceinline__ int qcode(float x, const QuantParams &q, const float2 *tp)
+template <int DPP_CTRL>
+__device__ __forceinline__ uint32_t dpp_or(uint32_t v)
 {
-    if (MODE == 0) return dsq_code(x, q.l, q.u, q.delta, q.top);
-    return dsq_code_thr<MODE == 1>(x, q.l, q.u, q.inv_delta, q.top, q.t1, q.t2, q.t3, tp);
+    return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, DPP_CTRL, 0xF, 0xF, true);
 }
 
-// Threshold pairs of this block: pair c = (thr[c], thr[c+1]), -inf below the first
-// threshold, NaN above the last.  Needs a barrier before use.
-__device__ __forceinline__ void fill_threshold_pairs(float2 *tp, const DsqThresholds &th)
+// Codes of four values, one per byte.  T(x) = (clip(x) - l)/Delta is evaluated twice, a
+// little below and a little above (q.t_lo and q.t_hi are -l/Delta -+ the error bound of
+// this evaluation plus that of the recipe, see DsqQuant), and rounded to the nearest
+// integer and packed by one instruction each (v_cvt_pk_u8_f32 rounds to nearest even).
+// Where both agree, T is far enough from every midpoint for the recipe to give that code
+// too.  Where a lane's do not (a few waves in ten thousand; every time for values that
+// sit on a midpoint, like 0 in a symmetric range), the wave runs the recipe: the quotient
+// of the subtraction by Delta from a correctly rounded 1/Delta and two corrections by its exact
+// remainder is the correctly rounded one (Markstein), so that nine instructions per value
+// stand for the IEEE division's two dozen; only steps so small or large that a remainder
+// might lose bits (q.plain) are divided.  A NaN gets code 0 as the last operand of
+// v_med3_f32, which then returns min(min(l, u), x): l, or for a signalling NaN a quiet one,
+// which converts to 0 (as the first operand it would give u).
+// `active`: lanes whose values count (the others may hold anything).
+__device__ __forceinline__ uint32_t quant4(float4 f, const DsqQuant &q, bool active)
 {
-    if (threadIdx.x < 16) {
-        float lo = -__builtin_inff(), hi = __builtin_nanf("");
+    const float x[4] = {f.x, f.y, f.z, f.w};
+    uint32_t lo = 0, hi = 0;
 #pragma unroll
-        for (int j = 1; j < 16; ++j) {
-            lo = (int)threadIdx.x == j ? th.thr[j] : lo;
-            hi = (int)threadIdx.x + 1 == j ? th.thr[j] : hi;
+    for (int j = 0; j < 4; ++j) {
+        const float v = __builtin_amdgcn_fmed3f(q.l, q.u, x[j]);
+        lo = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(v, q.inv_delta, q.t_lo), j, lo);
+        hi = __builtin_amdgcn_cvt_pk_u8_f32(__builtin_fmaf(v, q.inv_delta, q.t_hi), j, hi);
+    }
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(active && lo != hi) != 0, 0)) {
+        if (q.plain) {
+            asm volatile("");        // (a branch: left to itself the compiler computes both sides)
+            return dsq_bytes4(dsq_code(x[0], q.l, q.u, q.delta, q.top), dsq_code(x[1], q.l, q.u, q.delta, q.top),
+                              dsq_code(x[2], q.l, q.u, q.delta, q.top), dsq_code(x[3], q.l, q.u, q.delta, q.top));
         }
-        tp[threadIdx.x] = make_float2(lo, hi);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float s = __builtin_amdgcn_fmed3f(q.l, q.u, x[j]) - q.l;
+            const float t0 = s * q.inv_delta;
+            const float t1 = __builtin_fmaf(__builtin_fmaf(-t0, q.delta, s), q.inv_delta, t0);
+            const float t = __builtin_fmaf(__builtin_fmaf(-t1, q.delta, s), q.inv_delta, t1);
+            lo = __builtin_amdgcn_cvt_pk_u8_f32(floorf(t + 0.5f), j, lo);
+        }
     }
+    return lo;
 }
 
-template <bool VEC, int MODE>
-__device__ __forceinline__ uint32_t quant4(const float *px, int c0, int C, const QuantParams &qp,
-                                           const float2 *tp)
+// Codes of channels c..c+3 of a pixel whose channels lie `stride` floats apart; channels from C on
+// are not read and have code 0.
+__device__ __forceinline__ uint32_t quant4_of(const float *px, int stride, int c, int C, const DsqQuant &q)
 {
-    if (VEC) {
-        // C is a multiple of 4 here.  Branch-free: a group past the last channel
-        // reads the pixel's first four values instead and is blanked afterwards,
-        // so that all loads of a thread are in flight together.
-        const bool in = c0 < C;
-        const float4 f = *reinterpret_cast<const float4 *>(px + (in ? c0 : 0));
-        const uint32_t b = dsq_bytes4(qcode<MODE>(f.x, qp, tp), qcode<MODE>(f.y, qp, tp),
-                                      qcode<MODE>(f.z, qp, tp), qcode<MODE>(f.w, qp, tp));
-        return in ? b : 0u;
-    }
-    const bool in0 = c0 < C, in1 = c0 + 1 < C, in2 = c0 + 2 < C, in3 = c0 + 3 < C;
-    float v0 = 0.f, v1 = 0.f, v2 = 0.f, v3 = 0.f;
-    if (in0) v0 = px[c0];
-    if (in1) v1 = px[c0 + 1];
-    if (in2) v2 = px[c0 + 2];
-    if (in3) v3 = px[c0 + 3];
-    const int q0 = in0 ? qcode<MODE>(v0, qp, tp) : 0;
-    const int q1 = in1 ? qcode<MODE>(v1, qp, tp) : 0;
-    const int q2 = in2 ? qcode<MODE>(v2, qp, tp) : 0;
-    const int q3 = in3 ? qcode<MODE>(v3, qp, tp) : 0;
-    return dsq_bytes4(q0, q1, q2, q3);
+    const int left = C - c;
+    if (left <= 0) return 0u;
+    px += (size_t)c * stride;
+    float4 f = make_float4(px[0], 0.f, 0.f, 0.f);
+    if (left > 1) f.y = px[stride];
+    if (left > 2) f.z = px[2 * (size_t)stride];
+    if (left > 3) f.w = px[3 * (size_t)stride];
+    const uint32_t b = quant4(f, q, true);
+    return left >= 4 ? b : b & ((1u << (8 * left)) - 1u);
 }
 
-// NHWC input.  One thread produces one packed word (8 channels at 4-bit, 16 at
-// 2-bit).  A block owns PB whole pixels, so pixel sums never straddle blocks.
+// Sum of the four bytes of a word.
+__device__ __forceinline__ int bytesum(uint32_t w) { return (int)__builtin_amdgcn_sad_u8(w, 0u, 0u); }
+
+// NHWC input, C a multiple of 4 (and x 16-byte aligned, like every pointer of the
+// library): rows of G lanes take a pixel each, lane r of a row the float4 units r, r + G,
+// ... of it, so that a load instruction of a wave covers 64/G contiguous stretches.  From 16
+// lanes on, those past the last channel make the code-0 padding; below, the words without a
+// channel are written when the pixel is done.  The 2 (4-bit), 4 (2-bit) or 8
+// (dense 3-bit) neighbouring lanes of a packed word combine their bytes with DPP moves.
+// Code sums stay in the lanes until the pixel is done: no LDS, no atomics, no barrier.  A wave
+// walks `steps` groups of 64/G pixels, the loads of U units in flight together.  4 bits, us, against
+// a kernel that dealt float4 units to lanes block by block, looked codes up in LDS and added sums
+// there (its vector units busy 0.9 of the time at 144 channels): 144 channels at 56x56 x 64 27.0 ->
+// 23.5 (5.5 TB/s), 64 at 56x56 x 64 12.6 -> 10.8, 128 at 28x28 x 64 7.2 -> 5.2, 576 at 14x14 x 64 8.9 ->
+// 6.9, 64 at 224x224 x 32 84 -> 78 (5.6 TB/s from HBM).
+template <int CONT, int G, int U, bool NT>
+__global__ __launch_bounds__(256) void quantize_act_rows_kernel(
+    const float *__restrict__ x, uint32_t *__restrict__ codes, int32_t *__restrict__ pix_sum,
+    int total_pixels, int C, int DP, int steps, DsqQuant q)
+{
+    constexpr bool D3 = CONT == 3;
+    constexpr int LPW = D3 ? 8 : 8 / CONT;   // lanes per packed word (dense: per 12-byte unit)
+    constexpr int WPG = D3 ? G / 8 * 3 : G / LPW;            // words of G units
+    constexpr int PPS = 64 / G;              // pixels per step of a wave
+    const int lane = threadIdx.x & 63, r = lane & (G - 1), row = lane / G;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+    const int QP = C / 4;                                    // float4 units per pixel
+    constexpr bool PADDED = G >= 16;
+    // ... up to the end of the padding (a multiple of 16), or of the last word with a channel
+    const int QPP = PADDED ? (D3 ? DP / 3 * 8 : DP * LPW) : (QP + LPW - 1) / LPW * LPW;
+    const int J = (QPP + G - 1) / G;
+    const int first = wave * steps * PPS;
+    const int n = min(steps, (total_pixels - first + PPS - 1) / PPS);
+    if (n <= 0) return;
+    // (uniform bases, and 32-bit offsets of the lanes)
+    const char *xb = (const char *)x + (size_t)first * QP * 16;
+    uint32_t *cb = codes + (size_t)first * DP;
+    const uint32_t x_row = (uint32_t)row * (uint32_t)QP * 16;
+    const uint32_t c_off = (uint32_t)row * (uint32_t)DP + (D3 ? r / 8 * 3 + (lane & 7) : r / LPW);
+    int sum = 0, j = 0, k = 0;               // unit j * G + r of pixel first + k * PPS + row
+    while (k < n) {
+        float4 f[U];
+        int jl = j, kl = k;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // Never under a branch: lanes without a unit read the first one of the row, lanes without
+            // a pixel (of the last step) that of row 0, and past the last step the last one comes again
+            const char *base = xb + ((size_t)kl * PPS * QP + (size_t)jl * G) * 16;
+            const bool here = first + kl * PPS + row < total_pixels;
+            const uint32_t off = (here ? x_row : 0u) + (jl * G + r < QP ? (uint32_t)r * 16 : 0u);
+            if (NT) {
+                // a tensor larger than the last-level cache is read once and never again
+                typedef float v4f __attribute__((ext_vector_type(4)));
+                const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(base + off));
+                f[u] = make_float4(t.x, t.y, t.z, t.w);
+            } else {
+                f[u] = *reinterpret_cast<const float4 *>(base + off);
+            }
+            const bool wrap = jl + 1 == J;
+            const int kn = wrap ? kl + 1 : kl, jn = wrap ? 0 : jl + 1;
+            jl = kn < n ? jn : jl;
+            kl = kn < n ? kn : kl;
+        }
+        __builtin_amdgcn_sched_barrier(0);       // (all loads first)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u > 0 && k >= n) break;
+            const int unit = j * G + r, pixel = first + k * PPS + row;
+            const bool here = pixel < total_pixels, live = unit < QP && here;
+            uint32_t b = quant4(f[u], q, live);
+            b = live ? b : 0u;
+            sum = (int)__builtin_amdgcn_sad_u8(b, 0u, (uint32_t)sum);
+            uint32_t *out = cb + (size_t)k * PPS * DP + j * WPG;
+            if (D3) {
+                // lane g of a unit holds group g: its low bits go to word g / 4 at bit 2 (g % 4) of
+                // every byte, its high bits to word 2 at bit g of every byte; the eight lanes OR
+                // their shares together and lanes 0..2 store one word each
+                const int g = lane & 7;
+                const uint32_t low = (b & 0x03030303u) << (2 * (g & 3));
+                uint32_t w0 = g < 4 ? low : 0u, w1 = g < 4 ? 0u : low, w2 = ((b >> 2) & 0x01010101u) << g;
+                w0 = dpp_or<0x141>(dpp_or<0x4E>(dpp_or<0xB1>(w0)));
+                w1 = dpp_or<0x141>(dpp_or<0x4E>(dpp_or<0xB1>(w1)));
+                w2 = dpp_or<0x141>(dpp_or<0x4E>(dpp_or<0xB1>(w2)));
+                if (g < 3 && unit < QPP && here) out[c_off] = g == 0 ? w0 : g == 1 ? w1 : w2;
+            } else {
+                uint32_t word;
+                if (CONT == 4) {
+                    // word = channels 8w..8w+7: byte j = c[j] | c[j+4] << 4; the odd lane holds c[4..7]
+                    word = b | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, 0xB1, 0xF, 0xF, true) << 4;
+                } else {
+                    // word = 16 channels: byte j = c[j] | c[j+4] << 2 | c[j+8] << 4 | c[j+12] << 6
+                    word = dpp_or<0x4E>(dpp_or<0xB1>(b << (2 * (lane & 3))));
+                }
+                if ((lane & (LPW - 1)) == 0 && unit < QPP && here) out[c_off] = word;
+            }
+            if (j + 1 < J) {
+                ++j;
+            } else {
+                int s = dpp_add<0xB1>(sum);                      // lanes ^1   (quad_perm 1,0,3,2)
+                s = dpp_add<0x4E>(s);                            // lanes ^2   (quad_perm 2,3,0,1)
+                if (G >= 8) s = dpp_add<0x141>(s);               // other quad (row_half_mirror)
+                if (G >= 16) s = dpp_add<0x140>(s);              // other half row (row_mirror)
+                if (G == 64)
+                    s = __builtin_amdgcn_readlane(s, 0) + __builtin_amdgcn_readlane(s, 16) + __builtin_amdgcn_readlane(s, 32) +
+                        __builtin_amdgcn_readlane(s, 48);
+                if (r == 0 && here) pix_sum[pixel] = s;
+                if (!PADDED && here)
+                    for (int d = (D3 ? QPP / 8 * 3 : QPP / LPW) + r; d < DP; d += G)
+                        (cb + ((size_t)k * PPS + row) * DP)[d] = 0;
+                sum = 0;
+                j = 0;
+                ++k;
+            }
+        }
+    }
+}
+
+// NHWC input with any number of channels.  One thread produces one packed word (8 channels
+// at 4-bit, 16 at 2-bit).  A block owns PB whole pixels, so pixel sums never straddle blocks.
 // Because a pixel is a multiple of 8 (4-bit) or 4 (2-bit) words long and the
 // block starts on a pixel, every aligned group of 8 (4) lanes works on one
 // pixel: their code sums are combined with DPP adds before one lane either
 // stores the pixel sum (one group per pixel) or adds it into LDS.
-// THR: use the step-function form of the quantizer (large tensors, where the
-// division would cost more than the memory time); small, latency-bound tensors
-// keep the recipe itself and save the table set-up.
-template <int CONT, bool VEC, bool THR>
+template <int CONT>
 __global__ __launch_bounds__(256) void quantize_act_nhwc_kernel(
     const float *__restrict__ x, uint32_t *__restrict__ codes, int32_t *__restrict__ pix_sum,
-    int total_pixels, int C, int DP, int dp_shift, int PB, float l, float u, int top, DsqThresholds th)
+    int total_pixels, int C, int DP, int dp_shift, int PB, DsqQuant q)
 {
     constexpr int CPD = 32 / CONT;           // channels per packed word
     constexpr int GROUP = CPD == 8 ? 8 : 4;  // lanes that surely share a pixel
-    constexpr int MODE = !THR ? 0 : CONT == 2 ? 1 : 2;   // 1- and 2-bit codes: at most three thresholds
     __shared__ int spix[DSQ_QUANT_MAX_PB];
-    __shared__ float2 tpairs[16];
-    const QuantParams qp = {l, u, dsq_delta(l, u, top), th.inv_delta, th.thr[1], th.thr[2], th.thr[3], top};
-    if (MODE == 2) fill_threshold_pairs(tpairs, th);
-
     const int tid = threadIdx.x;
     const int pixel0 = blockIdx.x * PB;
     const int npix = min(PB, total_pixels - pixel0);
     const bool multi_group = DP != GROUP;
     if (multi_group) {
         for (int i = tid; i < npix; i += 256) spix[i] = 0;
+        __syncthreads();
     }
-    if (multi_group || MODE == 2) __syncthreads();
     const int ndw = npix * DP;
     const int ndw_up = (ndw + 255) & ~255;   // all lanes take part in the DPP adds
 
@@ -123,18 +234,11 @@ __global__ __launch_bounds__(256) void quantize_act_nhwc_kernel(
         int s = 0;
         if (active) {
             const float *px = x + (size_t)(pixel0 + p) * C;
-            if (CONT == 4) {
-                uint32_t lo = quant4<VEC, MODE>(px, c0, C, qp, tpairs);
-                uint32_t hi = quant4<VEC, MODE>(px, c0 + 4, C, qp, tpairs);
-                word = dsq_pack8x4(lo, hi);
-                s = dsq_bytesum(lo) + dsq_bytesum(hi);
-            } else {
-                uint32_t b0 = quant4<VEC, MODE>(px, c0, C, qp, tpairs);
-                uint32_t b1 = quant4<VEC, MODE>(px, c0 + 4, C, qp, tpairs);
-                uint32_t b2 = quant4<VEC, MODE>(px, c0 + 8, C, qp, tpairs);
-                uint32_t b3 = quant4<VEC, MODE>(px, c0 + 12, C, qp, tpairs);
-                word = b0 | (b1 << 2) | (b2 << 4) | (b3 << 6);
-                s = dsq_bytesum(b0) + dsq_bytesum(b1) + dsq_bytesum(b2) + dsq_bytesum(b3);
+#pragma unroll
+            for (int g = 0; g < CPD / 4; ++g) {
+                const uint32_t b = quant4_of(px, 1, c0 + 4 * g, C, q);
+                word |= b << (CONT * g);
+                s += bytesum(b);
             }
             codes[(size_t)(pixel0 + p) * DP + d] = word;
         }
@@ -152,163 +256,44 @@ __global__ __launch_bounds__(256) void quantize_act_nhwc_kernel(
     }
 }
 
-// NHWC input whose channel count is a multiple of one packed word (8 channels at
-// 4-bit containers, 16 at 2-bit) and whose base is 16-byte aligned -- the common
-// case.  Lane-contiguous version: consecutive lanes read consecutive float4
-// (every load instruction of a wave covers 1 KB of contiguous memory, where the
-// kernel above has each lane walk its own 32- or 64-byte segment), each lane
-// turns its four values into four code bytes, and the 2 (4) neighbouring lanes
-// that share a packed word combine their bytes with DPP moves.  A block owns PB
-// whole pixels; code sums are reduced over aligned lane groups inside a pixel
-// with DPP adds, then added into LDS counters.
-template <int CONT, bool NT = false>
-__global__ __launch_bounds__(256) void quantize_act_nhwc_coalesced_kernel(
-    const float *__restrict__ x, uint32_t *__restrict__ codes, int32_t *__restrict__ pix_sum,
-    int total_pixels, int C, int DP, int PB, float inv_qp, float l, float u, int top, DsqThresholds th)
-{
-    // CONT = 3: dense 3-bit output, eight lanes per 12-byte unit of 32 channels (C % 32 == 0)
-    constexpr bool D3 = CONT == 3;
-    constexpr int CPD = D3 ? 32 : 32 / CONT; // channels per packed word (dense: per unit)
-    constexpr int LPW = CPD / 4;             // lanes per packed word: 2 or 4 (dense: 8 per unit)
-    constexpr int WPU = D3 ? 3 : 1;          // words per packed word / unit
-    constexpr int MODE = CONT == 2 ? 1 : 2;  // 1- and 2-bit codes: at most three thresholds
-    __shared__ int spix[DSQ_QUANT_MAX_PB];
-    __shared__ float2 tpairs[16];
-    const QuantParams qp = {l, u, 0.f, th.inv_delta, th.thr[1], th.thr[2], th.thr[3], top};
-    if (MODE == 2) fill_threshold_pairs(tpairs, th);
-
-    const int tid = threadIdx.x;
-    const int pixel0 = blockIdx.x * PB;
-    const int npix = min(PB, total_pixels - pixel0);
-    const int QP = C / 4;                    // float4 units per pixel (a multiple of LPW)
-    const int real_words = C / CPD * WPU;    // packed words per pixel that carry channels
-    for (int i = tid; i < npix; i += 256) spix[i] = 0;
-    __syncthreads();
-
-    const int nunits = npix * QP;
-    const int nunits_up = (nunits + 255) & ~255;     // all lanes take part in the DPP moves
-    const float4 *xb = reinterpret_cast<const float4 *>(x + (size_t)pixel0 * C);
-    // lanes of an aligned group of `group` lanes belong to one pixel
-    const int group = (QP & 15) == 0 ? 16 : (QP & 7) == 0 ? 8 : (QP & 3) == 0 ? 4 : 2;
-
-    for (int i = tid; i < nunits_up; i += 256) {
-        const bool active = i < nunits;
-        uint32_t b = 0;
-        if (active) {
-            float4 f;
-            if (NT) {
-                // a tensor larger than the last-level cache is read once and never again
-                typedef float v4f __attribute__((ext_vector_type(4)));
-                const v4f t = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(xb) + i);
-                f = make_float4(t.x, t.y, t.z, t.w);
-            } else {
-                f = xb[i];
-            }
-            b = dsq_bytes4(qcode<MODE>(f.x, qp, tpairs), qcode<MODE>(f.y, qp, tpairs),
-                           qcode<MODE>(f.z, qp, tpairs), qcode<MODE>(f.w, qp, tpairs));
-        }
-        int p = (int)((float)i * inv_qp);            // i / QP with a float reciprocal and a fix-up (i < 2^22)
-        int q = i - p * QP;
-        if (q < 0) { --p; q += QP; }
-        if (q >= QP) { ++p; q -= QP; }
-        int s = dsq_bytesum(b);
-        uint32_t word;
-        if (D3) {
-            // lane g of a unit holds group g: its low bits go to word g / 4 at bit 2 (g % 4) of
-            // every byte, its high bits to word 2 at bit g of every byte; the eight lanes OR
-            // their shares together and lanes 0..2 store one word each
-            const int g = tid & 7;
-            const uint32_t low = (b & 0x03030303u) << (2 * (g & 3));
-            uint32_t w0 = g < 4 ? low : 0u, w1 = g < 4 ? 0u : low, w2 = ((b >> 2) & 0x01010101u) << g;
-            w0 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w0, 0xB1, 0xF, 0xF, true);
-            w1 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w1, 0xB1, 0xF, 0xF, true);
-            w2 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w2, 0xB1, 0xF, 0xF, true);
-            w0 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w0, 0x4E, 0xF, 0xF, true);
-            w1 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w1, 0x4E, 0xF, 0xF, true);
-            w2 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w2, 0x4E, 0xF, 0xF, true);
-            w0 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w0, 0x141, 0xF, 0xF, true);
-            w1 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w1, 0x141, 0xF, 0xF, true);
-            w2 |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)w2, 0x141, 0xF, 0xF, true);
-            word = g == 0 ? w0 : g == 1 ? w1 : w2;
-        } else if (CONT == 4) {
-            // word = channels 8w..8w+7: byte j = c[j] | c[j+4] << 4; the odd lane holds c[4..7]
-            const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)b, 0xB1, 0xF, 0xF, true);
-            word = b | (other << 4);
-        } else {
-            // word = 16 channels: byte j = c[j] | c[j+4] << 2 | c[j+8] << 4 | c[j+12] << 6
-            uint32_t v = b << (2 * (tid & 3));
-            v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
-            v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
-            word = v;
-        }
-        if (D3) {
-            if (active && (tid & 7) < 3) codes[(size_t)(pixel0 + p) * DP + (q >> 3) * 3 + (tid & 7)] = word;
-        } else if (active && (tid & (LPW - 1)) == 0) {
-            codes[(size_t)(pixel0 + p) * DP + q / LPW] = word;
-        }
-        s = dpp_add<0xB1>(s);                                   // lanes ^1
-        if (group >= 4) s = dpp_add<0x4E>(s);                   // lanes ^2
-        if (group >= 8) s = dpp_add<0x141>(s);                  // other quad (row_half_mirror)
-        if (group >= 16) s = dpp_add<0x140>(s);                 // other half row (row_mirror)
-        if (active && (tid & (group - 1)) == 0) atomicAdd(&spix[p], s);
-    }
-    __syncthreads();
-    for (int i = tid; i < npix; i += 256) pix_sum[pixel0 + i] = spix[i];
-    // channels C..Cp-1 of every pixel hold code 0
-    const int pad_words = DP - real_words;
-    for (int i = tid; i < npix * pad_words; i += 256) {
-        const int p = i / pad_words, d = real_words + i - p * pad_words;
-        codes[(size_t)(pixel0 + p) * DP + d] = 0;
-    }
-}
-
-// NHWC input of few, deep pixels (the input of a fully connected layer): a block of 1024
+// NHWC input of few, deep pixels (the input of a fully connected layer): a block of 256 or 1024
 // threads owns one pixel, and a thread has the loads of U packed words in flight.  Words past
-// the pixel's end are neither loaded nor quantized: with them 8192 channels, a quarter of the
-// block's words, took 6.4 us at 64 pixels, and the kernel was slower there than the one it
-// replaces.  Bound by the latency of the 4*C bytes that one compute unit reads.  4 bits, us,
-// against blocks of 256 threads with one word in flight each (tensor in the last-level cache):
-// 8192 channels x 1 / 64 / 512 pixels 4.3 -> 3.6 / 4.6 -> 3.9 / 6.6 -> 5.2, 25088 channels
-// 9.9 -> 5.6 / 10.6 -> 6.0 / 19.4 -> 12.6.  C is a multiple of 4.
-template <int CONT>
-__global__ __launch_bounds__(1024) void quantize_act_deep_kernel(const float *__restrict__ x, uint32_t *__restrict__ codes,
-                                                                 int32_t *__restrict__ pix_sum, int C, int DP, float l, float u,
-                                                                 int top, DsqThresholds th)
+// the pixel's end are neither loaded nor quantized (with them 8192 channels, a quarter of the
+// large block's words, took 6.4 us at 64 pixels).  Bound by the latency of the 4*C bytes that one
+// compute unit reads.  C is a multiple of 4.
+template <int CONT, int THREADS>
+__global__ __launch_bounds__(THREADS) void quantize_act_deep_kernel(const float *__restrict__ x, uint32_t *__restrict__ codes,
+                                                                 int32_t *__restrict__ pix_sum, int C, int DP, DsqQuant q)
 {
     constexpr int CPD = 32 / CONT, FPW = CPD / 4;    // channels and float4 groups per packed word
-    constexpr int MODE = CONT == 2 ? 1 : 2, U = 8 / FPW;
-    __shared__ int part[16];
-    __shared__ float2 tpairs[16];
-    const QuantParams qp = {l, u, 0.f, th.inv_delta, th.thr[1], th.thr[2], th.thr[3], top};
-    if (MODE == 2) fill_threshold_pairs(tpairs, th);
-    __syncthreads();
+    constexpr int U = 8 / FPW;
+    __shared__ int part[THREADS / 64];
     const int tid = threadIdx.x;
     const float *px = x + (size_t)blockIdx.x * C;
     uint32_t *row = codes + (size_t)blockIdx.x * DP;
     int sum = 0;
-    for (int base = tid; base < DP; base += 1024 * U) {
+    for (int base = tid; base < DP; base += THREADS * U) {
         float4 f[U][FPW];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            if (base + k * 1024 >= DP) continue;     // (whole waves, but for the one that holds the pixel's end)
+            if (base + k * THREADS >= DP) continue;     // (whole waves, but for the one that holds the pixel's end)
 #pragma unroll
             for (int g = 0; g < FPW; ++g) {
-                const int c = (base + k * 1024) * CPD + 4 * g;
+                const int c = (base + k * THREADS) * CPD + 4 * g;
                 f[k][g] = *reinterpret_cast<const float4 *>(px + (c < C ? c : 0));      // (blanked below)
             }
         }
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            const int d = base + k * 1024;
+            const int d = base + k * THREADS;
             if (d >= DP) continue;
             uint32_t word = 0;
 #pragma unroll
             for (int g = 0; g < FPW; ++g) {
-                const uint32_t b = dsq_bytes4(qcode<MODE>(f[k][g].x, qp, tpairs), qcode<MODE>(f[k][g].y, qp, tpairs),
-                                              qcode<MODE>(f[k][g].z, qp, tpairs), qcode<MODE>(f[k][g].w, qp, tpairs));
-                const uint32_t m = d * CPD + 4 * g < C ? b : 0u;
+                const bool in = d * CPD + 4 * g < C;
+                const uint32_t b = quant4(f[k][g], q, in), m = in ? b : 0u;
                 word |= m << (CONT * g);
-                sum += dsq_bytesum(m);
+                sum += bytesum(m);
             }
             row[d] = word;
         }
@@ -320,7 +305,7 @@ __global__ __launch_bounds__(1024) void quantize_act_deep_kernel(const float *__
     if (tid == 0) {
         int s = 0;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) s += part[w];
+        for (int w = 0; w < THREADS / 64; ++w) s += part[w];
         pix_sum[blockIdx.x] = s;
     }
 }
@@ -329,26 +314,18 @@ __global__ __launch_bounds__(1024) void quantize_act_deep_kernel(const float *__
 // fixed channel); the NW waves of a block take the packed words of those pixels in turn.
 // The words of up to 64 per pixel meet in LDS, from where the block writes them out as the
 // contiguous run that 64 pixels of the packed tensor are (lanes that store one word each
-// touch 64 separate rows per instruction).  Step-function form of the recipe, as in the NHWC
-// kernels.  4 bits, us, against word stores and divisions (tensor in the last-level cache): 128
-// channels at 28x28 x 64 16.1 -> 9.3, 3 channels at 224x224 x 32 35 -> 29 (42 while words without
-// channels were quantized too).
+// touch 64 separate rows per instruction).  4 bits, us, with the codes looked up between
+// thresholds in LDS -> now (tensor in the last-level cache): 128 channels at 28x28 x 64 9.5 -> 7.9,
+// 512 at 7x7 x 64 8.3 -> 6.5, 64 at 56x56 x 64 13.2 -> 11.2.
 template <int CONT, int NW>
 __global__ __launch_bounds__(64 * NW) void quantize_act_nchw_kernel(
     const float *__restrict__ x, uint32_t *__restrict__ codes, int32_t *__restrict__ pix_sum,
-    int C, int HW, int DP, float l, float u, int top, DsqThresholds th)
+    int C, int HW, int DP, DsqQuant q)
 {
     constexpr int CPD = 32 / CONT;
-    constexpr int MODE = CONT == 2 ? 1 : 2;
     constexpr int MOST = 64;                         // words per pixel and pass
     __shared__ uint32_t words[64 * (MOST + 1)];      // (odd row length: no bank conflicts)
     __shared__ int ssum[NW][64];
-    __shared__ float2 tpairs[16];
-    const QuantParams qp = {l, u, 0.f, th.inv_delta, th.thr[1], th.thr[2], th.thr[3], top};
-    if (MODE == 2) {
-        fill_threshold_pairs(tpairs, th);
-        __syncthreads();
-    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int hw0 = blockIdx.x * 64;
     const int npix = min(64, HW - hw0);
@@ -366,12 +343,15 @@ __global__ __launch_bounds__(64 * NW) void quantize_act_nchw_kernel(
 #pragma unroll
             for (int j = 0; j < CPD; ++j) v[j] = xn[(size_t)(c0 + j < C ? c0 + j : 0) * HW];
             uint32_t word = 0;
+            // channel j of the word sits in byte j%4 at bit offset CONT*(j/4)
 #pragma unroll
-            for (int j = 0; j < CPD; ++j) {
-                const int q = c0 + j < C ? qcode<MODE>(v[j], qp, tpairs) : 0;
-                s += q;
-                // channel j of the word sits in byte j%4 at bit offset CONT*(j/4)
-                word |= (uint32_t)q << (8 * (j & 3) + CONT * (j >> 2));
+            for (int g = 0; g < CPD / 4; ++g) {
+                const int left = C - (c0 + 4 * g);           // (uniform)
+                if (left <= 0) break;
+                uint32_t b = quant4(make_float4(v[4 * g], v[4 * g + 1], v[4 * g + 2], v[4 * g + 3]), q, true);
+                if (left < 4) b &= (1u << (8 * left)) - 1u;
+                word |= b << (CONT * g);
+                s += bytesum(b);
             }
             words[lane * (MOST + 1) + d] = word;
         }
@@ -396,46 +376,28 @@ __global__ __launch_bounds__(64 * NW) void quantize_act_nchw_kernel(
 }
 
 // ---- dense 3-bit output ---------------------------------------------------------
-// 32 channels of a pixel become one 12-byte unit (format: dsq_device.h).  The recipe
-// itself (dsq_code, IEEE division) runs per element.
+// 32 channels of a pixel become one 12-byte unit (format: dsq_device.h).
 //
-// NHWC: one thread per unit, the units of a pixel in neighbouring lanes; a block owns
-// whole pixels (PB of them, UPX units each) and adds up their code sums in LDS.
+// NHWC, any number of channels: one thread per unit, the units of a pixel in neighbouring
+// lanes; a block owns whole pixels (PB of them, UPX units each) and adds up their code sums in LDS.
 __global__ __launch_bounds__(256) void quantize_act_dense3_nhwc_kernel(const float *__restrict__ x, uint32_t *__restrict__ codes,
                                                                        int *__restrict__ pix_sum, int pixels, int C, int UPX,
-                                                                       int PB, float l, float u)
+                                                                       int PB, DsqQuant q)
 {
     __shared__ int psum[256];
     const int tid = threadIdx.x;
     psum[tid] = 0;
     __syncthreads();
-    const float delta = dsq_delta(l, u, 7);
     const int pl = tid / UPX, k = tid - pl * UPX;
     const long long p = (long long)blockIdx.x * PB + pl;
     if (pl < PB && p < pixels) {
         const float *row = x + (size_t)p * C;
-        const bool vec = (C & 3) == 0 && (((uintptr_t)x & 15) == 0);
         uint32_t d[8];
         int sum = 0;
 #pragma unroll
         for (int g = 0; g < 8; ++g) {
-            const int c = 32 * k + 4 * g;
-            float v[4] = {0.f, 0.f, 0.f, 0.f};
-            if (vec && c + 3 < C) {
-                const float4 t = *reinterpret_cast<const float4 *>(row + c);
-                v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (c + j < C) v[j] = row[c + j];
-            }
-            int q[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                q[j] = c + j < C ? dsq_code(v[j], l, u, delta, 7) : 0;       // padding channels: code 0
-                sum += q[j];
-            }
-            d[g] = dsq_bytes4(q[0], q[1], q[2], q[3]);
+            d[g] = quant4_of(row, 1, 32 * k + 4 * g, C, q);
+            sum += bytesum(d[g]);
         }
         uint32_t l0, l1, hi;
         dsq_pack32_d3(d, l0, l1, hi);
@@ -451,12 +413,11 @@ __global__ __launch_bounds__(256) void quantize_act_dense3_nhwc_kernel(const flo
 // reads of a channel are contiguous); the thread walks the pixel's units.
 __global__ __launch_bounds__(256) void quantize_act_dense3_nchw_kernel(const float *__restrict__ x, uint32_t *__restrict__ codes,
                                                                        int *__restrict__ pix_sum, int C, int HW, int UPX,
-                                                                       float l, float u)
+                                                                       DsqQuant q)
 {
     const int hw = blockIdx.x * 256 + threadIdx.x;
     const int n = blockIdx.y;
     if (hw >= HW) return;
-    const float delta = dsq_delta(l, u, 7);
     const float *img = x + (size_t)n * C * HW + hw;
     const size_t p = (size_t)n * HW + hw;
     int sum = 0;
@@ -464,14 +425,8 @@ __global__ __launch_bounds__(256) void quantize_act_dense3_nchw_kernel(const flo
         uint32_t d[8];
 #pragma unroll
         for (int g = 0; g < 8; ++g) {
-            int q[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c = 32 * k + 4 * g + j;
-                q[j] = c < C ? dsq_code(img[(size_t)c * HW], l, u, delta, 7) : 0;
-                sum += q[j];
-            }
-            d[g] = dsq_bytes4(q[0], q[1], q[2], q[3]);
+            d[g] = quant4_of(img, HW, 32 * k + 4 * g, C, q);
+            sum += bytesum(d[g]);
         }
         uint32_t l0, l1, hi;
         dsq_pack32_d3(d, l0, l1, hi);
@@ -481,17 +436,50 @@ __global__ __launch_bounds__(256) void quantize_act_dense3_nchw_kernel(const flo
     pix_sum[p] = sum;
 }
 
+// Rows of 4 to 64 lanes, units in flight, and steps per wave.  All figures in us, 4 bits, tensor in the
+// last-level cache where it fits.
+template <int CONT>
+void launch_rows(const float *x, uint32_t *codes, int32_t *pix_sum, int total_pixels, int C, int DP, const DsqQuant &q,
+                 hipStream_t stream)
+{
+    const int QP = C / 4, units = dsq_round_up(C, 64) / 4;
+    // 64 lanes where a pixel has as many units and there are few of them: 4 / 8 / 16 / 64 lanes take 11.4 / 6.9
+    // / 4.6 / 3.1 for 512 channels at 7x7 x 64, but at 64 channels, 56x56 x 64, 12.6 / 11.0 / 11.1 / 24.9 (with
+    // more loads than this the 16-lane rows are level or ahead).  Below 16 units a row of 16 is mostly
+    // idle: 16 channels at 56x56 x 64 4.9 / 6.3 / 8.4, 40 channels 8.8 / 9.1 / 9.1; 80 channels at 73x73 x
+    // 16 7.4 / 6.8 / 7.8.  (From 2^24 channels on the offsets of a row of pixels would not fit 32 bits.)
+    const long long loads = (long long)total_pixels * units / 64;
+    const int G = C >= (1 << 24) || (units >= 64 && loads < 32768) ? 64
+                : QP <= 12 ? (CONT == 3 ? 8 : 4) : QP < 24 && QP != 16 ? 8 : 16;
+    // Tensors of 192 MB and more (three quarters of the last-level cache) are read with
+    // non-temporal loads, in long waves with four in flight: 224x224 x 64 channels x 32 78 us, 88 with one in
+    // flight and two steps; 112x112 x 128 x 32 41, with one in flight 44.  Smaller tensors: two loads a wave
+    // (112x112 x 64 x 32 18.2, with one 19.3, with eight 19.1), one where that leaves the chip short of waves.
+    const bool nt = (long long)total_pixels * QP >= 12LL * 1024 * 1024;
+    const int pps = 64 / G, J = G >= 16 ? (units + G - 1) / G : (QP + G - 1) / G;
+    int steps = (nt ? 8 : 2) / J;
+    while (steps > 1 && (long long)total_pixels / (pps * steps) < 8192) steps >>= 1;
+    if (steps < 1) steps = 1;
+    const long long waves = ((long long)total_pixels + pps * steps - 1) / (pps * steps);
+    const dim3 grid((unsigned)((waves + 3) / 4));
+#define DSQ_ROWS(G, U, NT) quantize_act_rows_kernel<CONT, G, U, NT><<<grid, 256, 0, stream>>>(x, codes, pix_sum, total_pixels, C, DP, steps, q)
+    if (G == 64) DSQ_ROWS(64, 1, false);
+    else if (G == 8) DSQ_ROWS(8, 1, false);
+    else if (G == 16 && nt) DSQ_ROWS(16, 4, true);
+    else if (G == 16) DSQ_ROWS(16, 1, false);
+    else if constexpr (CONT != 3) DSQ_ROWS(4, 1, false);
+#undef DSQ_ROWS
+}
+
 }  // namespace
 
-hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C, int H, int W,
-                                   float l, float u, int bits, const DsqThresholds &th, void *codes,
-                                   int32_t *pix_sum, hipStream_t stream)
+hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C, int H, int W, int bits,
+                                   const DsqQuant &q, void *codes, int32_t *pix_sum, hipStream_t stream)
 {
     const int cont = dsq_container(bits);
-    const int top = (1 << bits) - 1;
-    const int Cp = dsq_round_up(C, 64);
-    const int DP = Cp * cont / 32;
+    const int DP = dsq_round_up(C, 64) * cont / 32;
     const int total_pixels = N * H * W;
+    uint32_t *cw = (uint32_t *)codes;
     // (one pixel per image: the two layouts are the same memory)
     if (layout_nchw && H * W > 1) {
         dim3 grid((H * W + 63) / 64, N);
@@ -501,12 +489,29 @@ hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C
         // 37 / 45; 512 channels 21.9 / 10.7 at 14x14 x 64, 95 / 89 at 56x56 x 64.  So from about 1000 blocks
         // on pixels of 16 to 24 words are up to 20 % better off with four, deeper ones with 16.
         const bool many = DP >= 16 && (long long)grid.x * grid.y < 4096;
-#define DSQ_NCHW_LAUNCH(CONT, NW)                                                            \
-        quantize_act_nchw_kernel<CONT, NW><<<grid, 64 * NW, 0, stream>>>(                    \
-            x, (uint32_t *)codes, pix_sum, C, H * W, DP, l, u, top, th)
+#define DSQ_NCHW_LAUNCH(CONT, NW) quantize_act_nchw_kernel<CONT, NW><<<grid, 64 * NW, 0, stream>>>(x, cw, pix_sum, C, H * W, DP, q)
         if (cont == 4) { if (many) DSQ_NCHW_LAUNCH(4, 16); else DSQ_NCHW_LAUNCH(4, 4); }
         else           { if (many) DSQ_NCHW_LAUNCH(2, 16); else DSQ_NCHW_LAUNCH(2, 4); }
 #undef DSQ_NCHW_LAUNCH
+        return hipGetLastError();
+    }
+    if (C % 4 == 0) {
+        // A block per pixel where pixels are few and deep (us, 4 bits, a wave of the rows kernel per pixel / blocks
+        // of 256 / of 1024 threads): 4096 channels x 1 5.7 / 2.5 / 2.4, x 64 6.7 / 2.8 / 2.8, x 600 6.6 / 3.6 / 4.0;
+        // 1024 channels at 7x7 x 64 4.1 / 4.1 / 8.4.  1024 threads from 8192 (2 bits: 16384) channels on, up to 512
+        // pixels.
+#define DSQ_DEEP(T) do { if (cont == 4) quantize_act_deep_kernel<4, T><<<total_pixels, T, 0, stream>>>(x, cw, pix_sum, C, DP, q); \
+            else quantize_act_deep_kernel<2, T><<<total_pixels, T, 0, stream>>>(x, cw, pix_sum, C, DP, q); } while (0)
+        if (DP >= 1024 && total_pixels <= 512) {
+            DSQ_DEEP(1024);
+        } else if (C >= 2048 && total_pixels <= 4096) {
+            DSQ_DEEP(256);
+        } else if (cont == 4) {
+            launch_rows<4>(x, cw, pix_sum, total_pixels, C, DP, q, stream);
+        } else {
+            launch_rows<2>(x, cw, pix_sum, total_pixels, C, DP, q, stream);
+        }
+#undef DSQ_DEEP
         return hipGetLastError();
     }
     // Words per thread: few for small tensors (enough blocks to cover the
@@ -519,89 +524,26 @@ hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C
     if (PB > DSQ_QUANT_MAX_PB) PB = DSQ_QUANT_MAX_PB;
     int dp_shift = -1;
     if ((DP & (DP - 1)) == 0) { dp_shift = 0; while ((1 << dp_shift) < DP) ++dp_shift; }
-    const bool vec = (C % 4 == 0) && (((uintptr_t)x & 15) == 0);
-    // us, the kernel below / the deep one, 4 bits: 8192 channels (1024 words) x 1 4.3 / 3.6, x 512 6.8 / 5.4,
-    // x 1024 10.2 / 9.1, x 2048 14.7 / 16.1; 25088 channels x 64 10.6 / 6.0, x 512 19.4 / 12.6; below, at 4096
-    // channels, level up to 512 pixels (3.5 / 3.5 x 64) and 6.0 / 6.5 x 1024.
-    if (vec && DP >= 1024 && total_pixels <= 512) {
-        if (cont == 4)
-            quantize_act_deep_kernel<4><<<total_pixels, 1024, 0, stream>>>(x, (uint32_t *)codes, pix_sum, C, DP, l, u, top, th);
-        else
-            quantize_act_deep_kernel<2><<<total_pixels, 1024, 0, stream>>>(x, (uint32_t *)codes, pix_sum, C, DP, l, u, top, th);
-        return hipGetLastError();
-    }
-    // The lane-contiguous kernel wins on tensors large enough to be bandwidth bound
-    // (measured: 4.0 -> 5.0 TB/s at 2 bits); small ones are latency bound and do
-    // better with the kernel below, which has less per-block set-up.
-    if (vec && C % (32 / cont) == 0 && (long long)total_pixels * (C / 4) >= 512 * 1024) {
-        const int QP = C / 4;
-        const long long total_units = (long long)total_pixels * QP;
-        int it = 8;
-        while (it > 2 && total_units / (256LL * it) < 2048) it >>= 1;
-        // (pixels that are not a multiple of 16 float4 long reduce their code sums in
-        // small lane groups; measured, such tensors do better with few pixels per block)
-        if ((QP & 15) != 0) it = 2;
-        int pb = (256 * it) / QP;
-        if (pb < 1) pb = 1;
-        if (pb > DSQ_QUANT_MAX_PB) pb = DSQ_QUANT_MAX_PB;
-        dim3 g((total_pixels + pb - 1) / pb);
-        // Tensors of 192 MB and more (three quarters of the last-level cache) are read with
-        // non-temporal loads: measured 5.2 -> 5.5 TB/s at 411 MB and 4.6 -> 5.1 at 206 MB, while
-        // tensors of 50-100 MB lose 5-10 % with them.
-        const bool nt = total_units >= 12LL * 1024 * 1024;
-        if (cont == 4 && nt)
-            quantize_act_nhwc_coalesced_kernel<4, true><<<g, 256, 0, stream>>>(
-                x, (uint32_t *)codes, pix_sum, total_pixels, C, DP, pb, 1.0f / (float)QP, l, u, top, th);
-        else if (cont == 4)
-            quantize_act_nhwc_coalesced_kernel<4><<<g, 256, 0, stream>>>(
-                x, (uint32_t *)codes, pix_sum, total_pixels, C, DP, pb, 1.0f / (float)QP, l, u, top, th);
-        else if (nt)
-            quantize_act_nhwc_coalesced_kernel<2, true><<<g, 256, 0, stream>>>(
-                x, (uint32_t *)codes, pix_sum, total_pixels, C, DP, pb, 1.0f / (float)QP, l, u, top, th);
-        else
-            quantize_act_nhwc_coalesced_kernel<2><<<g, 256, 0, stream>>>(
-                x, (uint32_t *)codes, pix_sum, total_pixels, C, DP, pb, 1.0f / (float)QP, l, u, top, th);
-        return hipGetLastError();
-    }
     dim3 grid((total_pixels + PB - 1) / PB);
-    const bool thr = total_dw >= 256 * 1024;       // large enough to be bandwidth bound
-#define DSQ_Q_LAUNCH(CONT, VEC)                                                              \
-    do {                                                                                     \
-        if (thr) quantize_act_nhwc_kernel<CONT, VEC, true><<<grid, 256, 0, stream>>>(        \
-            x, (uint32_t *)codes, pix_sum, total_pixels, C, DP, dp_shift, PB, l, u, top, th); \
-        else quantize_act_nhwc_kernel<CONT, VEC, false><<<grid, 256, 0, stream>>>(           \
-            x, (uint32_t *)codes, pix_sum, total_pixels, C, DP, dp_shift, PB, l, u, top, th); \
-    } while (0)
-    if (cont == 4) { if (vec) DSQ_Q_LAUNCH(4, true); else DSQ_Q_LAUNCH(4, false); }
-    else           { if (vec) DSQ_Q_LAUNCH(2, true); else DSQ_Q_LAUNCH(2, false); }
-#undef DSQ_Q_LAUNCH
+    if (cont == 4) quantize_act_nhwc_kernel<4><<<grid, 256, 0, stream>>>(x, cw, pix_sum, total_pixels, C, DP, dp_shift, PB, q);
+    else quantize_act_nhwc_kernel<2><<<grid, 256, 0, stream>>>(x, cw, pix_sum, total_pixels, C, DP, dp_shift, PB, q);
     return hipGetLastError();
 }
 
-hipError_t dsq_launch_quantize_act_dense3(const float *x, int layout_nchw, int N, int C, int H, int W,
-                                          float l, float u, const DsqThresholds &th, void *codes, int32_t *pix_sum,
-                                          hipStream_t stream)
+hipError_t dsq_launch_quantize_act_dense3(const float *x, int layout_nchw, int N, int C, int H, int W, const DsqQuant &q,
+                                          void *codes, int32_t *pix_sum, hipStream_t stream)
 {
     const int UPX = dsq_round_up(C, 64) / 32;        // units per pixel (<= 256: checked by the caller)
     const int pixels = N * H * W;
     if (layout_nchw) {
         dim3 grid((H * W + 255) / 256, N);
-        quantize_act_dense3_nchw_kernel<<<grid, 256, 0, stream>>>(x, (uint32_t *)codes, pix_sum, C, H * W, UPX, l, u);
-    } else if (C % 32 == 0 && (((uintptr_t)x & 15) == 0)) {
-        // whole units of real channels: the lane-contiguous kernel (step-function form of the recipe)
-        const int QP = C / 4;
-        const long long total_units = (long long)pixels * QP;
-        int it = 8;
-        while (it > 2 && total_units / (256LL * it) < 2048) it >>= 1;
-        int pb = (256 * it) / QP;
-        if (pb < 1) pb = 1;
-        if (pb > DSQ_QUANT_MAX_PB) pb = DSQ_QUANT_MAX_PB;
-        quantize_act_nhwc_coalesced_kernel<3><<<(pixels + pb - 1) / pb, 256, 0, stream>>>(
-            x, (uint32_t *)codes, pix_sum, pixels, C, UPX * 3, pb, 1.0f / (float)QP, l, u, 7, th);
+        quantize_act_dense3_nchw_kernel<<<grid, 256, 0, stream>>>(x, (uint32_t *)codes, pix_sum, C, H * W, UPX, q);
+    } else if (C % 4 == 0) {
+        launch_rows<3>(x, (uint32_t *)codes, pix_sum, pixels, C, UPX * 3, q, stream);
     } else {
         const int PB = 256 / UPX;
         quantize_act_dense3_nhwc_kernel<<<(pixels + PB - 1) / PB, 256, 0, stream>>>(x, (uint32_t *)codes, pix_sum,
-                                                                                    pixels, C, UPX, PB, l, u);
+                                                                                    pixels, C, UPX, PB, q);
     }
     return hipGetLastError();
 }
