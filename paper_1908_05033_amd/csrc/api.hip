@@ -39,8 +39,6 @@ DsqQuant quantizer(float l, float u, int bits)
     return q;
 }
 
-void quantizer_thresholds(float l, float u, int bits, float thr[16]);
-
 }  // namespace
 
 extern "C" {
@@ -194,70 +192,20 @@ dsq_status conv_args(const dsq_conv_desc *d, const void *act_packed, const int32
     a.out = nullptr; a.acc = nullptr; a.out_nchw = 0;
     a.rq = 0; a.rq_scale = nullptr; a.rq_shift = nullptr; a.rq_relu = 0;
     a.rq_l = 0.f; a.rq_u = 1.f; a.rq_bits = 4; a.rq_dense = 0; a.rq_Cp = 0; a.rq_codes = nullptr; a.rq_pix = nullptr; a.rq_store = 0; a.rq_share = 0; a.rq_zeroed = 0;
-    for (int j = 0; j < 16; ++j) a.rq_thr[j] = 0.f;
-    a.rq_inv_delta = 0.f; a.rq_bias = 0.f;
-    a.rq_fast = 0; a.rq_t_lo = 0.5f; a.rq_t_hi = 0.5f; a.rq_t_margin = -1.f; a.rq_sa_max = 0.f; a.rq_w_max = 0.f;
-    a.rq_inv_dn = 0.0; a.rq_c0 = 0.0;
+    a.rq_delta = 1.f;
+    a.rq_fast = 0; a.rq_t_lo = 0.f; a.rq_t_hi = 0.f; a.rq_t_slack = 1.f; a.rq_sa_max = 0.f; a.rq_w_max = 0.f;
+    a.rq_inv_dn = 0.0; a.rq_c0 = 0.0; a.rq_da_dn = 0.0;
     return DSQ_OK;
 }
 
-// ---- the quantizer as a step function (host side) ---------------------------
-// The same binary32 recipe as the device function dsq_code, operation for
-// operation (this file is compiled without contraction of a*b+c).
+// The binary32 recipe of the device function dsq_code, operation for operation (this file
+// is compiled without contraction of a*b+c).
 int host_code(float x, float l, float u, float delta, int top)
 {
     const float v = fminf(fmaxf(x, l), u);
     const float t = (v - l) / delta;
     int c = (int)floorf(t + 0.5f);
     return c < 0 ? 0 : c > top ? top : c;
-}
-
-// Finite floats in increasing order <-> unsigned keys in increasing order.
-uint32_t key_of(float x)
-{
-    uint32_t b;
-    memcpy(&b, &x, 4);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-float float_of(uint32_t k)
-{
-    const uint32_t b = (k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k;
-    float x;
-    memcpy(&x, &b, 4);
-    return x;
-}
-
-// thr[j], j = 1..top: the smallest finite float whose code is >= j.  code() is monotone
-// non-decreasing, so a bisection over the ordered floats finds it; it begins with a bracket
-// grown from the real-valued threshold l + (j - 1/2)*Delta, a few floats away as a rule
-// (0.7 us a call on the host, over all widths and ranges; 5.4 us from the whole range).
-void quantizer_thresholds(float l, float u, int bits, float thr[16])
-{
-    const int top = (1 << bits) - 1;
-    const float delta = (u - l) / (float)top;
-    const uint32_t least = key_of(-3.4028234e38f), most = key_of(3.4028234e38f);   // code(least) = 0, code(most) = top
-    for (int j = 0; j < 16; ++j) thr[j] = NAN;          // unused: no value compares >= NaN
-    for (int j = 1; j <= top; ++j) {
-        auto reached = [&](uint32_t key) { return host_code(float_of(key), l, u, delta, top) >= j; };
-        const uint32_t guess = key_of((float)((double)l + ((double)j - 0.5) * (double)delta));
-        uint32_t lo = guess, hi = guess;
-        if (reached(guess)) {
-            for (uint32_t step = 1; lo != least && reached(lo); step *= 2) {
-                hi = lo;
-                lo = lo - least > step ? lo - step : least;
-            }
-        } else {
-            for (uint32_t step = 1; hi != most && !reached(hi); step *= 2) {
-                lo = hi;
-                hi = most - hi > step ? hi + step : most;
-            }
-        }
-        while (hi - lo > 1) {                           // code(lo) < j <= code(hi)
-            const uint32_t mid = lo + (hi - lo) / 2;
-            if (reached(mid)) hi = mid; else lo = mid;
-        }
-        thr[j] = float_of(hi);
-    }
 }
 
 // Every launcher checks its plan and kernel attributes first and only then
@@ -383,27 +331,21 @@ dsq_status dsq_conv2d_requant(const dsq_conv_desc *d, const void *act_packed,
     a.rq_l = l_next; a.rq_u = u_next; a.rq_bits = bits_next;
     a.rq_Cp = dsq_round_up(a.C_out, 64);
     a.rq_codes = codes_next; a.rq_pix = pix_code_sum_next;
-    quantizer_thresholds(l_next, u_next, bits_next, a.rq_thr);
     {
-        const float delta_n = (u_next - l_next) / (float)((1 << bits_next) - 1);
-        a.rq_inv_delta = 1.0f / delta_n;
-        a.rq_bias = 0.5f;
         // constants of the code-unit form (see DsqConvArgs)
         const int top_n = (1 << bits_next) - 1;
-        const double inv_dn = 1.0 / (double)delta_n, c0 = 0.5 - (double)l_next * inv_dn;
-        double e_thr = 0.0;
-        for (int j = 1; j <= top_n; ++j) e_thr = fmax(e_thr, fabs((double)a.rq_thr[j] * inv_dn + c0 - (double)j));
-        const int code0 = host_code(0.0f, l_next, u_next, delta_n, top_n);
+        const float delta_n = (u_next - l_next) / (float)top_n;
+        a.rq_delta = delta_n;
         const double c_max = a.cont == 2 ? 3.0 : 15.0;                   // largest code a container field holds
         const double depth = (double)a.R * a.R * a.C_in;
-        a.rq_inv_dn = inv_dn; a.rq_c0 = c0;
-        a.rq_t_lo = relu ? (float)code0 + 0.5f : 0.5f;
-        a.rq_t_hi = (float)top_n + 0.5f;
-        a.rq_t_margin = (float)(0.5 - e_thr - 0x1p-20);
+        a.rq_inv_dn = 1.0 / (double)delta_n; a.rq_c0 = -(double)l_next * a.rq_inv_dn;
+        a.rq_da_dn = (double)a.delta_a * a.rq_inv_dn;
+        a.rq_t_lo = relu ? (float)host_code(0.0f, l_next, u_next, delta_n, top_n) : 0.0f;
+        a.rq_t_hi = (float)top_n;
+        a.rq_t_slack = (float)(3 * 0x1p-24 * (top_n + 1) + 0x1p-20);
         a.rq_sa_max = (float)(c_max * depth);
         a.rq_w_max = (float)c_max;
-        a.rq_fast = c_max * c_max * depth < 0x1p24 && delta_n >= 0x1p-60f && delta_n <= 0x1p60f &&
-                    fabsf(l_next) <= 0x1p60f && a.rq_t_margin > 0.0f;
+        a.rq_fast = c_max * c_max * depth < 0x1p24 && delta_n >= 0x1p-60f && delta_n <= 0x1p60f && fabsf(l_next) <= 0x1p60f;
     }
     return launch_conv(a, (hipStream_t)hip_stream);
 }

@@ -135,26 +135,6 @@ __device__ __forceinline__ uint32_t dsq_requant4(const DsqConvArgs &a, int o0, c
     return dsq_bytes4(c[0], c[1], c[2], c[3]);
 }
 
-// Codes of four consecutive channels from their fp32 results, one per byte.
-// relu_floor is 0 with ReLU and -inf without (max(z, -inf) = z; a NaN becomes
-// -inf, which has code 0 like the NaN itself); byte_mask blanks the bytes of
-// channels >= C_out.
-__device__ __forceinline__ uint32_t dsq_requant4_thr(const float (&y)[4], const float (&sc)[4],
-                                                     const float (&sh)[4], float relu_floor, float l_n,
-                                                     float u_n, float inv_delta, int top_n,
-                                                     const float2 *thr_pairs, uint32_t byte_mask)
-{
-    int c[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        float z = y[j] * sc[j];
-        z = z + sh[j];
-        z = fmaxf(z, relu_floor);
-        c[j] = dsq_code_thr<false>(z, l_n, u_n, inv_delta, top_n, 0.f, 0.f, 0.f, thr_pairs);
-    }
-    return dsq_bytes4(c[0], c[1], c[2], c[3]) & byte_mask;
-}
-
 // Packs and stores one pixel's 32 channels [o_tile, o_tile + 32) of the next
 // layer's input.  In the accumulator layout of the 32x32x32 matrix instruction
 // lane L (pixel L%32, h = L/32) holds channels o_tile + 8q + 4h + 0..3 for

@@ -69,52 +69,62 @@ __device__ __forceinline__ void lds_barrier()
 }
 
 // Chained mode, per output channel o: the constants of the code-unit form of the
-// layer-to-layer map.  With P = Da*Dw[o], Q = Da*l_w[o] (binary64, exact), scale sc
-// and shift sh, the real value of the next layer's input in units of its quantizer
-// step is
-//   t = ((P*ACC + Q*SA)*sc + sh - l_n)/D_n + 1/2 = A*(ACC + rho*SA) + s,
-//   A = P*sc/D_n, rho = Q/P = l_w/Dw, s = sh/D_n + c0, c0 = 1/2 - l_n/D_n,
-// and the code is floor(t) clamped to the code range.  The kernel evaluates
+// layer-to-layer map.  With P = Da*Dw[o], Q = Da*l_w[o], scale sc and shift sh, the real
+// value of the next layer's input in units of its quantizer step, counted from l_n, is
+//   T = ((P*ACC + Q*SA)*sc + sh - l_n)/D_n = A*(ACC + rho*SA) + s,
+//   A = P*sc/D_n, rho = Q/P = l_w/Dw, s = sh/D_n + c0, c0 = -l_n/D_n,
+// and the code is T rounded to the nearest integer, clamped to the code range.  The kernel
+// evaluates
 //   u = fma(SA, rho32, ACC)             one rounding, of the small difference: the two
 //                                       large terms cancel inside the fma
-//   t = fma(u, A32, fma(SA, B32, s32))  B = A*(rho - rho32): the part of rho that
+//   T = fma(u, A32, fma(SA, B32, s32))  B = A*(rho - rho32): the part of rho that
 //                                       binary32 drops
 // The exact sequence (fp32 value of the layer, times scale, plus shift: three
 // roundings) and this one (three roundings, four rounded constants) each differ from
-// the real t by a few 2^-24 of |t| + S, S = |sh|/D_n + |c0|, in total less than
+// the real T by a few 2^-24 of |T| + S, S = |sh|/D_n + |c0| + 1, in total less than
 //   E = 2^-21*(2^bits + S) + 2^-45*|Q*sc/D_n|*SA_max
-// for t inside the code range (6|t| + 7S times 2^-24 to first order; the last term
+// for T inside the code range (6|T| + 7S times 2^-24 to first order; the last term
 // covers the rounding of B and of the fma that uses it).  Outside the range both
-// clamp alike when E < 1/2.  Returns te = margin - E (margin: see DsqConvArgs), what
-// |fract(t) - 1/2| must stay below for floor(t) to be the exact sequence's code;
-// te = -1 (never safe) for channels whose magnitudes would let an intermediate of
-// either sequence overflow, or lose bits to denormals, and when the host disabled
-// the form: those keep harmless constants, so that t stays finite.  Channels past
-// C_out get constants that give code 0 safely (their bytes are blanked anyway).
+// clamp alike when E < 1/2.  Returns how far T must stay from every half-integer for its
+// nearest integer to be the exact sequence's code: E plus what the host adds for the
+// quantizer's own roundings (DsqConvArgs); 1 (never) for channels whose magnitudes
+// would let an intermediate of either sequence overflow, or lose bits to denormals, and
+// when the host disabled the form: those keep harmless constants, so that T stays
+// finite.  Channels past C_out get constants that give code 0 safely (their bytes are
+// blanked anyway).
+//
+// A wave computes the constants of 64 channels before the main loop, in binary32 but for A
+// and s: rho32 is the quotient corrected by its remainder, r the remainder of that,
+// r/Dw = rho - rho32 to 22 bits.  (With a binary64 division, after the main loop where every
+// wave waits for it, the constants took 1400 clocks of a workgroup's 24000.)
 //
 // `unit`: the kernel's accumulators hold ACC/unit (the FP4 form counts in quarter
 // units): A*unit and rho32/unit are stored, both exact scalings by a power of two.
-__device__ __forceinline__ float chained_channel_constants(const DsqConvArgs &a, int o, double P, double Q, float scale,
-                                                           float shift, float unit, float4 &k)
+__device__ __forceinline__ float chained_channel_constants(const DsqConvArgs &a, bool real, float dw, float lw, float sc,
+                                                           float sh, float unit, float4 &k)
 {
-    k = make_float4(0.f, 0.f, 0.f, 0.5f);
-    if (o >= a.C_out) return 0.25f;
-    const double sc = (double)scale, sh = (double)shift, inv_dn = a.rq_inv_dn;
-    const double rho = Q / P;
-    const float rho32 = (float)rho;
-    const double A = P * sc * inv_dn;
-    const double s = __builtin_fma(sh, inv_dn, a.rq_c0);
-    const double S = __builtin_fabs(sh) * inv_dn + __builtin_fabs(a.rq_c0);
-    const double samax = (double)a.rq_sa_max;
-    const double E = 0x1p-21 * ((double)(1 << a.rq_bits) + S) + 0x1p-45 * __builtin_fabs(Q * sc * inv_dn) * samax;
-    const double ymax = (__builtin_fabs(P) * (double)a.rq_w_max + __builtin_fabs(Q)) * samax;    // bound on the layer's |output|
-    // (every comparison is false for a NaN, which then ends in te = -1)
-    const bool ok = a.rq_fast && ymax < 0x1p100 && ymax * __builtin_fabs(sc) < 0x1p100 && __builtin_fabs(sh) < 0x1p100 &&
-                    (__builtin_fabs(sc) + 1.0) * inv_dn < 0x1p100 && __builtin_fabs(A) < 0x1p60 &&
-                    __builtin_fabs(rho) < 0x1p20 && E < (double)a.rq_t_margin;
-    if (!ok) return -1.0f;
-    k = make_float4((float)A * unit, rho32 / unit, (float)(A * (rho - (double)rho32)), (float)s);
-    return (float)((double)a.rq_t_margin - E);
+    k = make_float4(0.f, 0.f, 0.f, 0.f);
+    float y = __builtin_amdgcn_rcpf(dw);
+    y = __builtin_fmaf(__builtin_fmaf(-dw, y, 1.0f), y, y);
+    float rho = lw * y;
+    rho = __builtin_fmaf(__builtin_fmaf(-rho, dw, lw), y, rho);
+    const float rest = __builtin_fmaf(-rho, dw, lw) * y;
+    const float A = (float)((double)dw * (double)sc * a.rq_da_dn);
+    const float s = (float)__builtin_fma((double)sh, a.rq_inv_dn, a.rq_c0);
+    const float inv_dn = (float)a.rq_inv_dn, c0 = __builtin_fabsf((float)a.rq_c0), samax = a.rq_sa_max;
+    const float S = __builtin_fabsf(sh) * inv_dn + c0 + 1.0f, q = __builtin_fabsf(a.delta_a * lw);
+    // (1.001: the roundings of the bound itself)
+    const float E = 1.001f * (0x1p-21f * ((float)(1 << a.rq_bits) + S) + 0x1p-45f * (q * __builtin_fabsf(sc)) * inv_dn * samax) + a.rq_t_slack;
+    const float ymax = (__builtin_fabsf(a.delta_a * dw) * a.rq_w_max + q) * samax;               // bound on the layer's |output|
+    // (every comparison is false for a NaN, which then ends in 1)
+    const bool ok = a.rq_fast && dw >= 0x1p-80f && __builtin_fabsf(lw) < 0x1p100f && ymax < 0x1p100f &&
+                    ymax * __builtin_fabsf(sc) < 0x1p100f && __builtin_fabsf(sh) < 0x1p100f &&
+                    (__builtin_fabsf(sc) + 1.0f) * inv_dn < 0x1p100f && __builtin_fabsf(A) < 0x1p60f &&
+                    __builtin_fabsf(rho) < 0x1p20f && E < 0.5f;
+    if (!real) return 0.25f;
+    if (!ok) return 1.0f;
+    k = make_float4(A * unit, rho / unit, A * rest, s);
+    return E;
 }
 
 // What the kernel's results become; chosen at compile time, so that the register
@@ -157,18 +167,17 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     constexpr int BC = 32 * CT * WC;
     double *pq_lds = reinterpret_cast<double *>(lds + pl.aux_off);
     int *pix_lds = reinterpret_cast<int *>(pq_lds + 2 * BC);
-    // chained mode: scale and shift of the workgroup's channels (16-byte aligned)
-    float *ss_lds = reinterpret_cast<float *>(lds + ((pl.aux_off + 2 * BC * 8 + pl.PR * pl.PC * 4 + 15) & ~15));
-    // chained mode: the next quantizer's thresholds as 16 (lower, upper) pairs
-    float2 *thr_lds = reinterpret_cast<float2 *>(ss_lds + 2 * BC);
-    // chained mode: per channel the constants (A, rho, B, s) of the code-unit form, and the
-    // largest distance from 1/2 of the fraction of t at which every channel's code is safe
-    float4 *ft_lds = reinterpret_cast<float4 *>(thr_lds + 16);
-    int *te_lds = reinterpret_cast<int *>(ft_lds + BC);              // (the bits of a float: see below)
+    // chained mode: in the place of the binary64 tables (Dw, l_w, scale, shift) of the
+    // workgroup's channels; behind the code sums, 16-byte aligned, the constants (A, rho, B, s)
+    // of the code-unit form, and per 64 channels the distance from a half-integer at which
+    // every channel's code is safe
+    float4 *raw_lds = reinterpret_cast<float4 *>(pq_lds);
+    float4 *ft_lds = reinterpret_cast<float4 *>(lds + ((pl.aux_off + 2 * BC * 8 + pl.PR * pl.PC * 4 + 15) & ~15));
+    float *te_lds = reinterpret_cast<float *>(ft_lds + BC);
     // general results of a layer with l_a != 0 (in the place of the chained mode's tables):
     // l_a*Dw and l_a*l_w of the workgroup's channels, the sum of a full pixel's border terms,
     // and the weight code sums of every tap as [tap][channel]
-    double *la_lds = reinterpret_cast<double *>(ss_lds);
+    double *la_lds = reinterpret_cast<double *>(ft_lds);
     int *swt_lds = reinterpret_cast<int *>(la_lds + 3 * BC);
 
     // KS = 2: two groups of four waves work on alternating 64-channel blocks of K
@@ -195,6 +204,8 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
                  "s"(pl.buf_bytes), "s"(pl.Hp), "s"(pl.aux_off), "s"(pl.step_q), "s"(pl.step_r),
                  "s"(pl.tiles_c), "s"(pl.total_blocks), "s"(pl.xcd_chunk), "s"(pl.mg_tiles_c), "s"(pl.mg_PC),
                  "s"(pl.mg_TW), "s"(pl.mg_Hp), "s"(pl.mg_Ho), "s"(pl.mg_tiles_w));
+    // (chained mode: the one cache line of them that the above does not touch)
+    if (RQ) asm volatile("" ::"s"(a.rq_t_lo));
 
     // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Give
     // every XCD a contiguous range of tiles, channel tiles of one pixel tile
@@ -322,12 +333,17 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     // the wait for it, and for everything issued before it, up to this point)
     const int chan_i = tid < 2 * BC ? tid : 0;
     const int chan_o = blk_y * BC + (chan_i < BC ? chan_i : chan_i - BC);      // < Cop by construction
-    const float chan_const = (chan_i < BC ? a.delta_w : a.l_w)[chan_o];
-    float rq_const = 0.f;
-    if (RQ && grp == 0 && tid < 2 * BC) {
-        const int o = blk_y * BC + (tid < BC ? tid : tid - BC);
-        const float *tab = tid < BC ? a.rq_scale : a.rq_shift;
-        rq_const = tab != nullptr && o < a.C_out ? tab[o] : (tid < BC ? 1.0f : 0.0f);
+    float chan_const = 0.f;
+    if (!RQ) chan_const = (chan_i < BC ? a.delta_w : a.l_w)[chan_o];
+    // chained mode: step and level of the channels, scale and shift (one channel per thread)
+    float4 raw = make_float4(0.f, 0.f, 0.f, 0.f);
+    const int rq_o = blk_y * BC + (tid < BC ? tid : 0);
+    if (RQ) {
+        const int in = rq_o < a.C_out ? rq_o : 0;
+        raw.x = a.delta_w[rq_o];
+        raw.y = a.l_w[rq_o];
+        raw.z = (a.rq_scale != nullptr ? a.rq_scale : a.delta_w)[in];
+        raw.w = (a.rq_shift != nullptr ? a.rq_shift : a.delta_w)[in];
     }
 
     const bool has_la = OUT == OUT_GENERAL && a.l_a != 0.0f;
@@ -488,19 +504,17 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         }
         // Da*Dw[o] and Da*l_w[o] of this workgroup's channels, in binary64
         const double da0 = (double)a.delta_a;
-        if (tid < 2 * BC) pq_lds[tid] = da0 * (double)chan_const;
-        if (RQ && tid < 2 * BC) ss_lds[tid] = rq_const;
-        if (RQ && tid < 16) {
-            // pair c = (thr[c], thr[c+1]); -inf below the first threshold, NaN above the last
-            float lo = -__builtin_inff(), hi = __builtin_nanf("");
+        if (!RQ && tid < 2 * BC) pq_lds[tid] = da0 * (double)chan_const;
+    }
+    if (RQ && grp == KS - 1 && tid < BC) {       // (whole waves: BC is a multiple of 64)
+        if (a.rq_scale == nullptr) raw.z = 1.0f;
+        if (a.rq_shift == nullptr) raw.w = 0.0f;
+        raw_lds[tid] = raw;
+        // (RAWF below: the FP4 accumulators are used as they are, in quarter units)
+        float d = chained_channel_constants(a, rq_o < a.C_out, raw.x, raw.y, raw.z, raw.w, F4 && KS == 1 ? 4.0f : 1.0f, ft_lds[tid]);
 #pragma unroll
-            for (int j = 1; j < 16; ++j) {
-                lo = tid == j ? a.rq_thr[j] : lo;
-                hi = tid + 1 == j ? a.rq_thr[j] : hi;
-            }
-            thr_lds[tid] = make_float2(lo, hi);
-            if (tid == 0) *te_lds = __float_as_int(0.5f);
-        }
+        for (int sft = 32; sft >= 1; sft >>= 1) d = __builtin_fmaxf(d, __shfl_xor(d, sft));
+        if (lane == 0) te_lds[tid >> 6] = d;
     }
     lds_barrier();
 
@@ -577,18 +591,6 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     // chained mode, one wave group: the code-unit form reads the FP4 accumulators as
     // they are (quarter units); the integers are only formed where the exact sequence runs
     constexpr bool RAWF = RQ && F4 && KS == 1;
-    if (RQ && grp == 0 && tid < BC) {
-        const float te = chained_channel_constants(a, blk_y * BC + tid, pq_lds[tid], pq_lds[BC + tid], ss_lds[tid],
-                                                   ss_lds[BC + tid], RAWF ? 4.0f : 1.0f, ft_lds[tid]);
-        // the smallest margin of the workgroup's channels: reduced over the wave first
-        // (BC is a multiple of 64, so whole waves get here), then one LDS operation per
-        // wave (te is -1 or in (0, 1/2]: as signed integers the bit patterns of such
-        // floats are ordered like the floats)
-        float m = te;
-#pragma unroll
-        for (int sft = 32; sft >= 1; sft >>= 1) m = __builtin_fminf(m, __shfl_xor(m, sft));
-        if (lane == 0) atomicMin(te_lds, __float_as_int(m));
-    }
     lds_barrier();                              // every wave is done with the patch buffers
     if (KS == 2) {
         // each group finishes the channel tiles c with c % 2 == grp: it hands the
@@ -638,79 +640,137 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         // their use, to keep the register footprint of this path small.  Lanes of tile
         // pixels past the end compute on patch pixel 0 and are never stored; at worst
         // they send their wave through the exact sequence once more.)
-        const int top_n = (1 << a.rq_bits) - 1;
-        const float relu_floor = a.rq_relu ? 0.0f : -__builtin_inff();
-        const float l_n = a.rq_l, u_n = a.rq_u, inv_delta_n = a.rq_inv_delta;
         const float t_lo = a.rq_t_lo, t_hi = a.rq_t_hi;
-        const float te_wg = __int_as_float(*te_lds);
+        float near_wg = te_lds[0];
+#pragma unroll
+        for (int i = 1; i < BC / 64; ++i) near_wg = __builtin_fmaxf(near_wg, te_lds[i]);
+        // this lane's share of the codes: a pixel's 32 channels of a tile lie in the two lanes of
+        // a pair, which exchange halves so that each holds two whole words (4-bit containers) or
+        // one (2-bit) of it
+        const bool four = dsq_container(a.rq_bits) == 4;
+        char *dst[PF];
+#pragma unroll
+        for (int f = 0; f < PF; ++f) {
+            const size_t at = (size_t)(frag_m[f] < 0 ? 0 : frag_m[f]) * a.rq_Cp;
+            dst[f] = (char *)a.rq_codes + (four ? at / 2 + 8 * h : at / 4 + 4 * h);
+        }
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             if (KS == 2 && (c & 1) != grp) continue;
             const int o_tile = (ct0 + c) * 32;
             const int ol = (wc * CT + c) * 32 + 4 * h;   // this lane's first channel inside the workgroup
-            // bytes of channels >= C_out are blanked (their codes must be 0)
-            uint32_t mask[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int left = a.C_out - (o_tile + 8 * q + 4 * h);      // valid channels from here on
-                mask[q] = left >= 4 ? 0xFFFFFFFFu : left <= 0 ? 0u : (1u << (8 * left)) - 1u;
-            }
-            // The code in code units, t = A*(ACC + rho*SA) + (B*SA + s) (see
-            // chained_channel_constants): seven or eight binary32 instructions per output,
-            // no binary64; the constants of four channels serve all fragments.  far[f]: the
-            // largest distance of a fract(t) from 1/2 among the outputs of fragment f.
+            // The code in code units, T = A*(ACC + rho*SA) + (B*SA + s) (see
+            // chained_channel_constants): eight or nine binary32 instructions per output,
+            // no binary64; the constants of four channels serve all fragments.  near[f][q]: the
+            // smallest distance of a T from a half-integer among four outputs of fragment f.
             uint32_t bytes[PF][4];
-            float far[PF];
+            float near[PF][4];
+            float4 k[2][4];
 #pragma unroll
-            for (int f = 0; f < PF; ++f) far[f] = 0.0f;
+            for (int j = 0; j < 4; ++j) k[0][j] = ft_lds[ol + j];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                float4 k[4];
+                if (q < 3) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) k[j] = ft_lds[ol + 8 * q + j];
+                    for (int j = 0; j < 4; ++j) k[(q + 1) & 1][j] = ft_lds[ol + 8 * (q + 1) + j];
+                }
 #pragma unroll
                 for (int f = 0; f < PF; ++f) {
-                    int cd[4];
+                    uint32_t b = 0;
+                    float least = 1.0f;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
+                        const float4 kj = k[q & 1][j];
                         float fa;
                         if constexpr (RAWF) fa = macc[f][c][4 * q + j];
                         else fa = (float)acc[f][c][4 * q + j];
-                        const float u = __builtin_fmaf(fsa[f], k[j].y, fa);
-                        const float t = __builtin_fmaf(u, k[j].x, __builtin_fmaf(fsa[f], k[j].z, k[j].w));
+                        const float u = __builtin_fmaf(fsa[f], kj.y, fa);
+                        const float t = __builtin_fmaf(u, kj.x, __builtin_fmaf(fsa[f], kj.z, kj.w));
                         const float tc = __builtin_amdgcn_fmed3f(t, t_lo, t_hi);
-                        cd[j] = (int)tc;
-                        far[f] = __builtin_fmaxf(far[f], __builtin_fabsf(__builtin_amdgcn_fractf(tc) - 0.5f));
+                        b = __builtin_amdgcn_cvt_pk_u8_f32(tc, j, b);        // (rounds to nearest)
+                        least = __builtin_fminf(least, __builtin_fabsf(__builtin_amdgcn_fractf(tc) - 0.5f));
                     }
-                    bytes[f][q] = dsq_bytes4(cd[0], cd[1], cd[2], cd[3]) & mask[q];
+                    bytes[f][q] = b;
+                    near[f][q] = least;
                 }
             }
+            const int left = a.C_out - (o_tile + 4 * h);      // channels from this lane's first one on
 #pragma unroll
             for (int f = 0; f < PF; ++f) {
-                if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(far[f] < te_wg)) != 0, 0)) {
+                const float least = __builtin_fminf(__builtin_fminf(near[f][0], near[f][1]), __builtin_fminf(near[f][2], near[f][3]));
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(least > near_wg)) != 0, 0)) {
                     // the exact sequence: the binary32 value the plain call stores, scale,
-                    // shift, ReLU and the quantizer as a step function
+                    // shift, ReLU and the quantizer's recipe.  (Through this wave's idle slice of
+                    // the patch buffers, so that the loop needs no copy of itself per register:
+                    // code that seldom runs is not in the instruction cache when it does.  Only the
+                    // groups of channels that need it, as a rule one: the wave that has one is
+                    // the last of its launch)
+                    const int top_n = (1 << a.rq_bits) - 1;
+                    const double da = (double)a.delta_a;
+                    v4i *ex = reinterpret_cast<v4i *>(stage) + lane;
+                    uint32_t which = 0;
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        float y[4];
+                        if (__builtin_amdgcn_ballot_w64(!(near[f][q] > near_wg)) == 0) continue;
+                        which |= 1u << q;
+                        v4i t;
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
-                            int ai;
-                            if constexpr (RAWF) ai = (int)(macc[f][c][4 * q + j] * 4.0f);
-                            else ai = acc[f][c][4 * q + j];
-                            y[j] = (float)__builtin_fma(pq_lds[ol + 8 * q + j], (double)ai, pq_lds[BC + ol + 8 * q + j] * dsa[f]);
+                            if constexpr (RAWF) t[j] = (int)(macc[f][c][4 * q + j] * 4.0f);
+                            else t[j] = acc[f][c][4 * q + j];
                         }
-                        const float4 s4 = *reinterpret_cast<const float4 *>(ss_lds + ol + 8 * q);
-                        const float4 b4 = *reinterpret_cast<const float4 *>(ss_lds + BC + ol + 8 * q);
-                        const float sc[4] = {s4.x, s4.y, s4.z, s4.w}, sh[4] = {b4.x, b4.y, b4.z, b4.w};
-                        bytes[f][q] = dsq_requant4_thr(y, sc, sh, relu_floor, l_n, u_n, inv_delta_n, top_n, thr_lds, mask[q]);
+                        ex[64 * q] = t;
+                    }
+#pragma unroll 1
+                    for (uint32_t todo = which; todo != 0; todo &= todo - 1) {
+                        const int q = __builtin_ctz(todo);
+                        const v4i t = ex[64 * q];
+                        int cd[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const float4 r4 = raw_lds[ol + 8 * q + j];
+                            const float y = (float)__builtin_fma(da * (double)r4.x, (double)t[j], (da * (double)r4.y) * (double)fsa[f]);
+                            float z = y * r4.z;
+                            z = z + r4.w;
+                            if (a.rq_relu) z = fmaxf(z, 0.0f);
+                            cd[j] = dsq_code(z, a.rq_l, a.rq_u, a.rq_delta, top_n);
+                        }
+                        ex[64 * q].x = (int)dsq_bytes4(cd[0], cd[1], cd[2], cd[3]);
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        if (which >> q & 1) bytes[f][q] = (uint32_t)ex[64 * q].x;
+                }
+                if (o_tile + 32 > a.C_out) {
+                    // bytes of channels >= C_out are blanked (their codes must be 0)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        bytes[f][q] &= left - 8 * q >= 4 ? 0xFFFFFFFFu : left - 8 * q <= 0 ? 0u : (1u << (8 * (left - 8 * q))) - 1u;
+                }
+                if (a.rq_dense) {
+                    dsq_requant_store32(a, frag_m[f], o_tile, h, bytes[f], 0);
+                } else {
+                    // (v_permlane32_swap exchanges the upper half of its first operand with the
+                    // lower half of its second: lanes 0..31 get both halves' bytes of words 0 and 1,
+                    // lanes 32..63 those of words 2 and 3)
+                    const auto s0 = __builtin_amdgcn_permlane32_swap(bytes[f][0], bytes[f][2], false, false);
+                    const auto s1 = __builtin_amdgcn_permlane32_swap(bytes[f][1], bytes[f][3], false, false);
+                    const bool here = frag_m[f] >= 0 && o_tile < a.rq_Cp;
+                    if (four) {
+                        const v2i w = {(int)(s0[0] | s0[1] << 4), (int)(s1[0] | s1[1] << 4)};
+                        if (here) *reinterpret_cast<v2i *>(dst[f] + o_tile / 2) = w;
+                    } else {
+                        const uint32_t w = (s0[0] | s0[1] << 2) | (s1[0] | s1[1] << 2) << 4;
+                        if (here) *reinterpret_cast<uint32_t *>(dst[f] + o_tile / 4) = w;
                     }
                 }
-                const int sum = (int)__builtin_amdgcn_sad_u8(bytes[f][3], 0u, __builtin_amdgcn_sad_u8(bytes[f][2], 0u,
-                                __builtin_amdgcn_sad_u8(bytes[f][1], 0u, __builtin_amdgcn_sad_u8(bytes[f][0], 0u, 0u))));
-                psum[f] += dsq_requant_store32(a, frag_m[f], o_tile, h, bytes[f], sum);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) psum[f] = (int)__builtin_amdgcn_sad_u8(bytes[f][q], 0u, (uint32_t)psum[f]);
             }
         }
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+            psum[f] += (int)__builtin_amdgcn_permlane32_swap((uint32_t)psum[f], (uint32_t)psum[f], false, false)[1];
         // The waves that share a row of pixel fragments (wave columns, wave groups)
         // hand their sums to the row's first wave through their staging slices
         // (integer adds: exact in any order) ...
@@ -897,20 +957,20 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
 
 // ---- host side ---------------------------------------------------------------
 
-// tables behind the buffers: Da*Dw, Da*l_w (binary64), the patch pixels' code
-// sums; then the chained mode's scale, shift, quantizer thresholds and per-channel
-// constants of the code-unit form, or the general results' tables for l_a != 0
+// tables behind the buffers: Da*Dw, Da*l_w (binary64; chained mode: Dw, l_w, scale, shift), the
+// patch pixels' code sums; then the chained mode's per-channel constants of the code-unit
+// form, or the general results' tables for l_a != 0
 constexpr int border_table_bytes(int R, int BC) { return 3 * BC * 8 + (R > 1 ? R * R * BC * 4 : 0); }
 
 inline int plan_lds_bytes(const PatchPlan &p, int BC, const DsqConvArgs &a)
 {
     const int tables = (p.aux_off + 2 * BC * 8 + p.PR * p.PC * 4 + 15) & ~15;
-    const int chained = 2 * BC * 4 + 16 * 8 + BC * 16 + 16;
+    const int chained = BC * 16 + 16;
     return tables + (a.rq ? chained : a.l_a != 0.0f ? border_table_bytes(a.R, BC) : 0);
 }
 
 // What a plan is held against its limit with: the same for a layer with l_a != 0 as for one
-// with l_a = 0 (room for scale, shift and thresholds is always counted), so that which layers
+// with l_a = 0 (with some room for further tables counted always), so that which layers
 // and forced tiles the kernel takes does not depend on l_a.
 inline int plan_limit_bytes(const PatchPlan &p, int BC, const DsqConvArgs &a)
 {
@@ -977,7 +1037,7 @@ hipError_t dispatch_variant(const DsqConvArgs &a, const PatchPlan &pl, int which
         if (which == TILE_MEDIUM) return launch_cfg<CONT, RR, 2, 2, 2, 2, UPT, (RR == 3 ? 3 : 1), 3>(a, pl, stream); \
         if (which == TILE_TALL) return launch_cfg<CONT, RR, 4, 1, 2, 2, UPT, (RR == 3 ? 3 : 1), 3>(a, pl, stream); \
         if (ks == 2) return launch_cfg<CONT, RR, 4, 1, 1, 2, UPT, (RR == 3 ? 3 : 1), 2, 2>(a, pl, stream); \
-        return launch_cfg<CONT, RR, 4, 1, 1, 2, UPT, (RR == 3 ? 3 : 1), (UPT == 2 ? 4 : 3)>(a, pl, stream); \
+        return launch_cfg<CONT, RR, 4, 1, 1, 2, UPT, (RR == 3 ? 3 : 1), (UPT == 2 ? 4 : UPT >= 8 && CONT == 4 ? 2 : 3)>(a, pl, stream); \
     } while (0)
 #define DSQ_GO(CONT, RR)                                                                       \
     do {                                                                                       \

@@ -36,30 +36,22 @@ struct DsqConvArgs {
     float rq_l, rq_u;         // next layer's clip range
     int rq_bits;
     int rq_dense;             // next layer's codes in the dense 3-bit format (rq_bits == 3)
-    // The next layer's quantizer as a step function: rq_thr[j] (j = 1..2^bits-1)
-    // is the smallest binary32 value whose code is >= j, found on the host with
-    // the very recipe of dsq_code (every step of it is monotone, so
-    // code(z) = #{j : z >= rq_thr[j]} exactly); unused entries are NaN, which
-    // no value compares >= to.  rq_inv_delta gives a first guess
-    // (int)((v - l) * rq_inv_delta + rq_bias) of floor((v - l)/Delta + 0.5) that
-    // is off by at most one.
-    float rq_thr[16];
-    float rq_inv_delta, rq_bias;
+    float rq_delta;           // its step, the recipe's binary32 value
     // The LDS-patch kernel first decides a code in "code units":
-    //   t = ((y*scale + shift) - l)/Delta + 1/2,  code = floor(clamp(t, rq_t_lo, rq_t_hi)),
+    //   T = ((y*scale + shift) - l)/Delta,  code = clamp(T, rq_t_lo, rq_t_hi) rounded to nearest,
     // evaluated in binary32 from per-channel constants (conv_patch_kernel.h), and keeps
-    // that code when t is farther from every integer than the error bound of the
+    // that code when T is farther from every half-integer than the error bound of the
     // evaluation; otherwise it falls back on the exact sequence above.  The host part
-    // of that bound: rq_t_margin = 1/2 - max_j |t(rq_thr[j]) - j| - 2^-20 (how far the
-    // true thresholds sit from the integers of the ideal staircase, plus slack for
-    // absolute rounding errors); rq_t_lo = 1/2, or code(0) + 1/2 under the ReLU;
-    // rq_t_hi = 2^bits - 1/2; rq_inv_dn = 1/Delta and rq_c0 = 1/2 - l/Delta in binary64;
+    // of that bound: rq_t_slack = 3*2^-24*(top + 1), what the recipe's three roundings
+    // (subtraction, division, addition of 1/2) may move a value by, plus 2^-20 for
+    // absolute rounding errors; rq_t_lo = 0, or code(0) under the ReLU; rq_t_hi = top;
+    // rq_inv_dn = 1/Delta, rq_c0 = -l/Delta and rq_da_dn = Delta_a/Delta in binary64;
     // rq_sa_max bounds the sum of activation codes under one output, rq_w_max the
     // weight codes.  rq_fast = 0 (deep layers whose accumulators pass 2^24, extreme
     // ranges) sends every output through the exact sequence.
     int rq_fast;
-    float rq_t_lo, rq_t_hi, rq_t_margin, rq_sa_max, rq_w_max;
-    double rq_inv_dn, rq_c0;
+    float rq_t_lo, rq_t_hi, rq_t_slack, rq_sa_max, rq_w_max;
+    double rq_inv_dn, rq_c0, rq_da_dn;
     int rq_Cp;                // C_out rounded up to 64
     void *rq_codes;           // packed codes of the next layer's input
     int32_t *rq_pix;          // [N*Ho*Wo]; the kernels add to it (cleared before the launch) unless rq_store
