@@ -1,10 +1,11 @@
 """ctypes binding of libdsqconv: the same names as ``include/dsqconv.h``.
 
-Argument marshalling only.  PyTorch supplies device memory (``data_ptr()``)
+Argument marshalling only; calls whose arguments all have their plain form go through
+the native ``_marshal`` module instead of ctypes (csrc/marshal.cpp).  PyTorch supplies device memory (``data_ptr()``)
 and the HIP stream handle (``torch.cuda.current_stream().cuda_stream`` is
 PyTorch-ROCm's name for the hipStream_t); every step of the path runs in the
-library's HIP kernels.  There is no CPU fallback: if the shared library has
-not been built, the first call raises.
+library's HIP kernels.  There is no CPU fallback: if the shared library or the module
+has not been built, the first call raises.
 """
 import ctypes as C
 import os
@@ -96,6 +97,26 @@ def load_library():
     return lib
 
 
+_marshal = None
+
+
+def load_marshal():
+    """The native marshalling module, bound to the library's entry points; raises if it has not been built."""
+    global _marshal
+    if _marshal is None:
+        lib = load_library()
+        try:
+            from . import _marshal as module
+        except ImportError as e:
+            raise RuntimeError("the _marshal module of paper_1908_05033_amd is missing or does not load (%s): build it first "
+                               "(python -c 'import __graft_entry__ as g; g.build()')." % e) from e
+        module.init(dsq_conv_desc, *(C.cast(getattr(lib, name), C.c_void_p).value for name in
+                                     ("dsq_quantize_act", "dsq_conv2d", "dsq_conv2d_requant", "dsq_conv2d_wq",
+                                      "dsq_soft_quantize_fwd", "dsq_soft_quantize_bwd")))
+        _marshal = module
+    return _marshal
+
+
 def _check(status):
     if status != DSQ_OK:
         raise DsqError(status, load_library().dsq_status_string(status).decode())
@@ -142,10 +163,14 @@ def dsq_wgt_aux_bytes(C_out, R, S):
 
 
 def dsq_quantize_act(x, layout, N, C, H, W, l, u, bits, codes_packed, pix_code_sum, stream=None):
-    _check(load_library().dsq_quantize_act(
-        _dev_ptr(x, torch.float32), layout, N, C, H, W, l, u, bits,
-        _dev_ptr(codes_packed, torch.uint8), codes_packed.numel() if codes_packed is not None else 0,
-        _dev_ptr(pix_code_sum, torch.int32), _stream(stream)))
+    status = (_marshal or load_marshal()).quantize_act(x, layout, N, C, H, W, l, u, bits, codes_packed, pix_code_sum, stream)
+    if status is None:
+        _check(load_library().dsq_quantize_act(
+            _dev_ptr(x, torch.float32), layout, N, C, H, W, l, u, bits,
+            _dev_ptr(codes_packed, torch.uint8), codes_packed.numel() if codes_packed is not None else 0,
+            _dev_ptr(pix_code_sum, torch.int32), _stream(stream)))
+    elif status != DSQ_OK:
+        _check(status)
 
 
 def dsq_quantize_act_ex(x, layout, N, C, H, W, l, u, bits, packing, codes_packed, pix_code_sum, stream=None):
@@ -179,42 +204,63 @@ def dsq_pack_weights_for(w_oihw, l_w, u_w, codes_oihw, C_out, C_in, R, S, bits_w
 
 def dsq_conv2d(desc, act_packed, pix_code_sum, l_a, u_a, w_packed, w_aux, out, out_layout,
                acc_or_none=None, stream=None):
-    _check(load_library().dsq_conv2d(
-        C.byref(desc) if desc is not None else None,
-        _dev_ptr(act_packed, torch.uint8), _dev_ptr(pix_code_sum, torch.int32), l_a, u_a,
-        _dev_ptr(w_packed, torch.uint8), _dev_ptr(w_aux, torch.uint8),
-        _dev_ptr(out, torch.float32), out_layout,
-        _dev_ptr(acc_or_none, torch.int32, True), _stream(stream)))
+    status = (_marshal or load_marshal()).conv2d(desc, act_packed, pix_code_sum, l_a, u_a, w_packed, w_aux, out, out_layout, acc_or_none, stream)
+    if status is None:
+        _check(load_library().dsq_conv2d(
+            C.byref(desc) if desc is not None else None,
+            _dev_ptr(act_packed, torch.uint8), _dev_ptr(pix_code_sum, torch.int32), l_a, u_a,
+            _dev_ptr(w_packed, torch.uint8), _dev_ptr(w_aux, torch.uint8),
+            _dev_ptr(out, torch.float32), out_layout,
+            _dev_ptr(acc_or_none, torch.int32, True), _stream(stream)))
+    elif status != DSQ_OK:
+        _check(status)
 
 
 def dsq_conv2d_requant(desc, act_packed, pix_code_sum, l_a, u_a, w_packed, w_aux, scale, shift, relu,
                        l_next, u_next, bits_next, codes_next, pix_code_sum_next, stream=None):
-    _check(load_library().dsq_conv2d_requant(
-        C.byref(desc) if desc is not None else None,
-        _dev_ptr(act_packed, torch.uint8), _dev_ptr(pix_code_sum, torch.int32), l_a, u_a,
-        _dev_ptr(w_packed, torch.uint8), _dev_ptr(w_aux, torch.uint8),
-        _dev_ptr(scale, torch.float32, True), _dev_ptr(shift, torch.float32, True), int(bool(relu)),
-        l_next, u_next, bits_next,
-        _dev_ptr(codes_next, torch.uint8), codes_next.numel() if codes_next is not None else 0,
-        _dev_ptr(pix_code_sum_next, torch.int32), _stream(stream)))
+    status = (_marshal or load_marshal()).conv2d_requant(desc, act_packed, pix_code_sum, l_a, u_a, w_packed, w_aux, scale, shift,
+                                                        relu, l_next, u_next, bits_next, codes_next, pix_code_sum_next, stream)
+    if status is None:
+        _check(load_library().dsq_conv2d_requant(
+            C.byref(desc) if desc is not None else None,
+            _dev_ptr(act_packed, torch.uint8), _dev_ptr(pix_code_sum, torch.int32), l_a, u_a,
+            _dev_ptr(w_packed, torch.uint8), _dev_ptr(w_aux, torch.uint8),
+            _dev_ptr(scale, torch.float32, True), _dev_ptr(shift, torch.float32, True), int(bool(relu)),
+            l_next, u_next, bits_next,
+            _dev_ptr(codes_next, torch.uint8), codes_next.numel() if codes_next is not None else 0,
+            _dev_ptr(pix_code_sum_next, torch.int32), _stream(stream)))
+    elif status != DSQ_OK:
+        _check(status)
 
 
 def dsq_conv2d_wq(desc, x, x_layout, w_packed, w_aux, out, out_layout, stream=None):
-    _check(load_library().dsq_conv2d_wq(
-        C.byref(desc) if desc is not None else None, _dev_ptr(x, torch.float32), x_layout,
-        _dev_ptr(w_packed, torch.uint8), _dev_ptr(w_aux, torch.uint8), _dev_ptr(out, torch.float32), out_layout,
-        _stream(stream)))
+    status = (_marshal or load_marshal()).conv2d_wq(desc, x, x_layout, w_packed, w_aux, out, out_layout, stream)
+    if status is None:
+        _check(load_library().dsq_conv2d_wq(
+            C.byref(desc) if desc is not None else None, _dev_ptr(x, torch.float32), x_layout,
+            _dev_ptr(w_packed, torch.uint8), _dev_ptr(w_aux, torch.uint8), _dev_ptr(out, torch.float32), out_layout,
+            _stream(stream)))
+    elif status != DSQ_OK:
+        _check(status)
 
 
 def dsq_soft_quantize_fwd(x, l, u, alpha, bits, y, stream=None):
-    _check(load_library().dsq_soft_quantize_fwd(_dev_ptr(x, torch.float32), x.numel(), l, u, alpha, bits,
-                                                _dev_ptr(y, torch.float32), _stream(stream)))
+    status = (_marshal or load_marshal()).soft_quantize_fwd(x, l, u, alpha, bits, y, stream)
+    if status is None:
+        _check(load_library().dsq_soft_quantize_fwd(_dev_ptr(x, torch.float32), x.numel(), l, u, alpha, bits,
+                                                    _dev_ptr(y, torch.float32), _stream(stream)))
+    elif status != DSQ_OK:
+        _check(status)
 
 
 def dsq_soft_quantize_bwd(x, grad_y, l, u, alpha, bits, grad_x, grad_alpha_l_u, stream=None):
-    _check(load_library().dsq_soft_quantize_bwd(
-        _dev_ptr(x, torch.float32), _dev_ptr(grad_y, torch.float32), x.numel(), l, u, alpha, bits,
-        _dev_ptr(grad_x, torch.float32), _dev_ptr(grad_alpha_l_u, torch.float64), _stream(stream)))
+    status = (_marshal or load_marshal()).soft_quantize_bwd(x, grad_y, l, u, alpha, bits, grad_x, grad_alpha_l_u, stream)
+    if status is None:
+        _check(load_library().dsq_soft_quantize_bwd(
+            _dev_ptr(x, torch.float32), _dev_ptr(grad_y, torch.float32), x.numel(), l, u, alpha, bits,
+            _dev_ptr(grad_x, torch.float32), _dev_ptr(grad_alpha_l_u, torch.float64), _stream(stream)))
+    elif status != DSQ_OK:
+        _check(status)
 
 
 def dsq_conv2d_plan(desc, chained=False, l_a=0.0):

@@ -11,6 +11,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdsqconv.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 OBJ_DIR = os.path.join(HERE, "_build")
 
 HIPCC_FLAGS = [
@@ -77,6 +78,25 @@ def build_library(verbose=False, incremental=False, jobs=None):
     return LIB
 
 
+def build_marshal():
+    """The argument marshalling of binding.py (csrc/marshal.cpp) as an extension module next to it."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    tmp = MARSHAL + ".tmp.%d" % os.getpid()
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I" + sysconfig.get_paths()["include"], "-isystem", os.path.join(base, "include"),
+           "-isystem", os.path.join(base, "include", "torch", "csrc", "api", "include"), "-isystem", "/opt/rocm/include",
+           os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + os.path.join(base, "lib"),
+           "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    proc = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("compiling marshal.cpp failed:\n" + proc.stdout)
+    os.replace(tmp, MARSHAL)
+    return MARSHAL
+
+
 def build_ceilings_probe():
     """The stand-alone micro-benchmark of the machine's ceilings (matrix
     instruction rates, LDS, vector L1, HBM): ceilings/ceilings_probe."""
@@ -94,5 +114,6 @@ def build_ceilings_probe():
 if __name__ == "__main__":
     import sys
     print(build_library(verbose="-q" not in sys.argv, incremental="-i" in sys.argv))
+    print(build_marshal())
     if "-i" not in sys.argv:
         print(build_ceilings_probe())
