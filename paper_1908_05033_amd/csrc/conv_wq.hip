@@ -158,7 +158,10 @@ __device__ __forceinline__ float centre_of(float l, float d, int top)
 // WP x WC waves of PF x CT 32x32 tiles; KW > 1: the waves share one such block and
 // take every KW-th 16-channel step of K (layers that yield few blocks).
 // VEC: NHWC activations with whole float4s (C_in a multiple of 4).
-template <int R, int WP, int WC, int KW, int PF, int CT, int OCC, bool VEC>
+// LUT: codes of at most 3 bits, whose centred levels a lane keeps as two tables of eight bytes
+// (low and high halves of the bf16 numbers): v_perm_b32 looks four codes up at once, 11 vector
+// instructions for eight levels where forming them takes 28.
+template <int R, int WP, int WC, int KW, int PF, int CT, int OCC, bool VEC, bool LUT>
 __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const float *__restrict__ x, int x_nchw, int top, WqPlan pl)
 {
     constexpr int T = R * R;
@@ -239,6 +242,20 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
     float zq[CT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) zq[c] = zq_lds[(wc * CT + c) * 32 + col];
+    uint32_t tab[CT][4];                                  // low bytes of codes 0..3, 4..7, high bytes of the same
+    if constexpr (LUT) {
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                uint32_t e[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) e[j] = __float_as_uint((float)(4 * i + j) + zq[c]);
+                const uint32_t p01 = __builtin_amdgcn_perm(e[1], e[0], 0x07030602u), p23 = __builtin_amdgcn_perm(e[3], e[2], 0x07030602u);
+                tab[c][i] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
+                tab[c][2 + i] = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
+            }
+    }
 
     v16f acc[PF][CT];
 #pragma unroll
@@ -358,6 +375,15 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
                 dsq_unpack4(wreg[j][c], b[0], b[1]);
                 seen |= wreg[j][c];
                 v4i w;
+                if constexpr (LUT) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const uint32_t lo = __builtin_amdgcn_perm(tab[c][1], tab[c][0], b[i]);
+                        const uint32_t hi = __builtin_amdgcn_perm(tab[c][3], tab[c][2], b[i]);
+                        w[2 * i] = (int)__builtin_amdgcn_perm(hi, lo, 0x05010400u);
+                        w[2 * i + 1] = (int)__builtin_amdgcn_perm(hi, lo, 0x07030602u);
+                    }
+                } else
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float e0 = (float)((b[i >> 1] >> (16 * (i & 1))) & 0xFFu) + zq[c];
@@ -478,8 +504,9 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
 template <int R, int WP, int WC, int KW, int PF, int CT, int OCC>
 hipError_t launch(const DsqConvArgs &a, const float *x, int x_nchw, const WqPlan &pl, int lds, hipStream_t stream)
 {
-    auto kern = !x_nchw && (a.C_in & 3) == 0 ? conv_wq_kernel<R, WP, WC, KW, PF, CT, OCC, true>
-                                             : conv_wq_kernel<R, WP, WC, KW, PF, CT, OCC, false>;
+    const bool vec = !x_nchw && (a.C_in & 3) == 0;
+    auto kern = a.bits <= 3 ? (vec ? conv_wq_kernel<R, WP, WC, KW, PF, CT, OCC, true, true> : conv_wq_kernel<R, WP, WC, KW, PF, CT, OCC, false, true>)
+                            : (vec ? conv_wq_kernel<R, WP, WC, KW, PF, CT, OCC, true, false> : conv_wq_kernel<R, WP, WC, KW, PF, CT, OCC, false, false>);
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
