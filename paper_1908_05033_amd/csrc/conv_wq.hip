@@ -28,9 +28,11 @@
 // the input patch under its taps is read once, split, and kept in LDS (as three bf16
 // planes per pixel); the R*R taps read shifted windows of it.  Weight codes go from
 // global memory to registers, all of a stage's in flight while the patch is staged.
-// Bound by staging and LDS reads between the matrix instructions: 128 -> 128 3x3 at
-// 28x28 x 64, of 18 us at the instruction's nominal rate, 188 us on the binary32 instruction
-// and 48 now (304 TFLOP/s) with the tensor in the last-level cache; 50 to 57 cold.
+// Bound by staging between the matrix instructions (128 -> 128 3x3 at 28x28 x 64, clocks of a
+// wave: set-up 4700, staging and its barriers 22000, multiplication 40000, of which 28000 are the
+// matrix instruction's, results 8200) and by 392 tiles on 256 compute units: 188 us on the binary32
+// instruction, 49 with levels formed one by one and a sum of x for every layer, 45 now
+// (330 TFLOP/s) with the tensor in the last-level cache.
 #include "dsq_device.h"
 #include "dsq_kernels.h"
 #include "wq_plan.h"
@@ -148,11 +150,8 @@ __device__ __forceinline__ float centre_of(float l, float d, int top)
     const double z = (double)l / (double)d;
     const double m = __builtin_fmax(__builtin_fabs(z), __builtin_fabs(z + top));
     if (!(m < 256.0)) return 0.0f;
-    int e = 0;                                            // 2^(e-1) <= m < 2^e (m >= top/2)
-    if (m < 1.0) e = 0;
-    else while (m >= (double)(1 << e)) ++e;
-    const double grid = (double)(1 << e) / 256.0;
-    return (float)(__builtin_rint(z / grid) * grid);
+    const int e = max(__builtin_amdgcn_frexp_exp(m), 0);  // 2^(e-1) <= m < 2^e (m >= top/2)
+    return (float)__builtin_amdgcn_ldexp(__builtin_rint(__builtin_amdgcn_ldexp(z, 8 - e)), e - 8);      // grid 2^(e-8)
 }
 
 // WP x WC waves of PF x CT 32x32 tiles; KW > 1: the waves share one such block and
@@ -194,6 +193,8 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
     const int NCB = a.Cp / 64;
 
     // ---- tables: where the patch pixels are, and the channels' constants ---------
+    static_assert(BC <= 128, "two flags");
+    if (lane == 0 && wave < 2) whole_lds[1 + wave] = 0;   // (this wave's own, read behind the barrier)
     for (int p = tid; p < pl.npx; p += 256) {
         int n, ih, iw;
         bool ok;
@@ -219,10 +220,15 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
         zq_lds[tid] = zq;
         dw_lds[tid] = d * kDown;
         unscalable = __builtin_fabsf(d) == __builtin_inff() || (d != 0.0f && __builtin_fabsf(d) < 0x1p-72f);
-        lr_lds[tid] = (float)((double)l - (double)d * (double)zq);
+        const float lr = (float)((double)l - (double)d * (double)zq);
+        lr_lds[tid] = lr;
+        // (a NaN counts)
+        if (__builtin_amdgcn_ballot_w64(!(lr == 0.0f)) != 0 && lane == 0) whole_lds[1 + wave] = 1;
     }
     if (tid == 0) *whole_lds = 0;
     __syncthreads();
+    // sums of x are taken where a channel's levels have a remainder off the grid
+    const bool sums = __builtin_amdgcn_readfirstlane(whole_lds[1] | whole_lds[2]) != 0;
 
     // ---- the lane's pixels and weight rows ----------------------------------------
     int frag_off[PF], frag_pp[PF], frag_m[PF], frag_n[PF], frag_y[PF], frag_x[PF];
@@ -281,7 +287,6 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
             const float r1 = z - __uint_as_float(hi[j]);
             mid[j] = __float_as_uint(r1) & 0xFFFF0000u;
             lo[j] = __float_as_uint(r1 - __uint_as_float(mid[j]));
-            s += v[j];
         }
         v4i w[3];
 #pragma unroll
@@ -292,7 +297,11 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
         }
 #pragma unroll
         for (int p = 0; p < 3; ++p) *reinterpret_cast<v4i *>(lds + px * PIXB + p * KC * 2 + g * 16) = w[p];
-        sx_lds[g * pl.npx + px] = first ? s : sx_lds[g * pl.npx + px] + s;
+        if (sums) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s += v[j];
+            sx_lds[g * pl.npx + px] = first ? s : sx_lds[g * pl.npx + px] + s;
+        }
     };
     // Unit k of a thread: one patch pixel, 8 channels.  NHWC with whole float4s: a thread keeps
     // its channels and the G groups of a pixel sit in neighbouring lanes; otherwise (NCHW, odd
@@ -410,12 +419,26 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
     if (max_bits >= kMostBits || (seen & ~((uint32_t)top * 0x11111111u))) *whole_lds = 1;
     float sx[PF];                                         // sum of x under the pixel's taps
 #pragma unroll
-    for (int f = 0; f < PF; ++f) {
-        sx[f] = 0.f;
+    for (int f = 0; f < PF; ++f) sx[f] = 0.f;
+    if (sums && T == 1) {
 #pragma unroll
-        for (int t = 0; t < T; ++t)
+        for (int f = 0; f < PF; ++f)
 #pragma unroll
-            for (int g = 0; g < G; ++g) sx[f] += sx_lds[g * pl.npx + frag_pp[f] + (t / R) * pl.PC + t % R];
+            for (int g = 0; g < G; ++g) sx[f] += sx_lds[g * pl.npx + frag_pp[f]];
+    } else if (sums) {
+        // (a pixel's groups first: every tap of every pixel would add them up again)
+        __syncthreads();
+        for (int p = tid; p < pl.npx; p += 256) {
+            float s = sx_lds[p];
+#pragma unroll
+            for (int g = 1; g < G; ++g) s += sx_lds[g * pl.npx + p];
+            sx_lds[p] = s;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < PF; ++f)
+#pragma unroll
+            for (int t = 0; t < T; ++t) sx[f] += sx_lds[frag_pp[f] + (t / R) * pl.PC + t % R];
     }
     __syncthreads();                                      // the patch is free from here on
     const bool exact = __builtin_amdgcn_readfirstlane(*whole_lds) != 0;
@@ -473,7 +496,15 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
     char *mine = lds + wave * (32 * ROWB);
     const bool staged = !a.out_nchw && (a.C_out & 3) == 0;
 #pragma unroll
-    for (int c = 0; c < CT; ++c)
+    for (int c = 0; c < CT; ++c) {
+        // (the channels' constants once for all fragments)
+        float dw[16], lr[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int ol = (wc * CT + c) * 32 + 8 * (i / 4) + 4 * h + i % 4;
+            dw[i] = dw_lds[ol];
+            lr[i] = lr_lds[ol];
+        }
 #pragma unroll
         for (int f = 0; f < PF; ++f) {
 #pragma unroll
@@ -481,7 +512,7 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
                 const int ol = (wc * CT + c) * 32 + 8 * q + 4 * h;
                 float v[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] = __builtin_fmaf(dw_lds[ol + j], acc[f][c][4 * q + j], lr_lds[ol + j] * sx[f]);
+                for (int j = 0; j < 4; ++j) v[j] = __builtin_fmaf(dw[4 * q + j], acc[f][c][4 * q + j], lr[4 * q + j] * sx[f]);
                 if (staged) *reinterpret_cast<v4f *>(mine + col * ROWB + (8 * q + 4 * h) * 4) = (v4f){v[0], v[1], v[2], v[3]};
                 else store4(f, blk_c * BC + ol, v);
             }
@@ -497,6 +528,7 @@ __global__ __launch_bounds__(256, OCC) void conv_wq_kernel(DsqConvArgs a, const 
                 }
             }
         }
+    }
 }
 
 // ---- host side -------------------------------------------------------------------

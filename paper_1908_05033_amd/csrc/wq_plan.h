@@ -22,7 +22,7 @@ DSQ_BOTH constexpr int pixel_bytes(int R) { return kc_of(R) * 6 + 16; }       //
 constexpr int ROWB = 128 + 16;                                       // staged bytes per output pixel
 
 // LDS: [patch, then the epilogue's staging][channel-group sums of x][patch addresses]
-//      [zq, Dw * 2^-54, lr of BC channels][whether the tile cannot be split]
+//      [zq, Dw * 2^-54, lr of BC channels][whether the tile cannot be split, whether any lr is not 0]
 DSQ_BOTH constexpr int tables_at(int R, int KW, int tiles, int npx)
 {
     const int staging = KW > 1 ? KW * tiles * 4096 : 4 * 32 * ROWB;      // (tiles: 32x32 tiles of a wave)
