@@ -127,18 +127,45 @@ __device__ __forceinline__ float chained_channel_constants(const DsqConvArgs &a,
     return E;
 }
 
+// Which of the three taps from row (column) i on lie inside an image of n rows: 0 all, 1 all but
+// the first, 2 all but the last; 0 as well where n = 1 and i = -1, whose pixels have the middle tap
+// only.  (One row of padding: what two rows of it add, OUT_ROWS and OUT_GENERAL work out from
+// the taps themselves.)
+__device__ __forceinline__ int border_class(int i, int n) { return n == 1 ? 0 : i < 0 ? 1 : i + 2 >= n ? 2 : 0; }
+
+// The border term of channel o of a pixel with the taps of the mask `taps` inside the image.
+template <int T>
+__device__ __forceinline__ double border_term(const DsqConvArgs &a, int o, int taps)
+{
+    int sw = 0;
+    for (int t = 0; t < T; ++t)
+        if (taps >> t & 1) sw += a.sw_tap[(size_t)o * T + t];
+    const double la = (double)a.l_a;
+    return (la * (double)a.delta_w[o]) * (double)sw + (double)(a.C_in * __builtin_popcount((unsigned)taps)) * (la * (double)a.l_w[o]);
+}
+
 // What the kernel's results become; chosen at compile time, so that the register
 // allocation of each epilogue is its own.
 //   OUT_PLAIN    fp32 NHWC tensor, l_a = 0, C_out a multiple of 4, no raw accumulators
 //   OUT_CODES    the next layer's codes (chained mode)
+//   OUT_ROWS     fp32 NHWC tensors of any C_out and l_a, a lane holding a channel instead of a pixel
 //   OUT_GENERAL  everything else: NCHW, l_a != 0 (terms that depend on which taps lie
-//                inside the image), any C_out, raw accumulators
-enum { OUT_PLAIN = 0, OUT_CODES = 1, OUT_GENERAL = 2 };
+//                inside the image), raw accumulators
+enum { OUT_PLAIN = 0, OUT_CODES = 1, OUT_GENERAL = 2, OUT_ROWS = 3 };
 
-inline int output_mode(const DsqConvArgs &a)
+// BC: channels of the workgroup's tile.  OUT_ROWS where C_out is not a multiple of 4 (single floats
+// are staged badly: 64 -> 66 3x3 at 56x56 x 8 9.5 us, 8.0 so) and for 1x1 layers with l_a != 0 a fifth of
+// whose tiles' channels or more do not exist (it leaves those out: 24 -> 144 at 56x56 x 64 37.4 and 32.7 us,
+// 144 -> 24 14.6 and 14.2); the other way round without that (320 -> 1280 at 7x7 x 64 8.2 and 8.6) and
+// on 3x3 layers (64 -> 64 at 56x56 x 64 19.2 and 20.7).
+inline int output_mode(const DsqConvArgs &a, int BC)
 {
     if (a.rq) return OUT_CODES;
-    return !a.out_nchw && (a.C_out & 3) == 0 && a.l_a == 0.0f && a.acc == nullptr ? OUT_PLAIN : OUT_GENERAL;
+    if (a.out_nchw || a.acc != nullptr) return OUT_GENERAL;
+    if ((a.C_out & 3) != 0) return OUT_ROWS;
+    if (a.l_a == 0.0f) return OUT_PLAIN;
+    const int padded = (a.C_out + BC - 1) / BC * BC;
+    return a.R == 1 && 5 * (padded - a.C_out) >= padded ? OUT_ROWS : OUT_GENERAL;
 }
 
 template <int CONT, int R, int WP, int WC, int PF, int CT, int UPT, int WD, int OCC, int KS, int OUT>
@@ -174,11 +201,10 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     float4 *raw_lds = reinterpret_cast<float4 *>(pq_lds);
     float4 *ft_lds = reinterpret_cast<float4 *>(lds + ((pl.aux_off + 2 * BC * 8 + pl.PR * pl.PC * 4 + 15) & ~15));
     float *te_lds = reinterpret_cast<float *>(ft_lds + BC);
-    // general results of a layer with l_a != 0 (in the place of the chained mode's tables):
-    // l_a*Dw and l_a*l_w of the workgroup's channels, the sum of a full pixel's border terms,
-    // and the weight code sums of every tap as [tap][channel]
-    double *la_lds = reinterpret_cast<double *>(ft_lds);
-    int *swt_lds = reinterpret_cast<int *>(la_lds + 3 * BC);
+    // results of a layer with l_a != 0 (in the place of the chained mode's tables): the border
+    // terms l_a*Dw*SW + KV*l_a*l_w of the workgroup's channels, [class][channel], a class for each of
+    // the sets of taps that lie inside the image (see border_class)
+    double *wt_lds = reinterpret_cast<double *>(ft_lds);
 
     // KS = 2: two groups of four waves work on alternating 64-channel blocks of K
     // (each with its own patch buffers) and add their accumulators at the end, so
@@ -346,21 +372,20 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         raw.w = (a.rq_shift != nullptr ? a.rq_shift : a.delta_w)[in];
     }
 
-    const bool has_la = OUT == OUT_GENERAL && a.l_a != 0.0f;
+    const bool has_la = (OUT == OUT_GENERAL || OUT == OUT_ROWS) && a.l_a != 0.0f;
+    // (one channel per thread; behind the patch, so that the wait for that is not one for these)
+    int la_sw[T];
+    float la_dw = 0.f, la_lw = 0.f;
+#pragma unroll
+    for (int t = 0; t < T; ++t) la_sw[t] = 0;
     if (has_la) {
-        const double la = (double)a.l_a;
-        for (int i = (int)threadIdx.x; i < BC; i += 256 * KS) {
-            const int o = blk_y * BC + i;                     // < Cop: the side tables cover it
-            const double ldw = la * (double)a.delta_w[o], llw = la * (double)a.l_w[o];
-            la_lds[i] = ldw;
-            la_lds[BC + i] = llw;
-            la_lds[2 * BC + i] = ldw * (double)a.sw_total[o] + (double)(a.C_in * T) * llw;
-        }
-        if (T > 1)
-            for (int i = (int)threadIdx.x; i < BC * T; i += 256 * KS) {
-                const int o = i / T, t = i - o * T;
-                swt_lds[t * BC + o] = a.sw_tap[(size_t)blk_y * BC * T + i];
-            }
+        const int o = blk_y * BC + (tid < BC ? tid : 0);          // < Cop: the side tables cover it
+        la_dw = a.delta_w[o];
+        la_lw = a.l_w[o];
+#pragma unroll
+        for (int t = 0; t < T; ++t) la_sw[t] = a.sw_tap[(size_t)o * T + t];
+        if (T == 1 && grp == KS - 1 && tid < BC)
+            wt_lds[tid] = ((double)a.l_a * (double)la_dw) * (double)la_sw[0] + (double)a.C_in * ((double)a.l_a * (double)la_lw);
     }
 
     // ---- per-lane LDS offsets of the fragments' pixels -----------------------
@@ -370,7 +395,8 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     int frag_pp[PF];        // index of that patch pixel (prow*PC + pcol)
     int frag_m[PF];         // output pixel index n*Ho*Wo + oy*Wo + ox, or -1
     int frag_base[PF];      // general results, NCHW: element index of the pixel in channel 0
-    int frag_taps[PF];      // general results, l_a != 0: bit t set = tap t lies inside the image
+    int frag_taps[PF];      // l_a != 0 and two rows of padding: bit t set = tap t lies inside the image
+    int frag_cls[PF];       // l_a != 0: class of the set of those taps
 #pragma unroll
     for (int f = 0; f < PF; ++f) {
         const int t = t0 + (wp * PF + f) * 32 + col;
@@ -381,19 +407,22 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         int prow = 0, pcol = 0;
         frag_base[f] = 0;
         frag_taps[f] = (1 << T) - 1;
+        frag_cls[f] = 0;
         if (ok) {
             int oh;
             const int n = dsq_idiv(gr, a.Ho, pl.mg_Ho, oh);
             prow = n * pl.Hp + oh * a.stride - v0;
             pcol = tc * a.stride;
-            if (OUT == OUT_GENERAL) {
+            if (OUT == OUT_GENERAL || OUT == OUT_ROWS) {
                 frag_base[f] = n * (a.C_out - 1) * (a.Ho * a.Wo) + gr * a.Wo + ow;
-                if (T > 1) {
+                if (T > 1 && has_la) {
+                    const int ih = oh * a.stride - a.pad, iw = ow * a.stride - a.pad;
+                    frag_cls[f] = 3 * border_class(ih, a.H) + border_class(iw, a.W);
                     int rows = 0, cols = 0;                  // taps of a column / of a row inside the image
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
-                        if ((unsigned)(oh * a.stride - a.pad + r) < (unsigned)a.H) rows |= 1 << (r * R);
-                        if ((unsigned)(ow * a.stride - a.pad + r) < (unsigned)a.W) cols |= 1 << r;
+                        if ((unsigned)(ih + r) < (unsigned)a.H) rows |= 1 << (r * R);
+                        if ((unsigned)(iw + r) < (unsigned)a.W) cols |= 1 << r;
                     }
                     frag_taps[f] = rows * cols;              // (no carries: each bit of rows places its own copy of cols)
                 }
@@ -470,7 +499,12 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
                 for (int c = 0; c < CT; ++c)
 #pragma unroll
                     for (int f = 0; f < PF; ++f) {
-                        if constexpr (F4)
+                        // (OUT_ROWS: pixels in the rows, a lane holds one channel of 16 of them)
+                        if constexpr (F4 && OUT == OUT_ROWS)
+                            macc[f][c] = dsq_mfma_fp4(af[t & 1][f][kh], wf[c][kh], macc[f][c]);
+                        else if constexpr (OUT == OUT_ROWS)
+                            macc[f][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(af[t & 1][f][kh], wf[c][kh], macc[f][c], 0, 0, 0);
+                        else if constexpr (F4)
                             macc[f][c] = dsq_mfma_fp4(wf[c][kh], af[t & 1][f][kh], macc[f][c]);
                         else
                             macc[f][c] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wf[c][kh], af[t & 1][f][kh], macc[f][c], 0, 0, 0);
@@ -505,6 +539,25 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         // Da*Dw[o] and Da*l_w[o] of this workgroup's channels, in binary64
         const double da0 = (double)a.delta_a;
         if (!RQ && tid < 2 * BC) pq_lds[tid] = da0 * (double)chan_const;
+    }
+    if (T > 1 && has_la && grp == KS - 1 && tid < BC) {
+        // border terms of the channel, in the order of operations of conv_epilogue.h
+        // (an image of one row or column: its pixels have only the middle taps)
+        const double ldw = (double)a.l_a * (double)la_dw, llw = (double)a.l_a * (double)la_lw;
+        const bool row = a.H == 1 && a.pad > 0, column = a.W == 1 && a.pad > 0;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+            if ((row && t / R != 1) || (column && t % R != 1)) la_sw[t] = 0;
+#pragma unroll
+        for (int k = 0; k < 9; ++k) {
+            const int r0 = k / 3 == 1, r1 = k / 3 == 2 ? 2 : 3, c0 = k % 3 == 1, c1 = k % 3 == 2 ? 2 : 3;
+            int sw = 0;
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (t / R >= r0 && t / R < r1 && t % R >= c0 && t % R < c1) sw += la_sw[t];
+            const int taps = (row ? 1 : r1 - r0) * (column ? 1 : c1 - c0);
+            wt_lds[k * BC + tid] = ldw * (double)sw + (double)(a.C_in * taps) * llw;
+        }
     }
     if (RQ && grp == KS - 1 && tid < BC) {       // (whole waves: BC is a multiple of 64)
         if (a.rq_scale == nullptr) raw.z = 1.0f;
@@ -858,17 +911,84 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
                     }
             }
         }
+    } else if (OUT == OUT_ROWS) {
+        // The values of OUT_PLAIN plus, for l_a != 0, the terms of conv_epilogue.h that depend on
+        // which taps lie inside the image, in its order of operations (the same bits).  A lane
+        // holds one channel of 16 pixels, so that a channel's binary64 constants stay in registers:
+        // with the pixel in the lane they come from LDS for every output, which keeps the LDS busy
+        // for 0.6 of the time on 1x1 layers.  The pixels' code sums and places come from LDS, for all
+        // channel tiles at once; a store writes 128 consecutive bytes of two pixels.  Channel tiles
+        // past C_out are left out.
+        double *sa_stage = reinterpret_cast<double *>(stage);                       // [fragment][pixel]
+        int *at_stage = reinterpret_cast<int *>(stage + PF * 256), *cls_stage = at_stage + PF * 32;
+        const bool wide = T > 1 && has_la && a.pad == 2;     // (the classes do not cover two rows of padding)
+        if (h == 0) {
+#pragma unroll
+            for (int f = 0; f < PF; ++f) {
+                sa_stage[f * 32 + col] = dsa[f];
+                at_stage[f * 32 + col] = frag_m[f] < 0 ? -1 : frag_m[f] * a.C_out;   // (an element index: below 2^31)
+                cls_stage[f * 32 + col] = wide ? frag_taps[f] : frag_cls[f] * BC;
+            }
+        }
+        double P[CT], Q[CT], W[CT];
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int ol = (wc * CT + c) * 32 + col;
+            P[c] = pq_lds[ol];
+            Q[c] = pq_lds[BC + ol];
+            W[c] = has_la ? wt_lds[ol] : 0.0;
+        }
+#pragma unroll
+        for (int f = 0; f < PF; ++f) {
+            // (LDS operations of one wave execute in order: no barrier needed)
+            const bool border = T > 1 && has_la && __builtin_amdgcn_ballot_w64(wide || frag_cls[f] != 0) != 0;
+            const bool all = __builtin_amdgcn_ballot_w64(frag_m[f] < 0) == 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                double sa[4];
+                int at[4], cls[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    sa[j] = sa_stage[f * 32 + 8 * q + 4 * h + j];
+                    at[j] = at_stage[f * 32 + 8 * q + 4 * h + j];
+                    cls[j] = border ? cls_stage[f * 32 + 8 * q + 4 * h + j] : 0;
+                }
+#pragma unroll
+                for (int c = 0; c < CT; ++c) {
+                    if (KS == 2 && (c & 1) != grp) continue;
+                    const int o_tile = (ct0 + c) * 32, o = o_tile + col, ol = (wc * CT + c) * 32 + col;
+                    if (o_tile >= a.C_out) continue;
+                    float res[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        double v = __builtin_fma(P[c], (double)acc[f][c][4 * q + j], Q[c] * sa[j]);
+                        if (has_la) {
+                            double w = W[c];
+                            if (border) w = wide ? border_term<T>(a, o, cls[j]) : wt_lds[cls[j] + ol];
+                            v += w;
+                        }
+                        res[j] = (float)v;
+                    }
+                    if (all && o_tile + 32 <= a.C_out) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) __builtin_nontemporal_store(res[j], a.out + (size_t)(uint32_t)at[j] + o);
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (at[j] >= 0 && o < a.C_out) a.out[(size_t)(uint32_t)at[j] + o] = res[j];
+                    }
+                }
+            }
+        }
     } else {
         // The values of OUT_PLAIN plus, for l_a != 0, the terms of conv_epilogue.h that depend on
-        // which taps lie inside the image, in its order of operations (the same bits).  A pixel
-        // with all taps inside takes them from a table; fragments that hold other pixels add up
-        // the tap sums under their masks.  NCHW: the accumulator layout already has 32
+        // which taps lie inside the image, from the table of its class, in its order of
+        // operations (the same bits).  NCHW: the accumulator layout already has 32
         // consecutive pixels of a channel in 32 lanes, so each store writes two runs of 128
-        // bytes.  NHWC: staged like OUT_PLAIN, in single floats where C_out is not a
-        // multiple of 4.  Bound by the store of the tensor; measured against the out-of-line
-        // per-lane function that stood here (it worked out the pixel's divisions and code sums
-        // again for every four channels): 24 -> 144 at 56x56 x 64 with l_a != 0 201 -> 41 us,
-        // 128 -> 256 stride 2 at 28x28 x 64 to NCHW 40 -> 14 us.
+        // bytes.  NHWC (with raw accumulators): staged like OUT_PLAIN, in single floats where C_out
+        // is not a multiple of 4.  Bound by the store of the tensor; 128 -> 256 stride 2 at 28x28 x 64
+        // to NCHW 14 us; with l_a != 0 (tap sums added up for every pixel at a border -> now): 64 -> 64
+        // at 32x32 x 1 9.2 -> 6.5, 64 -> 64 at 56x56 x 64 23.4 -> 19.0, 256 -> 256 at 14x14 x 64 16.5 -> 13.8.
         if (h == 0) {
 #pragma unroll
             for (int f = 0; f < PF; ++f) m_stage[f * 32 + col] = frag_m[f];
@@ -881,7 +1001,6 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
             const int ol = (wc * CT + c) * 32 + 4 * h;     // this lane's first channel inside the workgroup
 #pragma unroll
             for (int f = 0; f < PF; ++f) {
-                const bool border = T > 1 && has_la && __builtin_amdgcn_ballot_w64(frag_taps[f] != (1 << T) - 1) != 0;
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int o0 = o_tile + 8 * q + 4 * h;
@@ -893,22 +1012,9 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
                     if (has_la) {
                         double w[4];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) w[j] = la_lds[2 * BC + ol + 8 * q + j];
-                        if (border) {
-                            int sw[4] = {0, 0, 0, 0};
-#pragma unroll
-                            for (int t = 0; t < T; ++t) {
-                                const v4i s4 = *reinterpret_cast<const v4i *>(swt_lds + t * BC + ol + 8 * q);
-                                const int in = -(frag_taps[f] >> t & 1);
-                                sw[0] += s4.x & in; sw[1] += s4.y & in; sw[2] += s4.z & in; sw[3] += s4.w & in;
-                            }
-                            const double kv = (double)(a.C_in * __builtin_popcount((unsigned)frag_taps[f]));
-#pragma unroll
-                            for (int j = 0; j < 4; ++j) {
-                                const double e = la_lds[ol + 8 * q + j] * (double)sw[j] + kv * la_lds[BC + ol + 8 * q + j];
-                                w[j] = frag_taps[f] == (1 << T) - 1 ? w[j] : e;
-                            }
-                        }
+                        for (int j = 0; j < 4; ++j) w[j] = wt_lds[frag_cls[f] * BC + ol + 8 * q + j];
+                        if (T > 1 && a.pad == 2)             // (the classes do not cover two rows of padding)
+                            for (int j = 0; j < 4; ++j) w[j] = border_term<T>(a, o0 + j, frag_taps[f]);
 #pragma unroll
                         for (int j = 0; j < 4; ++j) v[j] += w[j];
                     }
@@ -960,7 +1066,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
 // tables behind the buffers: Da*Dw, Da*l_w (binary64; chained mode: Dw, l_w, scale, shift), the
 // patch pixels' code sums; then the chained mode's per-channel constants of the code-unit
 // form, or the general results' tables for l_a != 0
-constexpr int border_table_bytes(int R, int BC) { return 3 * BC * 8 + (R > 1 ? R * R * BC * 4 : 0); }
+constexpr int border_table_bytes(int R, int BC) { return (R > 1 ? 9 : 1) * BC * 8; }
 
 inline int plan_lds_bytes(const PatchPlan &p, int BC, const DsqConvArgs &a)
 {
@@ -1010,10 +1116,11 @@ hipError_t launch_kernel(const DsqConvArgs &a, const PatchPlan &pl, hipStream_t 
 template <int CONT, int R, int WP, int WC, int PF, int CT, int UPT, int WD, int OCC, int KS = 1, bool CHAINED = true>
 hipError_t launch_cfg(const DsqConvArgs &a, const PatchPlan &pl, hipStream_t stream)
 {
-    const int out = output_mode(a);
+    const int out = output_mode(a, 32 * CT * WC);
     if constexpr (CHAINED)
         if (out == OUT_CODES) return launch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, OUT_CODES>(a, pl, stream);
     if (out == OUT_GENERAL) return launch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, OUT_GENERAL>(a, pl, stream);
+    if (out == OUT_ROWS) return launch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, OUT_ROWS>(a, pl, stream);
     return launch_kernel<CONT, R, WP, WC, PF, CT, UPT, WD, OCC, KS, OUT_PLAIN>(a, pl, stream);
 }
 

@@ -57,3 +57,23 @@ def test_largest_patch_with_the_tables_of_l_a(layout):
     want = _run(geom, 2, B.DSQ_CONV_KERNEL(1), -2.1, layout, True)
     got = _run(geom, 2, B.DSQ_CONV_KERNEL(6), -2.1, layout, True)
     assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+
+
+# one case per form of the results' epilogue: channel tiles that do not exist, images of one row or
+# column (only the middle taps), two rows of padding, two wave groups, 9 classes of borders, and on both
+# sides of the rule between the two layouts of a lane (1x1, l_a != 0, a fifth of the channels missing)
+@pytest.mark.parametrize("geom", [(2, 64, 5, 8, 96, 3, 1, 1), (1, 512, 7, 7, 97, 3, 1, 1), (2, 40, 1, 9, 36, 3, 1, 1),
+                                  (2, 40, 9, 1, 36, 3, 2, 1), (1, 64, 6, 5, 40, 3, 1, 2), (1, 64, 6, 5, 41, 3, 2, 2),
+                                  (2, 64, 7, 7, 48, 1, 1, 0), (2, 64, 7, 7, 52, 1, 1, 0), (3, 24, 20, 20, 144, 1, 1, 0),
+                                  (3, 30, 33, 17, 31, 1, 2, 0)])
+@pytest.mark.parametrize("bits", [1, 3])
+def test_nhwc_results_with_an_offset(geom, bits):
+    want = _run(geom, bits, B.DSQ_CONV_KERNEL(1), -0.9, B.DSQ_NHWC, False)
+    for kernel in (2, 3, 4, 5, 6):
+        try:
+            got = _run(geom, bits, B.DSQ_CONV_KERNEL(kernel), -0.9, B.DSQ_NHWC, False)
+        except B.DsqError as e:
+            if e.status != 5 or kernel == 2:
+                raise
+            continue
+        assert np.array_equal(got[0], want[0]), kernel
