@@ -119,7 +119,8 @@ typedef enum { DSQ_PACK_CONTAINER = 0, DSQ_PACK_DENSE3 = 1 } dsq_packing;
  * interfere.
  *
  * DSQ_CONV_KERNEL(k), k = 0..7, selects the kernel (for tests and
- *   benchmarking): 0 = automatic, 1 = the simple one-wave-per-tile kernel,
+ *   benchmarking): 0 = automatic (layers of at most a few hundred 32x32 output
+ *   tiles run on a split-K kernel that no k selects), 1 = the simple one-wave-per-tile kernel,
  *   2 = the LDS-patch kernel with its tile chosen by problem size, 3 / 4 / 5 / 6
  *   = the LDS-patch kernel with the 128x64 / 128x128 / 256x128 / 256x64
  *   (pixels x channels) tile, 7 = the split-K kernel for 1x1 layers with few

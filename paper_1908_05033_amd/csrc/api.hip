@@ -214,7 +214,8 @@ int host_code(float x, float l, float u, float delta, int top)
 // untouched.
 dsq_status launch_conv(const DsqConvArgs &a, hipStream_t stream)
 {
-    // 0 auto, 1 simple, 2 patch (auto tile), 3..6 patch with a fixed tile, 7 split-K 1x1
+    // 0 auto (the only one that takes the split-K kernel for few tiles), 1 simple, 2 patch (auto tile),
+    // 3..6 patch with a fixed tile, 7 split-K 1x1
     const int kernel = a.kernel;
     hipError_t e;
     if (kernel == 7 || kernel == 0) {
@@ -222,6 +223,10 @@ dsq_status launch_conv(const DsqConvArgs &a, hipStream_t stream)
         if (kernel == 7 && !fc_ok) return DSQ_ERR_UNSUPPORTED;
         if (fc_ok) {
             e = dsq_launch_conv_fc(a, stream);
+            return e == hipSuccess ? DSQ_OK : DSQ_ERR_HIP;
+        }
+        if (kernel == 0 && dsq_conv_split_preferred(a)) {
+            e = dsq_launch_conv_split(a, stream);
             return e == hipSuccess ? DSQ_OK : DSQ_ERR_HIP;
         }
     }
@@ -245,6 +250,10 @@ dsq_status describe_conv(const DsqConvArgs &a, char *text, size_t n)
                      a.rq ? ", chained epilogue" : "");
             return DSQ_OK;
         }
+        if (kernel == 0 && dsq_conv_split_preferred(a)) {
+            snprintf(text, n, "split-K kernel for few output tiles: container %d%s", a.cont, a.rq ? ", chained epilogue" : "");
+            return DSQ_OK;
+        }
     }
     const int force_tile = kernel >= 3 ? kernel - 3 : -1;
     if (kernel != 1 && dsq_conv_patch_describe(a, force_tile, text, n)) return DSQ_OK;
@@ -266,6 +275,7 @@ dsq_status dsq_conv2d_plan(const dsq_conv_desc *d, int chained, float l_a, char 
     const dsq_status st = conv_args(d, dummy, (const int32_t *)dummy, l_a, l_a + 1.0f, dummy, dummy, a);
     if (st != DSQ_OK) return st;
     a.rq = chained != 0;
+    a.rq_zeroed = chained && (d->flags & DSQ_CONV_NEXT_SUMS_ZERO);
     a.rq_Cp = dsq_round_up(a.C_out, 64);
     return describe_conv(a, text, text_bytes);
 }

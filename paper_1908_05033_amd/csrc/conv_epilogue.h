@@ -47,45 +47,55 @@ __device__ __forceinline__ DsqPixel dsq_pixel_info(const DsqConvArgs &a, int m, 
 }
 
 // The binary32 results of one lane: one pixel, four consecutive output channels
-// o0..o0+3 (o0 % 4 == 0, o0 + 3 < Cop).
-__device__ __forceinline__ void dsq_out4(const DsqConvArgs &a, const DsqPixel &p, int o0, v4i acc,
-                                         float delta_a, float (&res)[4])
+// whose steps and levels are dw and lw and whose weight code sums over the pixel's in-image taps are
+// sw (LA: l_a may differ from 0, sw counts).
+template <bool LA>
+__device__ __forceinline__ void dsq_out4_of(const DsqConvArgs &a, const DsqPixel &p, v4i acc, float delta_a, float4 dw,
+                                            float4 lw, v4i sw, float (&res)[4])
 {
-    const float4 dw = *reinterpret_cast<const float4 *>(a.delta_w + o0);
-    const float4 lw = *reinterpret_cast<const float4 *>(a.l_w + o0);
     const float dwv[4] = {dw.x, dw.y, dw.z, dw.w};
     const float lwv[4] = {lw.x, lw.y, lw.z, lw.w};
     const int accv[4] = {acc.x, acc.y, acc.z, acc.w};
-    const int T = a.R * a.R;
-    const bool full = p.ntaps == T;
+    const int swv[4] = {sw.x, sw.y, sw.z, sw.w};
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const double da = (double)delta_a, dwj = (double)dwv[j], lwj = (double)lwv[j];
         double v = __builtin_fma(da * dwj, (double)accv[j], (da * lwj) * (double)p.sa);
-        if (a.l_a != 0.0f) {
-            int sw;
-            if (full) sw = a.sw_total[o0 + j];
-            else {
-                sw = 0;
-                for (int t = 0; t < T; ++t)
-                    if (p.tapmask >> t & 1) sw += a.sw_tap[(size_t)(o0 + j) * T + t];
-            }
+        if (LA && a.l_a != 0.0f) {
             const double la = (double)a.l_a;
-            v += (la * dwj) * (double)sw + (double)(a.C_in * p.ntaps) * (la * lwj);
+            v += (la * dwj) * (double)swv[j] + (double)(a.C_in * p.ntaps) * (la * lwj);
         }
         res[j] = (float)v;
     }
 }
 
+// The same for channels o0..o0+3 (o0 % 4 == 0, o0 + 3 < Cop), everything of theirs read here.
+__device__ __forceinline__ void dsq_out4(const DsqConvArgs &a, const DsqPixel &p, int o0, v4i acc,
+                                         float delta_a, float (&res)[4])
+{
+    const int T = a.R * a.R;
+    int sw[4] = {0, 0, 0, 0};
+    if (a.l_a != 0.0f) {
+        const bool full = p.ntaps == T;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (full) sw[j] = a.sw_total[o0 + j];
+            else
+                for (int t = 0; t < T; ++t)
+                    if (p.tapmask >> t & 1) sw[j] += a.sw_tap[(size_t)(o0 + j) * T + t];
+        }
+    }
+    dsq_out4_of<true>(a, p, acc, delta_a, *reinterpret_cast<const float4 *>(a.delta_w + o0),
+                *reinterpret_cast<const float4 *>(a.l_w + o0), (v4i){sw[0], sw[1], sw[2], sw[3]}, res);
+}
+
 // Stores the results of one lane: one pixel, four consecutive output channels
 // o0..o0+3 (o0 % 4 == 0, o0 + 3 < Cop).
-__device__ __forceinline__ void dsq_store4(const DsqConvArgs &a, const DsqPixel &p, int m, int o0,
-                                           v4i acc, float delta_a)
+__device__ __forceinline__ void dsq_store4_of(const DsqConvArgs &a, const DsqPixel &p, int m, int o0, v4i acc,
+                                              const float (&res)[4])
 {
     if (!p.valid || o0 >= a.C_out) return;
     const int accv[4] = {acc.x, acc.y, acc.z, acc.w};
-    float res[4];
-    dsq_out4(a, p, o0, acc, delta_a, res);
     if (!a.out_nchw) {
         const size_t base = (size_t)m * a.C_out + o0;
         if ((a.C_out & 3) == 0) {
@@ -108,6 +118,15 @@ __device__ __forceinline__ void dsq_store4(const DsqConvArgs &a, const DsqPixel 
                 if (a.acc) a.acc[idx] = accv[j];
             }
     }
+}
+
+__device__ __forceinline__ void dsq_store4(const DsqConvArgs &a, const DsqPixel &p, int m, int o0,
+                                           v4i acc, float delta_a)
+{
+    if (!p.valid || o0 >= a.C_out) return;
+    float res[4];
+    dsq_out4(a, p, o0, acc, delta_a, res);
+    dsq_store4_of(a, p, m, o0, acc, res);
 }
 
 // ---- chained mode: the next layer's codes instead of the fp32 tensor --------

@@ -122,6 +122,10 @@ bool dsq_conv_fc_supported(const DsqConvArgs &a);   // the kernel takes this lay
 bool dsq_conv_fc_preferred(const DsqConvArgs &a);   // ... and is the faster choice for it
 hipError_t dsq_launch_conv_fc(const DsqConvArgs &a, hipStream_t stream);
 
+// Split-K kernel for layers of few output tiles (one image or a few, of a small map).
+bool dsq_conv_split_preferred(const DsqConvArgs &a);
+hipError_t dsq_launch_conv_split(const DsqConvArgs &a, hipStream_t stream);
+
 // Weight-only quantized layer: binary32 activations x (NHWC or NCHW), weights in the
 // packed 4-bit layout; uses the geometry, wq, delta_w, l_w, out and out_nchw of `a`.
 hipError_t dsq_launch_conv_wq(const DsqConvArgs &a, const float *x, int x_nchw, hipStream_t stream);
