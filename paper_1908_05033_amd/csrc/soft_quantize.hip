@@ -12,11 +12,15 @@
 namespace {
 
 // tanh(z) and 1 - tanh(z)^2 from e = exp(-2|z|): accurate in the saturated
-// tails, where 1 - t*t computed from a rounded t would lose all its digits.
+// tails, where 1 - t*t computed from a rounded t would lose all its digits.  1/(1 + e), a
+// reciprocal of a number in [1, 2], is the hardware's with one Newton step: four instructions
+// for the dozen of an IEEE division, and as good (its error is the last rounding's).
 __device__ __forceinline__ void tanh_sech2(float z, float &t, float &sech2)
 {
     const float e = __expf(-2.0f * fabsf(z));
-    const float r = 1.0f / (1.0f + e);
+    const float d = 1.0f + e;
+    float r = __builtin_amdgcn_rcpf(d);
+    r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
     t = copysignf((1.0f - e) * r, z);
     sech2 = 4.0f * e * r * r;
 }
@@ -46,28 +50,34 @@ __global__ __launch_bounds__(256) void soft_fwd_kernel(const float *__restrict__
     if (blockIdx.x == 0 && tail < n) y[tail] = soft_fwd(x[tail], p);
 }
 
-// One element of the backward pass: returns dL/dx, adds to the three sums.
+// One element of the backward pass: returns dL/dx, adds to the three sums.  Vector instructions, not
+// bandwidth, bound the pass on tensors that fit the last-level cache (300 clocks of a SIMD an element
+// and wave with an IEEE division, a branch for either side of the range, and every product rounded
+// before its sum).  So products and sums of the three derivatives are fused, and each sum takes one value, selected,
+// whichever side of the range x is on.  us with the clearing launch, before -> now: 590 000 elements
+// 7.7 -> 7.4, 2.4 M 13.6 -> 12.8, 12.8 M 32.5 -> 30.8 (5.0 TB/s).
 __device__ __forceinline__ float soft_bwd(float x, float g, const DsqSoftArgs &p, double &sa, double &sl,
                                           double &su)
 {
-    if (x < p.l) { sl += (double)g; return 0.0f; }
-    if (x > p.u) { su += (double)g; return 0.0f; }
-    const float i = fminf(floorf((x - p.l) * p.inv_delta), p.last_interval);
-    const float m = p.l + (i + 0.5f) * p.delta;
-    const float xm = x - m;
+    const bool below = x < p.l, above = x > p.u, outside = below || above;
+    const float ih = fminf(floorf((x - p.l) * p.inv_delta), p.last_interval) + 0.5f;
+    const float xm = x - (p.l + ih * p.delta);
     float t, sech2;
     tanh_sech2(p.k * xm, t, sech2);
-    const float q_over_levels = (i + 0.5f * (p.s * t + 1.0f)) * p.inv_levels;
-    const float m_u = (i + 0.5f) * p.inv_levels, m_l = 1.0f - m_u;
+    const float q_over_levels = __builtin_fmaf(0.5f * p.s, t, ih) * p.inv_levels;
+    const float m_u = ih * p.inv_levels, m_l = 1.0f - m_u;
     const float ss = p.s * sech2;
-    const float phi_a = p.s_a * t + ss * (p.k_a * xm);
-    const float phi_l = p.s_l * t + ss * (p.k_l * xm - p.k * m_l);
-    const float phi_u = p.s_u * t + ss * (p.k_u * xm - p.k * m_u);
+    const float phi_a = __builtin_fmaf(ss, p.k_a * xm, p.s_a * t);
+    const float phi_l = __builtin_fmaf(ss, __builtin_fmaf(p.k_l, xm, -(p.k * m_l)), p.s_l * t);
+    const float phi_u = __builtin_fmaf(ss, __builtin_fmaf(p.k_u, xm, -(p.k * m_u)), p.s_u * t);
     const float half_delta = 0.5f * p.delta;
-    sa += (double)(g * (half_delta * phi_a));
-    sl += (double)(g * (1.0f - q_over_levels + half_delta * phi_l));
-    su += (double)(g * (q_over_levels + half_delta * phi_u));
-    return g * (half_delta * ss * p.k);
+    const float ga = g * (half_delta * phi_a);
+    const float gl = g * __builtin_fmaf(half_delta, phi_l, 1.0f - q_over_levels);
+    const float gu = g * __builtin_fmaf(half_delta, phi_u, q_over_levels);
+    sa += (double)(outside ? 0.0f : ga);
+    sl += (double)(below ? g : above ? 0.0f : gl);
+    su += (double)(above ? g : below ? 0.0f : gu);
+    return outside ? 0.0f : g * (half_delta * ss * p.k);
 }
 
 __device__ __forceinline__ double wave_sum(double v)
