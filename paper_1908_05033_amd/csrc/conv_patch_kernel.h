@@ -116,8 +116,9 @@ __device__ __forceinline__ float chained_channel_constants(const DsqConvArgs &a,
     // (1.001: the roundings of the bound itself)
     const float E = 1.001f * (0x1p-21f * ((float)(1 << a.rq_bits) + S) + 0x1p-45f * (q * __builtin_fabsf(sc)) * inv_dn * samax) + a.rq_t_slack;
     const float ymax = (__builtin_fabsf(a.delta_a * dw) * a.rq_w_max + q) * samax;               // bound on the layer's |output|
-    // (every comparison is false for a NaN, which then ends in 1)
-    const bool ok = a.rq_fast && dw >= 0x1p-80f && __builtin_fabsf(lw) < 0x1p100f && ymax < 0x1p100f &&
+    // (every comparison is false for a NaN, which then ends in 1.  Dw is bounded above as well: from 2^126 on
+    // its reciprocal is a denormal, which v_rcp_f32 returns as 0, and rho with it)
+    const bool ok = a.rq_fast && dw >= 0x1p-80f && dw < 0x1p100f && __builtin_fabsf(lw) < 0x1p100f && ymax < 0x1p100f &&
                     ymax * __builtin_fabsf(sc) < 0x1p100f && __builtin_fabsf(sh) < 0x1p100f &&
                     (__builtin_fabsf(sc) + 1.0f) * inv_dn < 0x1p100f && __builtin_fabsf(A) < 0x1p60f &&
                     __builtin_fabsf(rho) < 0x1p20f && E < 0.5f;

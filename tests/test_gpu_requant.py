@@ -354,6 +354,44 @@ def test_extreme_scale_shift_and_ranges(bits, bits_n, relu, l_n, u_n, kernel):
         assert_codes_match(got[..., ordinary], want[:, ordinary], z[:, ordinary], l_n, u_n, bits_n, Co - 3 * n)
 
 
+@pytest.mark.parametrize("kernel", [0, 3, 4, 5, 6])
+@pytest.mark.parametrize("Ci", [64, 128])                 # one wave group, two
+@pytest.mark.parametrize("bits", [1, 2])
+def test_weight_steps_up_to_the_largest(bits, Ci, kernel):
+    """Channels whose step Dw reaches 2^127 (1 bit) or 2^126.4 (2 bits): 1/Dw is no normal number from
+    2^126 on.  Their codes are 0, so that the output is l_w*Da*SA alone, over the whole range of codes;
+    equal to the simple kernel's, which runs the recipe on every output."""
+    H, W, Co, R = 9, 8, 64, 3
+    delta_a, bits_n, l_n, u_n = 2.0 ** -50, 4, 0.0, 3.0
+    g = torch.Generator().manual_seed(31 + bits)
+    step = torch.tensor([2.0 ** e for e in (60, 98, 99, 100, 101, 120, 125, 125.9, 126, 126.1, 126.3, 126.4)] +
+                        ([2.0 ** e for e in (126.9, 127, 127.3, 127.9)] if bits == 1 else []), dtype=torch.float64)
+    step = step.repeat(Co // len(step) + 1)[:Co]
+    l_w = torch.full((Co,), 2.0 ** 98.5, dtype=torch.float64).minimum(step * 2 ** 12).float()
+    u_w = (l_w.double() + step * (2 ** bits - 1)).float()
+    assert torch.isfinite(u_w).all()
+    wc = torch.zeros((Co, Ci, R, R), dtype=torch.uint8)
+    wc[::5] = torch.randint(0, 2 ** bits, wc[::5].shape, generator=g, dtype=torch.uint8)      # ordinary codes beside them
+    x = torch.randint(0, 2 ** bits, (1, H, W, Ci), generator=g).float() * delta_a
+    buf = B.alloc_layer(1, Ci, H, W, Co, R, R, 1, 1, bits)
+    u_a = delta_a * (2 ** bits - 1)
+    B.dsq_quantize_act(x.cuda(), B.DSQ_NHWC, 1, Ci, H, W, 0.0, u_a, bits, buf.act_packed, buf.pix_code_sum)
+    B.dsq_pack_weights(None, l_w.cuda(), u_w.cuda(), wc.cuda(), Co, Ci, R, R, bits, buf.w_packed, buf.w_aux)
+    most = 9 * Ci * (2 ** bits - 1)
+    scale = (4.0 / (delta_a * l_w.double() * most)).float().cuda()       # l_w*Da*SA*scale goes up to 4, past u_n
+    got = []
+    for k in (1, kernel):
+        codes = torch.zeros(B.dsq_act_packed_bytes(1, H, W, Co, bits_n), dtype=torch.uint8, device="cuda")
+        pix = torch.zeros(H * W, dtype=torch.int32, device="cuda")
+        buf.desc.flags = B.DSQ_CONV_KERNEL(k)
+        B.dsq_conv2d_requant(buf.desc, buf.act_packed, buf.pix_code_sum, 0.0, u_a, buf.w_packed, buf.w_aux, scale, None, True,
+                             l_n, u_n, bits_n, codes, pix)
+        got.append((unpack_act(codes.cpu().numpy(), 1, H, W, Co, bits_n).reshape(H * W, -1), pix.cpu().numpy()))
+    assert all(len(np.unique(got[0][0][:, o])) > 3 for o in range(Co) if o % 5)
+    wrong = [(o, int(step[o].log2())) for o in range(Co) if not np.array_equal(got[1][0][:, o], got[0][0][:, o])]
+    assert not wrong and np.array_equal(got[1][1], got[0][1]), wrong
+
+
 def test_depth_beyond_the_binary32_integers():
     """A 4-bit layer deep enough that an accumulator may pass 2^24 (225 * 9 * C_in): the
     tuned kernels' short evaluation would convert it inexactly and is switched off by
