@@ -54,8 +54,8 @@ __global__ __launch_bounds__(256) void soft_fwd_kernel(const float *__restrict__
 // bandwidth, bound the pass on tensors that fit the last-level cache (300 clocks of a SIMD an element
 // and wave with an IEEE division, a branch for either side of the range, and every product rounded
 // before its sum).  So products and sums of the three derivatives are fused, and each sum takes one value, selected,
-// whichever side of the range x is on.  us with the clearing launch, before -> now: 590 000 elements
-// 7.7 -> 7.4, 2.4 M 13.6 -> 12.8, 12.8 M 32.5 -> 30.8 (5.0 TB/s).
+// whichever side of the range x is on.  us with the clearing launch and the kernel below, before -> now: 590 000
+// elements 7.7 -> 7.3, 2.4 M 13.3 -> 11.0, 12.8 M 31 -> 28.3 (5.4 TB/s), from HBM 36.0 -> 34.6, 51 M 125.7 -> 123.6.
 __device__ __forceinline__ float soft_bwd(float x, float g, const DsqSoftArgs &p, double &sa, double &sl,
                                           double &su)
 {
@@ -104,10 +104,15 @@ __global__ __launch_bounds__(BWD_THREADS) void soft_bwd_kernel(const float *__re
     const size_t stride = (size_t)gridDim.x * BWD_THREADS;
     auto four = [&](const float4 a, const float4 g) {
         float4 r;
+        // (the sums are complete after every second element: left to itself the compiler carries the
+        // eight elements of a thread side by side, in 78 registers instead of 48, of which one workgroup fits
+        // a compute unit instead of two: 12.8 M elements 30.8 us for 28.3)
         r.x = soft_bwd(a.x, g.x, p, sa, sl, su);
         r.y = soft_bwd(a.y, g.y, p, sa, sl, su);
+        asm volatile("" : "+v"(sa), "+v"(sl), "+v"(su));
         r.z = soft_bwd(a.z, g.z, p, sa, sl, su);
         r.w = soft_bwd(a.w, g.w, p, sa, sl, su);
+        asm volatile("" : "+v"(sa), "+v"(sl), "+v"(su));
         return r;
     };
     size_t v = (size_t)blockIdx.x * BWD_THREADS + threadIdx.x;
@@ -156,7 +161,11 @@ hipError_t dsq_launch_soft_bwd(const float *x, const float *gy, float *gx, size_
     hipError_t e = dsq_launch_fill_zero(reinterpret_cast<int32_t *>(sums), 6, stream);
     if (e != hipSuccess) return e;
     const size_t want = (n / 4 + BWD_THREADS - 1) / BWD_THREADS;
-    const unsigned grid = (unsigned)(want < 1 ? 1 : want > 512 ? 512 : want);
+    // Two workgroups per compute unit; up to six vectors a thread of one (6.3 M elements) one, whose half as many
+    // atomics at the end weigh more.  us, 256 / 512 workgroups: 1.6 M elements 9.3 / 11.1, 3.3 M 13.3 / 15.3, 6 M 18.0 /
+    // 18.3, 7.3 M 20.6 / 20.6, 10 M 24.1 / 23.9, 12.8 M 29.0 / 28.3
+    const unsigned most = want <= 6 * 256 ? 256 : 512;
+    const unsigned grid = (unsigned)(want < 1 ? 1 : want > most ? most : want);
     soft_bwd_kernel<<<grid, BWD_THREADS, 0, stream>>>(x, gy, gx, n, p, sums);
     return hipGetLastError();
 }

@@ -69,6 +69,12 @@ def test_backward(l, u, alpha, bits, n):
         assert abs(got - terms.sum()) <= 1e-5 * np.abs(terms).sum() + 1e-12
 
 
+@pytest.mark.parametrize("n", [6 * (1 << 20), 6 * (1 << 20) + 1, 6 * (1 << 20) + 4099])
+def test_backward_on_either_side_of_the_workgroup_rule(n):
+    """Up to 6 * 2^20 elements one workgroup per compute unit, above it two."""
+    test_backward(-1.0, 2.0, 0.2, 2, n)
+
+
 def test_largest_tensor():
     """n = 2^31 - 1 elements (the limit, and an odd count): forward values and the
     elementwise gradient at the head, the tail and a million places in between,

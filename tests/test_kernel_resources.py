@@ -34,7 +34,8 @@ def _device_asm(src):
 
 @pytest.mark.parametrize("source", ["conv_patch_c4r3.hip", "conv_patch_c4r1.hip", "conv_patch_c2r3.hip", "conv_patch_c2r1.hip",
                                     "conv_patch_c3r3.hip", "conv_patch_c3r1.hip",
-                                    "conv_simple.hip", "conv_fc.hip", "conv_wq.hip", "quantize_act.hip"])
+                                    "conv_simple.hip", "conv_fc.hip", "conv_wq.hip", "quantize_act.hip",
+                                    "soft_quantize.hip"])
 def test_kernels_stay_inside_their_register_budget(source):
     asm = _device_asm(os.path.join(CSRC, source))
     kernels = re.findall(r"\.name:\s+(\S+).*?\.vgpr_count:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)", asm, re.S)
@@ -62,6 +63,14 @@ def test_split_k_workgroups_share_a_cu():
     kernels = re.findall(r"\.name:\s+(\S+).*?\.vgpr_count:\s+(\d+)", asm, re.S)
     short = [(n, int(v)) for n, v in kernels if not re.search(r"conv_fc_kernelILi\dELb1E", n)]
     assert short and all(v <= 128 for _, v in short), short
+
+
+def test_two_backward_workgroups_share_a_cu():
+    """The backward training quantizer's workgroups are 16 waves and large tensors launch two per compute unit:
+    both are resident up to 64 registers."""
+    asm = _device_asm(os.path.join(CSRC, "soft_quantize.hip"))
+    kernels = re.findall(r"\.name:\s+(\S*soft_bwd\S*).*?\.vgpr_count:\s+(\d+)", asm, re.S)
+    assert kernels and all(int(v) <= 64 for _, v in kernels), kernels
 
 
 def test_1x1_stages_do_not_wait_for_the_next_weights():
