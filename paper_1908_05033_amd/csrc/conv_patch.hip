@@ -78,8 +78,10 @@ namespace {
 
 bool plan_patch(const DsqConvArgs &a, int BP, int BC, int PF, int CT, int UPT, int lds_limit, int KS, PatchPlan &best)
 {
-    // epilogue staging of the four waves (+ the partial sums of a second wave group)
-    const int epi_bytes = 4 * KS * (32 * (128 + 16) + PF * 128) + (KS == 2 ? 8 * PF * (CT / 2) * 4096 : 0);
+    // epilogue staging of the four waves; behind it the partial sums of a second wave group, then the table of
+    // border terms for two rows of padding
+    const int partial = KS == 2 ? 8 * PF * (CT / 2) * 4096 : 0, wide = has_wide_border(a) ? wide_table_bytes(BC) : 0;
+    const int epi_bytes = 4 * KS * (32 * (128 + 16) + PF * 128) + (partial > wide ? partial : wide);
     const int cont = a.cont;
     const int UPP = cont == 2 ? 1 : 2;
     const int PIX_STRIDE = pix_stride(cont);

@@ -129,20 +129,11 @@ __device__ __forceinline__ float chained_channel_constants(const DsqConvArgs &a,
 }
 
 // Which of the three taps from row (column) i on lie inside an image of n rows: 0 all, 1 all but
-// the first, 2 all but the last; 0 as well where n = 1 and i = -1, whose pixels have the middle tap
-// only.  (One row of padding: what two rows of it add, OUT_ROWS and OUT_GENERAL work out from
-// the taps themselves.)
-__device__ __forceinline__ int border_class(int i, int n) { return n == 1 ? 0 : i < 0 ? 1 : i + 2 >= n ? 2 : 0; }
-
-// The border term of channel o of a pixel with the taps of the mask `taps` inside the image.
-template <int T>
-__device__ __forceinline__ double border_term(const DsqConvArgs &a, int o, int taps)
+// the first, 2 all but the last, 3 the last, 4 the first; 0 as well where n = 1 and i = -1, whose pixels have
+// the middle tap only.  (3 and 4 with two rows of padding only.)
+__device__ __forceinline__ int border_class(int i, int n)
 {
-    int sw = 0;
-    for (int t = 0; t < T; ++t)
-        if (taps >> t & 1) sw += a.sw_tap[(size_t)o * T + t];
-    const double la = (double)a.l_a;
-    return (la * (double)a.delta_w[o]) * (double)sw + (double)(a.C_in * __builtin_popcount((unsigned)taps)) * (la * (double)a.l_w[o]);
+    return i < -1 ? 3 : i > n - 2 ? 4 : n == 1 ? 0 : i < 0 ? 1 : i + 2 >= n ? 2 : 0;
 }
 
 // What the kernel's results become; chosen at compile time, so that the register
@@ -153,6 +144,10 @@ __device__ __forceinline__ double border_term(const DsqConvArgs &a, int o, int t
 //   OUT_GENERAL  everything else: NCHW, l_a != 0 (terms that depend on which taps lie
 //                inside the image), raw accumulators
 enum { OUT_PLAIN = 0, OUT_CODES = 1, OUT_GENERAL = 2, OUT_ROWS = 3 };
+
+// Two rows of padding and l_a != 0: 25 classes of borders instead of 9, in a table of their own.
+__host__ __device__ inline bool has_wide_border(const DsqConvArgs &a) { return a.l_a != 0.0f && a.pad == 2; }
+constexpr int wide_table_bytes(int BC) { return 25 * BC * 8; }
 
 // BC: channels of the workgroup's tile.  OUT_ROWS where C_out is not a multiple of 4 (single floats
 // are staged badly: 64 -> 66 3x3 at 56x56 x 8 9.5 us, 8.0 so) and for 1x1 layers with l_a != 0 a fifth of
@@ -374,6 +369,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     }
 
     const bool has_la = (OUT == OUT_GENERAL || OUT == OUT_ROWS) && a.l_a != 0.0f;
+    const bool wide = T > 1 && has_la && has_wide_border(a);
     // (one channel per thread; behind the patch, so that the wait for that is not one for these)
     int la_sw[T];
     float la_dw = 0.f, la_lw = 0.f;
@@ -396,8 +392,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
     int frag_pp[PF];        // index of that patch pixel (prow*PC + pcol)
     int frag_m[PF];         // output pixel index n*Ho*Wo + oy*Wo + ox, or -1
     int frag_base[PF];      // general results, NCHW: element index of the pixel in channel 0
-    int frag_taps[PF];      // l_a != 0 and two rows of padding: bit t set = tap t lies inside the image
-    int frag_cls[PF];       // l_a != 0: class of the set of those taps
+    int frag_cls[PF];       // l_a != 0: class of the set of taps that lie inside the image
 #pragma unroll
     for (int f = 0; f < PF; ++f) {
         const int t = t0 + (wp * PF + f) * 32 + col;
@@ -407,7 +402,6 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         const bool ok = gr < NHo && ow < a.Wo;
         int prow = 0, pcol = 0;
         frag_base[f] = 0;
-        frag_taps[f] = (1 << T) - 1;
         frag_cls[f] = 0;
         if (ok) {
             int oh;
@@ -418,14 +412,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
                 frag_base[f] = n * (a.C_out - 1) * (a.Ho * a.Wo) + gr * a.Wo + ow;
                 if (T > 1 && has_la) {
                     const int ih = oh * a.stride - a.pad, iw = ow * a.stride - a.pad;
-                    frag_cls[f] = 3 * border_class(ih, a.H) + border_class(iw, a.W);
-                    int rows = 0, cols = 0;                  // taps of a column / of a row inside the image
-#pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        if ((unsigned)(ih + r) < (unsigned)a.H) rows |= 1 << (r * R);
-                        if ((unsigned)(iw + r) < (unsigned)a.W) cols |= 1 << r;
-                    }
-                    frag_taps[f] = rows * cols;              // (no carries: each bit of rows places its own copy of cols)
+                    frag_cls[f] = (wide ? 5 : 3) * border_class(ih, a.H) + border_class(iw, a.W);
                 }
             }
         }
@@ -545,19 +532,27 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         // border terms of the channel, in the order of operations of conv_epilogue.h
         // (an image of one row or column: its pixels have only the middle taps)
         const double ldw = (double)a.l_a * (double)la_dw, llw = (double)a.l_a * (double)la_lw;
-        const bool row = a.H == 1 && a.pad > 0, column = a.W == 1 && a.pad > 0;
+        if (wide) {
+            // (what the table of 25 classes is made from, behind the main loop)
 #pragma unroll
-        for (int t = 0; t < T; ++t)
-            if ((row && t / R != 1) || (column && t % R != 1)) la_sw[t] = 0;
-#pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            const int r0 = k / 3 == 1, r1 = k / 3 == 2 ? 2 : 3, c0 = k % 3 == 1, c1 = k % 3 == 2 ? 2 : 3;
-            int sw = 0;
+            for (int t = 0; t < T; ++t) reinterpret_cast<int *>(wt_lds)[t * BC + tid] = la_sw[t];
+            wt_lds[5 * BC + tid] = ldw;
+            wt_lds[6 * BC + tid] = llw;
+        } else {
+            const bool row = a.H == 1 && a.pad > 0, column = a.W == 1 && a.pad > 0;
 #pragma unroll
             for (int t = 0; t < T; ++t)
-                if (t / R >= r0 && t / R < r1 && t % R >= c0 && t % R < c1) sw += la_sw[t];
-            const int taps = (row ? 1 : r1 - r0) * (column ? 1 : c1 - c0);
-            wt_lds[k * BC + tid] = ldw * (double)sw + (double)(a.C_in * taps) * llw;
+                if ((row && t / R != 1) || (column && t % R != 1)) la_sw[t] = 0;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) {
+                const int r0 = k / 3 == 1, r1 = k / 3 == 2 ? 2 : 3, c0 = k % 3 == 1, c1 = k % 3 == 2 ? 2 : 3;
+                int sw = 0;
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    if (t / R >= r0 && t / R < r1 && t % R >= c0 && t % R < c1) sw += la_sw[t];
+                const int taps = (row ? 1 : r1 - r0) * (column ? 1 : c1 - c0);
+                wt_lds[k * BC + tid] = ldw * (double)sw + (double)(a.C_in * taps) * llw;
+            }
         }
     }
     if (RQ && grp == KS - 1 && tid < BC) {       // (whole waves: BC is a multiple of 64)
@@ -679,6 +674,44 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
                 }
             }
     }
+    // border terms of the workgroup's channels, [class][channel]
+    int border_at = (int)(reinterpret_cast<char *>(wt_lds) - lds);
+    if (wide) {
+        // Two rows of padding: pixels that lack two rows or columns of taps have classes too.  Their table takes
+        // the place of the partial sums, behind the staging (25 classes do not fit beside the largest patches).
+        // us, added up from the taps for every output of such a layer (which also kept the compiler from unrolling
+        // the loops of OUT_GENERAL: the 256x128 tile's accumulators went through scratch memory, on every layer) ->
+        // now: 64 -> 64 at 56x56 x 64 53 -> 19.3, 4 bits 72 -> 23.5, 128 -> 128 at 28x28 x 64 to NCHW 57 -> 18;
+        // the 256x128 tile to NCHW, 256 -> 512 at 28x28 x 32, 46 -> 29.5.
+        if (KS == 2) lds_barrier();
+        border_at = 4 * KS * EPI_WAVE;
+        double *wide_lds = reinterpret_cast<double *>(lds + border_at);
+        // a thread forms every G-th row of classes of one channel
+        constexpr int G = 256 * KS / BC;
+        const int ch = (int)threadIdx.x % BC, g = __builtin_amdgcn_readfirstlane((int)threadIdx.x / BC);
+        const double ldw = wt_lds[5 * BC + ch], llw = wt_lds[6 * BC + ch];
+        int sw[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) sw[t] = reinterpret_cast<const int *>(wt_lds)[t * BC + ch];
+#pragma unroll
+        for (int kr = 0; kr < 5; ++kr) {
+            if (kr % G != g) continue;
+            const int r0 = kr == 3 ? 2 : kr == 1 || (kr == 0 && a.H == 1), r1 = kr == 4 ? 1 : kr == 2 || (kr == 0 && a.H == 1) ? 2 : 3;
+            int s[3] = {0, 0, 0};                    // sums of the columns over the class's rows
+#pragma unroll
+            for (int t = 0; t < T; ++t) s[t % R] += t / R >= r0 && t / R < r1 ? sw[t] : 0;
+#pragma unroll
+            for (int kc = 0; kc < 5; ++kc) {
+                const bool one = kc == 0 && a.W == 1;
+                const int sum = kc == 3 ? s[2] : kc == 4 ? s[0] : s[1] + (kc == 1 || one ? 0 : s[0]) + (kc == 2 || one ? 0 : s[2]);
+                const int columns = kc >= 3 || one ? 1 : kc == 0 ? 3 : 2;
+                wide_lds[(kr * 5 + kc) * BC + ch] = ldw * (double)sum + (double)(a.C_in * ((r1 - r0) * columns)) * llw;
+            }
+        }
+        lds_barrier();
+    }
+    // (16-byte aligned either way, which the compiler has to see to read two terms at once)
+    const double *border_lds = reinterpret_cast<const double *>(lds + (border_at & ~15));
     char *stage = lds + (grp * 4 + wave) * EPI_WAVE;
     int *m_stage = reinterpret_cast<int *>(stage + 32 * ROWB);
 
@@ -922,13 +955,12 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         // past C_out are left out.
         double *sa_stage = reinterpret_cast<double *>(stage);                       // [fragment][pixel]
         int *at_stage = reinterpret_cast<int *>(stage + PF * 256), *cls_stage = at_stage + PF * 32;
-        const bool wide = T > 1 && has_la && a.pad == 2;     // (the classes do not cover two rows of padding)
         if (h == 0) {
 #pragma unroll
             for (int f = 0; f < PF; ++f) {
                 sa_stage[f * 32 + col] = dsa[f];
                 at_stage[f * 32 + col] = frag_m[f] < 0 ? -1 : frag_m[f] * a.C_out;   // (an element index: below 2^31)
-                cls_stage[f * 32 + col] = wide ? frag_taps[f] : frag_cls[f] * BC;
+                cls_stage[f * 32 + col] = frag_cls[f] * BC;
             }
         }
         double P[CT], Q[CT], W[CT];
@@ -937,12 +969,12 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
             const int ol = (wc * CT + c) * 32 + col;
             P[c] = pq_lds[ol];
             Q[c] = pq_lds[BC + ol];
-            W[c] = has_la ? wt_lds[ol] : 0.0;
+            W[c] = has_la ? border_lds[ol] : 0.0;
         }
 #pragma unroll
         for (int f = 0; f < PF; ++f) {
             // (LDS operations of one wave execute in order: no barrier needed)
-            const bool border = T > 1 && has_la && __builtin_amdgcn_ballot_w64(wide || frag_cls[f] != 0) != 0;
+            const bool border = T > 1 && has_la && __builtin_amdgcn_ballot_w64(frag_cls[f] != 0) != 0;
             const bool all = __builtin_amdgcn_ballot_w64(frag_m[f] < 0) == 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -963,11 +995,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         double v = __builtin_fma(P[c], (double)acc[f][c][4 * q + j], Q[c] * sa[j]);
-                        if (has_la) {
-                            double w = W[c];
-                            if (border) w = wide ? border_term<T>(a, o, cls[j]) : wt_lds[cls[j] + ol];
-                            v += w;
-                        }
+                        if (has_la) v += border ? border_lds[cls[j] + ol] : W[c];
                         res[j] = (float)v;
                     }
                     if (all && o_tile + 32 <= a.C_out) {
@@ -1013,9 +1041,7 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
                     if (has_la) {
                         double w[4];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) w[j] = wt_lds[frag_cls[f] * BC + ol + 8 * q + j];
-                        if (T > 1 && a.pad == 2)             // (the classes do not cover two rows of padding)
-                            for (int j = 0; j < 4; ++j) w[j] = border_term<T>(a, o0 + j, frag_taps[f]);
+                        for (int j = 0; j < 4; ++j) w[j] = border_lds[frag_cls[f] * BC + ol + 8 * q + j];
 #pragma unroll
                         for (int j = 0; j < 4; ++j) v[j] += w[j];
                     }

@@ -77,3 +77,13 @@ def test_nhwc_results_with_an_offset(geom, bits):
                 raise
             continue
         assert np.array_equal(got[0], want[0]), kernel
+
+
+# two rows of padding: pixels that lack one and two rows or columns of taps, images of one to three rows or
+# columns, all of whose pixels do, one and two wave groups, tiles that hold several images
+@pytest.mark.parametrize("layout", [B.DSQ_NHWC, B.DSQ_NCHW])
+@pytest.mark.parametrize("geom", [(2, 64, 1, 9, 40, 3, 1, 2), (2, 40, 9, 1, 41, 3, 2, 2), (3, 130, 2, 2, 66, 3, 1, 2),
+                                  (3, 64, 3, 2, 96, 3, 2, 2), (2, 257, 13, 10, 130, 3, 1, 2), (5, 24, 28, 30, 70, 3, 1, 2)])
+@pytest.mark.parametrize("bits", [1, 3])
+def test_two_rows_of_padding(geom, bits, layout):
+    test_same_bits_as_the_simple_kernel(geom, bits, 0.7, layout)

@@ -18,6 +18,7 @@ from paper_1908_05033_amd import build as B
 
 CSRC = os.path.join(os.path.dirname(B.__file__), "csrc")
 MAX_SPILLED_VGPRS = 40            # whole kernel
+MAX_SCRATCH_BYTES = 4 * MAX_SPILLED_VGPRS + 16     # per lane: an array in scratch memory is no spill to the compiler
 MAX_SCRATCH_IN_MFMA_BLOCK = 48    # scratch instructions in a basic block that issues MFMAs
 
 
@@ -42,6 +43,10 @@ def test_kernels_stay_inside_their_register_budget(source):
     assert kernels, "no kernel metadata found in the device assembly"
     over = [(n, int(v), int(s)) for n, v, s in kernels if int(s) > MAX_SPILLED_VGPRS]
     assert not over, "kernels spilling more than %d registers: %s" % (MAX_SPILLED_VGPRS, over[:5])
+    scratch = re.findall(r"\.name:\s+(\S+).*?\.private_segment_fixed_size:\s+(\d+)", asm, re.S)
+    assert len(scratch) == len(kernels)
+    over = [(n, int(b)) for n, b in scratch if int(b) > MAX_SCRATCH_BYTES]
+    assert not over, "kernels with more than %d bytes of scratch a lane: %s" % (MAX_SCRATCH_BYTES, over[:5])
     # no variant may spill inside the blocks that feed the matrix cores
     hot = []
     for fn in re.split(r"\n(?=_Z\S+:)", asm):
