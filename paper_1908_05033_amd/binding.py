@@ -1,14 +1,17 @@
 """ctypes binding of libdsqconv: the same names as ``include/dsqconv.h``.
 
 Argument marshalling only; calls whose arguments all have their plain form go through
-the native ``_marshal`` module instead of ctypes (csrc/marshal.cpp).  PyTorch supplies device memory (``data_ptr()``)
+the native ``_marshal`` module instead of ctypes (csrc/marshal.cpp) where it loads: it is
+built against one PyTorch, and without it, with a warning, every call takes the ctypes path.
+PyTorch supplies device memory (``data_ptr()``)
 and the HIP stream handle (``torch.cuda.current_stream().cuda_stream`` is
 PyTorch-ROCm's name for the hipStream_t); every step of the path runs in the
-library's HIP kernels.  There is no CPU fallback: if the shared library or the module
-has not been built, the first call raises.
+library's HIP kernels.  There is no CPU fallback: if the shared library has
+not been built, the first call raises.
 """
 import ctypes as C
 import os
+import warnings
 from dataclasses import dataclass
 
 import torch
@@ -100,16 +103,30 @@ def load_library():
 _marshal = None
 
 
+class _NoMarshal:
+    """In the module's place where it does not load: leaves every call to the ctypes path."""
+
+    @staticmethod
+    def quantize_act(*args):
+        return None
+
+    conv2d = conv2d_requant = conv2d_wq = soft_quantize_fwd = soft_quantize_bwd = quantize_act
+
+
 def load_marshal():
-    """The native marshalling module, bound to the library's entry points; raises if it has not been built."""
+    """The native marshalling module, bound to the library's entry points; where it is missing or does not load
+    (built for another PyTorch), a warning and a stand-in that leaves the calls to ctypes: 5 us a call, same results."""
     global _marshal
     if _marshal is None:
         lib = load_library()
         try:
             from . import _marshal as module
         except ImportError as e:
-            raise RuntimeError("the _marshal module of paper_1908_05033_amd is missing or does not load (%s): build it first "
-                               "(python -c 'import __graft_entry__ as g; g.build()')." % e) from e
+            warnings.warn("the _marshal module of paper_1908_05033_amd is missing or does not load (%s): calls are marshalled "
+                          "by ctypes, some 5 us slower each (python -c 'import __graft_entry__ as g; g.build()' builds it)" % e,
+                          RuntimeWarning, stacklevel=3)
+            _marshal = _NoMarshal
+            return _marshal
         module.init(dsq_conv_desc, *(C.cast(getattr(lib, name), C.c_void_p).value for name in
                                      ("dsq_quantize_act", "dsq_conv2d", "dsq_conv2d_requant", "dsq_conv2d_wq",
                                       "dsq_soft_quantize_fwd", "dsq_soft_quantize_bwd")))

@@ -77,6 +77,34 @@ def test_other_forms_are_left_alone(recorded):
     assert m.conv2d(*good) == 7
 
 
+def test_module_that_does_not_load(monkeypatch):
+    """Without the module (missing, or built for another PyTorch) the calls work through ctypes, with one warning."""
+    import sys
+    import warnings
+    import paper_1908_05033_amd as package
+    monkeypatch.setattr(B, "_marshal", None)
+    monkeypatch.delattr(package, "_marshal", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_1908_05033_amd._marshal", None)          # its import raises ImportError
+    # (no codes, no descriptor: refused before anything is launched)
+    calls = [lambda: B.dsq_quantize_act(64, 0, 0, 64, 2, 2, 0.0, 1.0, 4, None, 64, 0),
+             lambda: B.dsq_conv2d(None, 64, 64, 0.0, 1.0, 64, 64, 64, 0, None, 0),
+             lambda: B.dsq_conv2d_requant(None, 64, 64, 0.0, 1.0, 64, 64, None, None, True, 0.0, 1.0, 4, None, 64, 0),
+             lambda: B.dsq_conv2d_wq(None, 64, 0, 64, 64, 64, 0, 0),
+             lambda: B.dsq_soft_quantize_fwd(torch.zeros(0), 0.0, 1.0, 0.2, 2, None),
+             lambda: B.dsq_soft_quantize_bwd(torch.zeros(0), None, 0.0, 1.0, 0.2, 2, None, None)]
+    with pytest.warns(RuntimeWarning, match="_marshal"):
+        with pytest.raises(B.DsqError):
+            calls[0]()
+    with warnings.catch_warnings():
+        warnings.simplefilter("error")
+        for call in calls[1:4]:
+            with pytest.raises(B.DsqError):
+                call()
+        for call in calls[4:]:
+            with pytest.raises(TypeError):                   # (a host tensor: refused as ever)
+                call()
+
+
 @pytest.mark.gpu
 def test_device_tensors_and_streams(recorded):
     m, calls = recorded
