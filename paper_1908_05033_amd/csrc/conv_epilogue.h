@@ -46,47 +46,57 @@ __device__ __forceinline__ DsqPixel dsq_pixel_info(const DsqConvArgs &a, int m, 
     return p;
 }
 
-// The binary32 results of one lane: one pixel, four consecutive output channels
-// whose steps and levels are dw and lw and whose weight code sums over the pixel's in-image taps are
-// sw (LA: l_a may differ from 0, sw counts).
-template <bool LA>
-__device__ __forceinline__ void dsq_out4_of(const DsqConvArgs &a, const DsqPixel &p, v4i acc, float delta_a, float4 dw,
-                                            float4 lw, v4i sw, float (&res)[4])
+// The terms of one pixel and channel that do not depend on l_a, and those that do, `sw` being the sum of the
+// channel's weight codes over the pixel's in-image taps; the layer's output is their sum rounded to binary32.
+__device__ __forceinline__ double dsq_terms(const DsqPixel &p, int acc, float delta_a, float dw, float lw)
 {
-    const float dwv[4] = {dw.x, dw.y, dw.z, dw.w};
-    const float lwv[4] = {lw.x, lw.y, lw.z, lw.w};
-    const int accv[4] = {acc.x, acc.y, acc.z, acc.w};
-    const int swv[4] = {sw.x, sw.y, sw.z, sw.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const double da = (double)delta_a, dwj = (double)dwv[j], lwj = (double)lwv[j];
-        double v = __builtin_fma(da * dwj, (double)accv[j], (da * lwj) * (double)p.sa);
-        if (LA && a.l_a != 0.0f) {
-            const double la = (double)a.l_a;
-            v += (la * dwj) * (double)swv[j] + (double)(a.C_in * p.ntaps) * (la * lwj);
-        }
-        res[j] = (float)v;
-    }
+    const double da = (double)delta_a;
+    return __builtin_fma(da * (double)dw, (double)acc, (da * (double)lw) * (double)p.sa);
 }
 
-// The same for channels o0..o0+3 (o0 % 4 == 0, o0 + 3 < Cop), everything of theirs read here.
+__device__ __forceinline__ double dsq_terms_la(const DsqConvArgs &a, const DsqPixel &p, float dw, float lw, int sw)
+{
+    const double la = (double)a.l_a;
+    return (la * (double)dw) * (double)sw + (double)(a.C_in * p.ntaps) * (la * (double)lw);
+}
+
+// The binary32 results of one lane: one pixel, four consecutive output channels
+// o0..o0+3 (o0 % 4 == 0, o0 + 3 < Cop).  AT_ONCE: the code sums of full pixels are read together, ahead of their
+// use, not one channel after the other: 24 -> 144 1x1 chained with l_a != 0 76 -> 69 us in the simple kernel.  The
+// short 2-bit form of the split-K kernel for few pixels, whose fourth workgroup of a compute unit ends at 64
+// registers, does without (68 with it: 512 -> 512 chained, 784 tiles, 8.7 -> 9.5 us).  The tap sums of pixels at a border
+// are added up channel by channel, right before their use: those of four channels before the first
+// use took the simple kernel from 92 to 108 registers, 64 -> 64 3x3 at 28x28 x 64 from 14.4 to 19.7 us and, chained
+// with l_a != 0, from 33 to 50.
+template <bool AT_ONCE>
 __device__ __forceinline__ void dsq_out4(const DsqConvArgs &a, const DsqPixel &p, int o0, v4i acc,
                                          float delta_a, float (&res)[4])
 {
+    const float4 dw = *reinterpret_cast<const float4 *>(a.delta_w + o0);
+    const float4 lw = *reinterpret_cast<const float4 *>(a.l_w + o0);
+    const float dwv[4] = {dw.x, dw.y, dw.z, dw.w};
+    const float lwv[4] = {lw.x, lw.y, lw.z, lw.w};
+    const int accv[4] = {acc.x, acc.y, acc.z, acc.w};
     const int T = a.R * a.R;
-    int sw[4] = {0, 0, 0, 0};
-    if (a.l_a != 0.0f) {
-        const bool full = p.ntaps == T;
+    const bool full = p.ntaps == T;
+    v4i total = {0, 0, 0, 0};
+    if (AT_ONCE && a.l_a != 0.0f) total = *reinterpret_cast<const v4i *>(a.sw_total + o0);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (full) sw[j] = a.sw_total[o0 + j];
-            else
+    for (int j = 0; j < 4; ++j) {
+        double v = dsq_terms(p, accv[j], delta_a, dwv[j], lwv[j]);
+        if (a.l_a != 0.0f) {
+            int sw = total[j];
+            if (full) {
+                if (!AT_ONCE) sw = a.sw_total[o0 + j];
+            } else {
+                sw = 0;
                 for (int t = 0; t < T; ++t)
-                    if (p.tapmask >> t & 1) sw[j] += a.sw_tap[(size_t)(o0 + j) * T + t];
+                    if (p.tapmask >> t & 1) sw += a.sw_tap[(size_t)(o0 + j) * T + t];
+            }
+            v += dsq_terms_la(a, p, dwv[j], lwv[j], sw);
         }
+        res[j] = (float)v;
     }
-    dsq_out4_of<true>(a, p, acc, delta_a, *reinterpret_cast<const float4 *>(a.delta_w + o0),
-                *reinterpret_cast<const float4 *>(a.l_w + o0), (v4i){sw[0], sw[1], sw[2], sw[3]}, res);
 }
 
 // Stores the results of one lane: one pixel, four consecutive output channels
@@ -120,12 +130,13 @@ __device__ __forceinline__ void dsq_store4_of(const DsqConvArgs &a, const DsqPix
     }
 }
 
+template <bool AT_ONCE = true>
 __device__ __forceinline__ void dsq_store4(const DsqConvArgs &a, const DsqPixel &p, int m, int o0,
                                            v4i acc, float delta_a)
 {
     if (!p.valid || o0 >= a.C_out) return;
     float res[4];
-    dsq_out4(a, p, o0, acc, delta_a, res);
+    dsq_out4<AT_ONCE>(a, p, o0, acc, delta_a, res);
     dsq_store4_of(a, p, m, o0, acc, res);
 }
 
@@ -200,11 +211,12 @@ __device__ __forceinline__ int dsq_requant_store32(const DsqConvArgs &a, int m, 
 // Four consecutive channels o0..o0+3 of one pixel through the general formulas
 // (any l_a, any border): accumulators -> fp32 results -> the next layer's
 // codes, one per byte; adds the codes to `sum`.  o0 < Cop: the side tables cover it.
+template <bool AT_ONCE = true>
 __device__ __forceinline__ uint32_t dsq_requant_quarter(const DsqConvArgs &a, const DsqPixel &px, int o0, v4i acc,
                                                         float delta_a, float delta_n, int top_n, int &sum)
 {
     float y[4], sc[4], sh[4];
-    dsq_out4(a, px, o0, acc, delta_a, y);
+    dsq_out4<AT_ONCE>(a, px, o0, acc, delta_a, y);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const bool in = o0 + j < a.C_out;

@@ -186,7 +186,7 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, i
             }
             const int top_n = (1 << a.rq_bits) - 1;
             int codes = 0;
-            exch[q * 64 + lane] = dsq_requant_quarter(a, px, ct * 32 + 8 * q + 4 * h, sum, a.delta_a,
+            exch[q * 64 + lane] = dsq_requant_quarter<CONT == 4 || LONG>(a, px, ct * 32 + 8 * q + 4 * h, sum, a.delta_a,
                                                       dsq_delta(a.rq_l, a.rq_u, top_n), top_n, codes);
             exch[(4 + q) * 64 + lane] = (uint32_t)codes;
         }
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, i
             sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
         }
         const DsqPixel px = dsq_pixel_info(a, m, M);
-        dsq_store4(a, px, m, ct * 32 + 8 * q + 4 * h, sum, a.delta_a);
+        dsq_store4<CONT == 4 || LONG>(a, px, m, ct * 32 + 8 * q + 4 * h, sum, a.delta_a);
     }
 }
 

@@ -161,7 +161,13 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_e
         }
         if (MODE != SPLIT_CODES) {
             float y[4];
-            dsq_out4_of<MODE == SPLIT_LA>(a, px, sum, a.delta_a, dw, lw, sw, y);
+            const float dwv[4] = {dw.x, dw.y, dw.z, dw.w}, lwv[4] = {lw.x, lw.y, lw.z, lw.w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                double v = dsq_terms(px, sum[j], a.delta_a, dwv[j], lwv[j]);
+                if (MODE == SPLIT_LA) v += dsq_terms_la(a, px, dwv[j], lwv[j], sw[j]);
+                y[j] = (float)v;
+            }
             dsq_store4_of(a, px, m, o0, sum, y);
         } else {
             const int top_n = (1 << a.rq_bits) - 1;

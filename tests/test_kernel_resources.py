@@ -70,6 +70,18 @@ def test_split_k_workgroups_share_a_cu():
     assert short and all(v <= 128 for _, v in short), short
 
 
+def test_general_epilogue_leaves_the_waves_per_simd():
+    """Kernels that form their results through the per-lane functions of conv_epilogue.h: four 2-bit workgroups of the
+    split-K kernel share a compute unit up to 64 registers (as many as its LDS allows), and the simple kernel
+    runs five waves per SIMD up to 96."""
+    asm = _device_asm(os.path.join(CSRC, "conv_fc.hip"))
+    short = re.findall(r"\.name:\s+\S*conv_fc_kernelILi2ELb0E\S*.*?\.vgpr_count:\s+(\d+)", asm, re.S)
+    assert len(short) == 1 and int(short[0]) <= 64, short
+    asm = _device_asm(os.path.join(CSRC, "conv_simple.hip"))
+    simple = re.findall(r"\.name:\s+\S*conv_simple_kernel\S*.*?\.vgpr_count:\s+(\d+)", asm, re.S)
+    assert len(simple) == 3 and all(int(v) <= 96 for v in simple), simple
+
+
 def test_two_backward_workgroups_share_a_cu():
     """The backward training quantizer's workgroups are 16 waves and large tensors launch two per compute unit:
     both are resident up to 64 registers."""
