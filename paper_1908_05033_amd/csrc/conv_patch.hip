@@ -169,9 +169,14 @@ int pick_tile(const DsqConvArgs &a)
     // otherwise the 128x64 tile
     const int c_pad = ((a.C_out + 127) / 128) * 128;
     // (a 1x1 layer with at most 64 input channels is one matrix instruction deep:
-    // wasted channels cost nothing there, fewer and wider output tiles still pay;
-    // not in chained mode, whose epilogue quantizes the wasted channels too)
-    const int waste_limit = (a.R == 1 && a.Cp <= 64 && !a.rq) ? 2 : 4;
+    // wasted channels cost nothing there, fewer and wider output tiles still pay)
+    // Chained layers gain more from fewer tiles: each adds to every pixel's sum, and one that holds all channels
+    // stores it, without a clearing launch.  us, 256x64 or 128x64 tile / 128x128, 4 bits: 24 -> 80 1x1 at 56x56 x 64 30.3 / 17.9,
+    // 256 -> 80 at 28x28 x 32 9.9 / 7.5, 64 -> 80 3x3 at 56x56 x 64 27.2 / 24.7, 64 -> 144 1x1 at 56x56 x 64 39.5 / 32.3,
+    // 100 -> 260 60.8 / 49.0; but 256 -> 144 1x1 at 28x28 x 32 11.5 / 11.7, and 3x3 layers of more than 128 channels
+    // pay for every wasted one: 64 -> 144 at 56x56 x 64 35.5 / 42.8.
+    const bool wide = a.rq ? a.C_out <= 128 || (a.R == 1 && a.Cp <= 128) : a.R == 1 && a.Cp <= 64;
+    const int waste_limit = wide ? 2 : 4;
     if (a.C_out > 64 && waste_limit * (c_pad - a.C_out) <= c_pad && blocks(kMedium) >= (a.R == 1 ? 320 : 192)) {
         // 2-bit layers (FP4 path: the 256x128 tile fits its registers): take that
         // tile when the 128x128 one leaves a nearly empty last round of workgroups

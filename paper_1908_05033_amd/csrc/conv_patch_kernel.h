@@ -90,8 +90,8 @@ __device__ __forceinline__ void lds_barrier()
 // quantizer's own roundings (DsqConvArgs); 1 (never) for channels whose magnitudes
 // would let an intermediate of either sequence overflow, or lose bits to denormals, and
 // when the host disabled the form: those keep harmless constants, so that T stays
-// finite.  Channels past C_out get constants that give code 0 safely (their bytes are
-// blanked anyway).
+// finite.  Channels past C_out get constants that give code 0 safely (T = 0, half a step from the nearest
+// half-integer; their bytes are blanked anyway), and a distance of 0: the workgroup's is the largest of its channels'.
 //
 // A wave computes the constants of 64 channels before the main loop, in binary32 but for A
 // and s: rho32 is the quotient corrected by its remainder, r the remainder of that,
@@ -122,7 +122,7 @@ __device__ __forceinline__ float chained_channel_constants(const DsqConvArgs &a,
                     ymax * __builtin_fabsf(sc) < 0x1p100f && __builtin_fabsf(sh) < 0x1p100f &&
                     (__builtin_fabsf(sc) + 1.0f) * inv_dn < 0x1p100f && __builtin_fabsf(A) < 0x1p60f &&
                     __builtin_fabsf(rho) < 0x1p20f && E < 0.5f;
-    if (!real) return 0.25f;
+    if (!real) return 0.0f;
     if (!ok) return 1.0f;
     k = make_float4(A * unit, rho / unit, A * rest, s);
     return E;

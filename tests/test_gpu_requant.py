@@ -392,6 +392,36 @@ def test_weight_steps_up_to_the_largest(bits, Ci, kernel):
     assert not wrong and np.array_equal(got[1][1], got[0][1]), wrong
 
 
+@pytest.mark.parametrize("geom,one_tile", [((16, 64, 56, 56, 65, 1, 1, 0), True), ((16, 24, 56, 57, 80, 1, 1, 0), True), ((8, 64, 56, 56, 72, 3, 1, 1), True),
+                                           ((8, 40, 57, 56, 97, 3, 1, 1), True), ((16, 64, 56, 56, 130, 1, 1, 0), False),
+                                           ((16, 100, 56, 56, 260, 1, 1, 0), False), ((8, 64, 56, 56, 144, 3, 1, 1), False)])
+@pytest.mark.parametrize("bits", [2, 4])
+def test_last_tile_of_channels_not_full(geom, one_tile, bits):
+    """Layers whose last channel tile is partly padding: up to 128 channels run in one tile, whose workgroups
+    store the pixel sums whatever they hold; codes and sums equal the simple kernel's."""
+    N, Ci, H, W, Co, R, stride, pad = geom
+    g = torch.Generator(device="cuda").manual_seed(sum(geom) + bits)
+    buf = B.alloc_layer(N, Ci, H, W, Co, R, R, stride, pad, bits)
+    x = torch.randn((N, H, W, Ci), generator=g, device="cuda").abs_()
+    w = torch.randn((Co, Ci, R, R), generator=g, device="cuda") * (2.0 / (Ci * R * R)) ** 0.5
+    flat = w.reshape(Co, -1)
+    B.dsq_quantize_act(x, B.DSQ_NHWC, N, Ci, H, W, 0.0, 2.8, bits, buf.act_packed, buf.pix_code_sum)
+    B.dsq_pack_weights(w, flat.amin(1).contiguous(), flat.amax(1).contiguous(), None, Co, Ci, R, R, bits, buf.w_packed, buf.w_aux)
+    scale, shift = torch.rand(Co, generator=g, device="cuda") + 0.5, torch.randn(Co, generator=g, device="cuda") * 0.3
+    buf.desc.flags = 0
+    plan = B.dsq_conv2d_plan(buf.desc, chained=True)
+    assert plan.startswith("patch kernel") and (not one_tile or "x128 (pixels" in plan), plan
+    got = []
+    for kernel in (1, 0):
+        buf.desc.flags = B.DSQ_CONV_KERNEL(kernel)
+        codes = torch.full((B.dsq_act_packed_bytes(N, H, W, Co, 4),), 0x5A, dtype=torch.uint8, device="cuda")
+        sums = torch.full((N * H * W,), -3, dtype=torch.int32, device="cuda")
+        B.dsq_conv2d_requant(buf.desc, buf.act_packed, buf.pix_code_sum, 0.0, 2.8, buf.w_packed, buf.w_aux, scale, shift, True,
+                             0.0, 3.0, 4, codes, sums)
+        got.append((codes, sums))
+    assert torch.equal(got[1][0], got[0][0]) and torch.equal(got[1][1], got[0][1])
+
+
 def test_depth_beyond_the_binary32_integers():
     """A 4-bit layer deep enough that an accumulator may pass 2^24 (225 * 9 * C_in): the
     tuned kernels' short evaluation would convert it inexactly and is switched off by
