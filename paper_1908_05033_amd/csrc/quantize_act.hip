@@ -436,7 +436,7 @@ __global__ __launch_bounds__(256) void quantize_act_dense3_nchw_kernel(const flo
     pix_sum[p] = sum;
 }
 
-// Rows of 4 to 64 lanes, units in flight, and steps per wave.  All figures in us, 4 bits, tensor in the
+// Rows of 4 to 64 lanes, units in flight, and steps per wave.  All figures in us, 4 bits unless stated, tensor in the
 // last-level cache where it fits.
 template <int CONT>
 void launch_rows(const float *x, uint32_t *codes, int32_t *pix_sum, int total_pixels, int C, int DP, const DsqQuant &q,
@@ -445,29 +445,51 @@ void launch_rows(const float *x, uint32_t *codes, int32_t *pix_sum, int total_pi
     const int QP = C / 4, units = dsq_round_up(C, 64) / 4;
     // 64 lanes where a pixel has as many units and there are few of them: 4 / 8 / 16 / 64 lanes take 11.4 / 6.9
     // / 4.6 / 3.1 for 512 channels at 7x7 x 64, but at 64 channels, 56x56 x 64, 12.6 / 11.0 / 11.1 / 24.9 (with
-    // more loads than this the 16-lane rows are level or ahead).  Below 16 units a row of 16 is mostly
+    // more loads than this the 16-lane rows are level or ahead).  However many there are where a 16-lane row would
+    // walk a pixel in twelve steps: 16 / 64 lanes 768 channels at 14x14 x 64 9.8 / 7.9, 1024 12.4 / 10.6, 1536 17.1 / 14.5.
+    // And 48 units where the lanes fit the chip at once: 192 channels at 28x28 x 1 2.89 / 2.43, x 4 2.94 / 2.64.
+    // Below 16 units a row of 16 is mostly
     // idle: 16 channels at 56x56 x 64 4.9 / 6.3 / 8.4, 40 channels 8.8 / 9.1 / 9.1; 80 channels at 73x73 x
-    // 16 7.4 / 6.8 / 7.8.  (From 2^24 channels on the offsets of a row of pixels would not fit 32 bits.)
-    const long long loads = (long long)total_pixels * units / 64;
-    const int G = C >= (1 << 24) || (units >= 64 && loads < 32768) ? 64
-                : QP <= 12 ? (CONT == 3 ? 8 : 4) : QP < 24 && QP != 16 ? 8 : 16;
+    // 16 7.4 / 6.8 / 7.8.  But a small tensor takes as long as a lane has steps: 4 / 8 lanes 32 channels at 28x28 x 1
+    // 2.57 / 2.39, x 8 2.62 / 2.43, 56x56 x 16 3.15 / 3.26; 48 at 28x28 x 1 4 / 8 / 16 2.79 / 2.56 / 2.4.  (From 2^24
+    // channels on the offsets of a row of pixels would not fit 32 bits.)
+    const long long loads = (long long)total_pixels * units / 64, all_units = (long long)total_pixels * QP;
+    const bool small = all_units < 128 * 1024;
+    const int G = C >= (1 << 24) || (units >= 64 && loads < 32768) || (units >= 48 && loads < 4096) || units >= 192 ? 64
+                : QP <= (small ? 4 : 12) && CONT != 3 ? 4 : QP == 16 || QP >= 24 || (small && QP > 8) ? 16 : 8;
     // Tensors of 192 MB and more (three quarters of the last-level cache) are read with
     // non-temporal loads, in long waves with four in flight: 224x224 x 64 channels x 32 78 us, 88 with one in
     // flight and two steps; 112x112 x 128 x 32 41, with one in flight 44.  Smaller tensors: two loads a wave
     // (112x112 x 64 x 32 18.2, with one 19.3, with eight 19.1), one where that leaves the chip short of waves.
-    const bool nt = (long long)total_pixels * QP >= 12LL * 1024 * 1024;
+    const bool nt = all_units >= 12LL * 1024 * 1024;
     const int pps = 64 / G, J = G >= 16 ? (units + G - 1) / G : (QP + G - 1) / G;
-    int steps = (nt ? 8 : 2) / J;
-    while (steps > 1 && (long long)total_pixels / (pps * steps) < 8192) steps >>= 1;
+    // Large tensors whose pixels are three units a lane: all three in flight together, two pixels a wave and row.  us, one
+    // (four, non-temporal) in flight / three: 144 channels at 56x56 x 64 24.1 / 22.2, 2 bits 22.7 / 21.6 (58 MB of them 13.5 /
+    // 13.0, but 43 MB 10.5 / 11.0), x 128 57.2 / 51.9, 2 bits 54.2 / 49.8, 192 channels x 128 65.5 / 60.5; rows of 8, 72
+    // channels x 64 16.2 / 13.8, 2 bits 14.5 / 13.3, 80 16.1 / 14.2, 2 bits 14.9 / 13.7.  Not where the third
+    // unit is one for nearly all lanes: 176 channels x 64 2 bits 24.5 / 24.8, 192 25.2 / 25.6.
+    // Rows of 4 lanes with more than one unit a lane: four, some of them twice.  32 channels at 56x56 x 128 13.1 /
+    // 12.2, 2 bits 12.5 / 11.1, 48 18.1 / 15.4, 2 bits 16.8 / 14.9, but at half the pixels 6.1 / 7.2 (32).
+    const bool large = all_units >= 3LL * 1024 * 1024;
+    const bool three = large && J == 3 && (G == 8 || (G == 16 && (nt || QP <= 40))), four = large && G == 4 && J > 1;
+    int steps = three ? 2 : four ? 1 : (nt ? 8 : 2) / J;
+    while (!three && steps > 1 && (long long)total_pixels / (pps * steps) < 8192) steps >>= 1;
     if (steps < 1) steps = 1;
     const long long waves = ((long long)total_pixels + pps * steps - 1) / (pps * steps);
     const dim3 grid((unsigned)((waves + 3) / 4));
 #define DSQ_ROWS(G, U, NT) quantize_act_rows_kernel<CONT, G, U, NT><<<grid, 256, 0, stream>>>(x, codes, pix_sum, total_pixels, C, DP, steps, q)
-    if (G == 64) DSQ_ROWS(64, 1, false);
+    if (G == 64 && nt) DSQ_ROWS(64, 4, true);
+    else if (G == 64) DSQ_ROWS(64, 1, false);
+    else if (G == 8 && three) DSQ_ROWS(8, 3, false);
     else if (G == 8) DSQ_ROWS(8, 1, false);
+    else if (G == 16 && three && nt) DSQ_ROWS(16, 3, true);
+    else if (G == 16 && three) DSQ_ROWS(16, 3, false);
     else if (G == 16 && nt) DSQ_ROWS(16, 4, true);
     else if (G == 16) DSQ_ROWS(16, 1, false);
-    else if constexpr (CONT != 3) DSQ_ROWS(4, 1, false);
+    else if constexpr (CONT != 3) {
+        if (four) DSQ_ROWS(4, 4, false);
+        else DSQ_ROWS(4, 1, false);
+    }
 #undef DSQ_ROWS
 }
 
@@ -496,15 +518,17 @@ hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C
         return hipGetLastError();
     }
     if (C % 4 == 0) {
-        // A block per pixel where pixels are few and deep (us, 4 bits, a wave of the rows kernel per pixel / blocks
-        // of 256 / of 1024 threads): 4096 channels x 1 5.7 / 2.5 / 2.4, x 64 6.7 / 2.8 / 2.8, x 600 6.6 / 3.6 / 4.0;
-        // 1024 channels at 7x7 x 64 4.1 / 4.1 / 8.4.  1024 threads from 8192 (2 bits: 16384) channels on, up to 512
-        // pixels.
+        // A block per pixel where pixels are deep (us, 4 bits, a wave of the rows kernel per pixel / blocks
+        // of 256 / of 1024 threads): 4096 channels x 1 5.7 / 2.5 / 2.4, x 64 6.7 / 2.8 / 2.8, x 600 6.6 / 3.6 / 4.0, x 3136
+        // 12.2 / 10.6 / 11.6, x 12544 35 / 34.6 / 36; 2048 x 6272 10.4 / 10.5 / 17.7 (16 lanes of the rows kernel 19.2), x 25088
+        // 34 / 33.9 / 61.  1024 threads from 8192 (2 bits: 16384) channels on, of which 512 blocks run at a time: 8192 x 784
+        // 4.8 / 5.4 (256 / 1024 threads), x 4096 24.2 / 23.9 / 22.1, x 12544 85 / 86 / 81.  Few pixels from 1024 channels on: 1024 x 49 3.16 / 2.63, x 784 3.25 / 2.86, x 1568 3.37 / 3.20, x 3136
+        // 3.96 / 4.10 / 8.4.
 #define DSQ_DEEP(T) do { if (cont == 4) quantize_act_deep_kernel<4, T><<<total_pixels, T, 0, stream>>>(x, cw, pix_sum, C, DP, q); \
             else quantize_act_deep_kernel<2, T><<<total_pixels, T, 0, stream>>>(x, cw, pix_sum, C, DP, q); } while (0)
-        if (DP >= 1024 && total_pixels <= 512) {
+        if (DP >= 1024 && (total_pixels <= 512 || total_pixels >= 2048)) {
             DSQ_DEEP(1024);
-        } else if (C >= 2048 && total_pixels <= 4096) {
+        } else if (C >= 2048 || (C >= 1024 && total_pixels <= 2048)) {
             DSQ_DEEP(256);
         } else if (cont == 4) {
             launch_rows<4>(x, cw, pix_sum, total_pixels, C, DP, q, stream);

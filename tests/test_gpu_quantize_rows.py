@@ -75,3 +75,32 @@ def test_several_steps_a_wave(shape, bits):
     ref = pack_codes_reference(_padded(want).reshape(-1, 64), bits)
     assert torch.equal(codes, ref.reshape(-1))
     assert torch.equal(sums, want.sum(dim=1, dtype=torch.int32))
+
+
+# What the size alone decides: rows of 4 and 8 lanes past the small tensors, four and three units in flight, with
+# and without non-temporal loads, 64 lanes for many deep pixels, and blocks of 256 and 1024 threads per pixel
+LARGE = [(40003, 20, 4), (13109, 44, 2), (10007, 72, 4), (700001, 20, 4), (300007, 48, 2), (180001, 72, 4), (150001, 92, 2),
+         (90001, 144, 4), (80011, 160, 2), (350003, 144, 4), (262147, 192, 2), (12547, 708, 4), (9001, 1000, 2), (65539, 768, 4),
+         (2048, 1024, 4), (2049, 1024, 4), (6001, 2048, 2), (700, 8192, 4), (2050, 8192, 4)]
+
+
+@pytest.mark.parametrize("pixels,C,bits", LARGE)
+def test_rows_and_blocks_of_larger_tensors(pixels, C, bits):
+    test_several_steps_a_wave((1, 1, pixels, C), bits)
+
+
+@pytest.mark.parametrize("pixels,C", [(10007, 72), (150001, 92), (90001, 144), (350003, 144), (65539, 768)])
+def test_dense_rows_of_larger_tensors(pixels, C):
+    from test_gpu_dense3 import _pack_dense3_torch
+    l, u, bits = 0.0, 2.5, 3
+    g = torch.Generator(device="cuda").manual_seed(inputs.BASE_SEED + C)
+    x = torch.randn((pixels, C), generator=g, device="cuda").abs_()
+    codes = torch.full((B.dsq_act_packed_bytes_ex(1, 1, pixels, C, bits, B.DSQ_PACK_DENSE3),), 0xAB, dtype=torch.uint8, device="cuda")
+    sums = torch.full((pixels,), -7, dtype=torch.int32, device="cuda")
+    B.dsq_quantize_act_ex(x, B.DSQ_NHWC, 1, C, 1, pixels, l, u, bits, B.DSQ_PACK_DENSE3, codes, sums)
+    want = torch.from_numpy(oracle.quantize(x.cpu().numpy(), l, u, bits)).cuda()
+    blocks = _padded(want).reshape(-1, 64)
+    got = codes.view(torch.int32).reshape(-1, 6)
+    for k in range(0, len(blocks), 1 << 18):
+        assert torch.equal(got[k:k + (1 << 18)], _pack_dense3_torch(blocks[k:k + (1 << 18)])), k
+    assert torch.equal(sums, want.sum(dim=1, dtype=torch.int32))
