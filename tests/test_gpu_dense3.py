@@ -223,8 +223,7 @@ def _pack_dense3_torch(oc):
 @pytest.mark.parametrize("l,u", [(0.0, 6.0), (-0.7301, 1.9102)])
 def test_every_float_bit_pattern_through_the_dense_quantizer(l, u, layout):
     """All 2^32 binary32 patterns against the oracle's recipe, dense words and pixel sums bit for bit: the
-    large-tensor NHWC kernel (step-function form of the quantizer, eight lanes per unit) and the NCHW kernel
-    (the recipe itself)."""
+    NHWC kernel whose rows of lanes own a pixel (eight lanes per unit) and the NCHW kernel."""
     from concurrent.futures import ThreadPoolExecutor
     l, u = float(np.float32(l)), float(np.float32(u))
     CH = 1 << 27

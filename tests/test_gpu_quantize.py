@@ -157,13 +157,14 @@ def test_weight_codes_at_cfg2_size():
 
 @pytest.mark.parametrize("layout", [B.DSQ_NHWC, B.DSQ_NCHW])
 @pytest.mark.parametrize("bits,l,u", [(4, 0.0, 2.3217), (2, -0.7301, 1.9102), (3, 0.0, 6.0), (1, -1.0, 1.0),
-                                      (4, 0.0, 1.5e-30), (4, -4e29, 5e29), (4, 1000.0, 1000.5)])
+                                      (4, 0.0, 1.5e-30), (4, -4e29, 5e29), (4, 1000.0, 1000.5), (4, 1e6, 1e6 + 1)])
 def test_every_float_bit_pattern_gets_the_oracle_code(bits, l, u, layout):
     """All 2^32 binary32 patterns (NaNs of both kinds, infinities, denormals) against
-    the oracle's division recipe, packed codes and pixel sums bit for bit: through
-    the large-tensor NHWC kernel and the NCHW kernel, whose quantizer is the
-    step-function form, and, in slices small enough for it, through the NHWC kernel
-    of small tensors, which evaluates the recipe itself on the device."""
+    the oracle's division recipe, packed codes and pixel sums bit for bit, through every
+    kernel: NHWC pixels of 64 channels (rows of lanes), of 63 (a thread per word), of 2048 and
+    of 16384 (a block of 256 and of 1024 threads per pixel), and NCHW.  Steps of 1e-31 and
+    6e28 run the recipe with its division; in the last range, so far from 0 that the
+    short evaluation's error bound passes 1/4, every value does."""
     from concurrent.futures import ThreadPoolExecutor
     l, u = float(np.float32(l)), float(np.float32(u))
     CH = 1 << 27                                 # patterns per launch: 2^21 pixels of 64 channels
@@ -201,14 +202,26 @@ def test_every_float_bit_pattern_gets_the_oracle_code(bits, l, u, layout):
                                      "(first differing pixel %d, codes equal: %s, sums equal: %s)"
                                      % (bits, l, u, start, where, same, sums_same))
             if layout == B.DSQ_NHWC:
-                small, step = torch.empty_like(codes), 1 << 20          # 2^14 pixels a call
-                small_pix = torch.empty_like(pix)
-                for k in range(0, CH, step):
-                    p0, p1 = k // C, (k + step) // C
-                    B.dsq_quantize_act(x[k:k + step], layout, 1, C, 16, 1024, l, u, bits, small.reshape(P, -1)[p0:p1].reshape(-1),
-                                       small_pix[p0:p1])
-                torch.cuda.synchronize()
-                assert torch.equal(small, codes) and torch.equal(small_pix, pix), "small tensors: chunk at 0x%08x" % start
+                # deep pixels: a pixel's 64-channel blocks follow one another, so the words are the same
+                for deep, most in ((2048, 4096), (16384, 512)):
+                    again, sums = torch.full_like(codes, 0xAB), torch.full((CH // deep,), -7, dtype=torch.int32, device="cuda")
+                    step = deep * most
+                    for k in range(0, CH, step):
+                        B.dsq_quantize_act(x[k:k + step], layout, 1, deep, 1, most, l, u, bits,
+                                           again.reshape(P, -1)[k // 64:(k + step) // 64].reshape(-1), sums[k // deep:(k + step) // deep])
+                    torch.cuda.synchronize()
+                    assert torch.equal(again, codes) and torch.equal(sums, pix.reshape(-1, deep // 64).sum(dim=1, dtype=torch.int32)), \
+                        "%d channels: chunk at 0x%08x" % (deep, start)
+                # 63 channels; the last pixel again for the patterns that a whole number of pixels leaves
+                flat, odd = oc.reshape(-1), CH // 63
+                for first, n in ((0, odd), (CH - 63, 1)):
+                    again = torch.full((B.dsq_act_packed_bytes(1, 1, n, 63, bits),), 0xAB, dtype=torch.uint8, device="cuda")
+                    sums = torch.full((n,), -7, dtype=torch.int32, device="cuda")
+                    B.dsq_quantize_act(x[first:first + 63 * n].clone(), layout, 1, 63, 1, n, l, u, bits, again, sums)
+                    o63 = flat[first:first + 63 * n].reshape(n, 63)
+                    torch.cuda.synchronize()
+                    same = torch.equal(again.reshape(n, -1), pack_codes_reference(torch.nn.functional.pad(o63, (0, 1)), bits))
+                    assert same and torch.equal(sums, o63.sum(dim=1, dtype=torch.int32)), "63 channels: chunk at 0x%08x" % start
             del x, oc, ref
 
 

@@ -104,8 +104,8 @@ SMALL = [  # N, C_in, H, W, C_out, R, stride, pad
 @pytest.mark.parametrize("geom", SMALL)
 def test_small_geometries(geom, bits, bits_n, l_a, relu, kernel):
     """l_a = 0 takes the tuned kernel's own chained epilogue; l_a != 0 (terms that
-    depend on which taps lie inside the image) is served by the simple kernel,
-    and the tuned kernel, when forced, must say so instead of computing."""
+    depend on which taps lie inside the image) is served by the simple kernel (and the split-K
+    kernel for few output tiles), and the tuned kernel, when forced, must say so instead of computing."""
     N, Ci, H, W, Co, R, stride, pad = geom
     layer, inp = inputs.small_random_case(sum(geom) + bits, N, Ci, H, W, Co, R, stride, pad, bits,
                                           l_a=l_a, u_a=2.1)
@@ -464,8 +464,8 @@ def _oracle_threshold(l, u, bits, j):
 @pytest.mark.parametrize("l_n,u_n,bits_n", [(0.0, 3.0, 4), (-0.35, 2.45, 4), (0.0, 1.7, 3), (-1.0, 1.0, 2),
                                             (0.0, 6.0, 2), (-1.0, 1.0, 1), (1000.0, 1000.5, 4)])
 def test_every_float_around_every_quantizer_threshold(l_n, u_n, bits_n, kernel):
-    """The tuned kernels evaluate the next layer's quantizer as a step function
-    (thresholds found on the host); the simple kernel and the oracle divide.
+    """The patch kernel decides the next layer's code in code units, (z - l)/Delta rounded, with an
+    error bound, and divides only where that cannot tell; the simple kernel and the oracle divide.
     With all-zero weight codes and l_w = 0 the layer output is exactly 0, so
     z = shift[o]: every float within three ulps of every threshold, and the
     special values, go through the chained epilogue unchanged."""
@@ -493,8 +493,8 @@ def test_every_float_around_every_quantizer_threshold(l_n, u_n, bits_n, kernel):
 def test_every_float_bit_pattern_through_the_chained_quantizer(l_n, u_n, bits_n, relu, kernel):
     """All 2^32 binary32 patterns as the value z that reaches the next layer's
     quantizer (zero weights make the layer output +0, so z = 0 * scale + shift[o]
-    = shift[o]), 2^20 output channels per launch, against the oracle: the tuned
-    kernel's step-function form and the simple kernel's division, with and
+    = shift[o]), 2^20 output channels per launch, against the oracle: the patch
+    kernel's code units and the simple kernel's division, with and
     without the ReLU, packed codes and pixel sums bit for bit."""
     from concurrent.futures import ThreadPoolExecutor
     l_n, u_n = float(np.float32(l_n)), float(np.float32(u_n))
