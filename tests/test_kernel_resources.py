@@ -36,7 +36,7 @@ def _device_asm(src):
 @pytest.mark.parametrize("source", ["conv_patch_c4r3.hip", "conv_patch_c4r1.hip", "conv_patch_c2r3.hip", "conv_patch_c2r1.hip",
                                     "conv_patch_c3r3.hip", "conv_patch_c3r1.hip",
                                     "conv_simple.hip", "conv_fc.hip", "conv_wq.hip", "quantize_act.hip",
-                                    "soft_quantize.hip"])
+                                    "conv_split.hip", "soft_quantize.hip"])
 def test_kernels_stay_inside_their_register_budget(source):
     asm = _device_asm(os.path.join(CSRC, source))
     kernels = re.findall(r"\.name:\s+(\S+).*?\.vgpr_count:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)", asm, re.S)
@@ -80,6 +80,16 @@ def test_general_epilogue_leaves_the_waves_per_simd():
     asm = _device_asm(os.path.join(CSRC, "conv_simple.hip"))
     simple = re.findall(r"\.name:\s+\S*conv_simple_kernel\S*.*?\.vgpr_count:\s+(\d+)", asm, re.S)
     assert len(simple) == 3 and all(int(v) <= 96 for v in simple), simple
+
+
+def test_few_tile_workgroups_share_a_cu():
+    """Split-K kernel for few output tiles: two workgroups of eight waves share a CU up to 128 registers.  Its variants
+    with the tap sums of l_a != 0 and with nine steps of 4 bits in flight may take twice as many."""
+    asm = _device_asm(os.path.join(CSRC, "conv_split.hip"))
+    kernels = re.findall(r"\.name:\s+\S*conv_split_kernelILi(\d)ELi(\d)ELi(\d)E\S*.*?\.vgpr_count:\s+(\d+)", asm, re.S)
+    assert len(kernels) == 18
+    over = [k for k in kernels if int(k[3]) > (256 if k[2] == "1" or k[:2] == ("4", "9") else 128)]
+    assert not over, over
 
 
 def test_small_tiles_of_strided_layers_run_three_waves_per_simd():
