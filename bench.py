@@ -199,7 +199,7 @@ def main():
             "conv_kernel": plan,
         })
         add("dsq_conv2d, " + plan.split(";")[0], L.count, tc, ops, st.conv_alg_bytes(), L.name)
-        add("dsq_quantize_act (lane-contiguous NHWC kernel)", L.count, tq, 0.0, st.quant_alg_bytes(), L.name)
+        add("dsq_quantize_act (NHWC kernel, rows of lanes per pixel)", L.count, tq, 0.0, st.quant_alg_bytes(), L.name)
     dom_key, dom = max(groups.items(), key=lambda kv: kv[1]["t"])
     peak = LB.matrix_peak_tops(bits)
     dom_bound = "mfma" if dom["ops"] / dom["bytes"] >= peak * 1e12 / (HBM_PEAK_GBS * 1e9) else "hbm"

@@ -360,8 +360,8 @@ dsq_status dsq_soft_quantize_bwd(const float *x, const float *grad_y, size_t n,
  * Writes into `text` (host memory, text_bytes bytes, NUL-terminated, truncated
  * if need be) a one-line description of the kernel and launch configuration
  * that dsq_conv2d (chained = 0) or dsq_conv2d_requant (chained != 0) would use
- * for this descriptor (geometry, bits, flags) and this l_a (a non-zero l_a sends
- * chained layers to the simple kernel).  Nothing is launched.  For benchmark
+ * for this descriptor (geometry, bits, flags) and this l_a (with a non-zero
+ * l_a chained layers of few output tiles run on the split-K kernel, others on the simple one).  Nothing is launched.  For benchmark
  * reports and tests; returns the status the call itself would return for the
  * descriptor (DSQ_ERR_UNSUPPORTED if a forced kernel cannot take it).
  */

@@ -13,8 +13,8 @@ namespace {
 bool bits_ok(int bits) { return bits >= 1 && bits <= 4; }
 bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 // A clip range must be finite, ordered, and of a width whose step Delta = (u - l) / (2^b - 1)
-// and the reciprocal of it are normal binary32 numbers with room to spare: the
-// step-function kernels start from the guess (v - l) * (1 / Delta).
+// and the reciprocal of it are normal binary32 numbers with room to spare: the quantizer
+// and the chained epilogue multiply by 1 / Delta.
 bool range_ok(float l, float u)
 {
     if (!(isfinite(l) && isfinite(u) && l < u)) return false;

@@ -214,7 +214,7 @@ bool choose_plan(const DsqConvArgs &a, int force_tile, int &which, int &ks, Patc
     which = force_tile >= 0 ? force_tile : pick_tile(a);
     // chained mode: the 256x128 tile has a variant for 2-bit containers only (at 3 and
     // 4 bits it does not fit the registers), and layers with l_a != 0 (border-dependent
-    // terms) go to the simple kernel
+    // terms) go to the split-K kernel for few output tiles or the simple kernel
     if (a.rq && ((which == TILE_LARGE && a.cont != 2) || a.l_a != 0.0f)) return false;
     const TileCfg &tc = tile_cfg(which);
     const int BP = 32 * tc.PF * tc.WP, BC = 32 * tc.CT * tc.WC;

@@ -722,8 +722,8 @@ __global__ __launch_bounds__(256 * KS) __attribute__((amdgpu_waves_per_eu(OCC, O
         int psum[PF];
 #pragma unroll
         for (int f = 0; f < PF; ++f) psum[f] = 0;
-        // (l_a = 0 here: the host sends chained layers with l_a != 0 to the simple
-        // kernel.  Constants are fetched four channels at a time, right before
+        // (l_a = 0 here: the host sends chained layers with l_a != 0 to the split-K kernel for
+        // few output tiles or the simple kernel.  Constants are fetched four channels at a time, right before
         // their use, to keep the register footprint of this path small.  Lanes of tile
         // pixels past the end compute on patch pixel 0 and are never stored; at worst
         // they send their wave through the exact sequence once more.)

@@ -37,32 +37,15 @@ __device__ __forceinline__ uint32_t dsq_bytes4(int c0, int c1, int c2, int c3)
     return (uint32_t)c0 | ((uint32_t)c1 << 8) | ((uint32_t)c2 << 16) | ((uint32_t)c3 << 24);
 }
 
-// 4-bit container: 8 consecutive channels per word, byte j = c[j] | c[j+4]<<4.
-__device__ __forceinline__ uint32_t dsq_pack8x4(uint32_t lo_bytes, uint32_t hi_bytes)
-{
-    return lo_bytes | (hi_bytes << 4);
-}
-
-// Unpack one 4-bit word into channels 0..3 (lo) and 4..7 (hi), one per byte.
+// 4-bit container: 8 consecutive channels per word, byte j = c[j] | c[j+4] << 4.  Unpacks one
+// word into channels 0..3 (lo) and 4..7 (hi), one per byte.
 __device__ __forceinline__ void dsq_unpack4(uint32_t w, uint32_t &lo, uint32_t &hi)
 {
     lo = w & 0x0F0F0F0Fu;
     hi = (w >> 4) & 0x0F0F0F0Fu;
 }
 
-// Unpack one 2-bit word (16 channels) into four words of four int8 each.
-__device__ __forceinline__ v4i dsq_unpack2(uint32_t w)
-{
-    v4i r;
-    r.x = (int)(w & 0x03030303u);
-    r.y = (int)((w >> 2) & 0x03030303u);
-    r.z = (int)((w >> 4) & 0x03030303u);
-    r.w = (int)((w >> 6) & 0x03030303u);
-    return r;
-}
-
-// 16 consecutive channels of one lane's MFMA operand from their packed form:
-// two words at 4-bit, one word at 2-bit.
+// 16 consecutive channels of one lane's MFMA operand from two words of the 4-bit container.
 __device__ __forceinline__ v4i dsq_unpack16_c4(v2i p)
 {
     v4i r;
