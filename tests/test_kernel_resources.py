@@ -96,7 +96,7 @@ def test_small_tiles_of_strided_layers_run_three_waves_per_simd():
     """The 128x64 tile with eight fetch units per thread and more, one wave group: layers of more workgroups than two
     per compute unit run the variant of which three are resident, up to 168 registers."""
     asm = _device_asm(os.path.join(CSRC, "conv_patch_c4r3.hip"))
-    kernels = re.findall(r"\.name:\s+(\S*conv_patch_kernelILi4ELi3ELi4ELi1ELi1ELi2ELi(?:8|12)ELi3ELi\dELi1E\S*).*?\.vgpr_count:\s+(\d+)",
+    kernels = re.findall(r"\.name:\s+(\S*conv_patch_kernelILi4ELi3ELi4ELi1ELi1ELi2ELi(?:8|12)ELi3ELi3ELi1E\S*).*?\.vgpr_count:\s+(\d+)",
                          asm, re.S)
     assert len(kernels) == 8 and all(int(v) <= 168 for _, v in kernels), kernels
 
