@@ -60,15 +60,20 @@ __device__ __forceinline__ double dsq_terms_la(const DsqConvArgs &a, const DsqPi
     return (la * (double)dw) * (double)sw + (double)(a.C_in * p.ntaps) * (la * (double)lw);
 }
 
+// How a lane comes by the weight code sums of its four channels where l_a is not 0:
+//   SUMS_EACH    channel by channel, right before the use
+//   SUMS_TOTALS  those of full pixels with one load ahead, the tap sums of pixels at a border channel by channel
+//   SUMS_FIRST   all four before the first use
+// Each for the kernels whose registers it suits (us): the split-K kernel for few output tiles has room for all four
+// (20 -> 17 1x1 at 73x73 x 2 chained 9.2 with SUMS_TOTALS, 8.7); the simple kernel goes from 92 to 108 with them, and
+// 64 -> 64 3x3 at 28x28 x 64 from 14.4 to 19.7, chained with l_a != 0 from 32 to 50, while reading the totals ahead gains
+// (24 -> 144 1x1 chained 76 -> 69); the split-K kernel for few pixels, 2 bits, ends at 64, where four workgroups
+// share a compute unit, with neither.
+enum { SUMS_EACH = 0, SUMS_TOTALS = 1, SUMS_FIRST = 2 };
+
 // The binary32 results of one lane: one pixel, four consecutive output channels
-// o0..o0+3 (o0 % 4 == 0, o0 + 3 < Cop).  AT_ONCE: the code sums of full pixels are read together, ahead of their
-// use, not one channel after the other: 24 -> 144 1x1 chained with l_a != 0 76 -> 69 us in the simple kernel.  The
-// short 2-bit form of the split-K kernel for few pixels, whose fourth workgroup of a compute unit ends at 64
-// registers, does without (68 with it: 512 -> 512 chained, 784 tiles, 8.7 -> 9.5 us).  The tap sums of pixels at a border
-// are added up channel by channel, right before their use: those of four channels before the first
-// use took the simple kernel from 92 to 108 registers, 64 -> 64 3x3 at 28x28 x 64 from 14.4 to 19.7 us and, chained
-// with l_a != 0, from 33 to 50.
-template <bool AT_ONCE>
+// o0..o0+3 (o0 % 4 == 0, o0 + 3 < Cop).
+template <int SUMS>
 __device__ __forceinline__ void dsq_out4(const DsqConvArgs &a, const DsqPixel &p, int o0, v4i acc,
                                          float delta_a, float (&res)[4])
 {
@@ -79,20 +84,25 @@ __device__ __forceinline__ void dsq_out4(const DsqConvArgs &a, const DsqPixel &p
     const int accv[4] = {acc.x, acc.y, acc.z, acc.w};
     const int T = a.R * a.R;
     const bool full = p.ntaps == T;
-    v4i total = {0, 0, 0, 0};
-    if (AT_ONCE && a.l_a != 0.0f) total = *reinterpret_cast<const v4i *>(a.sw_total + o0);
+    auto tap_sum = [&](int j) {
+        int sw = 0;
+        for (int t = 0; t < T; ++t)
+            if (p.tapmask >> t & 1) sw += a.sw_tap[(size_t)(o0 + j) * T + t];
+        return sw;
+    };
+    v4i first = {0, 0, 0, 0};
+    if (SUMS == SUMS_TOTALS && a.l_a != 0.0f) first = *reinterpret_cast<const v4i *>(a.sw_total + o0);
+    if (SUMS == SUMS_FIRST && a.l_a != 0.0f) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) first[j] = full ? a.sw_total[o0 + j] : tap_sum(j);
+    }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         double v = dsq_terms(p, accv[j], delta_a, dwv[j], lwv[j]);
         if (a.l_a != 0.0f) {
-            int sw = total[j];
-            if (full) {
-                if (!AT_ONCE) sw = a.sw_total[o0 + j];
-            } else {
-                sw = 0;
-                for (int t = 0; t < T; ++t)
-                    if (p.tapmask >> t & 1) sw += a.sw_tap[(size_t)(o0 + j) * T + t];
-            }
+            int sw = first[j];
+            if (SUMS == SUMS_EACH) sw = full ? a.sw_total[o0 + j] : tap_sum(j);
+            if (SUMS == SUMS_TOTALS && !full) sw = tap_sum(j);
             v += dsq_terms_la(a, p, dwv[j], lwv[j], sw);
         }
         res[j] = (float)v;
@@ -130,13 +140,13 @@ __device__ __forceinline__ void dsq_store4_of(const DsqConvArgs &a, const DsqPix
     }
 }
 
-template <bool AT_ONCE = true>
+template <int SUMS = SUMS_TOTALS>
 __device__ __forceinline__ void dsq_store4(const DsqConvArgs &a, const DsqPixel &p, int m, int o0,
                                            v4i acc, float delta_a)
 {
     if (!p.valid || o0 >= a.C_out) return;
     float res[4];
-    dsq_out4<AT_ONCE>(a, p, o0, acc, delta_a, res);
+    dsq_out4<SUMS>(a, p, o0, acc, delta_a, res);
     dsq_store4_of(a, p, m, o0, acc, res);
 }
 
@@ -211,12 +221,12 @@ __device__ __forceinline__ int dsq_requant_store32(const DsqConvArgs &a, int m, 
 // Four consecutive channels o0..o0+3 of one pixel through the general formulas
 // (any l_a, any border): accumulators -> fp32 results -> the next layer's
 // codes, one per byte; adds the codes to `sum`.  o0 < Cop: the side tables cover it.
-template <bool AT_ONCE = true>
+template <int SUMS = SUMS_TOTALS>
 __device__ __forceinline__ uint32_t dsq_requant_quarter(const DsqConvArgs &a, const DsqPixel &px, int o0, v4i acc,
                                                         float delta_a, float delta_n, int top_n, int &sum)
 {
     float y[4], sc[4], sh[4];
-    dsq_out4<AT_ONCE>(a, px, o0, acc, delta_a, y);
+    dsq_out4<SUMS>(a, px, o0, acc, delta_a, y);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const bool in = o0 + j < a.C_out;

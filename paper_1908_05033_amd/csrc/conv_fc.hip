@@ -51,7 +51,7 @@ struct FcLayout {
 // multiplied (162 registers at 4 bits, one workgroup per CU; held to 128 it spills and takes
 // twice the time).  Without it 73, and two workgroups share a CU: at 512 tiles (2048 -> 1000 x 512)
 // 5.5 us, 7.5 with the registers of the prefetch.
-template <int CONT, bool LONG>
+template <int CONT, bool LONG, int SUMS>
 __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, int tiles_m, uint32_t mg_tiles_m, int total, int xcd_chunk)
 {
     typedef FcLayout<CONT> Lay;
@@ -186,7 +186,7 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, i
             }
             const int top_n = (1 << a.rq_bits) - 1;
             int codes = 0;
-            exch[q * 64 + lane] = dsq_requant_quarter<CONT == 4 || LONG>(a, px, ct * 32 + 8 * q + 4 * h, sum, a.delta_a,
+            exch[q * 64 + lane] = dsq_requant_quarter<SUMS>(a, px, ct * 32 + 8 * q + 4 * h, sum, a.delta_a,
                                                       dsq_delta(a.rq_l, a.rq_u, top_n), top_n, codes);
             exch[(4 + q) * 64 + lane] = (uint32_t)codes;
         }
@@ -213,23 +213,28 @@ __global__ __launch_bounds__(64 * FC_WAVES) void conv_fc_kernel(DsqConvArgs a, i
             sum.x += t.x; sum.y += t.y; sum.z += t.z; sum.w += t.w;
         }
         const DsqPixel px = dsq_pixel_info(a, m, M);
-        dsq_store4<CONT == 4 || LONG>(a, px, m, ct * 32 + 8 * q + 4 * h, sum, a.delta_a);
+        dsq_store4<SUMS>(a, px, m, ct * 32 + 8 * q + 4 * h, sum, a.delta_a);
     }
 }
 
 template <int CONT, bool LONG>
 hipError_t launch_fc(const DsqConvArgs &a, hipStream_t stream)
 {
-    auto kern = conv_fc_kernel<CONT, LONG>;
     const int lds = FcLayout<CONT>::LDS_BYTES;
-    if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-        if (e != hipSuccess) return e;
-    }
     const int M = a.N * a.Ho * a.Wo;
     // (chained mode also writes the code-0 padding channels up to a multiple of 64)
     const int tiles_m = (M + 31) / 32, total = tiles_m * (((a.rq ? a.rq_Cp : a.C_out) + 31) / 32);
     const int xcd_chunk = (total + 7) / 8;
+    // Code sums of a lane's channels read together are four registers more, with which the short 2-bit form
+    // (68) has three workgroups to a compute unit instead of four: past as many tiles it does without (us, together /
+    // one by one: 512 -> 512 chained, 784 tiles, 9.6 / 8.7; 976 -> 64 of 500 pixels with l_a != 0 3.9 / 4.2)
+    auto kern = conv_fc_kernel<CONT, LONG, SUMS_TOTALS>;
+    if constexpr (CONT == 2 && !LONG)
+        if (total > 768) kern = conv_fc_kernel<CONT, LONG, SUMS_EACH>;
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+    }
     // chained mode: the channel tiles add to the next layer's pixel sums, which a
     // fill kernel clears first unless the caller did (no memset node: the call may be under graph capture)
     if (a.rq && !a.rq_zeroed) {

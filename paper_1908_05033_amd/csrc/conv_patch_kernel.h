@@ -1158,12 +1158,12 @@ enum { TILE_SMALL = 0, TILE_MEDIUM = 1, TILE_LARGE = 2, TILE_TALL = 3 };
 // (The 128x64 tile with two fetch units per thread runs four waves per SIMD: layers of
 // 784 k tiles, the 56x56 and 112x112 images, leave a nearly empty last round on 768
 // resident workgroups; measured 5-8 % off such layers, 8-15 % off their chained call,
-// no change elsewhere.  With eight units and more, the strided layers, three waves per SIMD cost 4-bit 3x3 layers up
-// to 28 spilled registers.  Layers of more workgroups than two per compute unit need the third resident one all the
-// same, and with a single channel block the registers of the next one's patch hardly count; deeper layers that two per
-// compute unit hold do without the spills.  us, two / three: 64 -> 64 stride 2 at 112x112 x 64 26.3 / 23.1, chained 25.5 / 21.1,
-// to NCHW 30.9 / 25.7; 48 -> 64 at 28x28 x 64 6.5 / 6.4; 256 -> 24 stride 2 at 112x112 x 16 with l_a != 0 27.1 / 28.5,
-// 300 -> 33 at 28x28 x 32 chained 16.3 / 18.0.)
+// no change elsewhere.  With eight units and more, the strided layers, three waves per SIMD cost 3x3 layers up to 28
+// spilled registers.  A layer with a single channel block has one patch buffer, of which three fit a compute unit, and needs
+// the third workgroup (us, two / three waves: 64 -> 64 stride 2 at 112x112 x 64 4 bits 26.3 / 23.1, chained 25.5 / 21.1,
+// to NCHW 30.9 / 25.7); the two buffers of deeper layers, of more than 512 pixels each at 4 bits and 1024 at 2, leave room for one, and
+// two waves do without the spills (256 -> 24 stride 2 at 112x112 x 16 with l_a != 0 27.1 / 28.5, 496 -> 80 at 85x85 x 5 with
+// l_a != 0 to NCHW 61.9 / 64.2).)
 template <int CONT, int RR>
 hipError_t dispatch_variant(const DsqConvArgs &a, const PatchPlan &pl, int which, int ks, int need, hipStream_t stream)
 {
@@ -1176,8 +1176,8 @@ hipError_t dispatch_variant(const DsqConvArgs &a, const PatchPlan &pl, int which
         if (which == TILE_MEDIUM) return launch_cfg<CONT, RR, 2, 2, 2, 2, UPT, (RR == 3 ? 3 : 1), 3>(a, pl, stream); \
         if (which == TILE_TALL) return launch_cfg<CONT, RR, 4, 1, 2, 2, UPT, (RR == 3 ? 3 : 1), 3>(a, pl, stream); \
         if (ks == 2) return launch_cfg<CONT, RR, 4, 1, 1, 2, UPT, (RR == 3 ? 3 : 1), 2, 2>(a, pl, stream); \
-        if constexpr (CONT == 4 && RR == 3 && UPT >= 8) \
-            if (a.Cp > 64 && pl.tiles_w * pl.row_tiles * ((a.C_out + 63) / 64) <= 512) return launch_cfg<CONT, RR, 4, 1, 1, 2, UPT, 3, 2>(a, pl, stream); \
+        if constexpr (RR == 3 && UPT >= 8) \
+            if (a.Cp > 64) return launch_cfg<CONT, RR, 4, 1, 1, 2, UPT, 3, 2>(a, pl, stream); \
         return launch_cfg<CONT, RR, 4, 1, 1, 2, UPT, (RR == 3 ? 3 : 1), (UPT == 2 ? 4 : 3)>(a, pl, stream); \
     } while (0)
 #define DSQ_GO(CONT, RR)                                                                       \

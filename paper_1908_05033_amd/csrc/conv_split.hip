@@ -165,14 +165,14 @@ __global__ __launch_bounds__(64 * SPLIT_WAVES) __attribute__((amdgpu_waves_per_e
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 double v = dsq_terms(px, sum[j], a.delta_a, dwv[j], lwv[j]);
-                if (MODE == SPLIT_LA) v += dsq_terms_la(a, px, dwv[j], lwv[j], sw[j]);
+                if (MODE == SPLIT_LA && a.l_a != 0.0f) v += dsq_terms_la(a, px, dwv[j], lwv[j], sw[j]);
                 y[j] = (float)v;
             }
             dsq_store4_of(a, px, m, o0, sum, y);
         } else {
             const int top_n = (1 << a.rq_bits) - 1;
             int codes = 0;
-            exch[wave * 64 + lane] = dsq_requant_quarter(a, px, o0, sum, a.delta_a, dsq_delta(a.rq_l, a.rq_u, top_n), top_n, codes);
+            exch[wave * 64 + lane] = dsq_requant_quarter<SUMS_FIRST>(a, px, o0, sum, a.delta_a, dsq_delta(a.rq_l, a.rq_u, top_n), top_n, codes);
             exch[(4 + wave) * 64 + lane] = (uint32_t)codes;
         }
     }

@@ -523,13 +523,14 @@ hipError_t dsq_launch_quantize_act(const float *x, int layout_nchw, int N, int C
         // of 256 / of 1024 threads): 4096 channels x 1 5.7 / 2.5 / 2.4, x 64 6.7 / 2.8 / 2.8, x 600 6.6 / 3.6 / 4.0, x 3136
         // 12.2 / 10.6 / 11.6, x 12544 35 / 34.6 / 36; 2048 x 6272 10.4 / 10.5 / 17.7 (16 lanes of the rows kernel 19.2), x 25088
         // 34 / 33.9 / 61.  1024 threads from 8192 (2 bits: 16384) channels on, of which 512 blocks run at a time: 8192 x 784
-        // 4.8 / 5.4 (256 / 1024 threads), x 4096 24.2 / 23.9 / 22.1, x 12544 85 / 86 / 81.  Few pixels from 1024 channels on: 1024 x 49 3.16 / 2.63, x 784 3.25 / 2.86, x 1568 3.37 / 3.20, x 3136
-        // 3.96 / 4.10 / 8.4.
+        // 4.8 / 5.4 (256 / 1024 threads), x 4096 24.2 / 23.9 / 22.1, x 12544 85 / 86 / 81.  Few pixels from 768 channels
+        // on: 768 x 512 2.85 / 2.68, x 3136 3.53 / 4.10, 1024 x 49 3.16 / 2.63, x 784 3.25 / 2.86, x 1568 3.37 / 3.20,
+        // x 3136 3.96 / 4.10 / 8.4.
 #define DSQ_DEEP(T) do { if (cont == 4) quantize_act_deep_kernel<4, T><<<total_pixels, T, 0, stream>>>(x, cw, pix_sum, C, DP, q); \
             else quantize_act_deep_kernel<2, T><<<total_pixels, T, 0, stream>>>(x, cw, pix_sum, C, DP, q); } while (0)
         if (DP >= 1024 && (total_pixels <= 512 || total_pixels >= 2048)) {
             DSQ_DEEP(1024);
-        } else if (C >= 2048 || (C >= 1024 && total_pixels <= 2048)) {
+        } else if (C >= 2048 || (C >= 1024 && total_pixels <= 2048) || (C >= 768 && total_pixels <= 512)) {
             DSQ_DEEP(256);
         } else if (cont == 4) {
             launch_rows<4>(x, cw, pix_sum, total_pixels, C, DP, q, stream);

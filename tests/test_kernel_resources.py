@@ -72,10 +72,10 @@ def test_split_k_workgroups_share_a_cu():
 
 def test_general_epilogue_leaves_the_waves_per_simd():
     """Kernels that form their results through the per-lane functions of conv_epilogue.h: four 2-bit workgroups of the
-    split-K kernel share a compute unit up to 64 registers (as many as its LDS allows), and the simple kernel
+    split-K kernel, in the variant for many tiles, share a compute unit up to 64 registers (as many as its LDS allows), and the simple kernel
     runs five waves per SIMD up to 96."""
     asm = _device_asm(os.path.join(CSRC, "conv_fc.hip"))
-    short = re.findall(r"\.name:\s+\S*conv_fc_kernelILi2ELb0E\S*.*?\.vgpr_count:\s+(\d+)", asm, re.S)
+    short = re.findall(r"\.name:\s+\S*conv_fc_kernelILi2ELb0ELi0E\S*.*?\.vgpr_count:\s+(\d+)", asm, re.S)
     assert len(short) == 1 and int(short[0]) <= 64, short
     asm = _device_asm(os.path.join(CSRC, "conv_simple.hip"))
     simple = re.findall(r"\.name:\s+\S*conv_simple_kernel\S*.*?\.vgpr_count:\s+(\d+)", asm, re.S)
@@ -93,8 +93,8 @@ def test_few_tile_workgroups_share_a_cu():
 
 
 def test_small_tiles_of_strided_layers_run_three_waves_per_simd():
-    """The 128x64 tile with eight fetch units per thread and more, one wave group: layers of more workgroups than two
-    per compute unit run the variant of which three are resident, up to 168 registers."""
+    """The 128x64 tile with eight fetch units per thread and more, one wave group: layers of one channel block run the
+    variant of which three workgroups are resident per compute unit, up to 168 registers."""
     asm = _device_asm(os.path.join(CSRC, "conv_patch_c4r3.hip"))
     kernels = re.findall(r"\.name:\s+(\S*conv_patch_kernelILi4ELi3ELi4ELi1ELi1ELi2ELi(?:8|12)ELi3ELi3ELi1E\S*).*?\.vgpr_count:\s+(\d+)",
                          asm, re.S)
